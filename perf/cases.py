@@ -1,0 +1,329 @@
+"""The work that a user of this library has it do, as timed cases.
+
+A pass hands freshly built host graphs to the library and takes them all the way: graph definition, upload,
+scheduling on the GPU, batched forward, batched backward, reads or update.  Sizes are those of the repository's own
+configurations (paper_1705_07860_amd/workloads.py), its batch-size sweep and its growing-graph demo, with the widths
+of the networks varied around them.
+
+`listed` names the cases, `draw` gives more of the same ranges, `prepare` makes what a program has in hand before the
+call, `run` is one pass, `work` what the pass cannot do without, `tolerance` how far another fp32 implementation may
+lie from this one.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+from paper_1705_07860_amd import binding as ob
+from paper_1705_07860_amd import grow_demo
+from paper_1705_07860_amd import workloads as wl
+
+MODES = {"depth": ob.OB_BYDEPTH, "agenda": ob.OB_BYAGENDA, "manual": ob.OB_MANUAL}
+SCHEDULE_CUS = 32          # compute units of the schedule stream in the pipelined loop, as in bench.py
+SEED_STEP = 1000003        # keeps the parameter and minibatch seeds of different states apart
+
+
+def listed():
+    return [
+        # a toy model, or the first steps of a tutorial: latency and launches are everything
+        dict(name="rnn_8", task="train", model="rnn", instances=8, hidden=32, mode="depth"),
+        # one instance at a time (Section 4.3): batching inside a single tree
+        dict(name="tree_1", task="train", model="tree", instances=1, hidden=256, mode="depth"),
+        # serving: tag one sentence, read the scores of every token
+        dict(name="tagger_predict_1", task="predict", model="tagger", instances=1, tokens=20, hidden=256, mode="depth"),
+        # the BiLSTM tagger, one minibatch and its update per step, the loss read every step
+        dict(name="tagger_64_update", task="train", model="tagger", instances=64, hidden=256, mode="depth", update=True),
+        # a small batch of a network whose widths are no powers of two nor multiples of four
+        dict(name="tagger_char_24_odd", task="train", model="tagger_char", instances=24, hidden=100, mode="depth"),
+        # the headline: the training loop of bench.py, four minibatches a pass, hand-over and scheduling of the
+        # next minibatch beside the execution of the current one
+        dict(name="tagger_char_64_loop", task="loop", model="tagger_char", instances=64, hidden=256, mode="depth"),
+        # tree-LSTM minibatch
+        dict(name="tree_64", task="train", model="tree", instances=64, hidden=256, mode="depth"),
+        # transition parser minibatch
+        dict(name="parser_64", task="train", model="parser", instances=64, hidden=128, mode="depth"),
+        # the same under agenda-based batching (Section 3.2's second strategy)
+        dict(name="parser_64_agenda", task="train", model="parser", instances=64, hidden=128, mode="agenda"),
+        # large minibatches, where the matrix products carry weight
+        dict(name="tagger_512", task="train", model="tagger", instances=512, hidden=256, mode="depth"),
+        # batching by hand over sentences of equal length (Section 4.1)
+        dict(name="sync_tagger_64_manual", task="train", model="sync_tagger", instances=64, hidden=256, mode="manual"),
+        # a graph that grows by one time step after each value read (Section 3.1), then the backward pass
+        dict(name="grow_64x40", task="grow", model="chains", instances=64, steps=40, hidden=256, mode="depth"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return max(lo, min(hi, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))))
+
+
+# most instances of a drawn training case, so that it costs no more than tagger_512
+MOST = {"rnn": 512, "tagger": 400, "tagger_char": 128, "tree": 400, "parser": 200, "sync_tagger": 96}
+
+
+def draw(rng):
+    task = rng.choice(["train"] * 6 + ["loop"] * 2 + ["predict", "grow"])
+    if task == "grow":
+        return dict(task=task, model="chains", instances=_log_int(rng, 2, 64), steps=_log_int(rng, 3, 40),
+                    hidden=rng.randint(32, 256), mode="depth")
+    model = "tagger" if task == "predict" else rng.choice(["rnn", "tagger", "tagger", "tagger_char", "tagger_char", "tree",
+                                                           "tree", "parser", "parser", "sync_tagger"])
+    most = {"predict": 8, "loop": 64}.get(task, MOST[model])
+    mode = rng.choice(["depth"] * 4 + ["agenda"])
+    if model == "sync_tagger" and task == "train":
+        mode = "manual"
+    top = {"rnn": 64, "parser": 128}.get(model, 256)
+    # half of the networks have widths as people choose them, the others any width at all
+    hidden = rng.choice([top, top // 2, top // 4]) if rng.random() < 0.5 else rng.randint(top // 8, top)
+    c = dict(task=task, model=model, instances=_log_int(rng, 1, min(most, MOST[model])), hidden=hidden, mode=mode)
+    if task == "predict":
+        c["tokens"] = _log_int(rng, 1, 60)
+    if task == "train" and rng.random() < 0.3:
+        c["update"] = True
+    return c
+
+
+# ---- inputs ----------------------------------------------------------------------------------------------------------
+
+def _params(case, seed):
+    m, h = case["model"], case["hidden"]
+    if m == "rnn":
+        return wl.rnn_params(seed, d_in=h, hidden=h)
+    if m in ("tagger", "tagger_char"):
+        ch = max(h // 4, 1)
+        return wl.tagger_params(seed, with_char=m == "tagger_char", emb=2 * ch, hidden=h, mlp=h, char_hidden=ch)
+    if m == "tree":
+        return wl.tree_params(seed, emb=h, hidden=h)
+    if m == "parser":
+        return wl.parser_params(seed, emb=h, hidden=h, mlp=4 * h)
+    return wl.sync_tagger_params(seed, hidden=h)
+
+
+def _minibatch(case, params, seed):
+    m, n = case["model"], case["instances"]
+    if m == "rnn":
+        return wl.rnn_minibatch(params, seed, n_inst=n)
+    if m in ("tagger", "tagger_char"):
+        lengths = [case["tokens"]] * n if "tokens" in case else None
+        return wl.tagger_minibatch(params, seed, n_sent=n, with_char=m == "tagger_char", lengths=lengths)
+    if m == "tree":
+        return wl.tree_minibatch(params, seed, n_trees=n)
+    if m == "parser":
+        return wl.parser_minibatch(params, seed, n_sent=n)
+    return wl.sync_tagger_minibatch(params, seed, n_sent=n)
+
+
+def _without_losses(g):
+    """The graph a tagger builds when there are no labels: the nodes up to the scores.  Returns the graph and the
+    score nodes' ids in token order."""
+    keep = g.op != wl.OP_PICK_NLS
+    keep[g.root] = False
+    new_id = np.cumsum(keep) - 1
+    scores = new_id[g.in_idx[g.in_off[:-1][g.op == wl.OP_PICK_NLS]]]
+    arity = np.diff(g.in_off.astype(np.int64))
+    idx = new_id[g.in_idx[np.repeat(keep, arity)]].astype(np.uint32)
+    off = np.concatenate([[0], np.cumsum(arity[keep])]).astype(np.uint32)
+    h = wl.Graph(op=g.op[keep], out_dim=g.out_dim[keep], in_off=off, in_idx=idx, param=g.param[keep], bias=g.bias[keep],
+                 aux0=g.aux0[keep], aux1=g.aux1[keep], payload=g.payload, root=int(keep.sum()) - 1,
+                 n_instances=g.n_instances)
+    return h, [int(v) for v in scores]
+
+
+def _graphs(case, seed):
+    """(parameters, host graphs of one pass)"""
+    if case["task"] == "grow":
+        p, g, bounds = grow_demo.build(case["instances"], case["steps"], hidden=case["hidden"], seed=seed)
+        return p, [grow_demo.part(g, bounds[k], bounds[k + 1]) for k in range(len(bounds) - 1)]
+    p = _params(case, seed)
+    n = 4 if case["task"] == "loop" else 1
+    return p, [_minibatch(case, p, seed + 1 + j) for j in range(n)]
+
+
+def _device_views(ctx, params, grads):
+    """The parameters (or their gradients) where they lie in the caller's arena, as tensors.  The library's calls give
+    ids, not addresses, so a small graph with a known gradient is run once and its bits are looked for: the sum of the
+    squared norms of a few rows of every parameter, whose gradient is twice those rows and zero elsewhere."""
+    want = []
+    losses = []
+    for pid, m in enumerate(params.mats):
+        w = np.zeros_like(m)
+        for row in range(0, min(m.shape[0], 16), 2):
+            losses.append(ctx.add_sqnorm(ctx.add_lookup(pid, row)))
+            w[row] = 2 * m[row]
+        want.append(w if grads else m)
+    root = ctx.add_nary(wl.OP_ADD, losses)
+    ctx.param_grad_zero()
+    ctx.forward(root)
+    ctx.backward(root)
+    ctx.sync()
+    words = ctx._arena.view(torch.int32)
+    starts = words[::64]                          # everything in the arena starts at a multiple of 256 bytes
+    views = []
+    for w in want:
+        bits = torch.from_numpy(np.ascontiguousarray(w).view(np.int32).reshape(-1)).to(words.device)
+        hits = [int(i) * 64 for i in torch.nonzero(starts == bits[0]).reshape(-1)
+                if int(i) * 64 + bits.numel() <= words.numel() and bool((words[int(i) * 64:int(i) * 64 + bits.numel()] == bits).all())]
+        if len(hits) != 1:
+            raise RuntimeError(f"a {w.shape} parameter block was found {len(hits)} times in the arena")
+        views.append(words[hits[0]:hits[0] + bits.numel()].view(torch.float32).view(w.shape))
+    ctx.graph_new()
+    ctx.param_grad_zero()
+    return views
+
+
+_STREAMS = []
+
+
+def _loop_streams():
+    """Execution stream and schedule stream on disjoint compute units (made once; a program keeps them)."""
+    if not _STREAMS:
+        n = torch.cuda.get_device_properties(0).multi_processor_count
+        _STREAMS.append(torch.cuda.ExternalStream(ob.stream_create_on_cus(SCHEDULE_CUS, n - SCHEDULE_CUS)))
+        _STREAMS.append(torch.cuda.ExternalStream(ob.stream_create_on_cus(0, SCHEDULE_CUS)))
+    return _STREAMS
+
+
+def _arena_bytes(case):
+    if case["task"] == "grow":
+        return 6 << 30
+    return (1 << 30) * max(1, -(-case["instances"] // 64))
+
+
+def prepare(case, seed):
+    base = wl.SEED_BASE + seed * SEED_STEP
+    params, graphs = _graphs(case, base)
+    st = dict(task=case["task"], graphs=graphs, update=bool(case.get("update")) or case["task"] == "loop",
+              lr=0.02 / case["instances"], labels=None)
+    stream = _loop_streams()[0] if case["task"] == "loop" else None
+    arena_bytes = _arena_bytes(case)
+    ctx = ob.Context(arena_bytes=arena_bytes, stream=stream, mode=MODES[case["mode"]] if case["mode"] != "manual" else ob.OB_BYDEPTH)
+    ctx._arena.zero_()
+    torch.cuda.synchronize()
+    ctx.params_create(params)
+    if case["task"] != "predict":
+        st["out"] = _device_views(ctx, params, grads=not st["update"])
+    if case["mode"] == "manual":
+        ctx.set_mode(ob.OB_MANUAL)
+        st["labels"] = wl.sync_tagger_manual_labels(graphs[0])
+    st["ctxs"] = [ctx]
+    if case["task"] == "predict":
+        g, st["scores"] = _without_losses(graphs[0])
+        st["graphs"] = graphs = [g]
+        st["dim"] = int(g.out_dim[st["scores"][0]])
+    if case["task"] == "loop":
+        st["ctxs"] += [ctx.fork(arena_bytes=arena_bytes, stream=stream) for _ in graphs[1:]]
+    # A program that runs has seen minibatches before: every context takes a graph once, so that the library's host
+    # buffers have their size (bench.py does the same).
+    for c, g in zip(st["ctxs"], graphs if case["task"] != "grow" else []):
+        c.graph_new()
+        if case["task"] == "loop":
+            c.set_schedule_stream(_loop_streams()[1])
+        c.add_bulk(g)
+        if st["labels"] is not None:
+            c.set_manual_batches(st["labels"])
+        c.schedule(g.root)
+        c.graph_new()
+    torch.cuda.synchronize()
+    return st
+
+
+# ---- one pass ----------------------------------------------------------------------------------------------------------
+
+def _train(st):
+    c, g = st["ctxs"][0], st["graphs"][0]
+    if not st["update"]:
+        c.param_grad_zero()
+    c.graph_new()
+    c.add_bulk(g)
+    if st["labels"] is not None:
+        c.set_manual_batches(st["labels"])
+    c.forward(g.root)
+    c.backward(g.root)
+    if st["update"]:
+        c.sgd_step(st["lr"], zero_grad=True)
+    return dict(loss=c.value_read(g.root, 1), out=st["out"])
+
+
+def _loop(st):
+    def hand_over(i):
+        c, g = st["ctxs"][i], st["graphs"][i]
+        c.graph_new()
+        c.add_bulk(g)
+        c.schedule_async(g.root)
+
+    hand_over(0)
+    for i, (c, g) in enumerate(zip(st["ctxs"], st["graphs"])):
+        if i + 1 < len(st["graphs"]):
+            hand_over(i + 1)
+        c.forward(g.root)
+        c.backward(g.root)
+        c.sgd_step(st["lr"], zero_grad=True)
+    return dict(out=st["out"])
+
+
+def _predict(st):
+    c, g = st["ctxs"][0], st["graphs"][0]
+    c.graph_new()
+    c.add_bulk(g)
+    c.forward(g.root)
+    return np.stack([c.value_read(v, st["dim"]) for v in st["scores"]])
+
+
+def _grow(st):
+    c = st["ctxs"][0]
+    c.graph_new()
+    c.param_grad_zero()
+    seen = []
+    for part in st["graphs"]:
+        c.add_bulk(part)
+        last = c.graph_size()[0] - 1
+        c.forward(last)
+        seen.append(float(c.value_read(last, 1)[0]))
+    c.backward(last)
+    c.sync()
+    return dict(losses=np.asarray(seen, np.float32), out=st["out"])
+
+
+def run(st):
+    return {"train": _train, "loop": _loop, "predict": _predict, "grow": _grow}[st["task"]](st)
+
+
+# ---- what a pass cannot do without --------------------------------------------------------------------------------------
+
+def work(case):
+    """Every graph array and every parameter that is used read once (of a table the rows looked up), the gradients of
+    the same parameters written once, an update read and written once; two operations per matrix element and use, three
+    times that with the backward pass."""
+    params, graphs = _graphs(case, wl.SEED_BASE)
+    nbytes = flops = 0.0
+    train = case["task"] != "predict"
+    update = bool(case.get("update")) or case["task"] == "loop"
+    rows = np.asarray([m.shape[0] for m in params.mats])
+    cols = np.asarray([m.shape[1] for m in params.mats])
+    dense, looked_up = set(), {}
+    for g in graphs:
+        first = g is graphs[0] or case["task"] != "grow"      # (pieces of a growing graph share one input block)
+        nbytes += 29.0 * g.n + 4.0 * g.n_edges + (4.0 * g.payload.size if first else 0.0)
+        mv = g.param[g.op == wl.OP_MATVEC]
+        flops += float(2.0 * (rows[mv] * cols[mv]).sum()) * (3.0 if train else 1.0)
+        dense |= set(mv.tolist()) | set(g.bias[g.bias >= 0].tolist())
+        lk = g.op == wl.OP_LOOKUP
+        for t in np.unique(g.param[lk]).tolist():
+            looked_up.setdefault(t, set()).update(g.aux0[lk & (g.param == t)].tolist())
+        if case["task"] == "loop" or g is graphs[-1]:           # each minibatch of a loop reads the updated parameters
+            floats = float(sum(rows[p] * cols[p] for p in dense) + sum(len(r) * cols[t] for t, r in looked_up.items()))
+            nbytes += 4.0 * floats * (1.0 + (1.0 if train else 0.0) + (1.0 if update else 0.0))
+            if case["task"] == "loop":
+                dense, looked_up = set(), {}
+    return dict(bytes=nbytes, flops=flops)
+
+
+def tolerance(case):
+    """About four times the distance from the fp64 interpreter of oracle/ on the same fp32 inputs, over these cases and
+    fourteen drawn ones: gradients and scores 6.5e-7 in the 2-norm, 2.5e-5 for the worst element; updated weights, which
+    are mostly the old weights, 3.2e-8 and 9e-8 after one update (a loop makes four, each on the result of the last)."""
+    if case.get("update") or case["task"] == "loop":
+        return dict(rel=1e-6, max=1e-5)
+    return dict(rel=3e-6, max=1e-4)

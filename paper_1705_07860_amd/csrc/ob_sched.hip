@@ -66,8 +66,6 @@ __device__ inline u32 consumer_of(const Tables &T, u32 e)
     return lo;
 }
 
-constexpr u32 DEPTH_PART = 4096;      // nodes per workgroup of the partitioned depth pass
-
 __global__ void k_edge_init(Tables T, u64 *keys, u32 *vals)
 {
     const u32 e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -77,7 +75,6 @@ __global__ void k_edge_init(Tables T, u64 *keys, u32 *vals)
     const u32 j = e - T.in_off[v];
     T.edge_cons[e] = v;
     atomicAdd(&T.outdeg[u], 1u);
-    if (u / DEPTH_PART != v / DEPTH_PART) { atomicAdd(&T.ext_indeg[v], 1u); atomicAdd(&T.ext_left[v], 1u); }   // operand owned by another partition
     atomicAdd((unsigned long long *)&T.sig[v], (unsigned long long)mix64(comb(0x5bd1e995ULL + j, T.out_dim[u])));
     keys[e] = u;
     vals[e] = e;
@@ -132,200 +129,203 @@ __global__ __launch_bounds__(FRONTIER_THREADS) void k_depth_frontier(Tables T, c
     }
 }
 
-// Partitioned frontier pass: the same dependency-counter algorithm, with the node ids cut into
-// ranges of DEPTH_PART nodes, one workgroup per range.  A workgroup keeps the counters, the
-// partial depths, its frontier queue and the successor lists of its range in LDS, so advancing
-// its frontier costs LDS latency only.  An edge into another range resolves through global
-// atomics: the producer raises the consumer's depth bound and lowers its count of unresolved
-// external operands; whoever resolves the last one posts the node to the owner's inbox, where it
-// counts as one more resolved dependency.  Ids are a topological order, so a range only ever
-// waits for lower ranges and the lowest never waits, whenever each workgroup happens to start (a
-// range reads its nodes' external counts from the fixed copy, never from the counters that lower
-// ranges are already taking down); every wait is bounded.
-constexpr u32 DEPTH_SCAP = 12288;     // successor entries of a range held in LDS
-constexpr u32 DEPTH_THREADS = 256;    // set-up and write-out; in between the waves have roles of their own
-constexpr u32 DEPTH_MAX_PARTS = 240;
-constexpr u32 DEPTH_NONE = 0xffffffffu;
-constexpr u32 DEPTH_UNROLL = 2;       // successors of a frontier node handled per pass of the inner loop
-constexpr u32 DEPTH_OUT_CAP = 1024;   // ring of resolutions that leave the range, waiting for the wave that posts them
+// Depth by id ranges.  Ids are a topological order, so depth(v) = 1 + the largest operand depth can be
+// taken range by range: a workgroup owns DEPTH_PART consecutive ids, a thread DEPTH_NPT of them, with the
+// operands of its nodes in registers (an operand inside the range is an LDS word, one of a lower range a word
+// of g_dep) and the depths of the range in LDS, one word per node: 0 = not known yet, depth + 1 otherwise.
+// A sweep looks at the operand words of all nodes of a wave at once and settles every node whose operands are
+// all settled; each word is written once, so waves need no barrier between sweeps and run freely.  A thread's
+// nodes are consecutive ids, which programs write along their recurrences, and a node settled in a sweep is
+// handed to the thread's later nodes in registers: an LSTM cell of sixteen nodes and eight levels takes four sweeps.  A settled
+// depth also goes to g_dep, where higher ranges poll for it: the word is its own flag, so no fence is needed.
+// Nodes with more than DEPTH_OPS operands are walked by their whole wave, eight reads per lane at a time,
+// whenever the wave's other nodes are not moving.
+// What bounds it: one dependent LDS read plus some forty instructions per level of the longest path, which is
+// why a wave holds no more than four nodes per lane and a workgroup one wave per SIMD.  The pass this
+// replaces kept a frontier queue per 4 096 ids (queue, counter, successor and queue again: five dependent LDS
+// operations per level).
+// Only lower ranges are waited for and the lowest waits for nobody; every wait is bounded.
+constexpr u32 DEPTH_THREADS = 256;
+constexpr u32 DEPTH_NPT = 4;          // nodes per thread
+constexpr u32 DEPTH_PART = DEPTH_THREADS * DEPTH_NPT;   // ids per workgroup
+constexpr u32 DEPTH_OPS = 4;          // operands of a node that are kept in registers
+constexpr u32 DEPTH_ONE = DEPTH_PART;         // LDS word that always holds 1: an absent operand
+constexpr u32 DEPTH_NEVER = DEPTH_PART + 1;   // LDS word that always holds 0: an operand that cannot be read here (yet)
+constexpr u32 DEPTH_EXT = 0x80000000u;        // operand of a lower range: this bit and its id (reads as DEPTH_NEVER)
+constexpr u32 DEPTH_WIDE_READS = 8;   // operands per lane of one step over a node with many operands
+constexpr u32 DEPTH_MAX_ARITY = 60000;   // beyond, the single-workgroup pass counts the operands down instead of walking them
 
 __device__ inline u32 lds_load(const u32 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
-
-// A resolution that leaves the range: raise the consumer's depth bound, take one of its external
-// dependencies off; whoever takes the last one posts the node to its owner's inbox.
-__device__ inline void depth_post_external(const Tables &T, u32 sn, u32 d1, u32 *g_dep, u32 *inbox, u32 *inbox_tail)
+__device__ inline void depth_settle(u32 *s_word, u32 *g_word, u32 d)
 {
-    atomicMax(&g_dep[sn], d1);
-    __threadfence();
-    if (atomicSub(&T.ext_left[sn], 1u) == 1u) {
-        const u32 k2 = sn / DEPTH_PART;
-        const u32 slot = atomicAdd(&inbox_tail[k2], 1u);
-        __hip_atomic_store(&inbox[k2 * DEPTH_PART + slot], sn, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    __hip_atomic_store(s_word, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_store(g_word, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ __launch_bounds__(DEPTH_THREADS) void k_depth_partitioned(Tables T, const u32 *succ_node, u32 *g_dep,
-                                                                         u32 *inbox, u32 *inbox_tail, u32 spin_limit)
+__global__ __launch_bounds__(DEPTH_THREADS) void k_depth_partitioned(Tables T, u32 *g_dep, u32 spin_limit)
 {
-    __shared__ u32 s_pending[DEPTH_PART];
-    __shared__ u32 s_dep[DEPTH_PART];
-    __shared__ unsigned short s_queue[DEPTH_PART];
-    __shared__ u32 s_soff[DEPTH_PART + 1];
-    __shared__ u32 s_snode[DEPTH_SCAP];
-    __shared__ u32 s_out_sn[DEPTH_OUT_CAP], s_out_d1[DEPTH_OUT_CAP];
-    __shared__ unsigned short s_in[DEPTH_PART];
-    __shared__ u32 s_next, s_done, s_out_tail, s_out_head, s_in_tail, s_fin;
-    const u32 tid = threadIdx.x;
-    const u32 k = blockIdx.x;
-    const u32 lo = k * DEPTH_PART;
-    const u32 hi = lo + DEPTH_PART < T.n ? lo + DEPTH_PART : T.n;
-    const u32 cnt = hi - lo;
-    const u32 ebase = T.succ_off[lo];
-    const u32 ecnt = T.succ_off[hi] - ebase;
-    if (tid == 0) { s_next = 0; s_done = 0; s_out_tail = 0; s_out_head = 0; s_in_tail = 0; s_fin = 0; }
-    __syncthreads();
-    for (u32 i = tid; i < cnt; i += DEPTH_THREADS) {
-        const u32 v = lo + i;
-        const u32 ext = T.ext_indeg[v];
-        const u32 pend = T.indeg[v] - ext + (ext ? 1u : 0u);
-        s_pending[i] = pend;
-        s_dep[i] = 0;
-        s_soff[i] = T.succ_off[v] - ebase;
-        if (pend == 0) s_queue[atomicAdd(&s_next, 1u)] = (unsigned short)i;
-    }
-    if (tid == 0) s_soff[cnt] = ecnt;
-    for (u32 e = tid; e < ecnt && e < DEPTH_SCAP; e += DEPTH_THREADS) s_snode[e] = succ_node[ebase + e];
-    __syncthreads();
-    // The frontier of a range is small (tens of nodes per level), so after the cooperative set-up
-    // wave 0 runs the level loop alone: its LDS operations complete in program order, the loop state
-    // (head, tail, counters) sits in scalar registers, new frontier entries get their queue
-    // positions from a ballot, and nothing in the loop waits for global memory.  Traffic with other
-    // ranges goes through the two helper waves: wave 1 watches this range's inbox (coherent memory)
-    // and hands what arrives to wave 0 through LDS, depth bound already applied; wave 2 takes the
-    // resolutions that leave the range from a ring in LDS and posts them with global atomics.
-    const u32 wave = tid >> 6, lane = tid & 63u;
+    __shared__ u32 s_dep[DEPTH_PART + 2];
+    __shared__ unsigned short s_wide[DEPTH_THREADS / 64][64 * DEPTH_NPT];
+    __shared__ u32 s_quit;
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const u64 lt_mask = (1ull << lane) - 1ull;
-    if (wave == 0) {
-        u32 head = 0, tail = __builtin_amdgcn_readfirstlane(s_next), done = 0, seen = 0, spin = 0, out_tail = 0;
-        while (!(head == tail && done == cnt)) {
-            const u32 avail = __builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_in_tail, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
-            u32 new_tail = tail;
-            for (u32 base = head; base < tail; base += 64) {
-                const u32 i = base + lane;
-                const bool act = i < tail;
-                const u32 ul = act ? s_queue[i] : 0u;
-                const u32 d1 = s_dep[ul] + 1u;
-                u32 e = s_soff[ul];
-                const u32 e1 = act ? s_soff[ul + 1] : e;
-                while (__ballot(e < e1) != 0ull) {
-                    // two successors per pass (most nodes have one or two): the loop is bound by the number of
-                    // instructions the one wave issues, so the common case is kept short
-                    u32 sn[DEPTH_UNROLL], was[DEPTH_UNROLL];
-                    bool any_ext = false;
+    const u32 lo = blockIdx.x * DEPTH_PART;
+    for (u32 i = tid; i < DEPTH_PART + 2; i += DEPTH_THREADS) s_dep[i] = i == DEPTH_ONE ? 1u : 0u;
+    if (tid == 0) s_quit = 0;
+    __syncthreads();
+    // node j of a lane: local id first + j
+    const u32 first = tid * DEPTH_NPT;
+    bool fwd0[DEPTH_NPT][DEPTH_NPT], fwd1[DEPTH_NPT][DEPTH_NPT];   // operand 0 / 1 of node j is the lane's own node i < j
+    u32 op[DEPTH_NPT][DEPTH_OPS], ext[DEPTH_NPT], dep[DEPTH_NPT];   // ext: largest word among settled operands of lower ranges
+    bool wide[DEPTH_NPT], has_ext = false, has_34 = false;
 #pragma unroll
-                    for (u32 j = 0; j < DEPTH_UNROLL; ++j)
-                        sn[j] = e + j < e1 ? (e + j < DEPTH_SCAP ? s_snode[e + j] : succ_node[ebase + e + j]) : DEPTH_NONE;
+    for (u32 j = 0; j < DEPTH_NPT; ++j) {
+        const u32 l = first + j, v = lo + l;
+        const bool live = v < T.n;
+        const u32 a = live ? T.in_off[v] : 0u, ar = live ? T.in_off[v + 1] - a : 0u;
+        ext[j] = 0;
+        dep[j] = ar ? 0u : 1u;
 #pragma unroll
-                    for (u32 j = 0; j < DEPTH_UNROLL; ++j) {   // successors have larger ids than their producer, so sn >= lo
-                        was[j] = 0;
-                        if (sn[j] < hi) { atomicMax(&s_dep[sn[j] - lo], d1); was[j] = atomicSub(&s_pending[sn[j] - lo], 1u); }
-                        else any_ext = any_ext || sn[j] != DEPTH_NONE;
-                    }
+        for (u32 q = 0; q < DEPTH_OPS; ++q) {
+            op[j][q] = DEPTH_ONE;
+            if (q < ar && ar <= DEPTH_OPS) {
+                const u32 u = T.in_idx[a + q];
+                op[j][q] = u >= lo ? u - lo : (DEPTH_EXT | u);
+                has_ext = has_ext || u < lo;
+            }
+        }
 #pragma unroll
-                    for (u32 j = 0; j < DEPTH_UNROLL; ++j) {
-                        const bool ready = was[j] == 1u;
-                        const u64 m = __ballot(ready);
-                        if (ready) s_queue[new_tail + (u32)__popcll(m & lt_mask)] = (unsigned short)(sn[j] - lo);
-                        new_tail += (u32)__popcll(m);
-                    }
-                    if (__ballot(any_ext) != 0ull) {
+        for (u32 i = 0; i < DEPTH_NPT; ++i) { fwd0[j][i] = op[j][0] == first + i; fwd1[j][i] = op[j][1] == first + i; }
+        if (live && ar == 0) depth_settle(&s_dep[l], &g_dep[v], 1u);
+        wide[j] = ar > DEPTH_OPS;
+        if (wide[j]) op[j][0] = DEPTH_NEVER;
+        has_34 = has_34 || (ar > 2u && !wide[j]);
+    }
+    // (in ascending order of ids: a node of the list never waits for a later one)
+    u32 at = 0, n_wide = 0;
 #pragma unroll
-                        for (u32 j = 0; j < DEPTH_UNROLL; ++j) {
-                            const bool ext = sn[j] != DEPTH_NONE && sn[j] >= hi;
-                            const u64 m = __ballot(ext);
-                            if (m == 0ull) continue;
-                            const u32 c = (u32)__popcll(m);
-                            if (out_tail + c - lds_load(&s_out_head) <= DEPTH_OUT_CAP) {
-                                if (ext) {
-                                    const u32 pos = (out_tail + (u32)__popcll(m & lt_mask)) % DEPTH_OUT_CAP;
-                                    s_out_sn[pos] = sn[j]; s_out_d1[pos] = d1;
-                                }
-                                out_tail += c;
-                                __hip_atomic_store(&s_out_tail, out_tail, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                            } else if (ext) {
-                                depth_post_external(T, sn[j], d1, g_dep, inbox, inbox_tail);   // ring full: post it here
-                            }
-                        }
-                    }
-                    e += DEPTH_UNROLL;
+    for (u32 j = 0; j < DEPTH_NPT; ++j) {
+        const u64 m = __ballot(wide[j]);
+        at += (u32)__popcll(m & lt_mask);
+        n_wide += (u32)__popcll(m);
+    }
+#pragma unroll
+    for (u32 j = 0; j < DEPTH_NPT; ++j)
+        if (wide[j]) s_wide[wave][at++] = (unsigned short)(first + j);
+    bool any_ext = __ballot(has_ext) != 0ull;
+    const bool any_34 = __ballot(has_34) != 0ull;
+    u32 wide_i = 0, wide_e = 0, wide_max = 0;     // node of the wave's list being walked, operands behind it, their largest word
+    u32 idle = 0, sweep = 0;
+    bool gave_up = false;
+    while (true) {
+        u32 w0[DEPTH_NPT], w1[DEPTH_NPT], w2[DEPTH_NPT], w3[DEPTH_NPT];
+#pragma unroll
+        for (u32 j = 0; j < DEPTH_NPT; ++j) {
+            w0[j] = lds_load(&s_dep[op[j][0] < DEPTH_NEVER ? op[j][0] : DEPTH_NEVER]);
+            w1[j] = lds_load(&s_dep[op[j][1] < DEPTH_NEVER ? op[j][1] : DEPTH_NEVER]);
+            w2[j] = w3[j] = 1u;
+        }
+        if (any_34) {
+#pragma unroll
+            for (u32 j = 0; j < DEPTH_NPT; ++j) {
+                w2[j] = lds_load(&s_dep[op[j][2] < DEPTH_NEVER ? op[j][2] : DEPTH_NEVER]);
+                w3[j] = lds_load(&s_dep[op[j][3] < DEPTH_NEVER ? op[j][3] : DEPTH_NEVER]);
+            }
+        }
+        bool moved = false, left = false;
+#pragma unroll
+        for (u32 j = 0; j < DEPTH_NPT; ++j) {
+            if (dep[j] == 0u) {
+                u32 x = w0[j], y = w1[j];
+#pragma unroll
+                for (u32 i = 0; i < j; ++i) { x = fwd0[j][i] ? dep[i] : x; y = fwd1[j][i] ? dep[i] : y; }
+                const u32 a = x < y ? x : y, b = w2[j] < w3[j] ? w2[j] : w3[j];
+                if ((a < b ? a : b) != 0u) {
+                    const u32 c = x > y ? x : y, d = w2[j] > w3[j] ? w2[j] : w3[j];
+                    const u32 e = c > d ? c : d;
+                    dep[j] = (e > ext[j] ? e : ext[j]) + 1u;
+                    depth_settle(&s_dep[first + j], &g_dep[lo + first + j], dep[j]);
+                    moved = true;
+                } else {
+                    left = true;
                 }
             }
-            // what wave 1 took from the inbox: the node's depth bound is applied, one dependency comes off
-            for (u32 base = seen; base < avail; base += 64) {
-                const u32 j = base + lane;
-                bool ready = false;
-                u32 sl = 0;
-                if (j < avail) { sl = s_in[j]; ready = atomicSub(&s_pending[sl], 1u) == 1u; }
-                const u64 m = __ballot(ready);
-                if (ready) s_queue[new_tail + (u32)__popcll(m & lt_mask)] = (unsigned short)sl;
-                new_tail += (u32)__popcll(m);
+        }
+        if (__ballot(left) == 0ull) break;
+        bool progress = __ballot(moved) != 0ull;
+        ++sweep;
+        if (any_ext && (idle > 1u || (sweep & 15u) == 0u)) {
+            // operands of lower ranges that are not known yet
+            bool got = false, more = false;
+#pragma unroll
+            for (u32 j = 0; j < DEPTH_NPT; ++j) {
+                u32 w[DEPTH_OPS];
+#pragma unroll
+                for (u32 q = 0; q < DEPTH_OPS; ++q) {
+                    w[q] = 0;
+                    if (op[j][q] & DEPTH_EXT)
+                        w[q] = __hip_atomic_load(&g_dep[op[j][q] & ~DEPTH_EXT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (u32 q = 0; q < DEPTH_OPS; ++q) {
+                    if (w[q]) { ext[j] = w[q] > ext[j] ? w[q] : ext[j]; op[j][q] = DEPTH_ONE; got = true; }
+                    more = more || (op[j][q] & DEPTH_EXT);
+                }
             }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            done += tail - head;
-            const bool idle = head == tail && new_tail == tail && seen == avail;   // nothing to do: waiting for another range
-            seen = avail;
-            head = tail;
-            tail = new_tail;
-            if (idle) {
-                if (++spin > spin_limit) break;     // bounded: the host then runs the single-workgroup pass instead
-                __builtin_amdgcn_s_sleep(4);
-            } else {
-                spin = 0;
+            any_ext = __ballot(more) != 0ull;
+            progress = progress || __ballot(got) != 0ull;
+        }
+        if (!progress && wide_i < n_wide) {
+            const u32 l = __builtin_amdgcn_readfirstlane((u32)s_wide[wave][wide_i]), v = lo + l;
+            const u32 a = T.in_off[v], ar = T.in_off[v + 1] - a;
+            u32 id[DEPTH_WIDE_READS], w[DEPTH_WIDE_READS];
+#pragma unroll
+            for (u32 q = 0; q < DEPTH_WIDE_READS; ++q) {
+                const u32 e = wide_e + 64u * q + lane;
+                id[q] = e < ar ? T.in_idx[a + e] : 0xffffffffu;
+            }
+#pragma unroll
+            for (u32 q = 0; q < DEPTH_WIDE_READS; ++q) {
+                w[q] = 1u;
+                if (id[q] < lo) w[q] = __hip_atomic_load(&g_dep[id[q]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else if (id[q] < v) w[q] = lds_load(&s_dep[id[q] - lo]);
+            }
+            bool all = true;
+#pragma unroll
+            for (u32 q = 0; q < DEPTH_WIDE_READS; ++q) {
+                all = all && __ballot(w[q] == 0u) == 0ull;
+                if (all) { wide_max = w[q] > wide_max ? w[q] : wide_max; wide_e += 64u; progress = true; }
+            }
+            if (wide_e >= ar) {
+                for (int o = 32; o > 0; o >>= 1) { const u32 t = (u32)__shfl_xor((int)wide_max, o); wide_max = t > wide_max ? t : wide_max; }
+                if (lane == 0) depth_settle(&s_dep[l], &g_dep[v], wide_max + 1u);
+#pragma unroll
+                for (u32 j = 0; j < DEPTH_NPT; ++j) if (first + j == l) dep[j] = wide_max + 1u;
+                ++wide_i; wide_e = 0; wide_max = 0;
             }
         }
-        if (lane == 0) s_done = done;
-        __hip_atomic_store(&s_fin, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-    } else if (wave == 1) {
-        // inbox entries are posted after their slot is reserved: take them in order, stop at a hole
-        u32 seen = 0;
-        while (lds_load(&s_fin) == 0u) {
-            const u32 avail = __builtin_amdgcn_readfirstlane(__hip_atomic_load(&inbox_tail[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            if (seen >= avail) { __builtin_amdgcn_s_sleep(2); continue; }
-            const u32 j = seen + lane;
-            u32 sn = DEPTH_NONE;
-            if (j < avail) sn = __hip_atomic_load(&inbox[k * DEPTH_PART + j], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-            const u32 in_chunk = avail - seen < 64u ? avail - seen : 64u;
-            const u64 holes = __ballot(j < avail && sn == DEPTH_NONE);
-            const u32 good = holes ? (u32)__builtin_ctzll(holes) : in_chunk;
-            if (lane < good) {
-                const u32 sl = sn - lo;
-                atomicMax(&s_dep[sl], __hip_atomic_load(&g_dep[sn], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                s_in[j] = (unsigned short)sl;
-            }
-            seen += good;
-            if (good) __hip_atomic_store(&s_in_tail, seen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (progress) { idle = 0; continue; }
+        if (++idle > spin_limit || lds_load(&s_quit) != 0u) { gave_up = true; break; }
+        // (a range that gave up leaves its error flag: ranges waiting for it need not run into their own bound)
+        if ((idle & 1023u) == 0u && (__hip_atomic_load(&T.hdr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (u32)ERR_CYCLE)) {
+            gave_up = true;
+            break;
         }
-    } else if (wave == 2) {
-        u32 head = 0;
-        while (true) {
-            const u32 fin = lds_load(&s_fin);
-            const u32 tail = __builtin_amdgcn_readfirstlane(__hip_atomic_load(&s_out_tail, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
-            if (head == tail) {
-                if (fin) break;
-                __builtin_amdgcn_s_sleep(1);
-                continue;
-            }
-            const u32 j = head + lane;
-            if (j < tail) depth_post_external(T, s_out_sn[j % DEPTH_OUT_CAP], s_out_d1[j % DEPTH_OUT_CAP], g_dep, inbox, inbox_tail);
-            head += tail - head < 64u ? tail - head : 64u;
-            __hip_atomic_store(&s_out_head, head, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        if (idle > 16u) __builtin_amdgcn_s_sleep(1);
     }
-    __syncthreads();
-    for (u32 i = tid; i < cnt; i += DEPTH_THREADS) T.step[lo + i] = s_dep[i];
-    if (tid == 0) {
-        atomicAdd(&T.hdr->frontier_done, s_done);
-        if (s_done != cnt) atomicOr(&T.hdr->err, (u32)ERR_CYCLE);
+    u32 done = 0;
+#pragma unroll
+    for (u32 j = 0; j < DEPTH_NPT; ++j) {
+        const u32 v = lo + first + j;
+        // A node that was given up on takes its own id as its step: above the step of every operand (a depth
+        // is at most the id), so what the later stages build from it before the host sees the error flag
+        // stays inside their tables.
+        if (v < T.n) T.step[v] = dep[j] ? dep[j] - 1u : v;
+        done += (u32)__popcll(__ballot(v < T.n && dep[j] != 0u));
+    }
+    if (lane == 0) {
+        atomicAdd(&T.hdr->frontier_done, done);
+        if (gave_up) { s_quit = 1u; atomicOr(&T.hdr->err, (u32)ERR_CYCLE); }
     }
 }
 
@@ -1751,19 +1751,17 @@ int sched_enqueue(ob_ctx *ctx)
     } while (0)
     // Tables that must start at zero lie next to each other, and so do those that start as all ones:
     // two fills clear them all.
-    u32 *g_dep, *inbox, *inbox_tail;
-    const u32 n_parts = (n + DEPTH_PART - 1) / DEPTH_PART;
+    u32 *g_dep;
     u32 *bset, *blist;
     AgendaTables AG{};
     char *zero_lo = (char *)ctx->arena + ctx->top;
     A(T.hdr, SchedHeader, 1);
-    A(T.outdeg, u32, n + 1); A(T.qcount, u32, 64); A(T.ext_indeg, u32, n + 1); A(T.ext_left, u32, n + 1);
-    A(g_dep, u32, n + 1); A(inbox_tail, u32, n_parts + 1);
+    A(T.outdeg, u32, n + 1); A(T.qcount, u32, 64); A(g_dep, u32, n + 1);
     A(T.pu_start, u32, n_slots); A(T.pu_end, u32, n_slots);
     A(T.ht_keys, u64, ht_size); A(bset, u32, BSET_SIZE);
     if (agenda) { A(AG.keys, u64, AG_TABLE); A(AG.sum, u64, AG_TABLE); A(AG.cnt, u32, AG_TABLE); }
     char *zero_hi = (char *)ctx->arena + ctx->top;
-    A(inbox, u32, (size_t)n_parts * DEPTH_PART); A(T.ht_vals, u32, ht_size);
+    A(T.ht_vals, u32, ht_size);
     if (agenda) A(AG.first, u32, AG_TABLE);
     char *ones_hi = (char *)ctx->arena + ctx->top;
     A(T.sig, u64, n); A(T.step, u32, n); A(T.indeg, u32, n);
@@ -1817,7 +1815,7 @@ int sched_enqueue(ob_ctx *ctx)
     // ---- stage 1 ----
     HIP_TRY(ctx, hipMemsetAsync(zero_lo, 0, (size_t)(zero_hi - zero_lo), s));
     HIP_TRY(ctx, hipMemsetAsync(zero_hi, 0xff, (size_t)(ones_hi - zero_hi), s));
-    const bool part_depth = by_depth && n_parts <= DEPTH_MAX_PARTS && ctx->max_arity < 60000 && !ctx->force_frontier;
+    const bool part_depth = by_depth && ctx->max_arity < DEPTH_MAX_ARITY && !ctx->force_frontier;
     ctx->depth_partitioned = part_depth;
     K(k_node_init, n, T, manual ? 2 : by_depth);
     if (E > 0) K(k_edge_init, E, T, ctx->key_a, ctx->val_a);
@@ -1834,8 +1832,8 @@ int sched_enqueue(ob_ctx *ctx)
     // ---- stage 2 / 3 ----
     if (by_depth) {
         if (part_depth)
-            hipLaunchKernelGGL(k_depth_partitioned, dim3(n_parts), dim3(DEPTH_THREADS), 0, s, T, succ_node, g_dep, inbox,
-                               inbox_tail, ctx->depth_spin_limit);
+            hipLaunchKernelGGL(k_depth_partitioned, dim3(blocks_for(n, DEPTH_PART)), dim3(DEPTH_THREADS), 0, s, T, g_dep,
+                               ctx->depth_spin_limit);
         else
             hipLaunchKernelGGL(k_depth_frontier, dim3(1), dim3(FRONTIER_THREADS), 0, s, T, succ_node);
         ++ctx->n_launch_sched;

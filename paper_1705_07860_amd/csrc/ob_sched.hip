@@ -22,62 +22,78 @@ __device__ inline u64 comb(u64 h, u64 x) { return mix64(h ^ (x + 0x9e3779b97f4a7
 // ---- stage 1: signatures, dependency counters, out-degrees, initial frontier ---------------
 // Signature tuple (Section 3.2 / Appendix A): operation, output dimension, arity, shared
 // parameter ids (the A and y of A x + y), slice range, operand dimensions.  LOOKUP's row,
-// PICK_NLS's label and INPUT's payload are data and stay out.  The node's own fields are hashed
-// here; every operand edge then adds a position-salted hash of the operand's dimension
-// (k_edge_init), so nodes with thousands of operands cost no more than a thread per edge.
-// steps: 0 = every node is its own step, 1 = steps come from the depth pass (leaves are queued
-// here), 2 = steps are the caller's batch labels.
-__global__ void k_node_init(Tables T, int steps)
+// PICK_NLS's label and INPUT's payload are data and stay out.  The operands' dimensions enter as a
+// sum of position-salted hashes, so that a node with many operands can be summed by many threads.
+// A thread takes a node with up to INIT_OPS operands, edges included; nodes with more are left to the whole
+// workgroup, one after the other.  (A launch with a thread per edge had to look its node up by bisection and
+// meet all operands of a wide sum in atomics on one signature: 23 us for 52 000 edges, 169 us for 480 000 of
+// which one node holds 10 000, beside 8 and 16 us of this kernel without the edges; 10.5 and 37 us together now.)
+// steps: 0 = every node is its own step, 1 = steps come from the depth pass by id ranges, 2 = steps are the
+// caller's batch labels, 3 = steps come from the single-workgroup depth pass (leaves are queued here).
+constexpr u32 INIT_OPS = 8;
+__device__ inline u64 operand_hash(const Tables &T, u32 u, u32 j) { return mix64(comb(0x5bd1e995ULL + j, T.out_dim[u])); }
+__global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *keys, u32 *vals)
 {
+    __shared__ u32 s_wide[TPB], s_n;
+    __shared__ u64 s_sum;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
     const u32 v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= T.n) return;
-    const u32 lo = T.in_off[v], hi = T.in_off[v + 1];
-    const u32 o = T.op[v];
-    u64 h = mix64(o + 1);
-    h = comb(h, T.out_dim[v]);
-    h = comb(h, hi - lo);
-    h = comb(h, (u64)(u32)(T.param[v] + 1));
-    h = comb(h, (u64)(u32)(T.bias[v] + 1));
-    h = comb(h, o == OP_SLICE ? (u64)(u32)T.aux0[v] : 0);
-    h = comb(h, o == OP_SLICE ? (u64)(u32)T.aux1[v] : 0);
-    T.sig[v] = h;
-    T.indeg[v] = hi - lo;
-    if (steps == 1) {
-        if (hi == lo) {
-            const u32 pos = atomicAdd(&T.qcount[0], 1u);
-            T.queue[pos] = v;
-            T.step[v] = 0;
+    if (v < T.n) {
+        const u32 lo = T.in_off[v], hi = T.in_off[v + 1];
+        const u32 o = T.op[v];
+        u64 h = mix64(o + 1);
+        h = comb(h, T.out_dim[v]);
+        h = comb(h, hi - lo);
+        h = comb(h, (u64)(u32)(T.param[v] + 1));
+        h = comb(h, (u64)(u32)(T.bias[v] + 1));
+        h = comb(h, o == OP_SLICE ? (u64)(u32)T.aux0[v] : 0);
+        h = comb(h, o == OP_SLICE ? (u64)(u32)T.aux1[v] : 0);
+        if (hi - lo <= INIT_OPS) {
+            for (u32 e = lo; e < hi; ++e) {
+                const u32 u = T.in_idx[e];
+                T.edge_cons[e] = v;
+                keys[e] = u;
+                vals[e] = e;
+                atomicAdd(&T.outdeg[u], 1u);
+                h += operand_hash(T, u, e - lo);
+            }
+        } else {
+            s_wide[atomicAdd(&s_n, 1u)] = v;
         }
-    } else if (steps == 2) {
-        T.step[v] = T.manual[v];   // manual batching: replaced by the label's rank once batches are cut
-    } else {
-        T.step[v] = v;   // unbatched: every node is its own step, in id order
+        T.sig[v] = h;
+        if (steps == 3) {
+            T.indeg[v] = hi - lo;
+            if (hi == lo) {
+                const u32 pos = atomicAdd(&T.qcount[0], 1u);
+                T.queue[pos] = v;
+                T.step[v] = 0;
+            }
+        } else if (steps == 2) {
+            T.step[v] = T.manual[v];   // manual batching: replaced by the label's rank once batches are cut
+        } else if (steps == 0) {
+            T.step[v] = v;   // unbatched: every node is its own step, in id order
+        }
     }
-}
-
-// consumer node of edge e: the v with in_off[v] <= e < in_off[v+1]
-__device__ inline u32 consumer_of(const Tables &T, u32 e)
-{
-    u32 lo = 0, hi = T.n;   // invariant: in_off[lo] <= e < in_off[hi]
-    while (hi - lo > 1) {
-        const u32 mid = (lo + hi) >> 1;
-        if (T.in_off[mid] <= e) lo = mid; else hi = mid;
+    __syncthreads();
+    for (u32 i = 0; i < s_n; ++i) {
+        const u32 w = s_wide[i], lo = T.in_off[w], hi = T.in_off[w + 1];
+        if (threadIdx.x == 0) s_sum = 0;
+        __syncthreads();
+        u64 sum = 0;
+        for (u32 e = lo + threadIdx.x; e < hi; e += TPB) {
+            const u32 u = T.in_idx[e];
+            T.edge_cons[e] = w;
+            keys[e] = u;
+            vals[e] = e;
+            atomicAdd(&T.outdeg[u], 1u);
+            sum += operand_hash(T, u, e - lo);
+        }
+        atomicAdd((unsigned long long *)&s_sum, (unsigned long long)sum);
+        __syncthreads();
+        if (threadIdx.x == 0) T.sig[w] += s_sum;
+        __syncthreads();
     }
-    return lo;
-}
-
-__global__ void k_edge_init(Tables T, u64 *keys, u32 *vals)
-{
-    const u32 e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= T.E) return;
-    const u32 v = consumer_of(T, e);
-    const u32 u = T.in_idx[e];
-    const u32 j = e - T.in_off[v];
-    T.edge_cons[e] = v;
-    atomicAdd(&T.outdeg[u], 1u);
-    atomicAdd((unsigned long long *)&T.sig[v], (unsigned long long)mix64(comb(0x5bd1e995ULL + j, T.out_dim[u])));
-    keys[e] = u;
-    vals[e] = e;
 }
 
 // after the sort: succ_edge[q] = edge id, succ_node[q] = its consumer (stored in T.queue's
@@ -606,6 +622,13 @@ __global__ void k_batch_off(Tables T, const u32 *head_flag, const Tri *before, u
     }
 }
 
+// Takes bits off a batch's flags.  Flags only fall, so whatever a look returns is safe to act on, and all
+// members of a batch mostly take off the same bits: only the first pay for an atomic on the one word.
+__device__ inline void flags_off(BatchRec &r, u32 bits)
+{
+    if (__hip_atomic_load(&r.vec4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bits) atomicAnd(&r.vec4, ~bits);
+}
+
 __host__ __device__ inline u32 cdiv(u64 a, u32 b) { return (u32)((a + b - 1) / b); }
 
 // one thread per batch: record + sizes for the layout scan (entries b >= n_batches are zero)
@@ -677,7 +700,7 @@ __global__ void k_node_offsets(Tables T)
         const u32 ar = T.in_off[v + 1] - T.in_off[v];
         bool ok = ar <= XP_MAX;
         for (u32 j = 0; ok && j < ar; ++j) ok = (T.out_dim[T.in_idx[T.in_off[v] + j]] & 3u) == 0;
-        if (!ok) atomicAnd(&r.vec4, ~(u32)TF_VIRT);
+        if (!ok) flags_off(r, TF_VIRT);
     }
     // a product whose operand is a CONCAT node: the lowest such CONCAT batch gives the piece structure of the batch
     if (r.op == OP_MATVEC && (r.vec4 & TF_XP)) {
@@ -714,7 +737,7 @@ __device__ inline void xp_check(const Tables &T, u32 p, BatchRec &r)
     const u32 P = rr.arity;
     bool ok = (rr.vec4 & TF_VIRT) && T.in_off[x + 1] - T.in_off[x] == P;
     for (u32 j = 0; ok && j < P; ++j) ok = T.out_dim[T.in_idx[T.in_off[x] + j]] == T.out_dim[T.in_idx[T.in_off[hr] + j]];
-    if (!ok) { atomicAnd(&r.vec4, ~(u32)TF_XP); return; }
+    if (!ok) { flags_off(r, TF_XP); return; }
     if (T.batch_of_pos[T.pos_of[x]] == (u32)r.aux0) {   // (every such row writes the same values)
         r.aux1 = (i32)P;
         for (u32 j = 0; j < P; ++j) T.b_indim[r.indim + j] = T.out_dim[T.in_idx[T.in_off[x] + j]];
@@ -738,10 +761,10 @@ __global__ void k_member_check(Tables T)
     if (r.op == OP_SLICE) vec = vec && ((u32)r.aux0 & 3u) == 0;
     if (r.op == OP_INPUT) vec = vec && ((u32)T.aux0[v] & 3u) == 0;
     if (!same) atomicOr(&T.hdr->err, (u32)ERR_COLLISION);
-    if (!vec) atomicAnd(&r.vec4, ~(u32)TF_VEC4);
+    if (!vec) flags_off(r, TF_VEC4);
     // A one-element MATVEC node may become the backward root (chosen after scheduling): its gradient is
     // the seed, not its consumer's row, so such batches never alias.
-    if (r.op == OP_MATVEC && (T.outdeg[v] != 1 || r.d == 1)) atomicAnd(&r.vec4, ~(u32)TF_G_ALIAS);
+    if (r.op == OP_MATVEC && (T.outdeg[v] != 1 || r.d == 1)) flags_off(r, TF_G_ALIAS);
     xp_check(T, p, r);
 }
 
@@ -769,7 +792,7 @@ __global__ void k_opnd(Tables T)
     // an edge into a CONCAT node: any reader that is not a product reading in pieces needs the row in place
     if (T.op[u] == OP_CONCAT && !xp) {
         BatchRec &ru = T.batches[T.batch_of_pos[T.pos_of[u]]];
-        if (ru.vec4 & TF_VIRT) atomicAnd(&ru.vec4, ~(u32)TF_VIRT);
+        if (ru.vec4 & TF_VIRT) flags_off(ru, TF_VIRT);
     }
     if (xp) {
         // the operand in pieces: the rows of a CONCAT node's operands (where the producers left them, whether or
@@ -781,15 +804,15 @@ __global__ void k_opnd(Tables T)
             u32 off = T.val_off[u];
             if (pieces) { const u32 w = T.in_idx[T.in_off[u] + q]; off = T.val_off[w] - start; start += T.out_dim[w]; }
             T.opnd_off[r.opnd + q * r.B + row] = off;
-            if (off & 3u) atomicAnd(&r.vec4, ~(u32)(TF_VEC4 | TF_ALIGNED));
+            if (off & 3u) flags_off(r, (TF_VEC4 | TF_ALIGNED));
         }
         return;
     }
     const u32 off = T.val_off[u];
     T.opnd_off[r.opnd + j * r.B + row] = off;
     if (row == 0) T.b_indim[r.indim + j] = du;
-    if (off & 3u) atomicAnd(&r.vec4, ~(u32)(TF_VEC4 | TF_ALIGNED));
-    else if (r.op == OP_CONCAT && (du & 3u)) atomicAnd(&r.vec4, ~(u32)TF_VEC4);
+    if (off & 3u) flags_off(r, (TF_VEC4 | TF_ALIGNED));
+    else if (r.op == OP_CONCAT && (du & 3u)) flags_off(r, TF_VEC4);
 }
 
 // ---- launch planning ---------------------------------------------------------------------------------
@@ -1641,7 +1664,7 @@ __global__ void k_edges(Tables T)
     if (T.op[u] == OP_MATVEC) {
         const u32 pu = T.pos_of[u];
         T.dx_gsrc[pu] = r.goff;
-        if (r.kind != EK_PLAIN || (r.goff & 3u)) atomicAnd(&T.batches[T.batch_of_pos[pu]].vec4, ~(u32)TF_G_ALIAS);
+        if (r.kind != EK_PLAIN || (r.goff & 3u)) flags_off(T.batches[T.batch_of_pos[pu]], TF_G_ALIAS);
     }
 }
 
@@ -1817,8 +1840,7 @@ int sched_enqueue(ob_ctx *ctx)
     HIP_TRY(ctx, hipMemsetAsync(zero_hi, 0xff, (size_t)(ones_hi - zero_hi), s));
     const bool part_depth = by_depth && ctx->max_arity < DEPTH_MAX_ARITY && !ctx->force_frontier;
     ctx->depth_partitioned = part_depth;
-    K(k_node_init, n, T, manual ? 2 : by_depth);
-    if (E > 0) K(k_edge_init, E, T, ctx->key_a, ctx->val_a);
+    K(k_node_init, n, T, manual ? 2 : (by_depth ? (part_depth ? 1 : 3) : 0), ctx->key_a, ctx->val_a);
     HIP_TRY(ctx, prim_scan_u32(T.outdeg, T.succ_off, (size_t)n + 1, nullptr, ctx->scratch, s));
     // a scan of a short array is one launch, up to 256 blocks of 1024 elements two, beyond that three
     const int scan_launches = (size_t)n + 1 <= 4096 ? 1 : ((size_t)n + 1 <= 256 * 1024 ? 2 : 3);

@@ -827,10 +827,7 @@ int ob_upload(ob_ctx *ctx)
     ctx->top = ctx->persist_top;
     if (ctx->params_dirty)
         if (int rc = upload_param_tables(ctx)) return rc;
-    if (!ctx->hdr_pinned) {
-        ctx->hdr_pinned_bytes = 1 << 16;
-        HIP_TRY(ctx, hipHostMalloc(&ctx->hdr_pinned, ctx->hdr_pinned_bytes, hipHostMallocDefault));
-    }
+    if (!ctx->hdr_pinned) HIP_TRY(ctx, hipHostMalloc(&ctx->hdr_pinned, PINNED_BYTES, hipHostMallocDefault));
 
     const size_t n = ctx->op.size(), E = ctx->in_idx.size(), P = ctx->payload.size();
     // one block of the arena: op | out_dim | in_off | in_idx | param | bias | aux0 | aux1 | payload | labels,
@@ -1367,12 +1364,20 @@ static int node_read(ob_ctx *ctx, int node, float *out, size_t cap, bool grad)
     }
     const u32 d = ctx->out_dim[node];
     if (cap < d) return ctx_fail(ctx, OB_E_RANGE, "buffer holds %zu of %u elements", cap, d);
-    if (!grad) if (int rc = fill_uncopied(ctx, ctx->stream)) return rc;
-    u32 off = 0;
-    HIP_TRY(ctx, hipMemcpyAsync(&off, (grad ? ctx->T.nat_off : ctx->T.val_off) + node, 4, hipMemcpyDeviceToHost, ctx->stream));
+    // (only a CONCAT node's row can be missing: a slice, the one node whose values lie in another's row, keeps a
+    // CONCAT it reads from staying uncopied)
+    if (!grad && ctx->op[node] == OP_CONCAT) if (int rc = fill_uncopied(ctx, ctx->stream)) return rc;
+    const float *arena = grad ? ctx->T.G : ctx->T.V;
+    u32 *head = (u32 *)((char *)ctx->hdr_pinned + READ_AT);
+    float *row = (float *)(head + 4);
+    const u32 here = d < (u32)READ_FLOATS ? d : (u32)READ_FLOATS;
+    HIP_TRY(ctx, exec_node_read(grad ? ctx->T.nat_off : ctx->T.val_off, arena, (u32)node, here, head, row, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(out, (grad ? ctx->T.G : ctx->T.V) + off, (size_t)d * 4, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    memcpy(out, row, (size_t)here * 4);
+    if (here < d) {
+        HIP_TRY(ctx, hipMemcpyAsync(out + here, arena + head[0] + here, (size_t)(d - here) * 4, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    }
     return OB_OK;
 }
 

@@ -60,6 +60,13 @@ struct HostParam {
 
 struct ob_ctx;
 
+// The context's pinned block: [schedule header, 256 B][first SLOT_WINDOW entries of the slot table][a row that is read]
+constexpr size_t SLOT_WINDOW = 2048;   // per-slot table entries read back together with the header
+constexpr size_t READ_AT = 256 + SLOT_WINDOW * sizeof(SlotRec);
+constexpr size_t READ_FLOATS = 4096;   // floats of a row that k_node_read leaves here itself (behind a 16-byte head)
+constexpr size_t PINNED_BYTES = READ_AT + 16 + READ_FLOATS * sizeof(float);
+static_assert(sizeof(SchedHeader) <= 256 && READ_AT % 16 == 0, "pinned block layout");
+
 // One later evaluation of a graph that grew after it was evaluated (Section 3.1): the nodes
 // [n0, n1) as a graph of their own in a context of their own, whose first proxy.size() nodes are
 // leaves that hold copies of the earlier values the new nodes read.
@@ -141,8 +148,7 @@ struct ob_ctx {
     u32 *tmp_u32_a = nullptr, *tmp_u32_b = nullptr;   // n+1 words each
     Lay *lay_in = nullptr, *lay_total = nullptr;
     u32 *scalars = nullptr;            // small device scalars
-    void *hdr_pinned = nullptr;        // pinned host mirror for the header + step tables
-    size_t hdr_pinned_bytes = 0;
+    void *hdr_pinned = nullptr;        // pinned host memory, PINNED_BYTES: header and slot tables of a schedule, value reads
 
     // events / stats
     hipEvent_t ev[10] = {};

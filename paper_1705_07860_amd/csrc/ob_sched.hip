@@ -1733,7 +1733,6 @@ inline int bit_width_u32(u32 x) { int b = 0; while (x) { ++b; x >>= 1; } return 
         }                                                                                               \
     } while (0)
 
-constexpr size_t SLOT_WINDOW = 2048;   // per-slot table entries read back together with the header
 
 // First half of scheduling: allocates the scheduler tables for n nodes / E edges in the arena and
 // queues every stage on the schedule stream, ending with the device-to-host copies of the header
@@ -1938,13 +1937,6 @@ int sched_enqueue(ob_ctx *ctx)
     // ---- queue the read-back of the header and of a first window of the per-slot tables ----
     // pinned layout: [header 256 B][first hdr_window entries of the slot table]
     ctx->hdr_window = (u32)(slot_cap < SLOT_WINDOW ? slot_cap : SLOT_WINDOW);
-    const size_t need = 256 + (size_t)ctx->hdr_window * sizeof(SlotRec);
-    if (need > ctx->hdr_pinned_bytes) {
-        if (ctx->hdr_pinned) HIP_TRY(ctx, hipHostFree(ctx->hdr_pinned));
-        ctx->hdr_pinned = nullptr;
-        ctx->hdr_pinned_bytes = need + 4096;
-        HIP_TRY(ctx, hipHostMalloc(&ctx->hdr_pinned, ctx->hdr_pinned_bytes, hipHostMallocDefault));
-    }
     char *hp = (char *)ctx->hdr_pinned;
     HIP_TRY(ctx, hipMemcpyAsync(hp, T.hdr, sizeof(SchedHeader), hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipMemcpyAsync(hp + 256, T.slots, (size_t)ctx->hdr_window * sizeof(SlotRec), hipMemcpyDeviceToHost, s));

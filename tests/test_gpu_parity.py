@@ -1517,3 +1517,31 @@ def test_full_size_pipelined_loop_as_benchmarked(workload_cache, mode, lookahead
         assert rel_err(ctxs[0].param_grad_read(pid, m.shape), oracles[last].param_grad(pid)) <= TOL, p.names[pid]
     for c in reversed(ctxs):
         c.close()
+
+
+@pytest.mark.parametrize("d", [1, 3, 255, 4095, 4096, 4097, 9001])
+def test_reading_one_node_of_any_width(d):
+    """ob_value_read / ob_grad_read leave up to 4096 elements of a row in pinned memory themselves and copy the rest:
+    widths around both sides of that.  An input's value must come back bit for bit (so must the row of a CONCAT
+    nobody reads, which the forward pass may leave unwritten); tanh rounds within 4 units of 2^-24, the gradient
+    g = 2 t (1 - t^2) of sum t^2 is four such roundings."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(d)
+    pb = wl.ParamBuilder(rng)
+    pb.add("W", 4, 4)
+    p = pb.done()
+    gb = wl.GraphBuilder(p)
+    x0, y0 = rng.standard_normal(d).astype(np.float32), rng.standard_normal(4).astype(np.float32)
+    x, y = gb.input(x0), gb.input(y0)
+    cat = gb.concat((y, y))
+    t = gb.tanh(x)
+    g = gb.finish(gb.sqnorm(t), 1)
+    c, root = run_gpu(p, g, ob.OB_BYDEPTH, arena=64 << 20)
+    c.backward(root)
+    th = np.tanh(x0.astype(np.float64))
+    assert np.array_equal(c.value_read(x, d), x0)
+    assert np.array_equal(c.value_read(cat, 8), np.concatenate([y0, y0]))
+    assert np.abs(c.value_read(t, d) - th).max() <= 4 * 2.0 ** -24
+    assert np.abs(c.grad_read(x, d) - 2 * th * (1 - th * th)).max() <= 32 * 2.0 ** -24
+    assert rel_err(c.value_read(root, 1), np.asarray([np.sum(th * th)])) <= TOL
+    c.close()

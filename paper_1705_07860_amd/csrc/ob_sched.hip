@@ -1265,7 +1265,8 @@ __global__ void k_slot_fill(Tables T)
 // ---- tile descriptors ------------------------------------------------------------------------------
 constexpr u32 CONTIG_MAX_ROWS = 64;   // tiles with more rows skip the even-spacing test
 
-// Where a tile of a fused chain sits: chain, member, block of groups [g0, g0 + ng).
+// Where a tile of a fused chain sits: chain, member, block of groups [g0, g0 + ng).  (Handed on by reference with a flag
+// beside it: a pointer that may be null would keep it in scratch memory.)
 struct ChainCtx { ChainRec cr; u32 m, g0, ng; };
 
 
@@ -1273,10 +1274,13 @@ struct ChainCtx { ChainRec cr; u32 m, g0, ng; };
 // through slot j; offsets in the value arena, which the gradient arena mirrors): state 0 = no
 // member of the chain produces these rows, 1 = all of them lie in this block's rows of one member
 // (LDS index = offset + delta[j]), 2 = produced in the chain but not covered by one region.
-__device__ inline void chain_lookup(const Tables &T, const ChainCtx &cc, u32 ns, const u32 *lo, const u32 *hi,
-                                    u32 *state, u32 *delta)
+// (Loops over slots and edges run to four with the count as a guard, here and below: an array that is indexed by
+// a counter the compiler cannot unroll lives in scratch memory, and these kernels are bound by their reads as it is.)
+__device__ inline void chain_lookup(const Tables &T, const ChainCtx &cc, u32 ns, const u32 (&lo)[4], const u32 (&hi)[4],
+                                    u32 (&state)[4], u32 (&delta)[4])
 {
-    for (u32 j = 0; j < ns; ++j) { state[j] = 0; delta[j] = 0; }
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) { state[j] = 0; delta[j] = 0; }
     u32 lds = 0;
     for (u32 mm = 0; mm < cc.cr.k; ++mm) {
         const BatchRec &y = T.batches[T.lorder[cc.cr.first + mm]];
@@ -1284,8 +1288,9 @@ __device__ inline void chain_lookup(const Tables &T, const ChainCtx &cc, u32 ns,
         const u32 full_lo = y.val_off, full_hi = y.val_off + y.B * y.d;
         const u32 ch_lo = y.val_off + cc.g0 * mult * y.d, ch_hi = ch_lo + cc.ng * mult * y.d;
         if (mm != cc.m) {
-            for (u32 j = 0; j < ns; ++j) {
-                if (hi[j] < full_lo || lo[j] >= full_hi) continue;
+#pragma unroll
+            for (u32 j = 0; j < 4; ++j) {
+                if (j >= ns || hi[j] < full_lo || lo[j] >= full_hi) continue;
                 if (state[j] == 0 && cc.cr.fused == 2u && lo[j] >= ch_lo && hi[j] < ch_hi) { state[j] = 1; delta[j] = lds - ch_lo; }
                 else state[j] = 2;
             }
@@ -1305,7 +1310,7 @@ __device__ inline u32 chain_own_delta(const Tables &T, const ChainCtx &cc, const
 // descriptor of a forward or dX tile of batch r.  Component-wise tiles (row_block) cover the rows
 // row0 + i * rstride, i < nrows; the other kinds derive their rows from the tile index t.
 __device__ inline void fill_tile_desc(const Tables &T, const BatchRec &r, u32 t, bool dx, bool row_block, u32 row0,
-                                      u32 nrows, u32 rstride, TileDesc &d, const ChainCtx *cc = nullptr)
+                                      u32 nrows, u32 rstride, TileDesc &d, bool in_chain, const ChainCtx &cc)
 {
     d.op = r.op; d.B = r.B; d.d = r.d; d.arity = r.arity;
     d.pos0 = r.pos0; d.val_off = r.val_off; d.dx_off = r.dx_off; d.k = r.k;
@@ -1365,7 +1370,10 @@ __device__ inline void fill_tile_desc(const Tables &T, const BatchRec &r, u32 t,
     const u32 ns = xp ? (u32)r.aux1 : (r.arity < 4 ? r.arity : 4);   // a product reading in pieces: one operand slot per piece
     if (xp) d.arity = ns;
     u32 lo[4], hi[4];
-    for (u32 j = 0; j < ns; ++j) {
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) {
+        lo[j] = hi[j] = 0;
+        if (j >= ns) continue;
         const u32 *op = T.opnd_off + r.opnd + j * r.B;
         const u32 base = op[row0];
         d.base[j] = base; d.sdim[j] = T.b_indim[r.indim + j];
@@ -1392,24 +1400,63 @@ __device__ inline void fill_tile_desc(const Tables &T, const BatchRec &r, u32 t,
     if (row_block && (d.flags & TF_VEC4) && r.arity >= 1 && r.arity <= 4 && (d.contig & 0xfu) == (1u << r.arity) - 1u &&
         (r.op == OP_ADD || r.op == OP_CMULT || r.op == OP_TANH || r.op == OP_SIGMOID || r.op == OP_SLICE))
         d.flags |= TF_SIMPLE;
-    if (!cc) return;
+    if (!in_chain) return;
     // tile of a fused chain: which operands come from the chain's LDS copy, and whether any
     // operand produced earlier in the same launch still has to come from global memory
-    if (cc->cr.fused != 2u || nrows > CONTIG_MAX_ROWS || r.arity > 4) { d.flags |= TF_GLOBAL_DEP; }
-    if (cc->cr.fused != 2u) return;
-    d.lds_out = chain_own_delta(T, *cc, r);
+    if (cc.cr.fused != 2u || nrows > CONTIG_MAX_ROWS || r.arity > 4) { d.flags |= TF_GLOBAL_DEP; }
+    if (cc.cr.fused != 2u) return;
+    d.lds_out = chain_own_delta(T, cc, r);
     d.flags |= TF_OUT_LDS;
     if (d.lds_out & 3u) d.flags &= ~(u32)(TF_VEC4 | TF_SIMPLE);   // (never with d % 4 == 0: regions and block rows start at multiples of 4)
     if (nrows > CONTIG_MAX_ROWS) return;
     u32 state[4], delta[4];
-    chain_lookup(T, *cc, ns, lo, hi, state, delta);
-    for (u32 j = 0; j < ns; ++j) {
+    chain_lookup(T, cc, ns, lo, hi, state, delta);
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) {
+        if (j >= ns) continue;
         if (state[j] == 1 && (!(d.flags & TF_VEC4) || (delta[j] & 3u) == 0)) { d.flags |= TF_SRC_LDS << j; d.lds_src[j] = delta[j]; }
         else if (state[j] != 0) d.flags |= TF_GLOBAL_DEP;
     }
 }
 
 constexpr u32 PULL_MAX_ROWS = 16;
+
+// The other rows of a pull tile must have the edges of its first row, shifted by constant strides.  Every step is a
+// read that depends on the one before (row -> node -> its consumer list -> the edge records), so each step is
+// taken for MAXR rows at once (rows past the tile's last repeat row 0: no read leaves the lists).
+template <u32 MAXR>
+__device__ inline bool pull_rows_uniform(const Tables &T, const BatchRec &r, u32 row0, u32 nrows, u32 rstride, u32 cnt,
+                                         PullDesc &d)
+{
+    u32 qs[MAXR];
+    bool same = true;
+#pragma unroll
+    for (u32 i = 1; i < MAXR; ++i) {
+        const u32 u = T.order[r.pos0 + row0 + (i < nrows ? i : 0u) * rstride];
+        qs[i] = T.succ_off[u];
+        same = same && T.succ_off[u + 1] - qs[i] == cnt;
+    }
+    if (!same) return false;
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) {
+        if (j >= cnt) continue;
+        EdgeRec er[MAXR];
+#pragma unroll
+        for (u32 i = 1; i < MAXR; ++i) er[i] = T.edges[qs[i] + j];
+        UEdge &f = d.e[j];
+        const u32 gs = er[1].goff - f.goff, vs = er[1].voff - f.voff;
+        bool ok = true;
+#pragma unroll
+        for (u32 i = 1; i < MAXR; ++i) {
+            if (i >= nrows) continue;
+            ok = ok && er[i].kind == f.kind && er[i].a0 == f.a0 && er[i].a1 == f.a1 && er[i].goff - f.goff == gs * i &&
+                 er[i].voff - f.voff == vs * i;
+        }
+        if (!ok) return false;
+        f.gs = gs; f.vs = vs;
+    }
+    return true;
+}
 
 __device__ inline void fill_pull_base(const Tables &T, const BatchRec &r, u32 row0, u32 nrows, u32 rstride, PullDesc &d)
 {
@@ -1418,86 +1465,67 @@ __device__ inline void fill_pull_base(const Tables &T, const BatchRec &r, u32 ro
     d.dshift = (r.d & (r.d - 1u)) == 0u && r.d ? (u32)__ffs(r.d) - 1u : PULL_NO_SHIFT;
     d.pos0 = r.pos0; d.B = r.B; d.d = r.d; d.val_off = r.val_off;
     d.depth = r.step; d.row0 = row0; d.nrows = nrows; d.n_uni = PULL_GENERIC; d.rstride = rstride;
-    for (int j = 0; j < 4; ++j) { UEdge z; z.kind = 0; z.goff = z.voff = z.gs = z.vs = 0; z.a0 = z.a1 = 0; z.dl = 0; d.e[j] = z; }
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) { UEdge z; z.kind = 0; z.goff = z.voff = z.gs = z.vs = 0; z.a0 = z.a1 = 0; z.dl = 0; d.e[j] = z; }
     d.grp_len = 1; d.vec4 = (r.vec4 & TF_VIEW) ? 2u : 0u;   // bit 1: the batch is a view (its values lie in its operands' rows)
     if (nrows > PULL_MAX_ROWS) return;
     const u32 u0 = T.order[r.pos0 + row0];
     const u32 q0 = T.succ_off[u0];
     const u32 cnt = T.succ_off[u0 + 1] - q0;
     if (cnt > 4) return;
-    EdgeRec first[4];
-    for (u32 j = 0; j < cnt; ++j) {
-        first[j] = T.edges[q0 + j];
-        if (first[j].kind == EK_NLS) return;     // the label is per-row data
-        if (first[j].kind == EK_SQN && (r.vec4 & TF_VIEW)) return;   // needs the rows' own values, which a view keeps elsewhere
-        UEdge ue; ue.kind = first[j].kind; ue.goff = first[j].goff; ue.voff = first[j].voff;
-        ue.gs = ue.vs = 0; ue.a0 = first[j].a0; ue.a1 = first[j].a1; ue.dl = 0;
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) {
+        if (j >= cnt) continue;
+        const EdgeRec first = T.edges[q0 + j];
+        if (first.kind == EK_NLS) return;     // the label is per-row data
+        if (first.kind == EK_SQN && (r.vec4 & TF_VIEW)) return;   // needs the rows' own values, which a view keeps elsewhere
+        UEdge ue; ue.kind = first.kind; ue.goff = first.goff; ue.voff = first.voff;
+        ue.gs = ue.vs = 0; ue.a0 = first.a0; ue.a1 = first.a1; ue.dl = 0;
         d.e[j] = ue;
     }
-    // The other rows must have the same edges, shifted by constant strides.  Every step is a read that
-    // depends on the one before (row -> node -> its consumer list -> the edge records), so each step is
-    // taken for all rows at once (rows past the tile's last repeat row 0: no read leaves the lists).
-    if (nrows > 1) {
-        u32 qs[PULL_MAX_ROWS];
-        bool same = true;
-#pragma unroll
-        for (u32 i = 1; i < PULL_MAX_ROWS; ++i) {
-            const u32 u = T.order[r.pos0 + row0 + (i < nrows ? i : 0u) * rstride];
-            qs[i] = T.succ_off[u];
-            same = same && T.succ_off[u + 1] - qs[i] == cnt;
-        }
-        if (!same) return;
-        for (u32 j = 0; j < cnt; ++j) {
-            EdgeRec er[PULL_MAX_ROWS];
-#pragma unroll
-            for (u32 i = 1; i < PULL_MAX_ROWS; ++i) er[i] = T.edges[qs[i] + j];
-            const u32 gs = er[1].goff - first[j].goff, vs = er[1].voff - first[j].voff;
-            bool ok = true;
-#pragma unroll
-            for (u32 i = 1; i < PULL_MAX_ROWS; ++i) {
-                if (i >= nrows) continue;
-                ok = ok && er[i].kind == first[j].kind && er[i].a0 == first[j].a0 && er[i].a1 == first[j].a1 &&
-                     er[i].goff - first[j].goff == gs * i && er[i].voff - first[j].voff == vs * i;
-            }
-            if (!ok) return;
-            d.e[j].gs = gs; d.e[j].vs = vs;
-        }
-    }
+    // (a tile of rows of 256 columns has four of them: sixteen rows' reads for four rows' use were most of this kernel)
+    if (nrows > 4u) { if (!pull_rows_uniform<PULL_MAX_ROWS>(T, r, row0, nrows, rstride, cnt, d)) return; }
+    else if (nrows > 1u) { if (!pull_rows_uniform<4>(T, r, row0, nrows, rstride, cnt, d)) return; }
     d.n_uni = cnt;
     bool vec = (r.d & 3u) == 0;
-    for (u32 j = 0; j < cnt; ++j) {
+    u32 worst = 0;
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) {
+        if (j >= cnt) continue;
         const UEdge &ue = d.e[j];
         const bool scalar_g = ue.kind == EK_SQN;                 // these read one gradient scalar per row
         if (!scalar_g && ((ue.goff | ue.gs) & 3u)) vec = false;
         if ((ue.kind == EK_MUL || ue.kind == EK_DTANH || ue.kind == EK_DSIGM) && ((ue.voff | ue.vs) & 3u)) vec = false;
         if (ue.kind == EK_RANGE && (((u32)ue.a0 | (u32)ue.a1) & 3u)) vec = false;
+        worst = ue.kind > worst ? ue.kind : worst;
     }
-    u32 worst = 0;
-    for (u32 j = 0; j < cnt; ++j) worst = d.e[j].kind > worst ? d.e[j].kind : worst;
     // (the short routine finds rows and columns by shifting: one row, or a power of two of columns)
     const bool shifts = nrows == 1u || d.dshift != PULL_NO_SHIFT;
     d.vec4 = (d.vec4 & 2u) | (vec ? 1u : 0u) | (vec && shifts && worst <= (u32)EK_DSIGM ? 4u : 0u);
 }
 
 __device__ inline void fill_pull_desc(const Tables &T, const BatchRec &r, u32 row0, u32 nrows, u32 rstride, PullDesc &d,
-                                      const ChainCtx *cc = nullptr)
+                                      bool in_chain, const ChainCtx &cc)
 {
     fill_pull_base(T, r, row0, nrows, rstride, d);
-    if (!cc) return;
+    if (!in_chain) return;
     // tile of a fused chain: consumer gradients computed earlier in the same launch come from the
     // chain's LDS copy where the whole tile finds them in one member's region
-    if (cc->cr.fused != 2u) { d.lflags = TF_GLOBAL_DEP; return; }
-    d.lds_out = chain_own_delta(T, *cc, r);
+    if (cc.cr.fused != 2u) { d.lflags = TF_GLOBAL_DEP; return; }
+    d.lds_out = chain_own_delta(T, cc, r);
     d.lflags = TF_OUT_LDS;
     if (d.lds_out & 3u) d.vec4 &= ~5u;
     if (d.n_uni == PULL_GENERIC) { d.lflags |= TF_GLOBAL_DEP; return; }
     u32 lo[4], hi[4], state[4], delta[4];
-    for (u32 j = 0; j < d.n_uni; ++j) {
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) {
         const u32 a = d.e[j].goff, b = d.e[j].goff + (nrows - 1) * d.e[j].gs;
         lo[j] = a < b ? a : b; hi[j] = a < b ? b : a;
     }
-    chain_lookup(T, *cc, d.n_uni, lo, hi, state, delta);
-    for (u32 j = 0; j < d.n_uni; ++j) {
+    chain_lookup(T, cc, d.n_uni, lo, hi, state, delta);
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) {
+        if (j >= d.n_uni) continue;
         if (state[j] == 1 && (!(d.vec4 & 1u) || (delta[j] & 3u) == 0)) { d.lflags |= TF_SRC_LDS << j; d.e[j].dl = delta[j]; }
         else if (state[j] != 0) d.lflags |= TF_GLOBAL_DEP;
     }
@@ -1507,7 +1535,9 @@ __device__ inline void fill_pull_desc(const Tables &T, const BatchRec &r, u32 ro
 __device__ inline void resolve_pull_desc(PullDesc &d)
 {
     if (d.n_uni == PULL_GENERIC) return;
-    for (u32 j = 0; j < d.n_uni; ++j) {
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) {
+        if (j >= d.n_uni) continue;
         if (d.e[j].kind == EK_RANGE) d.e[j].goff -= (u32)d.e[j].a0;
         if (d.lflags & (TF_SRC_LDS << j)) d.e[j].goff += d.e[j].dl;
     }
@@ -1529,7 +1559,10 @@ __device__ inline u32 chain_of_index(const CLay *clay_ex, u32 nc, int which, u32
     return lo;
 }
 
-__global__ void k_tiles(Tables T, const CLay *clay_ex, const CLay *total, u32 cap_f, u32 cap_a, u32 cap_b)
+// Bound by the chains of dependent reads behind an entry.  Everything an entry is put together from stays in registers
+// (147 of them, three waves a SIMD; with 400 bytes of scratch a lane it had four): 59 -> 27 us on the tagger, 200 -> 100 us
+// at 512 sentences, together with reading four rows' edges where a tile has at most four rows.
+__global__ __launch_bounds__(TPB) void k_tiles(Tables T, const CLay *clay_ex, const CLay *total, u32 cap_f, u32 cap_a, u32 cap_b)
 {
     const u32 nc = T.hdr->n_chains;
     const u32 gtid = blockIdx.x * blockDim.x + threadIdx.x, gsz = gridDim.x * blockDim.x;
@@ -1565,7 +1598,7 @@ __global__ void k_tiles(Tables T, const CLay *clay_ex, const CLay *total, u32 ca
             } else if (which == 2 || (which == 0 && !cr.fused)) {
                 const BatchRec r = T.batches[T.lorder[cr.first]];
                 TileDesc d;
-                fill_tile_desc(T, r, xx, which == 2, false, 0, 0, 1, d);
+                fill_tile_desc(T, r, xx, which == 2, false, 0, 0, 1, d, false, ChainCtx{});
                 (which == 0 ? T.tiles_f : T.tiles_b)[x] = d;
             } else {
                 // tile `it` of block rb: member m, its q-th row of every group in the block
@@ -1612,16 +1645,16 @@ __global__ void k_tiles(Tables T, const CLay *clay_ex, const CLay *total, u32 ca
                     }
                 }
                 ChainCtx cc; cc.cr = cr; cc.m = m; cc.g0 = g0; cc.ng = ng;
-                const ChainCtx *pcc = (cr.fused && ktx > 1) ? &cc : nullptr;
+                const bool in_chain = cr.fused && ktx > 1;
                 if (which == 1) {
                     PullDesc d;
-                    fill_pull_desc(T, r, row0, ng, mult, d, pcc);
+                    fill_pull_desc(T, r, row0, ng, mult, d, in_chain, cc);
                     resolve_pull_desc(d);
                     d.grp_len = glen;
                     T.tiles_a[x] = d;
                 } else {
                     TileDesc d;
-                    fill_tile_desc(T, r, xx, false, true, row0, ng, mult, d, pcc);
+                    fill_tile_desc(T, r, xx, false, true, row0, ng, mult, d, in_chain, cc);
                     d.contig |= (glen > 0xffffu ? 0xffffu : glen) << 16;
                     T.tiles_f[x] = d;
                 }

@@ -1545,3 +1545,32 @@ def test_reading_one_node_of_any_width(d):
     assert np.abs(c.grad_read(x, d) - 2 * th * (1 - th * th)).max() <= 32 * 2.0 ** -24
     assert rel_err(c.value_read(root, 1), np.asarray([np.sum(th * th)])) <= TOL
     c.close()
+
+
+@pytest.mark.parametrize("d", [512, 341, 256, 204, 64, 60])
+def test_pull_tiles_of_two_to_seventeen_rows(d):
+    """A pull tile holds as many rows as fit 1024 elements (2, 3, 4, 5, 16 and 17 here) and compares its rows' consumer
+    edges four or sixteen rows at a time.  Every odd group of nine rows has one row with one consumer more, at each
+    place of a tile in turn, so tiles with equal rows and with one row out of line both occur."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(d)
+    pb = wl.ParamBuilder(rng, std=0.3)
+    W = pb.add("W", d, 8)
+    p = pb.done()
+    gb = wl.GraphBuilder(p)
+    losses = []
+    for i in range(40):
+        y = gb.matvec(W, -1, gb.input(rng.standard_normal(8)))
+        t, s = gb.tanh(y), gb.sigmoid(y)
+        losses.append(gb.sqnorm(gb.cmult(t, s)))
+        if (i // 9) % 2 and i % 9 == (i // 9) % 9:
+            losses.append(gb.sqnorm(gb.tanh(t)))
+    root = gb.add(losses)
+    g = gb.finish(root, 40)
+    o = Oracle(g, p, "f64")
+    o.forward()
+    o.backward(g.root)
+    for fuse in (2, 0):
+        c, root_ = run_gpu(p, g, ob.OB_BYDEPTH, fuse=fuse, arena=128 << 20)
+        check_against_oracle(c, p, g, o, root_, what=f"pull rows/{d}/fuse {fuse}")
+        c.close()

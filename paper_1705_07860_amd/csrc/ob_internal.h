@@ -275,8 +275,8 @@ size_t prim_sort_scratch_bytes(size_t n);
 hipError_t prim_sort_pairs(u64 *keys, u32 *vals, u64 *keys_tmp, u32 *vals_tmp, size_t n, int lo_bit,
                            int n_bits, void *scratch, hipStream_t s, int *n_launches, const u32 *n_dev = nullptr);
 
-hipError_t prim_sort_pairs_swap(u64 *&keys, u32 *&vals, u64 *&keys_tmp, u32 *&vals_tmp, size_t n, int lo_bit,
-                                int n_bits, void *scratch, hipStream_t s, int *n_launches, const u32 *n_dev = nullptr);
+hipError_t prim_sort_pairs_swap(u64 *&keys, u32 *&vals, u64 *&keys_tmp, u32 *&vals_tmp, size_t n, int lo_bit, int n_bits,
+                                int lo2, int bits2, void *scratch, hipStream_t s, int *n_launches, const u32 *n_dev = nullptr);
 
 // ---- scheduler / executor entry points ---------------------------------------------------
 struct ob_ctx;

@@ -184,13 +184,46 @@ hipError_t scan_impl(const T *in, T *out, size_t n, T *total_dev, void *scratch,
 // ---- radix sort ------------------------------------------------------------------------------
 constexpr int RS_BITS = 8;
 constexpr int RS_RADIX = 1 << RS_BITS;
-constexpr int RS_THREADS = 256;                  // 4 waves
+constexpr int RS_THREADS = 1024;                 // 16 waves
 constexpr int RS_WAVES = RS_THREADS / 64;
-constexpr int RS_ROUNDS = 4;                     // keys per lane
-constexpr int RS_WAVE_KEYS = 64 * RS_ROUNDS;     // 256 consecutive keys per wave
-constexpr int RS_BLOCK = RS_WAVE_KEYS * RS_WAVES;  // 1024 keys per block
+constexpr int RS_ROUNDS = 2;                     // keys per lane
+constexpr int RS_WAVE_KEYS = 64 * RS_ROUNDS;     // 128 consecutive keys per wave
+constexpr int RS_BLOCK = RS_WAVE_KEYS * RS_WAVES;  // 2048 keys per block
+constexpr int RS_SEGS = RS_THREADS / RS_RADIX;   // threads per digit when the counts of all blocks are added up
+constexpr u32 RS_OWN_BLOCKS = 256;               // up to here every block adds up the counts of the others itself
 
 __device__ inline u32 digit_of(u64 key, int shift, u32 mask) { return (u32)(key >> shift) & mask; }
+
+// lanes of the wave whose digit equals this lane's (0 where the lane holds no key)
+__device__ inline u64 digit_peers(u32 d, bool ok)
+{
+    u64 peers = __ballot(ok);
+#pragma unroll
+    for (int b = 0; b < RS_BITS; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const u64 m = __ballot(bit);
+        peers &= bit ? m : ~m;
+    }
+    return ok ? peers : 0;
+}
+
+// Exclusive scan over the 256 digits: `mine` belongs to digit threadIdx.x, threads from 256 on only keep step at
+// the barrier.  tot: four words of LDS.
+__device__ inline u32 digit_exclusive(u32 mine, u32 *tot)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    u32 incl = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const u32 up = __shfl_up(incl, off);
+        if (lane >= off) incl += up;
+    }
+    if (w < RS_RADIX / 64 && lane == 63) tot[w] = incl;
+    __syncthreads();
+    u32 before = 0;
+    for (int i = 0; i < RS_RADIX / 64; ++i) before += i < w ? tot[i] : 0u;
+    return before + incl - mine;
+}
 
 // number of keys of block blk whose digit is d: table[blk * 256 + d], or (dmajor, many blocks: the
 // table is then scanned as it lies) table[d * nblk + blk]
@@ -198,118 +231,87 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const u64 *keys, size_t 
                                                        u32 *table, u32 nblk, u32 dmajor)
 {
     __shared__ u32 hist[RS_RADIX];
-    hist[threadIdx.x] = 0;
+    const u32 t = threadIdx.x;
+    if (t < RS_RADIX) hist[t] = 0;
     __syncthreads();
     const size_t base = (size_t)blockIdx.x * RS_BLOCK;
-    for (int i = 0; i < RS_BLOCK / RS_THREADS; ++i) {
-        const size_t idx = base + (size_t)i * RS_THREADS + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < RS_ROUNDS; ++i) {
+        const size_t idx = base + (size_t)i * RS_THREADS + t;
         if (idx < n) atomicAdd(&hist[digit_of(keys[idx], shift, mask)], 1u);
     }
     __syncthreads();
-    table[dmajor ? (size_t)threadIdx.x * nblk + blockIdx.x : (size_t)blockIdx.x * RS_RADIX + threadIdx.x] = hist[threadIdx.x];
+    if (t < RS_RADIX) table[dmajor ? (size_t)t * nblk + blockIdx.x : (size_t)blockIdx.x * RS_RADIX + t] = hist[t];
 }
 
-// One workgroup turns the per-block digit counts into the blocks' first output positions (an
-// exclusive scan in digit-major, block-minor order) in place: thread (segment, digit) first sums
-// its quarter of the blocks for its digit, the 256 digit totals are scanned in LDS, then every
-// thread walks its blocks again with a running position.  One launch where a general scan of the
-// table takes three.
-constexpr int RSO_THREADS = 1024;
-constexpr int RSO_SEGS = RSO_THREADS / RS_RADIX;
-constexpr u32 RSO_MAX_BLOCKS = 256;
-__global__ __launch_bounds__(RSO_THREADS) void k_rs_offsets(u32 *table, u32 nblk)
-{
-    __shared__ u32 seg_sum[RSO_SEGS][RS_RADIX];
-    __shared__ u32 dig[RS_RADIX];
-    const u32 d = threadIdx.x & (RS_RADIX - 1), seg = threadIdx.x / RS_RADIX;
-    const u32 per = (nblk + RSO_SEGS - 1) / RSO_SEGS;
-    const u32 b0 = seg * per < nblk ? seg * per : nblk, b1 = (seg + 1) * per < nblk ? (seg + 1) * per : nblk;
-    u32 sum = 0;
-    for (u32 b = b0; b < b1; b += 8) {       // eight loads in flight per thread
-        u32 c[8];
-#pragma unroll
-        for (u32 q = 0; q < 8; ++q) c[q] = b + q < b1 ? table[(size_t)(b + q) * RS_RADIX + d] : 0u;
-#pragma unroll
-        for (u32 q = 0; q < 8; ++q) sum += c[q];
-    }
-    seg_sum[seg][d] = sum;
-    __syncthreads();
-    if (seg == 0) {
-        u32 tot = 0;
-        for (int q = 0; q < RSO_SEGS; ++q) tot += seg_sum[q][d];
-        dig[d] = tot;
-    }
-    __syncthreads();
-    // inclusive scan of the digit totals (Kogge-Stone over 256 entries; the other threads only keep step at the barriers)
-    for (u32 off = 1; off < (u32)RS_RADIX; off <<= 1) {
-        u32 add = 0;
-        if (seg == 0 && d >= off) add = dig[d - off];
-        __syncthreads();
-        if (seg == 0) dig[d] += add;
-        __syncthreads();
-    }
-    u32 run = d ? dig[d - 1] : 0u;     // keys with a smaller digit
-    for (u32 q = 0; q < seg; ++q) run += seg_sum[q][d];
-    for (u32 b = b0; b < b1; b += 8) {
-        u32 c[8];
-#pragma unroll
-        for (u32 q = 0; q < 8; ++q) c[q] = b + q < b1 ? table[(size_t)(b + q) * RS_RADIX + d] : 0u;
-#pragma unroll
-        for (u32 q = 0; q < 8; ++q) {
-            if (b + q < b1) table[(size_t)(b + q) * RS_RADIX + d] = run;
-            run += c[q];
-        }
-    }
-}
-
-// Stable scatter.  Wave w of a block owns keys [w*256, w*256+256) of the block's chunk and
-// walks them in 4 rounds of 64; inside a round lanes with equal digits are ranked by lane id.
+// Stable scatter.  Wave w of a block owns 128 consecutive keys of the block's chunk and walks them in
+// rounds of 64; inside a round lanes with equal digits are ranked by lane id.
+// The first output positions come from the table of counts: thread (segment, digit) adds up a quarter of the
+// blocks for its digit, once over all of them and once over those before its own.  A pass is bound by its
+// launches and by latency (52 000 pairs are 0.6 MB), so every block reads the whole table (26 KB there, 16 loads in
+// flight per thread) where one workgroup turned it into positions in a launch of its own, and a block is
+// wide and its chunk short: four threads per digit, and few blocks to add up.
 __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const u64 *keys, const u32 *vals, u64 *keys_out,
                                                           u32 *vals_out, size_t n, int shift, u32 mask,
                                                           const u32 *table, u32 nblk, u32 dmajor)
 {
     __shared__ u32 cnt[RS_WAVES][RS_RADIX];
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    for (int i = 0; i < RS_WAVES; ++i) cnt[i][threadIdx.x] = 0;
-    __syncthreads();
-
-    const size_t wbase = (size_t)blockIdx.x * RS_BLOCK + (size_t)w * RS_WAVE_KEYS;
+    __shared__ u32 seg_all[RS_SEGS][RS_RADIX], seg_before[RS_SEGS][RS_RADIX], s_tot[RS_RADIX / 64];
+    const u32 t = threadIdx.x, lane = t & 63u, w = t >> 6, blk = blockIdx.x;
+    for (u32 i = lane; i < RS_RADIX; i += 64) cnt[w][i] = 0;
+    const size_t wbase = (size_t)blk * RS_BLOCK + (size_t)w * RS_WAVE_KEYS;
     u64 key[RS_ROUNDS];
     u32 val[RS_ROUNDS];
     bool ok[RS_ROUNDS];
+#pragma unroll
     for (int r = 0; r < RS_ROUNDS; ++r) {
         const size_t idx = wbase + (size_t)r * 64 + lane;
         ok[r] = idx < n;
         key[r] = ok[r] ? keys[idx] : 0;
         val[r] = ok[r] ? vals[idx] : 0;
-        if (ok[r]) atomicAdd(&cnt[w][digit_of(key[r], shift, mask)], 1u);
     }
-    __syncthreads();
-    {   // thread d turns the per-wave counts of digit d into per-wave start positions
-        const int d = threadIdx.x;
-        u32 run = table[dmajor ? (size_t)d * nblk + blockIdx.x : (size_t)blockIdx.x * RS_RADIX + d];
-        for (int i = 0; i < RS_WAVES; ++i) {
-            const u32 c = cnt[i][d];
-            cnt[i][d] = run;
-            run += c;
+    if (!dmajor) {
+        const u32 d = t & (RS_RADIX - 1), seg = t / RS_RADIX;
+        const u32 per = (nblk + RS_SEGS - 1) / RS_SEGS;
+        const u32 b0 = seg * per < nblk ? seg * per : nblk, b1 = b0 + per < nblk ? b0 + per : nblk;
+        u32 all = 0, before = 0;
+        for (u32 b = b0; b < b1; b += 16) {
+            u32 c[16];
+#pragma unroll
+            for (u32 q = 0; q < 16; ++q) c[q] = b + q < b1 ? table[(size_t)(b + q) * RS_RADIX + d] : 0u;
+#pragma unroll
+            for (u32 q = 0; q < 16; ++q) { all += c[q]; before += b + q < blk ? c[q] : 0u; }
         }
+        seg_all[seg][d] = all;
+        seg_before[seg][d] = before;
     }
     __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RS_ROUNDS; ++r)
+        if (ok[r]) atomicAdd(&cnt[w][digit_of(key[r], shift, mask)], 1u);
+    u32 run = 0, mine = 0;
+    if (t < RS_RADIX) {
+        if (dmajor) run = table[(size_t)t * nblk + blk];
+        else for (int q = 0; q < RS_SEGS; ++q) { mine += seg_all[q][t]; run += seg_before[q][t]; }
+    }
+    const u32 smaller = digit_exclusive(mine, s_tot);   // (its barrier also closes the counting)
+    if (t < RS_RADIX) {   // thread d turns the per-wave counts of digit d into per-wave start positions
+        run += smaller;
+        u32 c[RS_WAVES];
+#pragma unroll
+        for (int i = 0; i < RS_WAVES; ++i) c[i] = cnt[i][t];
+#pragma unroll
+        for (int i = 0; i < RS_WAVES; ++i) { cnt[i][t] = run; run += c[i]; }
+    }
+    __syncthreads();
+#pragma unroll
     for (int r = 0; r < RS_ROUNDS; ++r) {
         const u32 d = digit_of(key[r], shift, mask);
-        u64 peers = __ballot(ok[r]);
-        for (int b = 0; b < RS_BITS; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const u64 m = __ballot(bit);
-            peers &= bit ? m : ~m;
-        }
-        if (!ok[r]) peers = 0;
+        const u64 peers = digit_peers(d, ok[r]);
         const u32 rank = (u32)__popcll(peers & ((1ull << lane) - 1ull));
-        const u32 count = (u32)__popcll(peers);
-        const int leader = peers ? (__ffsll((unsigned long long)peers) - 1) : lane;
+        const int leader = peers ? (__ffsll((unsigned long long)peers) - 1) : (int)lane;
         u32 start = 0;
-        if (ok[r] && leader == lane) start = atomicAdd(&cnt[w][d], count);
+        if (ok[r] && leader == (int)lane) start = atomicAdd(&cnt[w][d], (u32)__popcll(peers));
         start = __shfl(start, leader);
         if (ok[r]) {
             keys_out[start + rank] = key[r];
@@ -318,83 +320,90 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const u64 *keys, cons
     }
 }
 
-// Short inputs: the whole sort in one workgroup, all passes in one launch.  Every pass counts the
-// digits of all keys, scans the 256 counts, then scatters tile by tile (1024 keys, one per thread):
-// lanes of a wave with equal digits are ranked by lane id, waves by their order in the tile, tiles
-// by the running start of every digit, which keeps the sort stable.  Passes alternate between the
-// two buffer pairs in global memory; a workgroup sees its own global writes after a barrier.
-constexpr int RSS_THREADS = 1024;
-constexpr int RSS_WAVES = RSS_THREADS / 64;
+// Short inputs: the whole sort in one workgroup and one launch, both fields, all passes.  Every wave owns R * 64
+// consecutive keys, in registers; a pass ranks them against the wave's own digit counts (lanes with equal digits by
+// lane id, rounds in order), turns the counts of the sixteen waves into start positions and hands the pairs
+// to their new owners through LDS.  Five barriers a pass whatever the size; memory is read and written once.
+// Bound by latency.  The version before kept the pairs in memory and walked tiles of 1024, four barriers each,
+// behind a scan of sixteen barriers.
 constexpr size_t RS_SMALL_MAX = 8192;
-__global__ __launch_bounds__(RSS_THREADS) void k_rs_small(u64 *keys, u32 *vals, u64 *keys_tmp, u32 *vals_tmp, u32 n,
-                                                         int lo_bit, int n_bits, const u32 *n_dev)
+struct RsFields { int lo[2], bits[2]; };
+struct RsSmall {
+    u64 key[RS_SMALL_MAX];
+    u32 val[RS_SMALL_MAX];
+    u32 cnt[RS_WAVES][RS_RADIX];
+    u32 tot[RS_RADIX / 64];
+};
+template <int R>
+__device__ inline void rs_small(RsSmall &S, u64 *keys, u32 *vals, u32 n, const RsFields &F)
 {
-    if (n_dev) n = *n_dev < n ? *n_dev : n;   // the same value for every thread: barriers below stay uniform
-    __shared__ u32 start[RS_RADIX];             // running first output position of every digit
-    __shared__ u32 cnt[RSS_WAVES][RS_RADIX];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, t = threadIdx.x;
-    u64 *kin = keys, *kout = keys_tmp;
-    u32 *vin = vals, *vout = vals_tmp;
-    for (int b = 0; b < n_bits; b += RS_BITS) {
-        const int bits = (n_bits - b < RS_BITS) ? (n_bits - b) : RS_BITS;
-        const u32 mask = (1u << bits) - 1u;
-        const int shift = lo_bit + b;
-        if (t < RS_RADIX) start[t] = 0;
-        __syncthreads();
-        for (u32 i = t; i < n; i += RSS_THREADS) atomicAdd(&start[digit_of(kin[i], shift, mask)], 1u);
-        __syncthreads();
-        if (t < RS_RADIX) cnt[0][t] = start[t];
-        __syncthreads();
-        for (int off = 1; off < RS_RADIX; off <<= 1) {
-            u32 add = 0;
-            if (t < RS_RADIX && t >= off) add = cnt[0][t - off];
-            __syncthreads();
-            if (t < RS_RADIX) cnt[0][t] += add;
-            __syncthreads();
-        }
-        if (t < RS_RADIX) start[t] = cnt[0][t] - start[t];   // inclusive -> exclusive
-        __syncthreads();
-        for (u32 t0 = 0; t0 < n; t0 += RSS_THREADS) {
-            for (int i = 0; i < RSS_WAVES * RS_RADIX / RSS_THREADS; ++i) (&cnt[0][0])[i * RSS_THREADS + t] = 0;
-            __syncthreads();
-            const u32 idx = t0 + t;
-            const bool ok = idx < n;
-            const u64 key = ok ? kin[idx] : 0;
-            const u32 val = ok ? vin[idx] : 0;
-            const u32 d = digit_of(key, shift, mask);
-            u64 peers = __ballot(ok);
-            for (int q = 0; q < RS_BITS; ++q) {
-                const bool bit = (d >> q) & 1u;
-                const u64 m = __ballot(bit);
-                peers &= bit ? m : ~m;
-            }
-            if (!ok) peers = 0;
-            const u32 rank = (u32)__popcll(peers & ((1ull << lane) - 1ull));
-            const int leader = peers ? (__ffsll((unsigned long long)peers) - 1) : lane;
-            if (ok && leader == lane) cnt[w][d] = (u32)__popcll(peers);
-            __syncthreads();
-            if (t < RS_RADIX) {
-                u32 run = start[t];
-                for (int i = 0; i < RSS_WAVES; ++i) {
-                    const u32 c = cnt[i][t];
-                    cnt[i][t] = run;
-                    run += c;
-                }
-                start[t] = run;
-            }
-            __syncthreads();
-            if (ok) {
-                const u32 pos = cnt[w][d] + rank;
-                kout[pos] = key;
-                vout[pos] = val;
-            }
-            __syncthreads();
-        }
-        u64 *tk = kin; kin = kout; kout = tk;
-        u32 *tv = vin; vin = vout; vout = tv;
+    const u32 t = threadIdx.x, lane = t & 63u, w = t >> 6;
+    const u32 base = w * (64u * R) + lane;
+    u64 key[R];
+    u32 val[R], rank[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const u32 i = base + 64u * r;
+        key[r] = i < n ? keys[i] : 0;
+        val[r] = i < n ? vals[i] : 0;
     }
-    if (kin != keys)   // an odd number of passes: the result sits in the second pair
-        for (u32 i = t; i < n; i += RSS_THREADS) { keys[i] = kin[i]; vals[i] = vin[i]; }
+    for (int f = 0; f < 2; ++f)
+        for (int b = 0; b < F.bits[f]; b += RS_BITS) {
+            const int bits = F.bits[f] - b < RS_BITS ? F.bits[f] - b : RS_BITS;
+            const u32 mask = (1u << bits) - 1u;
+            const int shift = F.lo[f] + b;
+            for (u32 i = lane; i < RS_RADIX; i += 64) S.cnt[w][i] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const bool ok = base + 64u * r < n;
+                const u32 d = digit_of(key[r], shift, mask);
+                const u64 peers = digit_peers(d, ok);
+                const int leader = peers ? (__ffsll((unsigned long long)peers) - 1) : (int)lane;
+                u32 start = 0;
+                if (ok && leader == (int)lane) start = atomicAdd(&S.cnt[w][d], (u32)__popcll(peers));
+                rank[r] = __shfl(start, leader) + (u32)__popcll(peers & ((1ull << lane) - 1ull));
+            }
+            __syncthreads();
+            u32 c[RS_WAVES], mine = 0;
+            if (t < RS_RADIX) {
+#pragma unroll
+                for (int i = 0; i < RS_WAVES; ++i) { c[i] = S.cnt[i][t]; mine += c[i]; }
+            }
+            u32 run = digit_exclusive(mine, S.tot);
+            if (t < RS_RADIX) {
+#pragma unroll
+                for (int i = 0; i < RS_WAVES; ++i) { S.cnt[i][t] = run; run += c[i]; }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (base + 64u * r < n) {
+                    const u32 pos = S.cnt[w][digit_of(key[r], shift, mask)] + rank[r];
+                    S.key[pos] = key[r];
+                    S.val[pos] = val[r];
+                }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const u32 i = base + 64u * r;
+                if (i < n) { key[r] = S.key[i]; val[r] = S.val[i]; }
+            }
+        }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const u32 i = base + 64u * r;
+        if (i < n) { keys[i] = key[r]; vals[i] = val[r]; }
+    }
+}
+__global__ __launch_bounds__(RS_THREADS) void k_rs_small(u64 *keys, u32 *vals, u32 n, RsFields F, const u32 *n_dev)
+{
+    __shared__ RsSmall S;
+    if (n_dev) n = *n_dev < n ? *n_dev : n;   // the same value for every thread: the barriers stay uniform
+    if (n <= 1024) rs_small<1>(S, keys, vals, n, F);
+    else if (n <= 2048) rs_small<2>(S, keys, vals, n, F);
+    else if (n <= 4096) rs_small<4>(S, keys, vals, n, F);
+    else rs_small<8>(S, keys, vals, n, F);
 }
 
 }  // namespace
@@ -444,14 +453,14 @@ size_t prim_sort_scratch_bytes(size_t n)
     return table + prim_scan_scratch_bytes((size_t)RS_RADIX * (nblk ? nblk : 1), sizeof(u32));
 }
 
-static hipError_t sort_pairs_impl(u64 *keys, u32 *vals, u64 *keys_tmp, u32 *vals_tmp, size_t n, int lo_bit,
-                                  int n_bits, void *scratch, hipStream_t s, int *n_launches, const u32 *n_dev, bool *in_tmp)
+// Stable sort by the bits [lo, lo + bits) of one or two fields, the less significant field first.
+static hipError_t sort_pairs_impl(u64 *keys, u32 *vals, u64 *keys_tmp, u32 *vals_tmp, size_t n, const RsFields &F,
+                                  void *scratch, hipStream_t s, int *n_launches, const u32 *n_dev, bool *in_tmp)
 {
     if (in_tmp) *in_tmp = false;
-    if (n <= 1 || n_bits <= 0) return hipSuccess;
+    if (n <= 1 || (F.bits[0] <= 0 && F.bits[1] <= 0)) return hipSuccess;
     if (n <= RS_SMALL_MAX) {
-        hipLaunchKernelGGL(k_rs_small, dim3(1), dim3(RSS_THREADS), 0, s, keys, vals, keys_tmp, vals_tmp, (u32)n, lo_bit,
-                           n_bits, n_dev);
+        hipLaunchKernelGGL(k_rs_small, dim3(1), dim3(RS_THREADS), 0, s, keys, vals, (u32)n, F, n_dev);
         if (n_launches) *n_launches += 1;
         return hipGetLastError();
     }
@@ -461,27 +470,26 @@ static hipError_t sort_pairs_impl(u64 *keys, u32 *vals, u64 *keys_tmp, u32 *vals
     u64 *kin = keys, *kout = keys_tmp;
     u32 *vin = vals, *vout = vals_tmp;
     int passes = 0;
-    for (int b = 0; b < n_bits; b += RS_BITS) {
-        const int bits = (n_bits - b < RS_BITS) ? (n_bits - b) : RS_BITS;
-        const u32 mask = (1u << bits) - 1u;
-        const int shift = lo_bit + b;
-        // up to RSO_MAX_BLOCKS blocks one workgroup turns the counts into positions in one launch; beyond, the
-        // table is laid out digit-major and scanned by the general three-launch scan
-        const u32 dmajor = nblk > RSO_MAX_BLOCKS ? 1u : 0u;
-        hipLaunchKernelGGL(k_rs_hist, dim3(nblk), dim3(RS_THREADS), 0, s, kin, n, shift, mask, table, nblk, dmajor);
-        if (dmajor) {
-            hipError_t e = scan_impl<u32>(table, table, (size_t)RS_RADIX * nblk, (u32 *)nullptr, scan_scratch, s);
-            if (e != hipSuccess) return e;
-        } else {
-            hipLaunchKernelGGL(k_rs_offsets, dim3(1), dim3(RSO_THREADS), 0, s, table, nblk);
+    // up to RS_OWN_BLOCKS blocks the scatter adds up the counts itself; what its blocks read together grows with the
+    // square of their number (64 MB there), so beyond the table is laid out digit-major and scanned
+    const u32 dmajor = nblk > RS_OWN_BLOCKS ? 1u : 0u;
+    for (int f = 0; f < 2; ++f)
+        for (int b = 0; b < F.bits[f]; b += RS_BITS) {
+            const int bits = (F.bits[f] - b < RS_BITS) ? (F.bits[f] - b) : RS_BITS;
+            const u32 mask = (1u << bits) - 1u;
+            const int shift = F.lo[f] + b;
+            hipLaunchKernelGGL(k_rs_hist, dim3(nblk), dim3(RS_THREADS), 0, s, kin, n, shift, mask, table, nblk, dmajor);
+            if (dmajor) {
+                hipError_t e = scan_impl<u32>(table, table, (size_t)RS_RADIX * nblk, (u32 *)nullptr, scan_scratch, s);
+                if (e != hipSuccess) return e;
+            }
+            hipLaunchKernelGGL(k_rs_scatter, dim3(nblk), dim3(RS_THREADS), 0, s, kin, vin, kout, vout, n, shift,
+                               mask, table, nblk, dmajor);
+            u64 *tk = kin; kin = kout; kout = tk;
+            u32 *tv = vin; vin = vout; vout = tv;
+            ++passes;
+            if (n_launches) *n_launches += !dmajor ? 2 : ((size_t)RS_RADIX * nblk <= (size_t)SCAN_THREADS * SCAN_BLOCK ? 4 : 5);
         }
-        hipLaunchKernelGGL(k_rs_scatter, dim3(nblk), dim3(RS_THREADS), 0, s, kin, vin, kout, vout, n, shift,
-                           mask, table, nblk, dmajor);
-        u64 *tk = kin; kin = kout; kout = tk;
-        u32 *tv = vin; vin = vout; vout = tv;
-        ++passes;
-        if (n_launches) *n_launches += dmajor ? 5 : 3;
-    }
     if ((passes & 1) && in_tmp) {   // the caller takes the result where it is
         *in_tmp = true;
     } else if (passes & 1) {  // result sits in the tmp arrays: copy back
@@ -496,16 +504,19 @@ static hipError_t sort_pairs_impl(u64 *keys, u32 *vals, u64 *keys_tmp, u32 *vals
 hipError_t prim_sort_pairs(u64 *keys, u32 *vals, u64 *keys_tmp, u32 *vals_tmp, size_t n, int lo_bit,
                            int n_bits, void *scratch, hipStream_t s, int *n_launches, const u32 *n_dev)
 {
-    return sort_pairs_impl(keys, vals, keys_tmp, vals_tmp, n, lo_bit, n_bits, scratch, s, n_launches, n_dev, nullptr);
+    return sort_pairs_impl(keys, vals, keys_tmp, vals_tmp, n, RsFields{{lo_bit, 0}, {n_bits, 0}}, scratch, s, n_launches, n_dev,
+                           nullptr);
 }
 
 // The same sort without the copy back after an odd number of passes: the two buffer pairs change
 // roles instead (on return keys / vals point at the sorted data, keys_tmp / vals_tmp at the other pair).
-hipError_t prim_sort_pairs_swap(u64 *&keys, u32 *&vals, u64 *&keys_tmp, u32 *&vals_tmp, size_t n, int lo_bit,
-                                int n_bits, void *scratch, hipStream_t s, int *n_launches, const u32 *n_dev)
+// By [lo2, lo2 + bits2), among equals by [lo_bit, lo_bit + n_bits).
+hipError_t prim_sort_pairs_swap(u64 *&keys, u32 *&vals, u64 *&keys_tmp, u32 *&vals_tmp, size_t n, int lo_bit, int n_bits,
+                                int lo2, int bits2, void *scratch, hipStream_t s, int *n_launches, const u32 *n_dev)
 {
     bool in_tmp = false;
-    hipError_t e = sort_pairs_impl(keys, vals, keys_tmp, vals_tmp, n, lo_bit, n_bits, scratch, s, n_launches, n_dev, &in_tmp);
+    hipError_t e = sort_pairs_impl(keys, vals, keys_tmp, vals_tmp, n, RsFields{{lo_bit, lo2}, {n_bits, bits2}}, scratch, s,
+                                   n_launches, n_dev, &in_tmp);
     if (in_tmp) {
         u64 *tk = keys; keys = keys_tmp; keys_tmp = tk;
         u32 *tv = vals; vals = vals_tmp; vals_tmp = tv;

@@ -1879,7 +1879,7 @@ int sched_enqueue(ob_ctx *ctx)
     ctx->n_launch_sched += scan_launches;
     if (E > 0) {
         HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, E, 0,
-                                     bit_width_u32(n - 1), ctx->scratch, s, &ctx->n_launch_sched));
+                                     bit_width_u32(n - 1), 0, 0, ctx->scratch, s, &ctx->n_launch_sched));
         K(k_succ_finish, E, T, ctx->val_a, succ_node);
     }
 
@@ -1903,13 +1903,11 @@ int sched_enqueue(ob_ctx *ctx)
     K(k_sort_keys, n, T, ctx->key_a, ctx->val_a, manual ? 2 : by_depth);
     if (manual) {
         HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n, 32, bit_width_u32(ctx->manual_max | 1u),
-                                     ctx->scratch, s, &ctx->n_launch_sched));
+                                     0, 0, ctx->scratch, s, &ctx->n_launch_sched));
     } else if (by_depth) {
         const int lb = bit_width_u32(n - 1);
-        HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n, 0, lb, ctx->scratch, s,
-                                     &ctx->n_launch_sched));
-        HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n, 32, lb, ctx->scratch, s,
-                                     &ctx->n_launch_sched));
+        HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n, 0, lb, 32, lb,
+                                     ctx->scratch, s, &ctx->n_launch_sched));
     }
 
     // ---- stage 4 ----
@@ -1939,7 +1937,7 @@ int sched_enqueue(ob_ctx *ctx)
         const size_t n_sort = n < SLOT_MAX_NB + 1 ? n : SLOT_MAX_NB + 1;
         // entries from n_batches on carry the largest key and stay where they are
         HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n_sort, 0, 2 * SLOT_BITS,
-                                     ctx->scratch, s, &ctx->n_launch_sched, &T.hdr->n_batches));
+                                     0, 0, ctx->scratch, s, &ctx->n_launch_sched, &T.hdr->n_batches));
     }
     u32 *cflag = ctx->tmp_u32_a, *cflag_excl = ctx->tmp_u32_b;
     K(k_chain_flags, n, T, ctx->val_a, cflag, n);
@@ -1959,10 +1957,8 @@ int sched_enqueue(ob_ctx *ctx)
     if (n_items > 0) {
         K(k_item_emit, n, T, s_items, ctx->key_a, ctx->val_a);
         HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n_items, 0,
-                                     bit_width_u32((u32)ctx->max_param_rows), ctx->scratch, s,
+                                     bit_width_u32((u32)ctx->max_param_rows), 32, bit_width_u32((u32)n_slots), ctx->scratch, s,
                                      &ctx->n_launch_sched));
-        HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n_items, 32,
-                                     bit_width_u32((u32)n_slots), ctx->scratch, s, &ctx->n_launch_sched));
         K(k_item_finish, n_items, T, ctx->key_a, ctx->val_a, n_items);
     }
     HIP_TRY(ctx, hipGetLastError());

@@ -54,6 +54,19 @@ def test_two_field_sort_matches_lexicographic_order(ctx):
     assert np.array_equal(v2, vals[order])
 
 
+# one workgroup with 1, 2, 4 and 8 keys per lane; blocks of 2048, whose counts the scatter adds up itself up to 256 blocks
+@pytest.mark.parametrize("n", [63, 65, 1024, 1025, 2048, 2049, 4096, 5000, 8191, 8193, 10240, 10241, 524288, 524289])
+@pytest.mark.parametrize("kind", ["equal", "falling", "random"])
+def test_radix_sort_at_the_edges_of_its_tiles(ctx, n, kind):
+    rng = np.random.default_rng(n)
+    keys = {"equal": np.full(n, (1 << 40) | 0x5a5a5), "falling": np.arange(n)[::-1] << 3,
+            "random": rng.integers(0, 1 << 40, size=n)}[kind].astype(np.uint64)
+    vals = np.arange(n, dtype=np.uint32)[::-1].copy()
+    ko, vo = ctx.test_sort(keys, vals, 2, 17)
+    order = np.argsort((keys >> np.uint64(2)) & np.uint64((1 << 17) - 1), kind="stable")
+    assert np.array_equal(ko, keys[order]) and np.array_equal(vo, vals[order])
+
+
 @pytest.mark.parametrize("M,N,K", [(32, 32, 8), (64, 1024, 256), (1, 5, 256), (33, 50, 512), (70, 35, 7),
                                    (3, 3, 1), (128, 96, 36)])
 def test_mfma_tile_gemm(ctx, M, N, K):

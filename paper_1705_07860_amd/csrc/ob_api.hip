@@ -850,15 +850,18 @@ int ob_upload(ob_ctx *ctx)
     if (!dev) return ctx_fail(ctx, OB_E_OOM, "arena too small for the graph (%zu bytes)", cur);
     hipStream_t us = ctx->sched_stream;
     HIP_TRY(ctx, hipEventRecord(ctx->ev[0], us));
-    const void *src[10] = {ctx->op.data(), ctx->out_dim.data(), ctx->in_off.data(), ctx->in_idx.data(), ctx->param.data(),
-                           ctx->bias.data(), ctx->aux0.data(), ctx->aux1.data(), ctx->payload.data(), ctx->pinned};
-    const size_t bytes[10] = {n, n * 4, (n + 1) * 4, E * 4, n * 4, n * 4, n * 4, n * 4, P * 4, labels ? n * 4 : 0};
+    UploadList L = {{ctx->op.data(), ctx->out_dim.data(), ctx->in_off.data(), ctx->in_idx.data(), ctx->param.data(),
+                     ctx->bias.data(), ctx->aux0.data(), ctx->aux1.data(), ctx->payload.data(), ctx->pinned},
+                    {n, n * 4, (n + 1) * 4, E * 4, n * 4, n * 4, n * 4, n * 4, P * 4, labels ? n * 4 : 0}, {}};
     size_t total = 0;
-    for (int i = 0; i < 10; ++i) {
-        if (!bytes[i]) continue;
-        HIP_TRY(ctx, hipMemcpyAsync(dev + off[i], src[i], bytes[i], hipMemcpyHostToDevice, us));
-        total += bytes[i];
-    }
+    for (int i = 0; i < 10; ++i) { L.at[i] = off[i]; total += L.bytes[i]; }
+    // One launch that reads all arrays where they lie, as a chain of copies costs some 10 us each.  On a schedule stream
+    // of its own the upload runs beside execution: there the copy engines are the better ones, which leave the
+    // compute units alone (four-minibatch loop against one version: 1.03 times as fast with copies, 1.00 with the kernel).
+    if (us == ctx->stream) HIP_TRY(ctx, exec_upload(L, dev, us));
+    else
+        for (int i = 0; i < 10; ++i)
+            if (L.bytes[i]) HIP_TRY(ctx, hipMemcpyAsync(dev + off[i], L.src[i], L.bytes[i], hipMemcpyHostToDevice, us));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[1], us));
     cur = total;
     Tables &T = ctx->T;

@@ -1570,6 +1570,27 @@ __global__ __launch_bounds__(WG) void k_node_read(const u32 *off_tab, const floa
     for (u32 c = threadIdx.x; c < count; c += WG) row[c] = arena[off + c];
 }
 
+// The graph's arrays, read where they lie in page-locked host memory: one launch instead of a copy each.
+// Bound by the host link, and for a small graph by the number of copies in a row, each with a start of its own.
+// Everything starts at a multiple of 16 bytes (page-locked allocations, sections of the arena); the last bytes of an
+// array go one by one, so nothing is read past its end.
+__global__ __launch_bounds__(WG) void k_upload(UploadList L, char *dst)
+{
+    const u32 a = blockIdx.y;
+    const size_t n16 = L.bytes[a] / 16, stride = (size_t)gridDim.x * WG;
+    const uint4 *src = (const uint4 *)L.src[a];
+    uint4 *out = (uint4 *)(dst + L.at[a]);
+    for (size_t i = (size_t)blockIdx.x * WG + threadIdx.x; i < n16; i += 4 * stride) {
+        uint4 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) if (i + q * stride < n16) v[q] = src[i + q * stride];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) if (i + q * stride < n16) out[i + q * stride] = v[q];
+    }
+    const size_t rest = n16 * 16 + threadIdx.x;
+    if (blockIdx.x == 0 && rest < L.bytes[a]) (dst + L.at[a])[rest] = ((const char *)L.src[a])[rest];
+}
+
 // Values of already evaluated nodes, copied into the payload block of a later evaluation stage
 // whose graph holds them as leaves: entry i copies dim[i] elements from the row of node src[i] in
 // the earlier evaluation's value arena to payload + dst[i].
@@ -1806,6 +1827,16 @@ hipError_t exec_gather_all(const Tables &T, int which, float *dst, const u32 *ds
 {
     if (T.n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_gather_all, dim3(T.n), dim3(64), 0, s, T, which ? T.G : T.V, which ? T.nat_off : T.val_off, dst, dst_off);
+    return hipGetLastError();
+}
+
+hipError_t exec_upload(const UploadList &L, char *dst, hipStream_t s)
+{
+    size_t most = 0;
+    for (size_t b : L.bytes) if (b > most) most = b;
+    size_t bx = (most / 16 + 4 * WG - 1) / (4 * WG);
+    bx = bx < 1 ? 1 : (bx > 128 ? 128 : bx);
+    hipLaunchKernelGGL(k_upload, dim3((unsigned)bx, 10), dim3(WG), 0, s, L, dst);
     return hipGetLastError();
 }
 

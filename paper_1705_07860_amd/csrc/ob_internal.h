@@ -288,6 +288,8 @@ hipError_t exec_gather_all(const Tables &T, int which, float *dst, const u32 *ds
 hipError_t exec_stage_scatter(const float *G, const u32 *nat_off, u32 first_proxy, const u32 *src, const u32 *dim, u32 count,
                               const u32 *owner_nat_off, float *owner_gx, hipStream_t s);
 hipError_t exec_fill_uncopied(const Tables &T, hipStream_t s);
+struct UploadList { const void *src[10]; size_t bytes[10], at[10]; };   // host arrays and where they go in one device block
+hipError_t exec_upload(const UploadList &L, char *dst, hipStream_t s);
 hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, hipStream_t s);
 hipError_t exec_gather_some(const Tables &T, int which, float *dst, const u32 *dst_off, hipStream_t s);
 hipError_t exec_stage_fill(const float *V, const u32 *val_off, const u32 *src, const u32 *dst, const u32 *dim, u32 count,

@@ -32,6 +32,15 @@ __device__ inline u64 comb(u64 h, u64 x) { return mix64(h ^ (x + 0x9e3779b97f4a7
 // caller's batch labels, 3 = steps come from the single-workgroup depth pass (leaves are queued here).
 constexpr u32 INIT_OPS = 8;
 __device__ inline u64 operand_hash(const Tables &T, u32 u, u32 j) { return mix64(comb(0x5bd1e995ULL + j, T.out_dim[u])); }
+// start values: the first `zeros` elements zero, the others all ones
+__global__ void k_clear(uint4 *p, size_t zeros, size_t n)
+{
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        const u32 v = i < zeros ? 0u : ~0u;
+        p[i] = make_uint4(v, v, v, v);
+    }
+}
+
 __global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *keys, u32 *vals)
 {
     __shared__ u32 s_wide[TPB], s_n;
@@ -1070,10 +1079,21 @@ __device__ inline u32 rows_per_block(u32 d) { return d >= (u32)EW_TILE ? 1u : (u
 // chains from the launch order: head flags, then one thread per chain head fills the record
 __device__ inline u64 chain_key(const Tables &T, u32 b) { return ((u64)T.slot_of[b] << 32) | T.label_of[b]; }
 
-__global__ void k_chain_flags(Tables T, const u32 *sval, u32 *flag, u32 n_pad)
+// (and the start values of the tables that the next kernels fill in: every slot entry a plan can use,
+// n_slots + 1 <= n + 2, starts out as "no batch here", every chain's layout as empty)
+__global__ void k_chain_flags(Tables T, const u32 *sval, u32 *flag, CLay *clay_in, u32 n_pad)
 {
     const u32 i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i <= T.hdr->n_slots) {
+        SlotRec r; r.wf = r.wa = r.tb = r.tf = r.ta = r.lmin = r.nlmax = r.dx_free = 0xffffffffu;
+        r.lds_need = 0;
+        r.lminf = r.nlmaxf = 0xffffffffu;
+        r.plain = 0xffffffffu;
+        T.slots[i] = r;
+    }
     if (i >= n_pad) return;
+    CLay L; L.tf = L.wf = L.ta = L.wa = L.tb = L.p0 = L.p1 = L.p2 = 0;
+    clay_in[i] = L;
     const u32 nb = T.hdr->n_batches;
     if (i < nb) T.lorder[i] = sval[i];
     flag[i] = (i < nb && (i == 0 || chain_key(T, sval[i]) != chain_key(T, sval[i - 1]))) ? 1u : 0u;
@@ -1186,28 +1206,8 @@ __global__ void k_chain_recs(Tables T, int agenda, const u32 *bset, const u32 *f
     }
 }
 
-__global__ void k_clay_zero(CLay *clay_in, u32 n_pad)
-{
-    const u32 i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_pad) return;
-    CLay L; L.tf = L.wf = L.ta = L.wa = L.tb = L.p0 = L.p1 = L.p2 = 0;
-    clay_in[i] = L;
-}
-
 // floats of a fused chain's LDS copy taken by one member: its rows of a block of groups, rounded up to 4
 __device__ inline u32 chain_region(const ChainRec &cr, const BatchRec &r) { return (cr.Rg * (r.B / cr.G) * r.d + 3u) & ~3u; }
-
-// every entry a plan can use (n_slots + 1 <= n + 2) starts out as "no batch here"
-__global__ void k_slot_init(Tables T)
-{
-    const u32 s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s > T.hdr->n_slots) return;
-    SlotRec r; r.wf = r.wa = r.tb = r.tf = r.ta = r.lmin = r.nlmax = r.dx_free = 0xffffffffu;
-    r.lds_need = 0;
-    r.lminf = r.nlmaxf = 0xffffffffu;
-    r.plain = 0xffffffffu;
-    T.slots[s] = r;
-}
 
 // per chain: first work item / tile of every launch slot and its run lengths, totals in the header
 __global__ void k_slot_tables(Tables T, const CLay *clay_ex, const CLay *total)
@@ -1754,6 +1754,16 @@ __global__ void k_item_finish(Tables T, const u64 *keys, const u32 *vals, u32 n_
     if (i == n_items - 1 || (u32)(keys[i + 1] >> 32) != slot) T.pu_end[slot] = i + 1;
 }
 
+// The header and the slot entries in use, written straight to page-locked host memory: one launch where two
+// copies in a row (the second of the whole window, 96 KB) each had a start of their own.
+__global__ void k_read_back(Tables T, u32 *hdr, u32 *slots, u32 window)
+{
+    const u32 i = blockIdx.x * blockDim.x + threadIdx.x, all = gridDim.x * blockDim.x;
+    if (i < sizeof(SchedHeader) / 4) hdr[i] = ((const u32 *)T.hdr)[i];
+    const u32 used = T.hdr->n_slots + 1, count = (used < window ? used : window) * (u32)(sizeof(SlotRec) / 4);
+    for (u32 k = i; k < count; k += all) slots[k] = ((const u32 *)T.slots)[k];
+}
+
 inline int bit_width_u32(u32 x) { int b = 0; while (x) { ++b; x >>= 1; } return b; }
 
 }  // namespace
@@ -1868,8 +1878,12 @@ int sched_enqueue(ob_ctx *ctx)
 #undef A
 
     // ---- stage 1 ----
-    HIP_TRY(ctx, hipMemsetAsync(zero_lo, 0, (size_t)(zero_hi - zero_lo), s));
-    HIP_TRY(ctx, hipMemsetAsync(zero_hi, 0xff, (size_t)(ones_hi - zero_hi), s));
+    {   // (sections of the arena start at multiples of 256 bytes)
+        const size_t words = (size_t)(ones_hi - zero_lo) / 16, zeros = (size_t)(zero_hi - zero_lo) / 16;
+        const size_t bx = (words + 4 * TPB - 1) / (4 * TPB);
+        hipLaunchKernelGGL(k_clear, dim3((unsigned)(bx < 2048 ? bx : 2048)), dim3(TPB), 0, s, (uint4 *)zero_lo, zeros, words);
+        ++ctx->n_launch_sched;
+    }
     const bool part_depth = by_depth && ctx->max_arity < DEPTH_MAX_ARITY && !ctx->force_frontier;
     ctx->depth_partitioned = part_depth;
     K(k_node_init, n, T, manual ? 2 : (by_depth ? (part_depth ? 1 : 3) : 0), ctx->key_a, ctx->val_a);
@@ -1940,13 +1954,11 @@ int sched_enqueue(ob_ctx *ctx)
                                      0, 0, ctx->scratch, s, &ctx->n_launch_sched, &T.hdr->n_batches));
     }
     u32 *cflag = ctx->tmp_u32_a, *cflag_excl = ctx->tmp_u32_b;
-    K(k_chain_flags, n, T, ctx->val_a, cflag, n);
+    K(k_chain_flags, (size_t)n + 2, T, ctx->val_a, cflag, clay_in, n);
     HIP_TRY(ctx, prim_scan_u32(cflag, cflag_excl, n, nullptr, ctx->scratch, s));
-    K(k_clay_zero, n, clay_in, n);
     K(k_chain_recs, n, T, agenda || manual, bset, cflag, cflag_excl, clay_in, n);
     HIP_TRY(ctx, prim_scan_clay(clay_in, T.clay, n, clay_total, ctx->scratch, s));
     ctx->n_launch_sched += 2 * scan_launches;
-    K(k_slot_init, (size_t)n + 2, T);
     K(k_slot_tables, n, T, T.clay, clay_total);
     if (fuse) K(k_slot_fill, (size_t)n + 2, T);
     hipLaunchKernelGGL(k_tiles, dim3(1024), dim3(TPB), 0, s, T, T.clay, clay_total, (u32)cap_f, (u32)cap_a,
@@ -1967,8 +1979,9 @@ int sched_enqueue(ob_ctx *ctx)
     // pinned layout: [header 256 B][first hdr_window entries of the slot table]
     ctx->hdr_window = (u32)(slot_cap < SLOT_WINDOW ? slot_cap : SLOT_WINDOW);
     char *hp = (char *)ctx->hdr_pinned;
-    HIP_TRY(ctx, hipMemcpyAsync(hp, T.hdr, sizeof(SchedHeader), hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(hp + 256, T.slots, (size_t)ctx->hdr_window * sizeof(SlotRec), hipMemcpyDeviceToHost, s));
+    hipLaunchKernelGGL(k_read_back, dim3(8), dim3(TPB), 0, s, T, (u32 *)hp, (u32 *)(hp + 256), ctx->hdr_window);
+    HIP_TRY(ctx, hipGetLastError());
+    ++ctx->n_launch_sched;
     ctx->n_items_sched = n_items;
     return 0;
 }

@@ -24,38 +24,51 @@ template <> __device__ inline Lay zero_of<Lay>() { Lay z; z.val = 0; z.dx = 0; z
 template <> __device__ inline Tri zero_of<Tri>() { Tri z; z.a = z.b = z.c = z.d = 0; return z; }
 template <> __device__ inline CLay zero_of<CLay>() { CLay z; z.tf = z.wf = z.ta = z.wa = z.tb = z.p0 = z.p1 = z.p2 = 0; return z; }
 
-// Exclusive scan of the 256 per-thread values of a block through LDS (Kogge-Stone).
-// Returns the exclusive prefix of this thread; *block_total gets the sum of all 256.
+// the element `off` lanes below (anything in the lanes that have none)
 template <typename T>
-__device__ inline T block_exclusive(T mine, T *lds, T *block_total)
+__device__ inline T lane_below(const T &x, int off)
 {
-    const int t = threadIdx.x;
-    lds[t] = mine;
-    __syncthreads();
-    for (int off = 1; off < SCAN_THREADS; off <<= 1) {
-        T add = zero_of<T>();
-        if (t >= off) add = lds[t - off];
-        __syncthreads();
-        if (t >= off) lds[t] = lds[t] + add;
-        __syncthreads();
+    static_assert(sizeof(T) % 4 == 0, "scan elements are whole words");
+    u32 w[sizeof(T) / 4];
+    __builtin_memcpy(w, &x, sizeof(T));
+#pragma unroll
+    for (u32 i = 0; i < sizeof(T) / 4; ++i) w[i] = __shfl_up(w[i], off);
+    T r;
+    __builtin_memcpy(&r, w, sizeof(T));
+    return r;
+}
+
+// Exclusive scan of the per-thread values of a block: inside the waves by lane shuffles, across them through one LDS
+// entry per wave, two barriers in all (a scan through LDS alone takes two per doubling).
+// Returns the exclusive prefix of this thread; *block_total gets the sum over the block.
+template <int WAVES, typename T>
+__device__ inline T block_exclusive(const T &mine, T *lds, T *block_total)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    T incl = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const T below = lane_below(incl, off);
+        if (lane >= off) incl = below + incl;
     }
-    T incl = lds[t];
-    T total = lds[SCAN_THREADS - 1];
+    T excl = lane_below(incl, 1);
+    if (lane == 0) excl = zero_of<T>();
+    if (lane == 63) lds[w] = incl;
+    __syncthreads();
+    T before = zero_of<T>(), total = zero_of<T>();
+    for (int i = 0; i < WAVES; ++i) {
+        if (i == w) before = total;
+        total = total + lds[i];
+    }
     __syncthreads();
     *block_total = total;
-    // exclusive = inclusive of the previous thread
-    T excl = zero_of<T>();
-    lds[t] = incl;
-    __syncthreads();
-    if (t > 0) excl = lds[t - 1];
-    __syncthreads();
-    return excl;
+    return before + excl;
 }
 
 template <typename T>
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_local(const T *in, T *out, T *block_sums, size_t n)
 {
-    __shared__ T lds[SCAN_THREADS];
+    __shared__ T lds[SCAN_THREADS / 64];
     const size_t base = (size_t)blockIdx.x * SCAN_BLOCK + (size_t)threadIdx.x * SCAN_ITEMS;
     T item[SCAN_ITEMS];
     T sum = zero_of<T>();
@@ -64,7 +77,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_local(const T *in, T *out
         sum = sum + item[i];
     }
     T total;
-    T run = block_exclusive<T>(sum, lds, &total);
+    T run = block_exclusive<SCAN_THREADS / 64, T>(sum, lds, &total);
     for (int i = 0; i < SCAN_ITEMS; ++i) {
         if (base + i < n) out[base + i] = run;
         run = run + item[i];
@@ -76,13 +89,13 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_local(const T *in, T *out
 template <typename T>
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_sums(T *block_sums, size_t nblk, T *total_out)
 {
-    __shared__ T lds[SCAN_THREADS];
+    __shared__ T lds[SCAN_THREADS / 64];
     T carry = zero_of<T>();
     for (size_t c0 = 0; c0 < nblk; c0 += SCAN_THREADS) {
         const size_t i = c0 + threadIdx.x;
         T mine = (i < nblk) ? block_sums[i] : zero_of<T>();
         T total;
-        T ex = block_exclusive<T>(mine, lds, &total);
+        T ex = block_exclusive<SCAN_THREADS / 64, T>(mine, lds, &total);
         if (i < nblk) block_sums[i] = carry + ex;
         carry = carry + total;
     }
@@ -129,31 +142,28 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_add_own(T *out, const T *
     }
 }
 
-// Short inputs: one workgroup walks the chunks with a carry, one launch instead of two or three
-// (the scheduler of a small graph is bound by the number of its launches).  in == out is fine.
-constexpr size_t SCAN_SMALL_MAX = 4 * SCAN_BLOCK;
+// Short inputs: one workgroup, one launch instead of two or three (the scheduler of a small graph is bound by the
+// number of its launches).  in == out is fine.
+constexpr int SCAN_SMALL_THREADS = 1024;
+constexpr size_t SCAN_SMALL_MAX = (size_t)SCAN_SMALL_THREADS * SCAN_ITEMS;
 template <typename T>
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_small(const T *in, T *out, size_t n, T *total_out)
+__global__ __launch_bounds__(SCAN_SMALL_THREADS) void k_scan_small(const T *in, T *out, size_t n, T *total_out)
 {
-    __shared__ T lds[SCAN_THREADS];
-    T carry = zero_of<T>();
-    for (size_t c0 = 0; c0 < n; c0 += SCAN_BLOCK) {
-        const size_t base = c0 + (size_t)threadIdx.x * SCAN_ITEMS;
-        T item[SCAN_ITEMS];
-        T sum = zero_of<T>();
-        for (int i = 0; i < SCAN_ITEMS; ++i) {
-            item[i] = (base + i < n) ? in[base + i] : zero_of<T>();
-            sum = sum + item[i];
-        }
-        T total;
-        T run = carry + block_exclusive<T>(sum, lds, &total);
-        for (int i = 0; i < SCAN_ITEMS; ++i) {
-            if (base + i < n) out[base + i] = run;
-            run = run + item[i];
-        }
-        carry = carry + total;
+    __shared__ T lds[SCAN_SMALL_THREADS / 64];
+    const size_t base = (size_t)threadIdx.x * SCAN_ITEMS;
+    T item[SCAN_ITEMS];
+    T sum = zero_of<T>();
+    for (int i = 0; i < SCAN_ITEMS; ++i) {
+        item[i] = (base + i < n) ? in[base + i] : zero_of<T>();
+        sum = sum + item[i];
     }
-    if (threadIdx.x == 0 && total_out) *total_out = carry;
+    T total;
+    T run = block_exclusive<SCAN_SMALL_THREADS / 64, T>(sum, lds, &total);
+    for (int i = 0; i < SCAN_ITEMS; ++i) {
+        if (base + i < n) out[base + i] = run;
+        run = run + item[i];
+    }
+    if (threadIdx.x == 0 && total_out) *total_out = total;
 }
 
 template <typename T>
@@ -165,7 +175,7 @@ hipError_t scan_impl(const T *in, T *out, size_t n, T *total_dev, void *scratch,
         return hipSuccess;
     }
     if (n <= SCAN_SMALL_MAX) {
-        hipLaunchKernelGGL(k_scan_small<T>, dim3(1), dim3(SCAN_THREADS), 0, s, in, out, n, total_dev);
+        hipLaunchKernelGGL(k_scan_small<T>, dim3(1), dim3(SCAN_SMALL_THREADS), 0, s, in, out, n, total_dev);
         return hipGetLastError();
     }
     const size_t nblk = (n + SCAN_BLOCK - 1) / SCAN_BLOCK;

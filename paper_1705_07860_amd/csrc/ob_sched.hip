@@ -558,30 +558,51 @@ __device__ inline u64 batch_key(u64 sig, u32 step)
     return k ? k : 1;
 }
 
-__global__ void k_rep_insert(Tables T)
+// Thousands of nodes share a key (all leaves of one kind, in the first place), and reads and atomics of one word from
+// all over the chip pass one after the other, about 10 ns each.  So the workgroup's nodes first meet in LDS, and one node
+// per distinct key goes to the table, with the smallest id; there it looks before it writes (keys never change once
+// set, values only fall, so whatever a look returns is safe to act on).
+constexpr u32 REP_THREADS = 1024, REP_SLOTS = 2048;
+__global__ __launch_bounds__(REP_THREADS) void k_rep_insert(Tables T)
 {
-    const u32 v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= T.n) return;
-    const u64 k = batch_key(T.sig[v], T.step[v]);
-    u32 slot = (u32)k & T.ht_mask;
-    // Thousands of nodes share a key: a node first looks (keys never change once set, values only fall, so
-    // whatever a look returns is safe to act on) and takes the atomic path only for an empty slot or a value
-    // above its own id; low ids mostly run first, so most nodes end up with two reads.
-    for (u32 probe = 0; probe <= T.ht_mask; ++probe) {
-        u64 cur = __hip_atomic_load(&T.ht_keys[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cur == 0) {
-            cur = atomicCAS((unsigned long long *)&T.ht_keys[slot], 0ULL, (unsigned long long)k);
-            if (cur == 0) cur = k;
+    __shared__ u64 s_key[REP_SLOTS];
+    __shared__ u32 s_min[REP_SLOTS], s_at[REP_SLOTS];
+    for (u32 i = threadIdx.x; i < REP_SLOTS; i += REP_THREADS) { s_key[i] = 0; s_min[i] = 0xffffffffu; }
+    __syncthreads();
+    const u32 v = blockIdx.x * REP_THREADS + threadIdx.x;
+    const bool live = v < T.n;
+    u64 k = 0;
+    u32 at = 0;
+    bool first = false;      // this node's key is new to the workgroup
+    if (live) {
+        k = batch_key(T.sig[v], T.step[v]);
+        for (at = (u32)(k >> 32) & (REP_SLOTS - 1);; at = (at + 1) & (REP_SLOTS - 1)) {   // (twice as many slots as nodes)
+            const u64 cur = atomicCAS((unsigned long long *)&s_key[at], 0ULL, (unsigned long long)k);
+            first = cur == 0;
+            if (first || cur == k) break;
         }
-        if (cur == k) {
-            if (__hip_atomic_load(&T.ht_vals[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > v) atomicMin(&T.ht_vals[slot], v);
-            T.ht_slot[v] = slot;
-            return;
-        }
-        slot = (slot + 1) & T.ht_mask;
+        atomicMin(&s_min[at], v);
     }
-    atomicOr(&T.hdr->err, (u32)ERR_TABLE_FULL);
-    T.ht_slot[v] = 0;
+    __syncthreads();
+    if (first) {
+        const u32 low = s_min[at];
+        u32 slot = (u32)k & T.ht_mask, probe = 0;
+        for (; probe <= T.ht_mask; ++probe, slot = (slot + 1) & T.ht_mask) {
+            u64 cur = __hip_atomic_load(&T.ht_keys[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (cur == 0) {
+                cur = atomicCAS((unsigned long long *)&T.ht_keys[slot], 0ULL, (unsigned long long)k);
+                if (cur == 0) cur = k;
+            }
+            if (cur == k) {
+                if (__hip_atomic_load(&T.ht_vals[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > low) atomicMin(&T.ht_vals[slot], low);
+                break;
+            }
+        }
+        if (probe > T.ht_mask) { atomicOr(&T.hdr->err, (u32)ERR_TABLE_FULL); slot = 0; }
+        s_at[at] = slot;
+    }
+    __syncthreads();
+    if (live) T.ht_slot[v] = s_at[at];
 }
 
 // rep_src: 0 = the node itself (unbatched), 1 = the representative found by k_rep_insert,
@@ -844,16 +865,6 @@ __device__ inline bool op_chain_source(u32 op, u32 arity)
     return op == OP_INPUT || op == OP_LOOKUP || op_chainable(op, arity);
 }
 
-// producer batch of operand slot j of the node at schedule position p, and the producer's row
-__device__ inline u32 producer_batch(const Tables &T, u32 p, u32 j, u32 *prow)
-{
-    const u32 v = T.order[p];
-    const u32 pu = T.pos_of[T.in_idx[T.in_off[v] + j]];
-    const u32 by = T.batch_of_pos[pu];
-    *prow = pu - T.batches[by].pos0;
-    return by;
-}
-
 constexpr u32 FUSE_MAX_MULT = 4;
 __device__ inline u32 gcd_u32(u32 a, u32 b) { while (b) { const u32 t = a % b; a = b; b = t; } return a; }
 
@@ -871,31 +882,27 @@ constexpr u32 BSET_SIZE = 1u << 16;   // open-addressing set of packed triples
 constexpr u32 BLIST_MAX = 20480;      // distinct triples the slot kernel keeps in LDS (80 KB)
 constexpr int SLOT_BITS = 13;         // bits of a slot or a label when the plan is fused
 
-__global__ void k_bedges(Tables T, u32 *bset, u32 *blist)
+// the dependency of the row at schedule position p (batch b) on operand u, packed; never 0
+__device__ inline u32 bedge_key(const Tables &T, u32 p, u32 b, const BatchRec &r, u32 u)
 {
-    const u32 e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= T.E) return;
-    if (T.hdr->n_batches > SLOT_MAX_NB) return;
-    const u32 v = T.edge_cons[e];
-    const u32 j = e - T.in_off[v];
-    const u32 p = T.pos_of[v];
-    const u32 b = T.batch_of_pos[p];
-    const BatchRec &r = T.batches[b];
-    u32 prow;
-    const u32 by = producer_batch(T, p, j, &prow);
+    const u32 pu = T.pos_of[u];
+    const u32 by = T.batch_of_pos[pu];
     const BatchRec &y = T.batches[by];
     bool ok = op_chainable(r.op, r.arity) && op_chain_source(y.op, y.arity);
     if (ok) {
         const u32 G = gcd_u32(r.B, y.B);
         const u32 mc = r.B / G, mp = y.B / G;
-        ok = mc <= FUSE_MAX_MULT && mp <= FUSE_MAX_MULT && (p - r.pos0) / mc == prow / mp;
+        ok = mc <= FUSE_MAX_MULT && mp <= FUSE_MAX_MULT && (p - r.pos0) / mc == (pu - y.pos0) / mp;
     }
-    const u32 key = ((b << 13) | (by << 1) | (ok ? 0u : 1u)) + 1u;
+    return ((b << 13) | (by << 1) | (ok ? 0u : 1u)) + 1u;
+}
+
+// puts a triple into the set, and into the list if it is new there
+__device__ inline void bedge_insert(const Tables &T, u32 *bset, u32 *blist, u32 key)
+{
     u32 h = (key * 2654435761u) & (BSET_SIZE - 1);
     for (u32 probe = 0; probe < BSET_SIZE; ++probe) {
-        // (all edges between two batches carry the same triple: look before the compare-and-swap)
         u32 old = __hip_atomic_load(&bset[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (old == key) return;
         if (old == 0u) old = atomicCAS(&bset[h], 0u, key);
         if (old == key) return;
         if (old == 0u) {
@@ -906,6 +913,56 @@ __global__ void k_bedges(Tables T, u32 *bset, u32 *blist)
         h = (h + 1) & (BSET_SIZE - 1);
     }
     atomicAdd(&T.hdr->n_bedges, BLIST_MAX);   // table full: forces the unfused plan
+}
+
+// A thread takes a row in schedule order with its operands: the rows of a batch lie side by side and mostly carry the
+// same triples, so a small set in LDS lets one of a workgroup's rows through to the set in memory (a thread
+// per edge in id order brought every edge there).  Rows with more than BEDGE_OPS operands are left to the
+// whole workgroup, one after the other.
+constexpr u32 BEDGE_SLOTS = 1024, BEDGE_PROBES = 8, BEDGE_OPS = 8;
+__device__ inline void bedge_add(const Tables &T, u32 *s_set, u32 *bset, u32 *blist, u32 key)
+{
+    u32 h = (key * 2654435761u) >> 22;
+    static_assert(BEDGE_SLOTS == 1u << (32 - 22), "the hash gives as many bits as the set has slots");
+    for (u32 probe = 0; probe < BEDGE_PROBES; ++probe) {
+        u32 old = lds_load(&s_set[h]);
+        if (old == 0u) old = atomicCAS(&s_set[h], 0u, key);
+        if (old == key) return;
+        if (old == 0u) break;
+        h = (h + 1) & (BEDGE_SLOTS - 1);
+    }
+    bedge_insert(T, bset, blist, key);   // new here, or the neighbourhood of its place is full
+}
+__global__ __launch_bounds__(TPB) void k_bedges(Tables T, u32 *bset, u32 *blist)
+{
+    __shared__ u32 s_set[BEDGE_SLOTS], s_wide[TPB], s_n;
+    if (T.hdr->n_batches > SLOT_MAX_NB) return;
+    for (u32 i = threadIdx.x; i < BEDGE_SLOTS; i += TPB) s_set[i] = 0;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const u32 p = blockIdx.x * TPB + threadIdx.x;
+    if (p < T.n) {
+        const u32 v = T.order[p], b = T.batch_of_pos[p];
+        const u32 lo = T.in_off[v], hi = T.in_off[v + 1];
+        if (hi - lo <= BEDGE_OPS) {
+            const BatchRec &r = T.batches[b];
+            for (u32 e = lo; e < hi; e += 2) {       // two operands at a time: their reads run side by side
+                const u32 k0 = bedge_key(T, p, b, r, T.in_idx[e]);
+                const u32 k1 = bedge_key(T, p, b, r, T.in_idx[e + 1 < hi ? e + 1 : e]);
+                bedge_add(T, s_set, bset, blist, k0);
+                if (k1 != k0) bedge_add(T, s_set, bset, blist, k1);
+            }
+        } else {
+            s_wide[atomicAdd(&s_n, 1u)] = p;
+        }
+    }
+    __syncthreads();
+    for (u32 i = 0; i < s_n; ++i) {
+        const u32 q = s_wide[i], v = T.order[q], b = T.batch_of_pos[q];
+        const BatchRec &r = T.batches[b];
+        for (u32 e = T.in_off[v] + threadIdx.x; e < T.in_off[v + 1]; e += TPB)
+            bedge_add(T, s_set, bset, blist, bedge_key(T, q, b, r, T.in_idx[e]));
+    }
 }
 
 // One workgroup.  Over the batch dependencies, where a fusable edge costs 0 and any other edge one
@@ -1912,7 +1969,8 @@ int sched_enqueue(ob_ctx *ctx)
             hipLaunchKernelGGL(k_agenda, dim3(1), dim3(AGENDA_THREADS), 0, s, T, AG, succ_node);
             ctx->n_launch_sched += 2;
         }
-        K(k_rep_insert, n, T);
+        hipLaunchKernelGGL(k_rep_insert, dim3(blocks_for(n, REP_THREADS)), dim3(REP_THREADS), 0, s, T);
+        ++ctx->n_launch_sched;
     }
     K(k_sort_keys, n, T, ctx->key_a, ctx->val_a, manual ? 2 : by_depth);
     if (manual) {
@@ -1943,7 +2001,7 @@ int sched_enqueue(ob_ctx *ctx)
 
     // ---- launch planning: slots, chains, tile descriptors ----
     const int fuse = batched && ctx->fuse;
-    if (fuse && E > 0) K(k_bedges, E, T, bset, blist);
+    if (fuse && E > 0) K(k_bedges, n, T, bset, blist);
     hipLaunchKernelGGL(k_slots, dim3(1), dim3(SLOT_THREADS), 0, s, T, (fuse && E > 0) ? ctx->fuse : 0, blist);
     ++ctx->n_launch_sched;
     K(k_launch_keys, n, T, ctx->key_a, ctx->val_a, n);

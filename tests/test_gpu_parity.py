@@ -1574,3 +1574,30 @@ def test_pull_tiles_of_two_to_seventeen_rows(d):
         c, root_ = run_gpu(p, g, ob.OB_BYDEPTH, fuse=fuse, arena=128 << 20)
         check_against_oracle(c, p, g, o, root_, what=f"pull rows/{d}/fuse {fuse}")
         c.close()
+
+
+@pytest.mark.parametrize("rows,arity", [(1, 8), (1, 9), (3, 9), (300, 2), (300, 8), (300, 9), (2, 700)])
+def test_batch_dependencies_of_rows_with_few_and_many_operands(rows, arity):
+    """The dependencies between batches are collected row by row, up to eight operands by the row's own thread and more
+    by its workgroup; the operands here come from many batches in another order for each row, and a workgroup's rows
+    meet more distinct dependencies than its set in LDS places close together."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(rows * 1000 + arity)
+    pb = wl.ParamBuilder(rng, std=0.3)
+    E = pb.add("E", 1, 4)
+    p = pb.done()
+    gb = wl.GraphBuilder(p)
+    level = [gb.input(rng.standard_normal(4)) for _ in range(40)]
+    pool = list(level)
+    for k in range(30):                       # chains of different depth: every level is a batch of its own
+        level = [gb.tanh(v) if (i + k) % 3 else gb.sigmoid(v) for i, v in enumerate(level)]
+        pool += level
+    losses = [gb.sqnorm(gb.add([pool[i] for i in rng.choice(len(pool), size=arity, replace=False)])) for _ in range(rows)]
+    g = gb.finish(gb.add(losses + [gb.sqnorm(gb.lookup(E, 0))]), rows)
+    o = Oracle(g, p, "f64")
+    o.forward()
+    o.backward(g.root)
+    for fuse in (2, 1):
+        c, root = run_gpu(p, g, ob.OB_BYDEPTH, fuse=fuse, arena=256 << 20)
+        check_against_oracle(c, p, g, o, root, what=f"dependencies/{rows}/{arity}/fuse {fuse}")
+        c.close()

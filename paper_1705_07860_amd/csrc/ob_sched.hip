@@ -969,9 +969,9 @@ __global__ __launch_bounds__(TPB) void k_bedges(Tables T, u32 *bset, u32 *blist)
 // launch boundary: head(b) = longest path from any source to b, tail(b) = longest path from b to any
 // sink.  Batch ids are a topological order (a batch's operands lie in earlier batches in every batching
 // mode), so the distinct dependencies are first put in the order of their consumer (a counting sort in
-// LDS) and then walked once by one wave, 64 at a time: forward for the heads (every producer of a chunk's
+// LDS) and then walked once by a wave, 64 at a time: forward for the heads (every producer of a chunk's
 // consumers was settled by an earlier chunk or is settled inside the chunk, which is passed over until
-// nothing changes), backward for the tails.  That is as many dependent steps as the list has chunks
+// nothing changes), and by a second wave beside it backward for the tails.  That is as many dependent steps as the list has chunks
 // instead of as many as the longest path has edges.  The
 // plan has L + 1 slots, L = max head.  fuse == 1 places a batch as early as possible (slot =
 // head), fuse == 2 as late as possible (slot = L - tail): batches off the critical path then
@@ -1021,42 +1021,35 @@ __global__ __launch_bounds__(SLOT_THREADS) void k_slots(Tables T, int fuse, cons
     __syncthreads();
     for (u32 b = tid; b < SLOT_MAX_NB; b += SLOT_THREADS) s_label[b] = 0;
     __syncthreads();
-    // ---- heads forward, tails backward: one wave, chunk by chunk (its LDS operations complete in order)
+    // ---- heads forward (wave 0, in s_slot) and tails backward (wave 1, in s_label), which know nothing of each
+    // other: chunk by chunk (a wave's LDS operations complete in order)
+    const u32 lane = tid & 63u;
     u32 walked = 0;      // passes over chunks, for the statistics
-    if (tid < 64) {
+    if (tid < 128) {
+        const bool tails = __builtin_amdgcn_readfirstlane(tid) >= 64u;
+        u32 *len = tails ? s_label : s_slot;
         const u32 n_chunks = (ne + 63u) / 64u;
-        for (u32 ch = 0; ch < n_chunks; ++ch) {
-            const u32 e = ch * 64u + tid;
+        for (u32 i = 0; i < n_chunks; ++i) {
+            const u32 e = (tails ? n_chunks - 1u - i : i) * 64u + lane;
             const bool valid = e < ne;
             const u32 k = valid ? s_edge[e] : 0u;
             const u32 c = k >> 13, y = (k >> 1) & 0xfffu, cost = k & 1u;
+            const u32 *from = &len[tails ? c : y];
+            u32 *to = &len[tails ? y : c];
             for (u32 rep = 0; rep < 66u; ++rep) {          // (a chain inside a chunk has at most 64 links)
                 bool changed = false;
                 if (valid) {
-                    const u32 want = lds_load(&s_slot[y]) + cost;
-                    if (want > lds_load(&s_slot[c])) { atomicMax(&s_slot[c], want); changed = true; }
-                }
-                ++walked;
-                if (__ballot(changed) == 0ull) break;
-            }
-        }
-        for (u32 ch = n_chunks; ch-- > 0;) {
-            const u32 e = ch * 64u + tid;
-            const bool valid = e < ne;
-            const u32 k = valid ? s_edge[e] : 0u;
-            const u32 c = k >> 13, y = (k >> 1) & 0xfffu, cost = k & 1u;
-            for (u32 rep = 0; rep < 66u; ++rep) {
-                bool changed = false;
-                if (valid) {
-                    const u32 tw = lds_load(&s_label[c]) + cost;
-                    if (tw > lds_load(&s_label[y])) { atomicMax(&s_label[y], tw); changed = true; }
+                    const u32 want = lds_load(from) + cost;
+                    if (want > lds_load(to)) { atomicMax(to, want); changed = true; }
                 }
                 ++walked;
                 if (__ballot(changed) == 0ull) break;
             }
         }
     }
+    if (tid == 64) s_wsum[0] = walked;
     __syncthreads();
+    walked += s_wsum[0];
     {   // number of slots; late placement; labels start as the batch's own id
         u32 mx = 0;
         for (u32 b = tid; b < nb; b += SLOT_THREADS) mx = s_slot[b] > mx ? s_slot[b] : mx;

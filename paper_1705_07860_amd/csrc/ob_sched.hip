@@ -5,6 +5,8 @@
 // addressable as one matrix; results are laid out contiguously in batch order).
 #include "ob_ctx.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int TPB = 256;
@@ -163,8 +165,13 @@ __global__ __launch_bounds__(FRONTIER_THREADS) void k_depth_frontier(Tables T, c
 // nodes are consecutive ids, which programs write along their recurrences, and a node settled in a sweep is
 // handed to the thread's later nodes in registers: an LSTM cell of sixteen nodes and eight levels takes four sweeps.  A settled
 // depth also goes to g_dep, where higher ranges poll for it: the word is its own flag, so no fence is needed.
-// Nodes with more than DEPTH_OPS operands are walked by their whole wave, eight reads per lane at a time,
-// whenever the wave's other nodes are not moving.
+// A node with more than DEPTH_OPS operands looks at three of them at a time: a settled one makes room for the next
+// of its list, all such nodes of a wave side by side, and the last three are waited for like any others.  That is
+// a third of a sweep per operand, so where a wave has few such nodes and they are long (a sum over a whole
+// minibatch), the wave walks them instead, one after the other, eight reads per lane at a time, whenever nothing else of
+// the wave moves.  A walk step takes about as long as four sweeps, which is where
+// DEPTH_WALK puts the line.  (With all of them walked, 64 recurrences of 60 steps with a sum of five operands each took
+// 5 100 us for this pass, sequences of 60 states with a sum over all earlier ones 2 280; now 120 and 210.)
 // What bounds it: one dependent LDS read plus some forty instructions per level of the longest path, which is
 // why a wave holds no more than four nodes per lane and a workgroup one wave per SIMD.  The pass this
 // replaces kept a frontier queue per 4 096 ids (queue, counter, successor and queue again: five dependent LDS
@@ -176,8 +183,11 @@ constexpr u32 DEPTH_PART = DEPTH_THREADS * DEPTH_NPT;   // ids per workgroup
 constexpr u32 DEPTH_OPS = 4;          // operands of a node that are kept in registers
 constexpr u32 DEPTH_ONE = DEPTH_PART;         // LDS word that always holds 1: an absent operand
 constexpr u32 DEPTH_NEVER = DEPTH_PART + 1;   // LDS word that always holds 0: an operand that cannot be read here (yet)
+constexpr u32 DEPTH_WALKED = DEPTH_PART + 2;  // reads as DEPTH_NEVER: the node's wave walks it
 constexpr u32 DEPTH_EXT = 0x80000000u;        // operand of a lower range: this bit and its id (reads as DEPTH_NEVER)
-constexpr u32 DEPTH_WIDE_READS = 8;   // operands per lane of one step over a node with many operands
+constexpr u32 DEPTH_LIST = DEPTH_OPS - 1;     // operands of a longer node that are looked at at a time (its first word holds it back until its list is through)
+constexpr u32 DEPTH_WALK = 4 * DEPTH_LIST;    // a wave walks the nodes with more operands than this times the number of its long nodes
+constexpr u32 DEPTH_WIDE_READS = 8;   // operands per lane of one step of such a walk
 constexpr u32 DEPTH_MAX_ARITY = 60000;   // beyond, the single-workgroup pass counts the operands down instead of walking them
 
 __device__ inline u32 lds_load(const u32 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
@@ -202,34 +212,41 @@ __global__ __launch_bounds__(DEPTH_THREADS) void k_depth_partitioned(Tables T, u
     const u32 first = tid * DEPTH_NPT;
     bool fwd0[DEPTH_NPT][DEPTH_NPT], fwd1[DEPTH_NPT][DEPTH_NPT];   // operand 0 / 1 of node j is the lane's own node i < j
     u32 op[DEPTH_NPT][DEPTH_OPS], ext[DEPTH_NPT], dep[DEPTH_NPT];   // ext: largest word among settled operands of lower ranges
-    bool wide[DEPTH_NPT], has_ext = false, has_34 = false;
+    u32 in0[DEPTH_NPT], ar[DEPTH_NPT], next[DEPTH_NPT];   // operand list; operands of a long node that have been looked at
+    bool wide[DEPTH_NPT], has_ext = false, has_34 = false, has_list = false;
+    u32 n_long = 0;
 #pragma unroll
     for (u32 j = 0; j < DEPTH_NPT; ++j) {
         const u32 l = first + j, v = lo + l;
         const bool live = v < T.n;
-        const u32 a = live ? T.in_off[v] : 0u, ar = live ? T.in_off[v + 1] - a : 0u;
+        in0[j] = live ? T.in_off[v] : 0u;
+        ar[j] = live ? T.in_off[v + 1] - in0[j] : 0u;
         ext[j] = 0;
-        dep[j] = ar ? 0u : 1u;
+        dep[j] = ar[j] ? 0u : 1u;
 #pragma unroll
         for (u32 q = 0; q < DEPTH_OPS; ++q) {
             op[j][q] = DEPTH_ONE;
-            if (q < ar && ar <= DEPTH_OPS) {
-                const u32 u = T.in_idx[a + q];
+            if (q < ar[j] && ar[j] <= DEPTH_OPS) {
+                const u32 u = T.in_idx[in0[j] + q];
                 op[j][q] = u >= lo ? u - lo : (DEPTH_EXT | u);
                 has_ext = has_ext || u < lo;
             }
         }
 #pragma unroll
         for (u32 i = 0; i < DEPTH_NPT; ++i) { fwd0[j][i] = op[j][0] == first + i; fwd1[j][i] = op[j][1] == first + i; }
-        if (live && ar == 0) depth_settle(&s_dep[l], &g_dep[v], 1u);
-        wide[j] = ar > DEPTH_OPS;
-        if (wide[j]) op[j][0] = DEPTH_NEVER;
-        has_34 = has_34 || (ar > 2u && !wide[j]);
+        if (live && ar[j] == 0) depth_settle(&s_dep[l], &g_dep[v], 1u);
+        n_long += (u32)__popcll(__ballot(ar[j] > DEPTH_OPS));
     }
-    // (in ascending order of ids: a node of the list never waits for a later one)
+    // (walked in ascending order of ids: such a node never waits for a later one)
     u32 at = 0, n_wide = 0;
 #pragma unroll
     for (u32 j = 0; j < DEPTH_NPT; ++j) {
+        const bool longer = ar[j] > DEPTH_OPS;
+        wide[j] = longer && ar[j] > DEPTH_WALK * n_long;
+        if (longer) op[j][0] = wide[j] ? DEPTH_WALKED : DEPTH_NEVER;
+        next[j] = longer && !wide[j] ? 0u : ar[j];
+        has_list = has_list || next[j] < ar[j];
+        has_34 = has_34 || (ar[j] > 2u && !wide[j]);
         const u64 m = __ballot(wide[j]);
         at += (u32)__popcll(m & lt_mask);
         n_wide += (u32)__popcll(m);
@@ -237,11 +254,13 @@ __global__ __launch_bounds__(DEPTH_THREADS) void k_depth_partitioned(Tables T, u
 #pragma unroll
     for (u32 j = 0; j < DEPTH_NPT; ++j)
         if (wide[j]) s_wide[wave][at++] = (unsigned short)(first + j);
-    bool any_ext = __ballot(has_ext) != 0ull;
+    bool any_ext = __ballot(has_ext) != 0ull, any_list = __ballot(has_list) != 0ull;
     const bool any_34 = __ballot(has_34) != 0ull;
     u32 wide_i = 0, wide_e = 0, wide_max = 0;     // node of the wave's list being walked, operands behind it, their largest word
     u32 idle = 0, sweep = 0;
     bool gave_up = false;
+    // (written out for waves without lists and with: beside the code for lists, sweeps took a sixth longer for everybody)
+    auto sweeps = [&](auto with_lists) __attribute__((always_inline)) {
     while (true) {
         u32 w0[DEPTH_NPT], w1[DEPTH_NPT], w2[DEPTH_NPT], w3[DEPTH_NPT];
 #pragma unroll
@@ -300,6 +319,47 @@ __global__ __launch_bounds__(DEPTH_THREADS) void k_depth_partitioned(Tables T, u
             any_ext = __ballot(more) != 0ull;
             progress = progress || __ballot(got) != 0ull;
         }
+        if (with_lists.value && any_list) {
+            // (reads of a step side by side: list entries first, then the words of those in lower ranges)
+            u32 id[DEPTH_NPT][DEPTH_LIST], w[DEPTH_NPT][DEPTH_LIST];
+            bool got = false, more = false, new_ext = false;
+#pragma unroll
+            for (u32 j = 0; j < DEPTH_NPT; ++j) {
+                const u32 seen[DEPTH_LIST] = {w1[j], w2[j], w3[j]};
+#pragma unroll
+                for (u32 q = 0; q < DEPTH_LIST; ++q) {
+                    id[j][q] = ~0u;
+                    if (next[j] >= ar[j] || seen[q] == 0u) continue;
+                    ext[j] = seen[q] > ext[j] ? seen[q] : ext[j];
+                    id[j][q] = T.in_idx[in0[j] + next[j]];
+                    ++next[j];
+                    got = true;
+                }
+            }
+#pragma unroll
+            for (u32 j = 0; j < DEPTH_NPT; ++j)
+#pragma unroll
+                for (u32 q = 0; q < DEPTH_LIST; ++q) {
+                    w[j][q] = 0;
+                    if (id[j][q] < lo)
+                        w[j][q] = __hip_atomic_load(&g_dep[id[j][q]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+            for (u32 j = 0; j < DEPTH_NPT; ++j) {
+#pragma unroll
+                for (u32 q = 0; q < DEPTH_LIST; ++q) {
+                    if (id[j][q] == ~0u) continue;
+                    ext[j] = w[j][q] > ext[j] ? w[j][q] : ext[j];
+                    op[j][1 + q] = id[j][q] >= lo ? id[j][q] - lo : (w[j][q] ? DEPTH_ONE : (DEPTH_EXT | id[j][q]));
+                    new_ext = new_ext || (op[j][1 + q] & DEPTH_EXT);
+                }
+                if (next[j] < ar[j]) more = true;
+                else if (op[j][0] == DEPTH_NEVER) op[j][0] = DEPTH_ONE;
+            }
+            any_list = __ballot(more) != 0ull;
+            any_ext = any_ext || __ballot(new_ext) != 0ull;
+            progress = progress || __ballot(got) != 0ull;
+        }
         if (!progress && wide_i < n_wide) {
             const u32 l = __builtin_amdgcn_readfirstlane((u32)s_wide[wave][wide_i]), v = lo + l;
             const u32 a = T.in_off[v], ar = T.in_off[v + 1] - a;
@@ -338,6 +398,9 @@ __global__ __launch_bounds__(DEPTH_THREADS) void k_depth_partitioned(Tables T, u
         }
         if (idle > 16u) __builtin_amdgcn_s_sleep(1);
     }
+    };
+    if (any_list) sweeps(std::true_type{});
+    else sweeps(std::false_type{});
     u32 done = 0;
 #pragma unroll
     for (u32 j = 0; j < DEPTH_NPT; ++j) {

@@ -1601,3 +1601,86 @@ def test_batch_dependencies_of_rows_with_few_and_many_operands(rows, arity):
         c, root = run_gpu(p, g, ob.OB_BYDEPTH, fuse=fuse, arena=256 << 20)
         check_against_oracle(c, p, g, o, root, what=f"dependencies/{rows}/{arity}/fuse {fuse}")
         c.close()
+
+
+def _median_schedule_ms(graphs, rounds=7):
+    """Median scheduling time (GPU events) of each of the given (params, graph) pairs, taken in turn, the first
+    round of each left out."""
+    from paper_1705_07860_amd import binding as ob
+    ctxs = []
+    for p, _ in graphs:
+        c = ob.Context(arena_bytes=512 << 20, mode=ob.OB_BYDEPTH)
+        c.params_create(p)
+        ctxs.append(c)
+    ms = [[] for _ in graphs]
+    for i in range(rounds + 1):
+        for k, (_, g) in enumerate(graphs):
+            ctxs[k].graph_new()
+            ctxs[k].add_bulk(g)
+            ctxs[k].forward(g.root)
+            if i:
+                ms[k].append(ctxs[k].stats()["ms_schedule"])
+    for c in ctxs:
+        c.close()
+    return [float(np.median(m)) for m in ms]
+
+
+def _sum_recurrences(n, steps, arity):
+    """n recurrences; every step adds up `arity` rows: the product of the state before it and looked-up rows."""
+    rng = np.random.default_rng(arity)
+    pb = wl.ParamBuilder(rng, std=0.1)
+    E, W = pb.add("E", 50, 16), pb.add("W", 16, 16)
+    p = pb.done()
+    gb = wl.GraphBuilder(p)
+    losses = []
+    for _ in range(n):
+        h = gb.lookup(E, 0)
+        for _ in range(steps):
+            h = gb.tanh(gb.add([gb.matvec(W, -1, h)] + [gb.lookup(E, int(r)) for r in rng.integers(0, 50, arity - 1)]))
+        losses.append(gb.sqnorm(h))
+    return p, gb.finish(gb.add(losses), n)
+
+
+@pytest.mark.parametrize("arity", [5, 12])
+def test_recurrences_over_wider_sums_schedule_about_as_fast(arity):
+    """The depth pass keeps four operands of a node at hand.  Nodes with more must not be what a schedule's time goes
+    to: the same recurrences with sums of 5 and 12 operands have 1.2 and 2.3 times the nodes and measure 1.2 and
+    1.6 times the time; walked one after the other by their waves they took 14 to 16 times as long."""
+    four, more = _median_schedule_ms([_sum_recurrences(64, 60, 4), _sum_recurrences(64, 60, arity)])
+    say(f"  4 operands {four:.3f} ms, {arity} operands {more:.3f} ms")
+    assert more <= 4 * four
+
+
+def _random_arity_graph(n, arities, reach, seed):
+    """n nodes of one element.  The arity of a node is drawn from `arities` (less where there are not as many nodes
+    before it), its operands from the `reach` nodes before it or, one time in four, from all of them."""
+    rng = np.random.default_rng(seed)
+    gb = wl.GraphBuilder(wl.Params([], []))
+    for v in range(n):
+        a = min(int(rng.choice(arities)), v)
+        if a == 0:
+            gb.input(rng.standard_normal(1))
+            continue
+        low = 0 if rng.integers(4) == 0 else max(0, v - reach)
+        ops = [int(u) for u in rng.integers(low, v, size=a)]
+        if rng.integers(2):
+            ops[int(rng.integers(a))] = v - 1
+        gb.tanh(ops[0]) if a == 1 else gb.add(ops)
+    return gb.finish(n - 1, 1)
+
+
+@pytest.mark.parametrize("n", [2, 1023, 1024, 1025, 2049, 6000])
+@pytest.mark.parametrize("arities,reach", [([0, 1, 2, 3, 4, 5], 40), ([0, 0, 0, 1, 4, 5, 6, 12, 13], 600), ([0] * 30 + [1, 511, 512, 513, 800], 1500),
+                                           ([5], 8), ([3, 9], 3000), ([0] * 200 + [1] * 20 + [2600], 5000)])
+def test_depths_of_nodes_of_any_arity_across_id_ranges(n, arities, reach):
+    """The depth pass goes by ranges of 1024 ids.  Up to four operands of a node are looked at together, more through a
+    window of three, and the longest lists by a whole wave 512 entries at a time (which of the two depends on how many such
+    nodes its wave has), with operands in the range itself and in lower ones: depths are exact and nothing is repeated."""
+    from paper_1705_07860_amd import binding as ob
+    g = _random_arity_graph(n, arities, reach, n + len(arities))
+    c = ob.Context(arena_bytes=512 << 20, mode=ob.OB_BYDEPTH)
+    c.add_bulk(g)
+    c.forward(g.root)
+    assert np.array_equal(c.debug_read(ob.OB_DBG_DEPTH).astype(np.int64), S.depths(g))
+    assert c.stats()["n_depth_retries"] == 0
+    c.close()

@@ -26,14 +26,40 @@ __device__ inline u64 comb(u64 h, u64 x) { return mix64(h ^ (x + 0x9e3779b97f4a7
 // parameter ids (the A and y of A x + y), slice range, operand dimensions.  LOOKUP's row,
 // PICK_NLS's label and INPUT's payload are data and stay out.  The operands' dimensions enter as a
 // sum of position-salted hashes, so that a node with many operands can be summed by many threads.
-// A thread takes a node with up to INIT_OPS operands, edges included; nodes with more are left to the whole
-// workgroup, one after the other.  (A launch with a thread per edge had to look its node up by bisection and
+// A thread takes a node with up to INIT_OPS operands, edges included; the edges of nodes with more are shared out over
+// the workgroup (WideRows).  (A launch with a thread per edge had to look its node up by bisection in memory and
 // meet all operands of a wide sum in atomics on one signature: 23 us for 52 000 edges, 169 us for 480 000 of
-// which one node holds 10 000, beside 8 and 16 us of this kernel without the edges; 10.5 and 37 us together now.)
+// which one node holds 10 000, beside 8 and 16 us of this kernel without the edges; 10.5 and 37 us together now.
+// With the wide nodes taken by the workgroup one after the other, 4 096 sums of nine operands side by side took
+// 768 us, 18 now.)
 // steps: 0 = every node is its own step, 1 = steps come from the depth pass by id ranges, 2 = steps are the
 // caller's batch labels, 3 = steps come from the single-workgroup depth pass (leaves are queued here).
 constexpr u32 INIT_OPS = 8;
 __device__ inline u64 operand_hash(const Tables &T, u32 u, u32 j) { return mix64(comb(0x5bd1e995ULL + j, T.out_dim[u])); }
+
+// The rows of a workgroup that have too many edges for a thread, as one list of edges that all its threads walk: an entry
+// finds its row by bisection in LDS.
+struct WideRows {
+    u64 n;                              // rows << 32 | edges: one atomic gives a row its place in both
+    u32 row[TPB], lo[TPB], at[TPB];     // row, its first edge, its first entry of the list
+};
+constexpr u32 WIDE_STEP = 4;            // entries a thread takes at a time: their reads run side by side
+__device__ inline void wide_add(WideRows &S, u32 row, u32 lo, u32 edges)
+{
+    const u64 was = atomicAdd((unsigned long long *)&S.n, (1ull << 32) | edges);
+    const u32 i = (u32)(was >> 32);
+    S.row[i] = row; S.lo[i] = lo; S.at[i] = (u32)was;
+}
+__device__ inline u32 wide_row(const WideRows &S, u32 rows, u32 x)
+{
+    u32 lo = 0, hi = rows;              // at[lo] <= x < at[hi]
+    while (hi - lo > 1) {
+        const u32 mid = (lo + hi) >> 1;
+        if (S.at[mid] <= x) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
 // start values: the first `zeros` elements zero, the others all ones
 __global__ void k_clear(uint4 *p, size_t zeros, size_t n)
 {
@@ -45,9 +71,10 @@ __global__ void k_clear(uint4 *p, size_t zeros, size_t n)
 
 __global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *keys, u32 *vals)
 {
-    __shared__ u32 s_wide[TPB], s_n;
-    __shared__ u64 s_sum;
-    if (threadIdx.x == 0) s_n = 0;
+    __shared__ WideRows S;
+    __shared__ u64 s_sum[TPB];
+    if (threadIdx.x == 0) S.n = 0;
+    s_sum[threadIdx.x] = 0;
     __syncthreads();
     const u32 v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v < T.n) {
@@ -70,7 +97,7 @@ __global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *key
                 h += operand_hash(T, u, e - lo);
             }
         } else {
-            s_wide[atomicAdd(&s_n, 1u)] = v;
+            wide_add(S, v, lo, hi - lo);
         }
         T.sig[v] = h;
         if (steps == 3) {
@@ -87,24 +114,36 @@ __global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *key
         }
     }
     __syncthreads();
-    for (u32 i = 0; i < s_n; ++i) {
-        const u32 w = s_wide[i], lo = T.in_off[w], hi = T.in_off[w + 1];
-        if (threadIdx.x == 0) s_sum = 0;
-        __syncthreads();
-        u64 sum = 0;
-        for (u32 e = lo + threadIdx.x; e < hi; e += TPB) {
-            const u32 u = T.in_idx[e];
-            T.edge_cons[e] = w;
-            keys[e] = u;
-            vals[e] = e;
-            atomicAdd(&T.outdeg[u], 1u);
-            sum += operand_hash(T, u, e - lo);
+    const u32 rows = (u32)(S.n >> 32), edges = (u32)S.n;
+    u32 mine = ~0u;         // row whose sum this thread is adding up
+    u64 sum = 0;
+    for (u32 x0 = threadIdx.x; x0 < edges; x0 += WIDE_STEP * TPB) {
+        u32 i[WIDE_STEP], j[WIDE_STEP], u[WIDE_STEP];
+#pragma unroll
+        for (u32 q = 0; q < WIDE_STEP; ++q) {
+            const u32 x = x0 + q * TPB < edges ? x0 + q * TPB : x0;
+            i[q] = wide_row(S, rows, x);
+            j[q] = x - S.at[i[q]];
+            u[q] = T.in_idx[S.lo[i[q]] + j[q]];
         }
-        atomicAdd((unsigned long long *)&s_sum, (unsigned long long)sum);
-        __syncthreads();
-        if (threadIdx.x == 0) T.sig[w] += s_sum;
-        __syncthreads();
+#pragma unroll
+        for (u32 q = 0; q < WIDE_STEP; ++q) {
+            if (x0 + q * TPB >= edges) continue;
+            const u32 e = S.lo[i[q]] + j[q];
+            T.edge_cons[e] = S.row[i[q]];
+            keys[e] = u[q];
+            vals[e] = e;
+            atomicAdd(&T.outdeg[u[q]], 1u);
+            if (i[q] != mine) {
+                if (mine != ~0u) atomicAdd((unsigned long long *)&s_sum[mine], (unsigned long long)sum);
+                mine = i[q]; sum = 0;
+            }
+            sum += operand_hash(T, u[q], j[q]);
+        }
     }
+    if (mine != ~0u) atomicAdd((unsigned long long *)&s_sum[mine], (unsigned long long)sum);
+    __syncthreads();
+    if (threadIdx.x < rows) T.sig[S.row[threadIdx.x]] += s_sum[threadIdx.x];
 }
 
 // after the sort: succ_edge[q] = edge id, succ_node[q] = its consumer (stored in T.queue's

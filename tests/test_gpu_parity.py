@@ -1675,7 +1675,8 @@ def _random_arity_graph(n, arities, reach, seed):
 def test_depths_of_nodes_of_any_arity_across_id_ranges(n, arities, reach):
     """The depth pass goes by ranges of 1024 ids.  Up to four operands of a node are looked at together, more through a
     window of three, and the longest lists by a whole wave 512 entries at a time (which of the two depends on how many such
-    nodes its wave has), with operands in the range itself and in lower ones: depths are exact and nothing is repeated."""
+    nodes its wave has), with operands in the range itself and in lower ones: depths are exact and nothing is repeated.
+    Signatures of such nodes are put together by one thread or by many: the batches are those of the reference."""
     from paper_1705_07860_amd import binding as ob
     g = _random_arity_graph(n, arities, reach, n + len(arities))
     c = ob.Context(arena_bytes=512 << 20, mode=ob.OB_BYDEPTH)
@@ -1683,4 +1684,27 @@ def test_depths_of_nodes_of_any_arity_across_id_ranges(n, arities, reach):
     c.forward(g.root)
     assert np.array_equal(c.debug_read(ob.OB_DBG_DEPTH).astype(np.int64), S.depths(g))
     assert c.stats()["n_depth_retries"] == 0
+    for got, want in zip(c.schedule_read(), S.by_depth(g)):
+        assert np.array_equal(got, want)
     c.close()
+
+
+def _sums_side_by_side(m, arity):
+    """m sums with neighbouring ids, each of `arity` of the same 2048 rows."""
+    rng = np.random.default_rng(arity)
+    pb = wl.ParamBuilder(rng, std=0.1)
+    E = pb.add("E", 50, 16)
+    p = pb.done()
+    gb = wl.GraphBuilder(p)
+    xs = [gb.lookup(E, int(r)) for r in rng.integers(0, 50, 2048)]
+    ys = [gb.add([xs[i] for i in rng.integers(0, 2048, arity)]) for _ in range(m)]
+    return p, gb.finish(gb.add([gb.sqnorm(y) for y in ys]), m)
+
+
+def test_sums_of_nine_operands_schedule_about_as_fast_as_of_eight():
+    """Up to eight operands of a node are taken by one thread where nodes are set up, more by its workgroup: neither may
+    be what a schedule's time goes to.  Taken by the workgroup node after node, the sums of nine made scheduling
+    4.1 times as long as those of eight; with the edges shared out it is 1.5."""
+    eight, nine = _median_schedule_ms([_sums_side_by_side(4096, 8), _sums_side_by_side(4096, 9)])
+    say(f"  8 operands {eight:.3f} ms, 9 operands {nine:.3f} ms")
+    assert nine <= 2 * eight

@@ -1702,9 +1702,10 @@ def _sums_side_by_side(m, arity):
 
 
 def test_sums_of_nine_operands_schedule_about_as_fast_as_of_eight():
-    """Up to eight operands of a node are taken by one thread where nodes are set up, more by its workgroup: neither may
-    be what a schedule's time goes to.  Taken by the workgroup node after node, the sums of nine made scheduling
-    4.1 times as long as those of eight; with the edges shared out it is 1.5."""
+    """Up to eight operands of a node are taken by one thread where nodes are set up and where the dependencies between
+    batches are collected, more by its workgroup: neither may be what a schedule's time goes to.  Taken by the workgroup
+    node after node in both, the sums of nine made scheduling 4.1 times as long as those of eight, in the second alone 1.5
+    times; with the operands shared out over the threads it is 1.0."""
     eight, nine = _median_schedule_ms([_sums_side_by_side(4096, 8), _sums_side_by_side(4096, 9)])
     say(f"  8 operands {eight:.3f} ms, 9 operands {nine:.3f} ms")
-    assert nine <= 2 * eight
+    assert nine <= 1.25 * eight

@@ -215,7 +215,9 @@ __global__ __launch_bounds__(FRONTIER_THREADS) void k_depth_frontier(Tables T, c
 // why a wave holds no more than four nodes per lane and a workgroup one wave per SIMD.  The pass this
 // replaces kept a frontier queue per 4 096 ids (queue, counter, successor and queue again: five dependent LDS
 // operations per level).
-// Only lower ranges are waited for and the lowest waits for nobody; every wait is bounded.
+// Only lower ranges are waited for and the lowest waits for nobody; every wait is bounded.  A workgroup takes the lowest
+// range that is not taken yet (T.qcount[1] counts them), so what it waits for is done or on the chip, however many ranges
+// there are, whatever part of the chip the stream has and in whichever order workgroups start.
 constexpr u32 DEPTH_THREADS = 256;
 constexpr u32 DEPTH_NPT = 4;          // nodes per thread
 constexpr u32 DEPTH_PART = DEPTH_THREADS * DEPTH_NPT;   // ids per workgroup
@@ -240,13 +242,14 @@ __global__ __launch_bounds__(DEPTH_THREADS) void k_depth_partitioned(Tables T, u
 {
     __shared__ u32 s_dep[DEPTH_PART + 2];
     __shared__ unsigned short s_wide[DEPTH_THREADS / 64][64 * DEPTH_NPT];
-    __shared__ u32 s_quit;
+    __shared__ u32 s_quit, s_range;
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const u64 lt_mask = (1ull << lane) - 1ull;
-    const u32 lo = blockIdx.x * DEPTH_PART;
+    if (tid == 0) s_range = gridDim.x > 1u ? atomicAdd(&T.qcount[1], 1u) : 0u;
     for (u32 i = tid; i < DEPTH_PART + 2; i += DEPTH_THREADS) s_dep[i] = i == DEPTH_ONE ? 1u : 0u;
     if (tid == 0) s_quit = 0;
     __syncthreads();
+    const u32 lo = __builtin_amdgcn_readfirstlane(s_range) * DEPTH_PART;
     // node j of a lane: local id first + j
     const u32 first = tid * DEPTH_NPT;
     bool fwd0[DEPTH_NPT][DEPTH_NPT], fwd1[DEPTH_NPT][DEPTH_NPT];   // operand 0 / 1 of node j is the lane's own node i < j

@@ -1689,6 +1689,31 @@ def test_depths_of_nodes_of_any_arity_across_id_ranges(n, arities, reach):
     c.close()
 
 
+def test_depths_of_more_id_ranges_than_the_chip_holds_at_once():
+    """1 026 ranges of 1 024 ids, operands drawn from all nodes before: a range waits for any lower one, also where not
+    all of them can be on the chip together."""
+    from paper_1705_07860_amd import binding as ob
+    n = 1024 * 1025 + 3
+    rng = np.random.default_rng(n)
+    arity = rng.integers(2, 4, size=n)
+    arity[rng.random(n) < 0.6] = 0
+    arity[:3] = 0
+    arity[-1] = 2
+    in_off = np.concatenate([[0], np.cumsum(arity)])
+    cons = np.repeat(np.arange(n), arity)
+    leaf = arity == 0
+    zero, none = np.zeros(n, np.int64), np.full(n, -1)
+    g = wl.Graph(op=np.where(leaf, wl.OP_INPUT, wl.OP_ADD), out_dim=zero + 1, in_off=in_off,
+                 in_idx=(rng.random(cons.size) * cons).astype(np.int64), param=none, bias=none,
+                 aux0=np.where(leaf, np.cumsum(leaf) - 1, 0), aux1=zero, payload=rng.standard_normal(int(leaf.sum())), root=n - 1)
+    c = ob.Context(arena_bytes=4 << 30, mode=ob.OB_BYDEPTH)
+    c.add_bulk(g)
+    c.forward(g.root)
+    assert np.array_equal(c.debug_read(ob.OB_DBG_DEPTH).astype(np.int64), S.depths(g))
+    assert c.stats()["n_depth_retries"] == 0
+    c.close()
+
+
 def _sums_side_by_side(m, arity):
     """m sums with neighbouring ids, each of `arity` of the same 2048 rows."""
     rng = np.random.default_rng(arity)

@@ -263,7 +263,8 @@ int ob_debug_read(ob_ctx *ctx, int which, uint32_t *host_out, size_t cap_words, 
 /* Internal knobs, for tests of the library's own error handling and of its alternative paths.  which: OB_DBG_SET_*;
  * unknown: OB_E_ARG. */
 #define OB_DBG_SET_DEPTH_SPIN 0 /* idle polls a workgroup of the partitioned depth pass (Section 3.2) allows itself while it
-                                 * waits for a lower id range, default 2^21; 0 makes every range that has to wait give up at
+                                 * waits for a lower id range, default 2^21 (counted anew when one finds, once in 1 024
+                                 * polls, that waves of other ranges have ended); 0 makes every range that has to wait give up at
                                  * once, so that scheduling falls back to the single-workgroup pass (see n_depth_retries) */
 #define OB_DBG_SET_CONCAT_COPY 1 /* nonzero: every CONCAT batch is copied by the forward pass from the next schedule on
                                   * (default 0: batches that only matrix products read stay uncopied, see ob_stats) */

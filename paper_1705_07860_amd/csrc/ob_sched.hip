@@ -299,7 +299,7 @@ __global__ __launch_bounds__(DEPTH_THREADS) void k_depth_partitioned(Tables T, u
     bool any_ext = __ballot(has_ext) != 0ull, any_list = __ballot(has_list) != 0ull;
     const bool any_34 = __ballot(has_34) != 0ull;
     u32 wide_i = 0, wide_e = 0, wide_max = 0;     // node of the wave's list being walked, operands behind it, their largest word
-    u32 idle = 0, sweep = 0;
+    u32 idle = 0, sweep = 0, seen = 0;            // seen: nodes of ended waves when last looked
     bool gave_up = false;
     // (written out for waves without lists and with: beside the code for lists, sweeps took a sixth longer for everybody)
     auto sweeps = [&](auto with_lists) __attribute__((always_inline)) {
@@ -433,12 +433,14 @@ __global__ __launch_bounds__(DEPTH_THREADS) void k_depth_partitioned(Tables T, u
         }
         if (progress) { idle = 0; continue; }
         if (++idle > spin_limit || lds_load(&s_quit) != 0u) { gave_up = true; break; }
-        // (a range that gave up leaves its error flag: ranges waiting for it need not run into their own bound)
-        if ((idle & 1023u) == 0u && (__hip_atomic_load(&T.hdr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (u32)ERR_CYCLE)) {
-            gave_up = true;
-            break;
-        }
         if (idle > 16u) __builtin_amdgcn_s_sleep(1);
+        if ((idle & 1023u) != 0u) continue;
+        // (a range that gave up leaves its error flag: ranges waiting for it need not run into their own bound)
+        if (__hip_atomic_load(&T.hdr->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (u32)ERR_CYCLE) { gave_up = true; break; }
+        // The bound is on waiting for nothing: while waves below end, a path that goes through many of them is being
+        // worked off, and the wait starts anew.
+        const u32 ended = __hip_atomic_load(&T.hdr->frontier_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (ended != seen) { seen = ended; idle = 0; }
     }
     };
     if (any_list) sweeps(std::true_type{});

@@ -1714,6 +1714,25 @@ def test_depths_of_more_id_ranges_than_the_chip_holds_at_once():
     c.close()
 
 
+def test_a_long_path_through_many_id_ranges_is_no_reason_to_give_up():
+    """The bound on a range's wait is on idle polls while nothing below it ends.  A chain of 100 000 nodes ends a wave of
+    256 ids every 30 to 40 us, some 50 polls; its last ranges wait some 20 000 polls in all, over three times the bound set here
+    (which must be above 1 024: ended waves are looked at once in as many polls)."""
+    from paper_1705_07860_amd import binding as ob
+    gb = wl.GraphBuilder(wl.Params([], []))
+    h = gb.input(np.ones(4))
+    for _ in range(100000):
+        h = gb.tanh(h)
+    g = gb.finish(gb.sqnorm(h), 1)
+    c = ob.Context(arena_bytes=1 << 30, mode=ob.OB_BYDEPTH)
+    c.debug_set(ob.OB_DBG_SET_DEPTH_SPIN, 6000)
+    c.add_bulk(g)
+    c.forward(g.root)
+    assert np.array_equal(c.debug_read(ob.OB_DBG_DEPTH), np.arange(g.n))
+    assert c.stats()["n_depth_retries"] == 0
+    c.close()
+
+
 def _sums_side_by_side(m, arity):
     """m sums with neighbouring ids, each of `arity` of the same 2048 rows."""
     rng = np.random.default_rng(arity)

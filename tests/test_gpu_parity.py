@@ -1547,33 +1547,62 @@ def test_reading_one_node_of_any_width(d):
     c.close()
 
 
-@pytest.mark.parametrize("d", [512, 341, 256, 204, 64, 60])
-def test_pull_tiles_of_two_to_seventeen_rows(d):
-    """A pull tile holds as many rows as fit 1024 elements (2, 3, 4, 5, 16 and 17 here) and compares its rows' consumer
-    edges four or sixteen rows at a time.  Every odd group of nine rows has one row with one consumer more, at each
-    place of a tile in turn, so tiles with equal rows and with one row out of line both occur."""
-    from paper_1705_07860_amd import binding as ob
-    rng = np.random.default_rng(d)
+def _pull_rows_graph(d, R, k, odd_by):
+    """40 rows t of width d, in order, with two consumers each; row k of every second tile of R rows, and of the last,
+    is out of line with the others.  Returns the parameters, the graph, the ids of the rows t and which are odd."""
+    rng = np.random.default_rng(d + k)
     pb = wl.ParamBuilder(rng, std=0.3)
     W = pb.add("W", d, 8)
     p = pb.done()
     gb = wl.GraphBuilder(p)
-    losses = []
+    odd = [i % R == k and ((i // R) % 2 == 1 or i // R == 39 // R) for i in range(40)]
+    ys = [gb.matvec(W, -1, gb.input(rng.standard_normal(8))) for _ in range(40)]
+    ts, ss = [gb.tanh(y) for y in ys], [gb.sigmoid(y) for y in ys]
+    losses, late = [], []
     for i in range(40):
-        y = gb.matvec(W, -1, gb.input(rng.standard_normal(8)))
-        t, s = gb.tanh(y), gb.sigmoid(y)
-        losses.append(gb.sqnorm(gb.cmult(t, s)))
-        if (i // 9) % 2 and i % 9 == (i // 9) % 9:
-            losses.append(gb.sqnorm(gb.tanh(t)))
-    root = gb.add(losses)
-    g = gb.finish(root, 40)
-    o = Oracle(g, p, "f64")
-    o.forward()
-    o.backward(g.root)
-    for fuse in (2, 0):
-        c, root_ = run_gpu(p, g, ob.OB_BYDEPTH, fuse=fuse, arena=128 << 20)
-        check_against_oracle(c, p, g, o, root_, what=f"pull rows/{d}/fuse {fuse}")
-        c.close()
+        # "value": the factor beside t comes from elsewhere, so the value that t's gradient is read with is out of line
+        losses.append(gb.sqnorm(gb.cmult(ts[i], ss[(i + 7) % 40] if odd_by == "value" and odd[i] else ss[i])))
+        if odd_by == "offset" and odd[i]:
+            late.append(i)         # "offset": same consumer, its gradient row behind those of all others
+        else:
+            losses.append(gb.sqnorm((gb.sigmoid if odd_by == "kind" and odd[i] else gb.tanh)(ts[i])))
+        if odd_by == "count" and odd[i]:
+            losses.append(gb.sqnorm(gb.sigmoid(ts[i])))
+    losses += [gb.sqnorm(gb.tanh(ts[i])) for i in late]
+    return p, gb.finish(gb.add(losses), 40), np.asarray(ts), np.asarray(odd)
+
+
+@pytest.mark.parametrize("odd_by", ["count", "kind", "offset", "value"])
+@pytest.mark.parametrize("d", [512, 341, 256, 204, 64, 60])
+def test_pull_tiles_of_two_to_seventeen_rows(d, odd_by):
+    """A pull tile holds as many rows as fit 1024 elements (2, 3, 5, 4, 16 and 17 here) and compares its rows' consumer
+    edges four or sixteen rows at a time.  One row of every second tile, and of the last, is out of line (a consumer more, a consumer
+    of another kind, a gradient or a value row at another distance), at each place of a tile in turn.  Tiles of like rows
+    are read as such (up to sixteen rows), and none with a row of another count or kind is."""
+    from paper_1705_07860_amd import binding as ob
+    R = 1024 // d
+    for k in range(R):
+        p, g, ts, odd = _pull_rows_graph(d, R, k, odd_by)
+        o = Oracle(g, p, "f64")
+        o.forward()
+        o.backward(g.root)
+        for fuse in (2, 0):
+            c, root = run_gpu(p, g, ob.OB_BYDEPTH, fuse=fuse, arena=128 << 20)
+            tiles = c.debug_read(ob.OB_DBG_TILES_PULL).reshape(-1, 48)
+            order = c.debug_read(ob.OB_DBG_ORDER)
+            seen = 0
+            for t in tiles:        # words 0, 5, 6, 7, 40: first schedule position of the batch, row0, edges (all ones: rows differ), rows, stride
+                rows = np.searchsorted(ts, order[t[0] + t[5] + np.arange(t[7]) * t[40]])
+                if (rows >= 40).any() or not np.array_equal(ts[rows], order[t[0] + t[5] + np.arange(t[7]) * t[40]]):
+                    continue
+                seen += rows.size
+                if not odd[rows].any():
+                    assert (t[6] == 2) == (rows.size <= 16), (d, k, fuse, rows)
+                elif odd_by in ("count", "kind") and rows.size > 1:
+                    assert t[6] == 0xffffffff, (d, k, fuse, rows)
+            assert seen == 40
+            check_against_oracle(c, p, g, o, root, what=f"pull rows/{d}/{odd_by} at {k}/fuse {fuse}")
+            c.close()
 
 
 @pytest.mark.parametrize("rows,arity", [(1, 8), (1, 9), (3, 9), (300, 2), (300, 8), (300, 9), (2, 700)])

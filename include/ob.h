@@ -274,6 +274,10 @@ int ob_debug_set(ob_ctx *ctx, int which, uint64_t value);
  * pointers are host; the context's arena beyond its current use serves as scratch. */
 int ob_test_sort(ob_ctx *ctx, size_t n, const uint64_t *keys, const uint32_t *vals, int lo_bit,
                  int n_bits, uint64_t *keys_out, uint32_t *vals_out);
+/* The sort as the scheduler calls it: stably by [lo2, lo2 + bits2), among equals by [lo_bit, lo_bit + n_bits).  count (may be
+ * NULL) goes to the device and is read there: only the first *count pairs need sorting, the rest carry the largest key. */
+int ob_test_sort_fields(ob_ctx *ctx, size_t n, const uint64_t *keys, const uint32_t *vals, int lo_bit, int n_bits, int lo2,
+                        int bits2, const uint32_t *count, uint64_t *keys_out, uint32_t *vals_out);
 int ob_test_scan(ob_ctx *ctx, size_t n, const uint32_t *in, uint32_t *out_exclusive,
                  uint32_t *total);
 /* For callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses that

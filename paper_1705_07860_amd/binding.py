@@ -112,6 +112,7 @@ def lib():
             "ob_debug_set": (i, [vp, i, c_uint64]),
             "ob_param_sgd_step": (i, [vp, c_float, i]),
             "ob_test_sort": (i, [vp, sz, vp, vp, i, i, vp, vp]),
+            "ob_test_sort_fields": (i, [vp, sz, vp, vp, i, i, i, i, vp, vp, vp]),
             "ob_sort_pairs_noalloc": (i, [vp, sz, vp, vp, i, i]),
             "ob_stream_create_on_cus": (i, [i, i, POINTER(vp)]),
             "ob_stream_destroy": (i, [vp]),
@@ -388,6 +389,15 @@ class Context:
         v = np.ascontiguousarray(vals, np.uint32)
         ko, vo = np.empty_like(k), np.empty_like(v)
         self._ck(self.L.ob_test_sort(self.h, k.shape[0], _ptr(k), _ptr(v), lo_bit, n_bits, _ptr(ko), _ptr(vo)))
+        return ko, vo
+
+    def test_sort_fields(self, keys, vals, lo_bit, n_bits, lo2, bits2, count=None):
+        k = np.ascontiguousarray(keys, np.uint64)
+        v = np.ascontiguousarray(vals, np.uint32)
+        ko, vo = np.empty_like(k), np.empty_like(v)
+        n = None if count is None else np.asarray([count], np.uint32)
+        self._ck(self.L.ob_test_sort_fields(self.h, k.shape[0], _ptr(k), _ptr(v), lo_bit, n_bits, lo2, bits2,
+                                            None if n is None else _ptr(n), _ptr(ko), _ptr(vo)))
         return ko, vo
 
     def test_scan(self, a):

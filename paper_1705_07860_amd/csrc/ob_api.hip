@@ -1577,19 +1577,31 @@ int ob_debug_read(ob_ctx *ctx, int which, uint32_t *host_out, size_t cap_words, 
 int ob_test_sort(ob_ctx *ctx, size_t n, const uint64_t *keys, const uint32_t *vals, int lo_bit, int n_bits,
                  uint64_t *keys_out, uint32_t *vals_out)
 {
+    return ob_test_sort_fields(ctx, n, keys, vals, lo_bit, n_bits, 0, 0, nullptr, keys_out, vals_out);
+}
+
+int ob_test_sort_fields(ob_ctx *ctx, size_t n, const uint64_t *keys, const uint32_t *vals, int lo_bit, int n_bits, int lo2,
+                        int bits2, const uint32_t *count, uint64_t *keys_out, uint32_t *vals_out)
+{
     CHECK_CTX(ctx);
     if (!ctx->arena) return ctx_fail(ctx, OB_E_STATE, "no arena");
     if (n == 0) return OB_OK;
     const size_t save = ctx->top;
     u64 *ka = arena_array<u64>(ctx, n), *kb = arena_array<u64>(ctx, n);
-    u32 *va = arena_array<u32>(ctx, n), *vb = arena_array<u32>(ctx, n);
+    u32 *va = arena_array<u32>(ctx, n), *vb = arena_array<u32>(ctx, n), *cnt = arena_array<u32>(ctx, 1);
     void *scratch = arena_alloc(ctx, prim_sort_scratch_bytes(n));
     int rc = OB_OK;
-    if (!ka || !kb || !va || !vb || !scratch) rc = ctx_fail(ctx, OB_E_OOM, "arena too small");
+    if (!ka || !kb || !va || !vb || !cnt || !scratch) rc = ctx_fail(ctx, OB_E_OOM, "arena too small");
     if (rc == OB_OK) {
         hipError_t e = hipMemcpyAsync(ka, keys, n * 8, hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(va, vals, n * 4, hipMemcpyHostToDevice, ctx->stream);
-        if (e == hipSuccess) e = prim_sort_pairs(ka, va, kb, vb, n, lo_bit, n_bits, scratch, ctx->stream, nullptr);
+        if (e == hipSuccess && count) e = hipMemcpyAsync(cnt, count, 4, hipMemcpyHostToDevice, ctx->stream);
+        if (e == hipSuccess) {
+            if (bits2 > 0 || count)     // as the scheduler sorts: the buffer pairs change roles after an odd number of passes
+                e = prim_sort_pairs_swap(ka, va, kb, vb, n, lo_bit, n_bits, lo2, bits2, scratch, ctx->stream, nullptr, count ? cnt : nullptr);
+            else
+                e = prim_sort_pairs(ka, va, kb, vb, n, lo_bit, n_bits, scratch, ctx->stream, nullptr);
+        }
         if (e == hipSuccess) e = hipMemcpyAsync(keys_out, ka, n * 8, hipMemcpyDeviceToHost, ctx->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(vals_out, va, n * 4, hipMemcpyDeviceToHost, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);

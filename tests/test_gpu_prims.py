@@ -40,18 +40,40 @@ def test_radix_sort_is_stable_and_exact(ctx, n, lo, bits):
     assert np.array_equal(ko, keys[order])
 
 
-def test_two_field_sort_matches_lexicographic_order(ctx):
-    # sort by the low field, then by the field at bit 32: the schedule's (depth, representative) key
-    rng = np.random.default_rng(7)
-    n = 50000
-    lo = rng.integers(0, 1 << 16, size=n, dtype=np.uint64)
-    hi = rng.integers(0, 600, size=n, dtype=np.uint64)
-    keys = (hi << np.uint64(32)) | lo
-    vals = np.arange(n, dtype=np.uint32)
-    k1, v1 = ctx.test_sort(keys, vals, 0, 16)
-    k2, v2 = ctx.test_sort(k1, v1, 32, 16)
-    order = np.lexsort((vals, lo, hi))
-    assert np.array_equal(v2, vals[order])
+def _two_fields(n, lo, hi):
+    """n pairs; the order by the field of `hi` bits at bit 32, then by that of `lo` bits at bit 3, then as they come."""
+    rng = np.random.default_rng(n + 100 * lo + hi)
+    a, b = rng.integers(0, 1 << lo, size=n, dtype=np.uint64), rng.integers(0, 1 << hi, size=n, dtype=np.uint64)
+    b[: n // 2] = b[0]            # half the pairs share the upper field
+    keys = (b << np.uint64(32)) | (a << np.uint64(3)) | rng.integers(0, 8, size=n, dtype=np.uint64)
+    return keys, np.arange(n, dtype=np.uint32)[::-1].copy(), np.lexsort((np.arange(n), a, b))
+
+
+@pytest.mark.parametrize("lo,hi", [(8, 8), (16, 10), (17, 17), (9, 5), (5, 0), (0, 9)])   # 2, 4, 6, 3, 1 and 2 passes
+@pytest.mark.parametrize("n", [1, 2, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 50000, 524288, 524289])
+def test_two_field_sort_matches_lexicographic_order(ctx, n, lo, hi):
+    """The schedule's sort: both fields in one call, the less significant one first."""
+    keys, vals, order = _two_fields(n, lo, hi)
+    ko, vo = ctx.test_sort_fields(keys, vals, 3, lo, 32, hi)
+    assert np.array_equal(ko, keys[order]) and np.array_equal(vo, vals[order])
+    if n <= 8193:                 # one field after the other gives the same
+        k1, v1 = ctx.test_sort(keys, vals, 3, lo)
+        k2, v2 = ctx.test_sort(k1, v1, 32, hi)
+        assert np.array_equal(k2, ko) and np.array_equal(v2, vo)
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 2049, 4097, 8192])
+@pytest.mark.parametrize("count", [0, 1, 1000, -1, None])
+def test_sort_of_a_length_known_on_the_device(ctx, n, count):
+    """The pairs from the count on carry the largest key and stay where they are, whichever width of the one-workgroup
+    sort the count selects."""
+    m = n if count is None else (n - 1 if count < 0 else count)
+    keys, vals, order = _two_fields(n, 13, 13)
+    keys[m:] = 0xffffffffffffffff
+    order = np.concatenate([np.lexsort((np.arange(m), (keys[:m] >> np.uint64(3)) & np.uint64(0x1fff),
+                                        (keys[:m] >> np.uint64(32)) & np.uint64(0x1fff))), np.arange(m, n)]).astype(np.int64)
+    ko, vo = ctx.test_sort_fields(keys, vals, 3, 13, 32, 13, count=m)
+    assert np.array_equal(ko, keys[order]) and np.array_equal(vo, vals[order])
 
 
 # one workgroup with 1, 2, 4 and 8 keys per lane; blocks of 2048, whose counts the scatter adds up itself up to 256 blocks

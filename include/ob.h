@@ -283,7 +283,7 @@ int ob_test_scan(ob_ctx *ctx, size_t n, const uint32_t *in, uint32_t *out_exclus
 /* For callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses that
  * forbid device allocation): the same stable radix sort as ob_test_sort, on the caller's DEVICE arrays,
  * in place, with every temporary (second key / value buffers, digit tables, scan sums) in a fixed
- * array inside the library's device image (about 3.5 MiB per GPU, held until the process ends).  The
+ * array inside the library's device image (about 3.3 MiB per GPU, held until the process ends).  The
  * call allocates nothing on the host or the device, needs no context, and only queues work on
  * hip_stream (a hipStream_t, NULL = default stream): the result is in keys_dev / vals_dev once the
  * stream gets there.  Sorts the n pairs stably by bits [lo_bit, lo_bit + n_bits) of the key.

@@ -208,7 +208,7 @@ struct Tri {
     __host__ __device__ Tri operator+(const Tri &o) const { Tri r; r.a = a + o.a; r.b = b + o.b; r.c = c + o.c; r.d = 0; return r; }
 };
 
-// Header the host reads back after scheduling (one small D2H copy).
+// Header of a schedule; k_read_back writes it and the first slot records to page-locked host memory.
 struct SchedHeader {
     u32 n_steps, n_batches, n_items, err;
     u64 val_floats, grad_floats;
@@ -230,7 +230,7 @@ struct Tables {
     const float *payload;
     const u32 *manual;     // the caller's batch label per node (manual batching only, else null)
     const ParamDesc *params;
-    // scheduler tables
+    // scheduler tables (indeg: unresolved operands, used by the single-workgroup depth pass only)
     u64 *sig; u32 *step; u32 *indeg; u32 *outdeg; u32 *succ_off; u32 *succ_edge; u32 *edge_cons;
     u32 *queue; u32 *qcount;            // frontier queue; [0] = its tail, [1] = id ranges handed out by the depth pass by ranges
     u64 *ht_keys; u32 *ht_vals; u32 ht_mask; u32 *ht_slot;

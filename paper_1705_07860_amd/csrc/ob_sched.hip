@@ -1,6 +1,6 @@
-// GPU scheduler: node signatures as integer hashes (Appendix B), depth by level-synchronous
-// frontier passes over a successor CSR with per-node unresolved-dependency counters
-// (Section 3.2), batches = equal (depth, signature) found by a stable radix sort, then the
+// GPU scheduler: node signatures as integer hashes (Appendix B), depth (Section 3.2) by ranges of node ids
+// that settle side by side (or, as the fallback, by frontier passes of one workgroup over the successor CSR),
+// batches = equal (depth, signature) found by a stable radix sort, then the
 // memory layout of the batched execution (Section 3.3: operands of a batch must be
 // addressable as one matrix; results are laid out contiguously in batch order).
 #include "ob_ctx.h"
@@ -21,22 +21,16 @@ __device__ inline u64 mix64(u64 x)
 }
 __device__ inline u64 comb(u64 h, u64 x) { return mix64(h ^ (x + 0x9e3779b97f4a7c15ULL + (h << 6) + (h >> 2))); }
 
-// ---- stage 1: signatures, dependency counters, out-degrees, initial frontier ---------------
-// Signature tuple (Section 3.2 / Appendix A): operation, output dimension, arity, shared
-// parameter ids (the A and y of A x + y), slice range, operand dimensions.  LOOKUP's row,
-// PICK_NLS's label and INPUT's payload are data and stay out.  The operands' dimensions enter as a
-// sum of position-salted hashes, so that a node with many operands can be summed by many threads.
-// A thread takes a node with up to INIT_OPS operands, edges included; the edges of nodes with more are shared out over
-// the workgroup (WideRows).  (A launch with a thread per edge had to look its node up by bisection in memory and
-// meet all operands of a wide sum in atomics on one signature: 23 us for 52 000 edges, 169 us for 480 000 of
-// which one node holds 10 000, beside 8 and 16 us of this kernel without the edges; 10.5 and 37 us together now.
-// With the wide nodes taken by the workgroup one after the other, 4 096 sums of nine operands side by side took
-// 768 us, 18 now.)
-// steps: 0 = every node is its own step, 1 = steps come from the depth pass by id ranges, 2 = steps are the
-// caller's batch labels, 3 = steps come from the single-workgroup depth pass (leaves are queued here).
-constexpr u32 INIT_OPS = 8;
-__device__ inline u64 operand_hash(const Tables &T, u32 u, u32 j) { return mix64(comb(0x5bd1e995ULL + j, T.out_dim[u])); }
+// start values: the first `zeros` elements zero, the others all ones
+__global__ void k_clear(uint4 *p, size_t zeros, size_t n)
+{
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        const u32 v = i < zeros ? 0u : ~0u;
+        p[i] = make_uint4(v, v, v, v);
+    }
+}
 
+// ---- stage 1: signatures, out-degrees, edges by producer -------------------------------------
 // The rows of a workgroup that have too many edges for a thread, as one list of edges that all its threads walk: an entry
 // finds its row by bisection in LDS.
 struct WideRows {
@@ -60,14 +54,20 @@ __device__ inline u32 wide_row(const WideRows &S, u32 rows, u32 x)
     return lo;
 }
 
-// start values: the first `zeros` elements zero, the others all ones
-__global__ void k_clear(uint4 *p, size_t zeros, size_t n)
-{
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const u32 v = i < zeros ? 0u : ~0u;
-        p[i] = make_uint4(v, v, v, v);
-    }
-}
+// Signature tuple (Section 3.2 / Appendix A): operation, output dimension, arity, shared
+// parameter ids (the A and y of A x + y), slice range, operand dimensions.  LOOKUP's row,
+// PICK_NLS's label and INPUT's payload are data and stay out.  The operands' dimensions enter as a
+// sum of position-salted hashes, so that a node with many operands can be summed by many threads.
+// A thread takes a node with up to INIT_OPS operands, edges included; the edges of nodes with more are shared out over
+// the workgroup (WideRows).  (A launch with a thread per edge had to look its node up by bisection in memory and
+// meet all operands of a wide sum in atomics on one signature: 23 us for 52 000 edges, 169 us for 480 000 of
+// which one node holds 10 000, beside 8 and 16 us of this kernel without the edges; 10.5 and 37 us together now.
+// With the wide nodes taken by the workgroup one after the other, 4 096 sums of nine operands side by side took
+// 768 us, 18 now.)
+// steps: 0 = every node is its own step, 1 = steps come from the depth pass by id ranges, 2 = steps are the
+// caller's batch labels, 3 = steps come from the single-workgroup depth pass (leaves are queued here).
+constexpr u32 INIT_OPS = 8;
+__device__ inline u64 operand_hash(const Tables &T, u32 u, u32 j) { return mix64(comb(0x5bd1e995ULL + j, T.out_dim[u])); }
 
 __global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *keys, u32 *vals)
 {
@@ -146,8 +146,8 @@ __global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *key
     if (threadIdx.x < rows) T.sig[S.row[threadIdx.x]] += s_sum[threadIdx.x];
 }
 
-// after the sort: succ_edge[q] = edge id, succ_node[q] = its consumer (stored in T.queue's
-// sibling array to save one hop in the frontier loop)
+// after the sort: succ_edge[q] = edge id, succ_node[q] = its consumer (which
+// saves the single-workgroup depth pass and the agenda a hop)
 __global__ void k_succ_finish(Tables T, const u32 *sorted_edge, u32 *succ_node)
 {
     const u32 q = blockIdx.x * blockDim.x + threadIdx.x;
@@ -157,7 +157,7 @@ __global__ void k_succ_finish(Tables T, const u32 *sorted_edge, u32 *succ_node)
     succ_node[q] = T.edge_cons[e];
 }
 
-// ---- stage 2: depth by frontier passes ---------------------------------------------------------
+// ---- stage 2: depth by frontier passes (the fallback) --------------------------------------------
 // One workgroup walks the graph level by level.  queue[head, tail) is the current frontier
 // (all nodes of depth `level`); a node joins the next frontier when its last unresolved
 // dependency is resolved, which is exactly when the deepest of its operands has been
@@ -1945,7 +1945,7 @@ inline int bit_width_u32(u32 x) { int b = 0; while (x) { ++b; x >>= 1; } return 
 
 
 // First half of scheduling: allocates the scheduler tables for n nodes / E edges in the arena and
-// queues every stage on the schedule stream, ending with the device-to-host copies of the header
+// queues every stage on the schedule stream, ending with the launch that writes the header
 // and the per-slot launch tables.  Does not wait.
 int sched_enqueue(ob_ctx *ctx)
 {
@@ -1981,8 +1981,8 @@ int sched_enqueue(ob_ctx *ctx)
         field = arena_array<type>(ctx, (count));                            \
         if (!field) return ctx_fail(ctx, -5, "arena too small for scheduler tables (%s)", #field); \
     } while (0)
-    // Tables that must start at zero lie next to each other, and so do those that start as all ones:
-    // two fills clear them all.
+    // Tables that must start at zero lie next to each other, those that start as all ones behind them: k_clear sets
+    // both in one launch.
     u32 *g_dep;
     u32 *bset, *blist;
     AgendaTables AG{};
@@ -2143,7 +2143,7 @@ int sched_enqueue(ob_ctx *ctx)
     }
     HIP_TRY(ctx, hipGetLastError());
 
-    // ---- queue the read-back of the header and of a first window of the per-slot tables ----
+    // ---- the header and a first window of the per-slot tables go to the host ----
     // pinned layout: [header 256 B][first hdr_window entries of the slot table]
     ctx->hdr_window = (u32)(slot_cap < SLOT_WINDOW ? slot_cap : SLOT_WINDOW);
     char *hp = (char *)ctx->hdr_pinned;
@@ -2160,8 +2160,8 @@ int sched_finish(ob_ctx *ctx)
 {
     Tables &T = ctx->T;
     hipStream_t s = ctx->sched_stream;
-    // wait for this context's own scheduling work only (its event was recorded behind the header
-    // copy): other contexts may already have queued theirs on the same stream
+    // wait for this context's own scheduling work only (its event was recorded behind the launch
+    // that writes the header): other contexts may already have queued theirs on the same stream
     HIP_TRY(ctx, hipEventSynchronize(ctx->ev[9]));
     const char *hp = (const char *)ctx->hdr_pinned;
     ctx->hdr = *(const SchedHeader *)hp;

@@ -29,9 +29,9 @@ def test_sort_without_allocation_matches_the_sort_entry_point():
     from paper_1705_07860_amd import binding as ob
     rng = np.random.default_rng(20171107)
     c = ob.Context(arena_bytes=64 << 20)
-    # 200 003 pairs: 196 blocks of 1024 and a ragged tail, three 8-bit passes (odd: the result is copied
+    # 200 003 pairs: 97 blocks of 2048 and a ragged tail, three 8-bit passes (odd: the result is copied
     # back from the second buffers); then 5 001 pairs on two passes through the one-workgroup path;
-    # then sizes around the block and the path boundaries
+    # then one pair more than that path takes, a single pair, and one more than it holds with a pair per thread
     for n, lo_bit, n_bits in [(200003, 0, 20), (5001, 16, 13), (8193, 32, 9), (1, 0, 8), (1025, 3, 64 - 3)]:
         keys, vals, lo, nb = _case(rng, n, lo_bit, n_bits)
         got_k, got_v = _noalloc(torch, ob, keys, vals, lo, nb)

@@ -210,7 +210,7 @@ __global__ __launch_bounds__(FRONTIER_THREADS) void k_depth_frontier(Tables T, c
 // minibatch), the wave walks them instead, one after the other, eight reads per lane at a time, whenever nothing else of
 // the wave moves.  A walk step takes about as long as four sweeps, which is where
 // DEPTH_WALK puts the line.  (With all of them walked, 64 recurrences of 60 steps with a sum of five operands each took
-// 5 100 us for this pass, sequences of 60 states with a sum over all earlier ones 2 280; now 120 and 210.)
+// 5 100 us for this pass, sequences of 60 states with a sum over all earlier ones 2 280; now 109 and 210.)
 // What bounds it: one dependent LDS read plus some forty instructions per level of the longest path, which is
 // why a wave holds no more than four nodes per lane and a workgroup one wave per SIMD.  The pass this
 // replaces kept a frontier queue per 4 096 ids (queue, counter, successor and queue again: five dependent LDS

@@ -1673,8 +1673,8 @@ def _sum_recurrences(n, steps, arity):
 @pytest.mark.parametrize("arity", [5, 12])
 def test_recurrences_over_wider_sums_schedule_about_as_fast(arity):
     """The depth pass keeps four operands of a node at hand.  Nodes with more must not be what a schedule's time goes
-    to: the same recurrences with sums of 5 and 12 operands have 1.2 and 2.3 times the nodes and measure 1.2 and
-    1.6 times the time; walked one after the other by their waves they took 14 to 16 times as long."""
+    to: the same recurrences with sums of 5 and 12 operands have 1.2 and 2.3 times the nodes and measure 1.2 times
+    the time; walked one after the other by their waves they took 14 to 16 times as long."""
     four, more = _median_schedule_ms([_sum_recurrences(64, 60, 4), _sum_recurrences(64, 60, arity)])
     say(f"  4 operands {four:.3f} ms, {arity} operands {more:.3f} ms")
     assert more <= 4 * four

@@ -24,6 +24,7 @@ __device__ inline float4 ld4(const float *p) { return *reinterpret_cast<const fl
 __device__ inline void st4(float *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
 __device__ inline float sigmoidf_(float x) { return 1.0f / (1.0f + expf(-x)); }
 
+__device__ inline u32 sreg(u32 v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ inline float wave_sum(float v)
 {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -1181,7 +1182,6 @@ __device__ inline uint4 lds_q(const PullDesc &d, u32 k)
     const vec4u t = ((lds_vec4u *)(&d))[k];
     return make_uint4(t.x, t.y, t.z, t.w);
 }
-__device__ inline u32 sreg(u32 v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // One or two edges of such a tile: loads first, sums after.
 template <u32 J0, u32 NJ>
@@ -1237,6 +1237,138 @@ __device__ inline void pull_tile_uni4(const Tables &T, const uint4 *q, lds_float
         st4(T.G + own, acc);
         if (lflags & TF_OUT_LDS) lds_st4(cl + (u32)(own + lds_out), acc);
     }
+}
+
+// ------------------------------------------------------------------------------------------------
+// gated cells: a row of an LSTM or tree-LSTM step, a thread per column, everything in registers
+// ------------------------------------------------------------------------------------------------
+// The rows of a work item are spread over the workgroup's waves, a row's columns over the lanes of one to four of them.  Same
+// operations in the same order as tile by tile, each rounded on its own, so the same bits.
+template <int NW>
+__device__ inline void cell_fwd_item(const Tables &T, const TileDesc *tiles, u32 rows)
+{
+    const u32 lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u32 per = NW / rows, t = wave / per, part = wave % per;
+    if (t >= rows) return;
+    const CellRec R = *reinterpret_cast<const CellRec *>(tiles + t);      // (copied: a store could change it for all the compiler knows)
+    if (R.mark != CELL_MARK) return;
+    float *V = T.V;
+    for (u32 col = part * 64u + lane; col < R.H; col += per * 64u) {
+        u32 at[3 + CELL_FORGET] = {R.at_i, R.at_g, R.at_o, R.at_f[0], R.at_f[1]};
+        float z[3 + CELL_FORGET], prev[CELL_FORGET];
+#pragma unroll
+        for (u32 k = 0; k < CELL_FORGET; ++k) prev[k] = k < R.nf ? V[R.prev[k] + col] : 0.f;
+        if (R.sums) {
+            float x[3 + CELL_FORGET], y[3 + CELL_FORGET];
+#pragma unroll
+            for (u32 k = 0; k < 3 + CELL_FORGET; ++k) {
+                x[k] = y[k] = 0.f;
+                if (k < 3u + R.nf) { x[k] = V[R.a + at[k] + col]; y[k] = V[R.b + at[k] + col]; }
+            }
+#pragma unroll
+            for (u32 k = 0; k < 3 + CELL_FORGET; ++k) {
+                z[k] = x[k] + y[k];
+                if (k < 3u + R.nf) V[R.S + at[k] + col] = z[k];
+            }
+        } else {
+#pragma unroll
+            for (u32 k = 0; k < 3 + CELL_FORGET; ++k) z[k] = k < 3u + R.nf ? V[R.S + at[k] + col] : 0.f;
+        }
+        const float i = sigmoidf_(z[0]), g = tanhf(z[1]), o = sigmoidf_(z[2]);
+        const float ic = mul_r(i, g);
+        float c = ic;
+        if (R.nf) {
+            const float f0 = sigmoidf_(z[3]), p0 = mul_r(f0, prev[0]);
+            V[R.f[0] + col] = f0;
+            V[R.fp[0] + col] = p0;
+            if (R.nf == 1u) {
+                c = R.ic_at == 0u ? add_r(ic, p0) : add_r(p0, ic);
+            } else {
+                const float f1 = sigmoidf_(z[4]), p1 = mul_r(f1, prev[1]);
+                V[R.f[1] + col] = f1;
+                V[R.fp[1] + col] = p1;
+                c = R.ic_at == 0u ? add_r(add_r(ic, p0), p1) : R.ic_at == 1u ? add_r(add_r(p0, ic), p1) : add_r(add_r(p0, p1), ic);
+            }
+            V[R.c + col] = c;
+        }
+        const float tc = tanhf(c);
+        V[R.i + col] = i; V[R.g + col] = g; V[R.o + col] = o; V[R.ic + col] = ic; V[R.tc + col] = tc;
+        V[R.h + col] = mul_r(o, tc);
+    }
+}
+
+// Gradients of all nodes of the cells' rows.  GX: gradients from later evaluation stages are added to every node's.
+template <int NW, bool GX>
+__device__ inline void cell_bwd_rows(const Tables &T, const PullDesc *tiles, u32 rows)
+{
+    const u32 lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u32 per = NW / rows, t = wave / per, part = wave % per;
+    if (t >= rows) return;
+    const CellRec R = *reinterpret_cast<const CellRec *>(tiles + t);
+    if (R.mark != CELL_MARK) return;
+    const float *V = T.V;
+    float *G = T.G;
+    const u32 nh = R.n_edges & 0xffu;
+    for (u32 col = part * 64u + lane; col < R.H; col += per * 64u) {
+        auto start = [&](u32 off) __attribute__((always_inline)) { return GX ? T.Gx[off + col] : 0.f; };
+        // everything that is read, before anything that waits for it
+        float eg[CELL_H_EDGES], ev[CELL_H_EDGES], cg = 0.f, cv = 0.f;
+#pragma unroll
+        for (u32 k = 0; k < CELL_H_EDGES; ++k) {
+            eg[k] = ev[k] = 0.f;
+            if (k >= nh) continue;
+            eg[k] = G[R.he[k].goff + col];
+            if (R.he[k].kind >= (u32)EK_MUL) ev[k] = V[R.he[k].voff + col];
+        }
+        if (R.n_edges >> 8) {
+            cg = G[R.ce.goff + col];
+            if (R.ce.kind >= (u32)EK_MUL) cv = V[R.ce.voff + col];
+        }
+        const float i = V[R.i + col], g = V[R.g + col], o = V[R.o + col], tc = V[R.tc + col];
+        float f[CELL_FORGET], prev[CELL_FORGET];
+#pragma unroll
+        for (u32 k = 0; k < CELL_FORGET; ++k) {
+            f[k] = prev[k] = 0.f;
+            if (k < R.nf) { f[k] = V[R.f[k] + col]; prev[k] = V[R.prev[k] + col]; }
+        }
+        float gh = start(R.h);
+#pragma unroll
+        for (u32 k = 0; k < CELL_H_EDGES; ++k)
+            if (k < nh) gh = add_r(gh, R.he[k].kind >= (u32)EK_MUL ? mul_r(eg[k], edge_factor(R.he[k].kind, ev[k])) : eg[k]);
+        const float gtc = add_r(start(R.tc), mul_r(gh, o)), go = add_r(start(R.o), mul_r(gh, tc));
+        float gc = add_r(start(R.c), mul_r(gtc, edge_factor(EK_DTANH, tc)));
+        if (R.n_edges >> 8) gc = add_r(gc, R.ce.kind >= (u32)EK_MUL ? mul_r(cg, edge_factor(R.ce.kind, cv)) : cg);
+        G[R.h + col] = gh; G[R.tc + col] = gtc; G[R.o + col] = go; G[R.c + col] = gc;
+        const float gic = R.nf ? add_r(start(R.ic), gc) : gc;
+        const float gi = add_r(start(R.i), mul_r(gic, g)), gg = add_r(start(R.g), mul_r(gic, i));
+        if (R.nf) G[R.ic + col] = gic;
+        G[R.i + col] = gi; G[R.g + col] = gg;
+        float s[3 + CELL_FORGET];
+        s[0] = add_r(start(R.sl_i), mul_r(gi, edge_factor(EK_DSIGM, i)));
+        s[1] = add_r(start(R.sl_g), mul_r(gg, edge_factor(EK_DTANH, g)));
+        s[2] = add_r(start(R.sl_o), mul_r(go, edge_factor(EK_DSIGM, o)));
+        G[R.sl_i + col] = s[0]; G[R.sl_g + col] = s[1]; G[R.sl_o + col] = s[2];
+#pragma unroll
+        for (u32 k = 0; k < CELL_FORGET; ++k) {
+            s[3 + k] = 0.f;
+            if (k >= R.nf) continue;
+            const float gp = add_r(start(R.fp[k]), gc), gf = add_r(start(R.f[k]), mul_r(gp, prev[k]));
+            s[3 + k] = add_r(start(R.sl_f[k]), mul_r(gf, edge_factor(EK_DSIGM, f[k])));
+            G[R.fp[k] + col] = gp; G[R.f[k] + col] = gf; G[R.sl_f[k] + col] = s[3 + k];
+        }
+        if (R.sums) {
+            const u32 at[3 + CELL_FORGET] = {R.at_i, R.at_g, R.at_o, R.at_f[0], R.at_f[1]};
+#pragma unroll
+            for (u32 k = 0; k < 3 + CELL_FORGET; ++k)
+                if (k < 3u + R.nf) G[R.S + at[k] + col] = add_r(start(R.S + at[k]), s[k]);
+        }
+    }
+}
+template <int NW>
+__device__ inline void cell_bwd_item(const Tables &T, const PullDesc *tiles, u32 rows)
+{
+    if (T.Gx) cell_bwd_rows<NW, true>(T, tiles, rows);
+    else cell_bwd_rows<NW, false>(T, tiles, rows);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1310,8 +1442,9 @@ __global__ __launch_bounds__(WG, KIND == FWD_LEAN ? 6 : 3) void k_fwd_step(u32 w
     const u32 lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (u32 w = work_lo + blockIdx.x; w < work_hi; w += gridDim.x) {
         WorkRec wr;
-        if (run_len) { wr.first = tile_lo + (w - work_lo) * run_len; wr.len = run_len; }
+        if (run_len) { wr.first = tile_lo + (w - work_lo) * (run_len & ~CELL_ITEM); wr.len = run_len; }
         else wr = works_f[w];
+        if (KIND == FWD_LEAN && (wr.len & CELL_ITEM)) { cell_fwd_item<WG / 64>(T, tiles_f + sreg(wr.first), sreg(wr.len) & ~CELL_ITEM); continue; }
         if (wr.len == 1) {
             const TileDesc d = tiles_f[wr.first];
             if (KIND == FWD_LEAN) ew_fwd_tile(T, d, (lds_float *)lds, threadIdx.x, WG);
@@ -1361,8 +1494,9 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_bwd_step(u32 work_lo, u32 wo
         }
         const u32 w = work_lo + (item - n_dx);
         WorkRec wr;
-        if (run_len) { wr.first = tile_lo + (w - work_lo) * run_len; wr.len = run_len; }
+        if (run_len) { wr.first = tile_lo + (w - work_lo) * (run_len & ~CELL_ITEM); wr.len = run_len; }
         else { wr = works_a[w]; wr.first = sreg(wr.first); wr.len = sreg(wr.len); }
+        if (LEAN && (wr.len & CELL_ITEM)) { cell_bwd_item<BWD_THREADS / 64>(T, tiles_a + sreg(wr.first), sreg(wr.len) & ~CELL_ITEM); continue; }
         if (wr.len == 1) {
             const PullDesc d = tiles_a[wr.first];
             pull_tile(T, d, (lds_float *)lds, threadIdx.x, BWD_THREADS);

@@ -154,6 +154,33 @@ struct PullDesc {
 // of the tile's i-th row is goff + i * gs + c in either memory.
 static_assert(sizeof(PullDesc) == 192, "PullDesc must be 192 bytes");
 
+// A gated cell: what the component-wise nodes of one row of an LSTM or tree-LSTM step compute.  From the gate sums S (S = a + b,
+// or a row as it is) come an input gate i, a candidate g, an output gate o and up to CELL_FORGET forget gates f, each a slice of S;
+// c = i g + sum of f_k p_k (p_k: rows from elsewhere), h = o tanh(c).  Offsets of rows are the same in both arenas, but for the
+// slices, which have rows in the gradient arena only.  The record takes a TileDesc's place (the forward pass needs its first words
+// only) and a PullDesc's.
+constexpr u32 CELL_FORGET = 2, CELL_H_EDGES = 4;
+constexpr u32 CELL_MARK = 0xffffffffu;      // no operation and no position
+struct CellEdge { u32 kind, goff, voff; };  // a consumer from elsewhere (EK_PLAIN, EK_MUL, EK_DTANH, EK_DSIGM)
+struct CellRec {
+    u32 mark, H, nf, ic_at;          // columns; forget gates; place of i g among the terms of c
+    u32 h, tc, o, c;                 // tc = tanh(c)
+    u32 ic, i, g, sums;              // ic = i g (c itself without forget gates); sums: 1 = S is the sum of a and b, 0 = a row as it is
+    u32 f[CELL_FORGET], fp[CELL_FORGET], prev[CELL_FORGET];   // gate, its product with p, p
+    u32 S, a, b;
+    u32 at_i, at_g, at_o, at_f[CELL_FORGET];      // first column of the gate's slice of S
+    u32 sl_i, sl_g, sl_o, sl_f[CELL_FORGET];      // gradient rows of the slices
+    u32 n_edges;                     // consumers of h | of c beside tanh (at most one) << 8
+    CellEdge he[CELL_H_EDGES], ce;
+    u32 pad;
+};
+static_assert(sizeof(CellRec) == sizeof(PullDesc), "a CellRec takes a PullDesc's place");
+constexpr u32 CELL_NODES = 4 + CELL_FORGET + 1 + 2 * (CELL_FORGET + 3);
+struct CellNodes { u32 batch[CELL_NODES]; };      // [0]: of h | number of nodes << 16 (a fused plan has at most 4 096 batches)
+constexpr u32 CELL_ITEM = 0x80000000u;      // in a work item's length: its tiles are CellRecs, a row each
+constexpr u32 CELL_WAVES = 4;               // waves of the forward kernel: a row takes one to four of them, a work item fills them
+__host__ __device__ inline u32 cell_row_waves(u32 H) { const u32 w = (H + 63u) / 64u; return w < 3u ? w : 4u; }
+
 // A launch chain: batches that run in the same launch slot.  A fused chain holds component-wise
 // batches whose rows fall into G groups (member b has B_b / G consecutive rows per group) such
 // that every in-chain operand of a row lies in the row's own group.  One workgroup then owns a
@@ -161,7 +188,7 @@ static_assert(sizeof(PullDesc) == 192, "PullDesc must be 192 bytes");
 // Every other batch is a chain of its own.
 struct ChainRec {
     u32 first, k;          // members are lorder[first .. first + k)
-    u32 slot, fused;       // fused: component-wise members tiled by group blocks (2: with results handed on through LDS)
+    u32 slot, fused;       // fused: component-wise members tiled by group blocks (2: with results handed on through LDS; 3: gated cells)
     u32 G, Rg, nrb, kt;    // groups, groups per block, number of blocks, tiles per block (sum of rows per group)
     u32 ktf, pad0, pad1, pad2;   // forward tiles per block: kt without the members that are views (they have no forward work)
 };
@@ -214,7 +241,7 @@ struct SchedHeader {
     u64 val_floats, grad_floats;
     u32 tiles_fwd, tiles_pull, tiles_dx, frontier_done;
     u32 n_slots, n_chains, works_fwd, works_pull;
-    u32 n_bedges, slot_sweeps, p0, p1;
+    u32 n_bedges, slot_sweeps, p0, n_cells;     // p0: the plan is not fused
     u32 view_batches, view_floats, virt_batches, virt_floats;   // SLICE batches that are views / CONCAT batches never copied, and their sizes
 };
 enum : u32 { ERR_CYCLE = 1, ERR_COLLISION = 2, ERR_TABLE_FULL = 4, ERR_OVERFLOW = 8, ERR_CLASSES = 16 };
@@ -243,6 +270,11 @@ struct Tables {
     u32 *slot_of; u32 *label_of; u32 *lorder;
     u32 *blevel;           // per batch: its step (depth mode) or its level inside its fused chain (agenda mode)
     u32 *chain_of_batch;   // per batch: index of its launch chain
+    CellRec *cells; u32 *cell_of;          // gated cells; per position of an output h: its cell
+    CellNodes *cell_nodes_of;              // per cell: the batches of its nodes
+    u32 *slot_mixed;                       // per slot: products, reductions or wide sums run in it
+    u32 *cell_rows, *cell_nodes;           // per batch of outputs: cells whose nodes lie in one chain, and the nodes they hold
+    u32 cells_cap;
     ChainRec *chains; CLay *clay; u32 *chain_of_lpos;
     SlotRec *slots;
     WorkRec *works_f; WorkRec *works_a;

@@ -1089,6 +1089,144 @@ __global__ __launch_bounds__(TPB) void k_bedges(Tables T, u32 *bset, u32 *blist)
     }
 }
 
+// ---- gated cells --------------------------------------------------------------------------------------
+// Nearly every run of an LSTM or tree-LSTM network is one computation: gates from slices of a sum, products, their sum, tanh, a
+// product.  Worked tile by tile from descriptors a level of it costs 1 400 to 2 600 cycles of one wave whatever it
+// computes (a wave issues an instruction every four or five cycles, a taken branch costs thirty: addresses, flags and
+// branches of a tile are 150 to 250 instructions).  So the cells of a plan are looked for in the graph, and
+// a chain that consists of them is worked a thread per column, in registers, from one record a row, forward and backward (64
+// sentences: forward runs 6.8 -> 3.4 us a launch, backward runs 9.8 -> 4.6).
+// Position p: does a cell end in this product?  Everything that the record relies on is checked here, edge by edge: every node
+// of a cell but its output and c is read inside the cell only.  That the nodes lie in one chain is checked by cell_in_chain, and that they
+// are all of the chain by k_chain_recs, which counts.  What bounds it is the chain of reads from the output back to the
+// operands of S, so each step asks for all nodes at once, whether they turn out to be what they should or not (an id from
+// the wrong place is brought into range), and it runs beside the one workgroup that works out the slots.
+__device__ inline void find_cell(const Tables &T, u32 p)
+{
+    constexpr u32 NT = CELL_FORGET + 1, NG = NT + 2;      // terms of c; gates: one a term, o, the candidate
+    if (p >= T.n) return;
+    const u32 h = T.order[p];
+    if (T.op[h] != OP_CMULT) return;
+    auto in = [&](u32 u, u32 j) { const u32 v = T.in_idx[T.in_off[u] + j]; return v < T.n ? v : h; };
+    u32 tc = in(h, 0), o = in(h, 1);
+    const u32 op0 = T.op[tc], op1 = T.op[o];
+    if (op0 == OP_SIGMOID) { const u32 x = tc; tc = o; o = x; }
+    if (!((op0 == OP_TANH && op1 == OP_SIGMOID) || (op0 == OP_SIGMOID && op1 == OP_TANH))) return;
+    const u32 c = in(tc, 0), cop = T.op[c], c0 = T.in_off[c], nt = cop == OP_ADD ? T.in_off[c + 1] - c0 : 1u;
+    if ((cop != OP_ADD && cop != OP_CMULT) || nt > NT || (cop == OP_ADD && nt < 2u)) return;
+    const u32 b = T.batch_of_pos[p], H = T.out_dim[h];
+    const u32 h0 = T.succ_off[h], nh = T.succ_off[h + 1] - h0, r0 = T.succ_off[c], nc = T.succ_off[c + 1] - r0;
+    bool ok = H > 1u && T.outdeg[tc] == 1u && nh <= CELL_H_EDGES && nc >= 1u && nc <= 2u;
+    // the terms of c, the gate of each and what it is multiplied by
+    u32 t[NT], gate[NT], with[NT], ic_at = NT;
+#pragma unroll
+    for (u32 q = 0; q < NT; ++q) t[q] = cop == OP_ADD ? in(c, q < nt ? q : 0u) : c;
+#pragma unroll
+    for (u32 q = 0; q < NT; ++q) {
+        const u32 x = in(t[q], 0), y = in(t[q], 1);
+        const bool first = T.op[x] == OP_SIGMOID;
+        gate[q] = first ? x : y; with[q] = first ? y : x;
+        const bool fine = T.op[t[q]] == OP_CMULT && (t[q] == c || T.outdeg[t[q]] == 1u);
+        ok = ok && (q >= nt || fine);
+    }
+    u32 cand = h;
+#pragma unroll
+    for (u32 q = NT; q-- > 0;) if (q < nt && T.op[with[q]] == OP_TANH) { ic_at = q; cand = with[q]; }
+    ok = ok && ic_at < NT;
+    // gates: one a term, o, the candidate; each the activation of a slice of S, and read nowhere else
+    u32 node[NG], sl[NG], at[NG], S = 0;
+#pragma unroll
+    for (u32 k = 0; k < NG; ++k) node[k] = k < NT ? gate[k < nt ? k : 0u] : (k == NT ? o : cand);
+#pragma unroll
+    for (u32 k = 0; k < NG; ++k) sl[k] = in(node[k], 0);
+    u32 seen = 0;
+#pragma unroll
+    for (u32 k = 0; k < NG; ++k) {
+        const u32 whole = in(sl[k], 0);
+        if (k == 0) S = whole;
+        const bool fine = T.op[node[k]] == (k == NT + 1u ? OP_TANH : OP_SIGMOID) && T.outdeg[node[k]] == 1u &&
+                          T.out_dim[node[k]] == H && T.op[sl[k]] == OP_SLICE && T.outdeg[sl[k]] == 1u && whole == S;
+        at[k] = (u32)T.aux0[sl[k]];
+        if (k >= nt && k < NT) continue;       // (no such term)
+        ok = ok && fine && at[k] % H == 0u;
+        seen |= 1u << (at[k] / H & 31u);
+    }
+    const u32 gates = nt + 2u;
+    ok = ok && seen == (1u << gates) - 1u && T.out_dim[S] == gates * H;
+    // S: a sum of two rows that nobody else reads belongs to the cell, any other row does not
+    const u32 s0 = T.in_off[S], s1 = T.in_off[S + 1];
+    const bool sums = T.op[S] == OP_ADD && s1 - s0 == 2u && T.outdeg[S] == gates;
+    const u32 a = sums ? T.in_idx[s0] : h, a2 = sums ? T.in_idx[s0 + 1] : h;
+    if (!ok) return;
+    // what reads h and c (c is read by its tanh first)
+    CellRec R;
+    auto edge = [&](u32 q, CellEdge &to) {
+        const EdgeRec e = T.edges[q];
+        to = CellEdge{e.kind, e.goff, e.voff};
+        ok = ok && (e.kind == EK_PLAIN || (e.kind >= EK_MUL && e.kind <= EK_DSIGM));
+    };
+#pragma unroll
+    for (u32 k = 0; k < CELL_H_EDGES; ++k) {
+        R.he[k] = CellEdge{0u, 0u, 0u};
+        if (k < nh) edge(h0 + k, R.he[k]);
+    }
+    R.ce = CellEdge{0u, 0u, 0u};
+    if (nc == 2u) edge(r0 + 1u, R.ce);
+    if (!ok || T.edge_cons[T.succ_edge[r0]] != tc) return;
+    R.mark = CELL_MARK; R.H = H; R.nf = nt - 1u; R.ic_at = ic_at; R.pad = 0;
+    R.n_edges = nh | (nc - 1u) << 8;
+    R.h = T.val_off[h]; R.tc = T.val_off[tc]; R.o = T.val_off[o]; R.c = T.val_off[c];
+    R.S = T.val_off[S]; R.sums = sums ? 1u : 0u;
+    R.a = sums ? T.val_off[a] : 0u; R.b = sums ? T.val_off[a2] : 0u;
+    R.at_o = at[NT]; R.sl_o = T.nat_off[sl[NT]];
+    R.g = T.val_off[cand]; R.at_g = at[NT + 1]; R.sl_g = T.nat_off[sl[NT + 1]];
+    R.ic = R.i = R.at_i = R.sl_i = 0;
+#pragma unroll
+    for (u32 k = 0; k < CELL_FORGET; ++k) {
+        const bool past = k >= ic_at;       // the k-th term that is not i g
+        R.f[k] = R.fp[k] = R.prev[k] = R.at_f[k] = R.sl_f[k] = 0;
+        if ((past ? k + 1u : k) >= nt) continue;
+        R.f[k] = T.val_off[past ? node[k + 1] : node[k]]; R.fp[k] = T.val_off[past ? t[k + 1] : t[k]];
+        R.prev[k] = T.val_off[past ? with[k + 1] : with[k]];
+        R.at_f[k] = past ? at[k + 1] : at[k]; R.sl_f[k] = T.nat_off[past ? sl[k + 1] : sl[k]];
+    }
+#pragma unroll
+    for (u32 q = 0; q < NT; ++q)
+        if (q == ic_at) { R.ic = T.val_off[t[q]]; R.i = T.val_off[node[q]]; R.at_i = at[q]; R.sl_i = T.nat_off[sl[q]]; }
+    const u32 cell = atomicAdd(&T.hdr->n_cells, 1u);
+    if (cell >= T.cells_cap) return;
+    T.cells[cell] = R;
+    T.cell_of[p] = cell;
+    // the batches of its nodes (what there is less than CELL_NODES of is filled up with the output's own)
+    CellNodes N;
+    N.batch[0] = b | (3u + (nt - 1u ? nt : 0u) + 2u * gates + (sums ? 1u : 0u)) << 16;
+    auto batch = [&](u32 u) { return T.batch_of_pos[T.pos_of[u]]; };
+    N.batch[1] = batch(tc); N.batch[2] = batch(c); N.batch[3] = sums ? batch(S) : b;
+#pragma unroll
+    for (u32 q = 0; q < NT; ++q) N.batch[4 + q] = q < nt ? batch(t[q]) : b;
+#pragma unroll
+    for (u32 k = 0; k < NG; ++k) {
+        const bool is = k < nt || k >= NT;
+        N.batch[4 + NT + 2 * k] = is ? batch(node[k]) : b;
+        N.batch[5 + NT + 2 * k] = is ? batch(sl[k]) : b;
+    }
+    T.cell_nodes_of[cell] = N;
+}
+
+// A cell counts for its output's batch when all its nodes have been placed in one chain.
+__device__ inline void cell_in_chain(const Tables &T, u32 cell)
+{
+    if (cell >= T.hdr->n_cells || cell >= T.cells_cap) return;
+    const CellNodes N = T.cell_nodes_of[cell];
+    const u32 b = N.batch[0] & 0xffffu, slot = T.slot_of[b], label = T.label_of[b];
+    bool one = true;
+#pragma unroll
+    for (u32 k = 1; k < CELL_NODES; ++k) one = one && T.slot_of[N.batch[k]] == slot && T.label_of[N.batch[k]] == label;
+    if (!one) return;
+    atomicAdd(&T.cell_rows[b], 1u);
+    atomicAdd(&T.cell_nodes[b], N.batch[0] >> 16);
+}
+
 // One workgroup.  Over the batch dependencies, where a fusable edge costs 0 and any other edge one
 // launch boundary: head(b) = longest path from any source to b, tail(b) = longest path from b to any
 // sink.  Batch ids are a topological order (a batch's operands lie in earlier batches in every batching
@@ -1101,7 +1239,7 @@ __global__ __launch_bounds__(TPB) void k_bedges(Tables T, u32 *bset, u32 *blist)
 // head), fuse == 2 as late as possible (slot = L - tail): batches off the critical path then
 // gather in the slots next to their consumers instead of trailing the recurrence one small
 // launch at a time.  Batches joined by fusable edges inside one slot then get a common chain
-// label (the smallest batch id of the chain).
+// label (the smallest batch id of the chain).  (The workgroups behind the first look for gated cells meanwhile.)
 constexpr int SLOT_THREADS = 1024;
 __global__ __launch_bounds__(SLOT_THREADS) void k_slots(Tables T, int fuse, const u32 *blist)
 {
@@ -1119,6 +1257,7 @@ __global__ __launch_bounds__(SLOT_THREADS) void k_slots(Tables T, int fuse, cons
         if (tid == 0) { T.hdr->n_slots = T.hdr->n_steps; T.hdr->slot_sweeps = 0; T.hdr->p0 = 1; }
         return;
     }
+    if (blockIdx.x > 0) { find_cell(T, (blockIdx.x - 1u) * SLOT_THREADS + tid); return; }
     // ---- the dependencies in the order of their consumer: count per consumer (in s_label), exclusive scan,
     // scatter (the order among one consumer's entries does not matter: only maxima and minima are taken)
     for (u32 b = tid; b < SLOT_MAX_NB; b += SLOT_THREADS) { s_slot[b] = 0; s_label[b] = 0; }
@@ -1224,6 +1363,7 @@ __global__ void k_launch_keys(Tables T, u64 *keys, u32 *vals, u32 n_pad)
 {
     const u32 b = blockIdx.x * blockDim.x + threadIdx.x;
     const bool in = b < n_pad;
+    if (T.cells) cell_in_chain(T, b);
     if (in) vals[b] = b;
     // batches without forward work, counted for the statistics: summed over the wave first (every lane takes
     // part), one atomic per wave
@@ -1233,6 +1373,7 @@ __global__ void k_launch_keys(Tables T, u64 *keys, u32 *vals, u32 n_pad)
         const BatchRec &r = T.batches[b];
         if (r.vec4 & TF_VIEW) { cnt[0] = 1u; cnt[1] = r.B * r.d; }
         if (r.vec4 & TF_VIRT) { cnt[2] = 1u; cnt[3] = r.B * r.d; }
+        if (T.cells && !op_chain_source(r.op, r.arity)) T.slot_mixed[T.slot_of[b]] = 1u;
     }
     if (__ballot(cnt[0] | cnt[2]) != 0ull) {
         for (int q = 0; q < 4; ++q)
@@ -1334,7 +1475,7 @@ __global__ void k_chain_recs(Tables T, int agenda, const u32 *bset, const u32 *f
         const BatchRec r0 = T.batches[T.lorder[i]];
         ChainRec cr;
         cr.first = i; cr.k = k; cr.slot = T.slot_of[T.lorder[i]];
-        cr.fused = (op_chainable(r0.op, r0.arity) || r0.op == OP_INPUT || r0.op == OP_LOOKUP) ? 1u : 0u;
+        cr.fused = op_chain_source(r0.op, r0.arity) ? 1u : 0u;
         u32 dmax = r0.d, G = r0.B;
         for (u32 m = 1; m < k; ++m) {
             const BatchRec &rm = T.batches[T.lorder[i + m]];
@@ -1342,8 +1483,12 @@ __global__ void k_chain_recs(Tables T, int agenda, const u32 *bset, const u32 *f
             G = gcd_u32(G, rm.B);
         }
         u32 kt = 0, ktf = 0, per_group = 0;   // tiles per block (all members / members with forward work); floats one group of every member takes
+        u32 out = 0xffffffffu, cells = 0, cell_nodes = 0, cell_d = 0;   // the member that gated cells end in
+        const bool look = T.cells && T.hdr->n_cells > 0;
         for (u32 m = 0; m < k; ++m) {
-            const BatchRec &rm = T.batches[T.lorder[i + m]];
+            const u32 id = T.lorder[i + m];
+            const BatchRec &rm = T.batches[id];
+            if (look && T.cell_rows[id]) { out = id; cells = T.cell_rows[id]; cell_nodes = T.cell_nodes[id]; cell_d = rm.d; }
             kt += rm.B / G;
             if (!(rm.vec4 & TF_NOFWD)) ktf += rm.B / G;
             per_group += (rm.B / G) * rm.d;
@@ -1355,8 +1500,16 @@ __global__ void k_chain_recs(Tables T, int agenda, const u32 *bset, const u32 *f
             const u32 fit = (CHAIN_LDS_FLOATS - 3u * k) / per_group;
             if (fit >= 1) { cr.fused = 2u; if (fit < cr.Rg) cr.Rg = fit; }
         }
+        cr.pad0 = cr.pad1 = cr.pad2 = 0;
+        if (cr.fused == 2u && cells == G && cell_nodes == kt * G && !T.slot_mixed[cr.slot]) {
+            // gated cells and nothing else (a launch with products in it takes seven microseconds anyway and keeps the kernel that
+            // has no code for cells: with it, and its scalar registers spilt for it, each product launch took 0.3 us more)
+            cr.fused = 3u; cr.pad0 = out;
+            cr.Rg = CELL_WAVES / cell_row_waves(cell_d);
+            kt = ktf = cr.Rg;      // a tile a row; the last block's may be left over
+        }
         cr.nrb = cdiv(G, cr.Rg); cr.kt = cr.fused ? kt : 1u;
-        cr.ktf = cr.fused ? ktf : 1u; cr.pad0 = cr.pad1 = cr.pad2 = 0;
+        cr.ktf = cr.fused ? ktf : 1u;
         if (cr.fused) {
             L.ta = cr.nrb * kt; L.wa = cr.nrb;
             L.tf = cr.nrb * ktf; L.wf = ktf ? cr.nrb : 0u;     // a chain of views only has no forward work
@@ -1403,10 +1556,11 @@ __global__ void k_slot_tables(Tables T, const CLay *clay_ex, const CLay *total)
         for (u32 m = 0; m < cr.k; ++m) need += chain_region(cr, T.batches[T.lorder[cr.first + m]]);
         atomicMax(&S.lds_need, need);
     }
-    const u32 len = cr.fused ? cr.kt : 1u;
+    const u32 cells = cr.fused == 3u ? CELL_ITEM : 0u;
+    const u32 len = cr.fused ? cr.kt | cells : 1u;
     atomicMin(&S.lmin, len);
     atomicMin(&S.nlmax, ~len);
-    const u32 lenf = cr.fused ? cr.ktf : 1u;
+    const u32 lenf = cr.fused ? cr.ktf | cells : 1u;
     if (lenf) {   // (a chain of views has no forward work item)
         atomicMin(&S.lminf, lenf);
         atomicMin(&S.nlmaxf, ~lenf);
@@ -1767,8 +1921,24 @@ __global__ __launch_bounds__(TPB) void k_tiles(Tables T, const CLay *clay_ex, co
                 const bool fwd = which == 3;
                 const u32 len = cr.fused ? (fwd ? cr.ktf : cr.kt) : 1u;
                 w.first = (fwd ? clay_ex[c].tf : clay_ex[c].ta) + xx * len;
-                w.len = len;
+                w.len = len | (cr.fused == 3u ? CELL_ITEM : 0u);
                 (fwd ? T.works_f : T.works_a)[x] = w;
+            } else if (cr.fused == 3u) {
+                const uint4 *from = nullptr;
+                if (xx < cr.G) from = (const uint4 *)&T.cells[T.cell_of[T.batches[cr.pad0].pos0 + xx]];
+                if (which == 0) {
+                    uint4 *to = (uint4 *)&T.tiles_f[x];
+                    if (from) {
+#pragma unroll
+                        for (u32 q = 0; q < sizeof(TileDesc) / 16; ++q) to[q] = from[q];
+                    } else to[0] = make_uint4(0u, 0u, 0u, 0u);
+                } else {
+                    uint4 *to = (uint4 *)&T.tiles_a[x];
+                    if (from) {
+#pragma unroll
+                        for (u32 q = 0; q < sizeof(PullDesc) / 16; ++q) to[q] = from[q];
+                    } else to[0] = make_uint4(0u, 0u, 0u, 0u);
+                }
             } else if (which == 2 || (which == 0 && !cr.fused)) {
                 const BatchRec r = T.batches[T.lorder[cr.first]];
                 TileDesc d;
@@ -1998,11 +2168,18 @@ int sched_enqueue(ob_ctx *ctx)
     A(T.outdeg, u32, n + 1); A(T.qcount, u32, 64); A(g_dep, u32, n + 1);
     A(T.pu_start, u32, n_slots); A(T.pu_end, u32, n_slots);
     A(T.ht_keys, u64, ht_size); A(bset, u32, BSET_SIZE);
+    const bool cells = batched && ctx->fuse && E > 0;      // a fused plan may hold gated cells
+    T.cells = nullptr;
+    if (cells) { A(T.cell_rows, u32, n); A(T.cell_nodes, u32, n); A(T.slot_mixed, u32, n); }
     if (agenda) { A(AG.keys, u64, AG_TABLE); A(AG.sum, u64, AG_TABLE); A(AG.cnt, u32, AG_TABLE); }
     char *zero_hi = (char *)ctx->arena + ctx->top;
     A(T.ht_vals, u32, ht_size);
     if (agenda) A(AG.first, u32, AG_TABLE);
     char *ones_hi = (char *)ctx->arena + ctx->top;
+    if (cells) {        // (a cell holds more than eight nodes)
+        T.cells_cap = n / 8 + 1;
+        A(T.cells, CellRec, T.cells_cap); A(T.cell_nodes_of, CellNodes, T.cells_cap); A(T.cell_of, u32, n);
+    }
     A(T.sig, u64, n); A(T.step, u32, n); A(T.indeg, u32, n);
     A(T.succ_off, u32, n + 1); A(T.succ_edge, u32, E + 1); A(T.edge_cons, u32, E + 1);
     A(T.queue, u32, n);
@@ -2119,7 +2296,7 @@ int sched_enqueue(ob_ctx *ctx)
     // ---- launch planning: slots, chains, tile descriptors ----
     const int fuse = batched && ctx->fuse;
     if (fuse && E > 0) K(k_bedges, n, T, bset, blist);
-    hipLaunchKernelGGL(k_slots, dim3(1), dim3(SLOT_THREADS), 0, s, T, (fuse && E > 0) ? ctx->fuse : 0, blist);
+    hipLaunchKernelGGL(k_slots, dim3(cells ? 1 + blocks_for(n, SLOT_THREADS) : 1), dim3(SLOT_THREADS), 0, s, T, (fuse && E > 0) ? ctx->fuse : 0, blist);
     ++ctx->n_launch_sched;
     K(k_launch_keys, n, T, ctx->key_a, ctx->val_a, n);
     if (fuse && E > 0) {

@@ -305,6 +305,85 @@ def test_small_gated_cells_at_every_fusion_level(rows, H, q):
     c.close()
 
 
+def _cell_graph(H, nf, sums, rows, odd, seed=5):
+    """Steps of gated cells with nf forget gates over `rows` rows; sums: the gates are slices of a sum of two rows (of one row
+    otherwise).  odd: what keeps a row's cell from being one, or is unusual and must not."""
+    rng = np.random.default_rng(seed)
+    pb = wl.ParamBuilder(rng, std=0.4)
+    D = (3 + nf) * H
+    W, U, b = pb.add("W", D, H), pb.add("U", D, H), pb.add("b", D, 1)
+    p = pb.done()
+    g = wl.GraphBuilder(p)
+    hs = [g.input(rng.standard_normal(H)) for _ in range(rows)]
+    cs = [[g.input(rng.standard_normal(H)) for _ in range(max(nf, 1))] for _ in range(rows)]
+    losses = []
+    at = list(rng.permutation(3 + nf))          # the gates' places in the sum
+    for step in range(3):
+        for r in range(rows):
+            s = g.matvec(U, b, hs[r])
+            if sums:
+                s = g.add((g.matvec(W, -1, g.input(rng.standard_normal(H))), s))
+            sl = [g.slice(s, int(k) * H, (int(k) + 1) * H) for k in at]
+            i, cand, o = g.sigmoid(sl[0]), g.tanh(sl[1]), g.sigmoid(sl[2])
+            f = [g.sigmoid(x) for x in sl[3:]]
+            terms = [g.cmult(cs[r][k], f[k]) if odd == "swapped" else g.cmult(f[k], cs[r][k]) for k in range(nf)]
+            terms.insert(min(nf, 1), g.cmult(cand, i) if odd == "swapped" else g.cmult(i, cand))
+            c = g.add(terms) if nf else terms[0]
+            tc = g.tanh(c)
+            h = g.cmult(tc, o) if odd == "swapped" else g.cmult(o, tc)
+            if odd == "gate read" and r == rows - 1:
+                losses.append(g.sqnorm(i))
+            if odd == "state read" and r % 2 == 0:
+                losses.append(g.sqnorm(c))
+            if odd == "output read":
+                losses.append(g.sqnorm(g.add((h, h))))
+            cs[r] = [c] + [g.input(rng.standard_normal(H)) for _ in range(nf - 1)] if nf else cs[r]
+            hs[r] = h
+            if odd == "three readers":
+                losses.append(g.sqnorm(g.tanh(h)))
+                losses.append(g.sqnorm(g.sigmoid(h)))
+    root = g.add(losses + [g.sqnorm(h) for h in hs] + [g.sqnorm(g.tanh(c[0])) for c in cs])
+    return p, g.finish(root, rows)
+
+
+@pytest.mark.parametrize("H,nf,sums,rows,odd,cells", [
+    (2, 1, True, 3, "", True), (25, 1, True, 9, "", True), (64, 1, True, 5, "swapped", True), (65, 1, True, 6, "three readers", True),
+    (100, 2, True, 7, "", True), (128, 0, False, 4, "", True), (130, 0, True, 5, "swapped", True), (192, 2, False, 3, "", True),
+    (256, 1, True, 16, "output read", True), (300, 1, True, 3, "", True), (20, 2, True, 21, "swapped", True),
+    (32, 1, True, 6, "gate read", False), (32, 1, True, 6, "state read", False), (1, 1, True, 4, "", False)])
+def test_gated_cells(H, nf, sums, rows, odd, cells):
+    """LSTM and tree-LSTM cells are worked row by row from one record: bit for bit what one launch per level gives, in one
+    evaluation and in two, and within tolerance of the oracle; a chain with a cell that is read in other ways is not."""
+    from paper_1705_07860_amd import binding as ob
+    p, g = _cell_graph(H, nf, sums, rows, odd)
+    o = Oracle(g, p, "f64")
+    o.forward()
+    o.backward(g.root)
+    total = int(o.v_off[-1])
+    out = {}
+    for level in (0, 1, 2):
+        c, root = run_gpu(p, g, ob.OB_BYDEPTH, fuse=level, arena=128 << 20)
+        kinds = c.debug_read(ob.OB_DBG_CHAINS).reshape(-1, 12)[:, 3]
+        n_cells = int(np.sum(kinds == 3))
+        say(f"  level {level}: {n_cells} chains of cells of {kinds.size} chains")
+        if level != 1:      # (placed early, what reads an output joins its chain; the last step's may be joined in any case)
+            assert (n_cells >= 2 if cells else n_cells == 0) if level else n_cells == 0, kinds
+        c.backward(root)
+        out[level] = [c.all_read(0, total), c.all_read(1, total)] + [c.param_grad_read(k, m.shape) for k, m in enumerate(p.mats)]
+        if level == 2:
+            for cut in (None, g.n * 2 // 3):      # in one evaluation, and in two: gradients arrive from the second one
+                c.graph_new()
+                c.param_grad_zero()
+                c.add_bulk(g)
+                if cut:
+                    c.forward(cut)
+                c.forward(g.root)
+                check_against_oracle(c, p, g, o, g.root, what=f"cells {H} {nf} {odd} {'in two stages' if cut else ''}")
+        c.close()
+    for k in range(len(out[0])):
+        assert np.array_equal(out[0][k], out[1][k]) and np.array_equal(out[0][k], out[2][k]), k
+
+
 @pytest.mark.parametrize("seed", range(950, 964))
 def test_random_dags_of_400_nodes(seed):
     """Unstructured graphs of 400 nodes, consecutive seeds, nothing left out: some of these graphs

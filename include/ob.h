@@ -268,6 +268,8 @@ int ob_debug_read(ob_ctx *ctx, int which, uint32_t *host_out, size_t cap_words, 
                                  * once, so that scheduling falls back to the single-workgroup pass (see n_depth_retries) */
 #define OB_DBG_SET_CONCAT_COPY 1 /* nonzero: every CONCAT batch is copied by the forward pass from the next schedule on
                                   * (default 0: batches that only matrix products read stay uncopied, see ob_stats) */
+#define OB_DBG_SET_WIDE_PLAN 2   /* nonzero: small graphs are scheduled by the launches that schedule large ones, not by the one
+                                  * launch of their own (default 0); the schedules are the same */
 int ob_debug_set(ob_ctx *ctx, int which, uint64_t value);
 
 /* Stand-alone device primitives, exposed so that tests can check them directly.  All

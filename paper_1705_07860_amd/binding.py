@@ -24,6 +24,7 @@ OB_DBG_DEPTH, OB_DBG_SIG, OB_DBG_SUCC_OFF, OB_DBG_SUCC_EDGE, OB_DBG_ORDER, OB_DB
 OB_DBG_TILES_FWD, OB_DBG_TILES_PULL, OB_DBG_CHAINS, OB_DBG_LORDER = 6, 7, 8, 9
 OB_DBG_SET_DEPTH_SPIN = 0
 OB_DBG_SET_CONCAT_COPY = 1
+OB_DBG_SET_WIDE_PLAN = 2
 
 ERRORS = {0: "OB_OK", -1: "OB_E_BADID", -2: "OB_E_DIM", -3: "OB_E_RANGE", -4: "OB_E_NOTSCALAR",
           -5: "OB_E_OOM", -6: "OB_E_STATE", -7: "OB_E_HIP", -8: "OB_E_ARG"}

@@ -13,7 +13,7 @@ HERE = Path(__file__).resolve().parent
 CSRC = HERE / "csrc"
 LIB = HERE / "libob.so"
 SOURCES = ["ob_prims.hip", "ob_sched.hip", "ob_exec.hip", "ob_api.hip"]
-HEADERS = ["ob_internal.h", "ob_ctx.h", "../../include/ob.h"]
+HEADERS = ["ob_internal.h", "ob_ctx.h", "ob_block.h", "../../include/ob.h"]
 
 # Packed fp32 instructions are switched off for all device code (the compiler would otherwise
 # form them from ordinary float arithmetic).

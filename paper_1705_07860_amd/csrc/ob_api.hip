@@ -1163,6 +1163,7 @@ static int stage_forward(ob_ctx *ctx, u32 n0, u32 n1)
     c->sched_stream = ctx->sched_stream;
     c->is_stage = true;
     c->concat_views = ctx->concat_views;
+    c->wide_plan = ctx->wide_plan;
     u32 *lists_dev = arena_array<u32>(c, (size_t)3 * P + 1);
     if (!lists_dev) return fail(ctx_fail(ctx, OB_E_OOM, "arena too small for another evaluation stage"));
     st.lists_dev = lists_dev;
@@ -1538,6 +1539,9 @@ int ob_debug_set(ob_ctx *ctx, int which, uint64_t value)
         return OB_OK;
     case OB_DBG_SET_CONCAT_COPY:
         ctx->concat_views = value == 0;
+        return OB_OK;
+    case OB_DBG_SET_WIDE_PLAN:
+        ctx->wide_plan = value != 0;
         return OB_OK;
     default:
         return ctx_fail(ctx, OB_E_ARG, "unknown knob %d", which);

@@ -136,6 +136,7 @@ struct ob_ctx {
     u32 hdr_window = 0, n_items_sched = 0;
     u32 depth_spin_limit = 1u << 21;   // idle polls a range of the partitioned depth pass allows itself before it gives up
     bool depth_partitioned = false;    // the last schedule used the partitioned depth pass
+    bool wide_plan = false;            // plan small graphs with the launches of large ones (the two are to give the same plan)
     bool force_frontier = false;       // schedule with the single-workgroup depth pass (retry after a range gave up)
     int n_depth_retries = 0;           // schedules of this context that had to be repeated that way
     bool forward_done = false, backward_done = false;

@@ -4,6 +4,7 @@
 // memory layout of the batched execution (Section 3.3: operands of a batch must be
 // addressable as one matrix; results are laid out contiguously in batch order).
 #include "ob_ctx.h"
+#include "ob_block.h"
 
 #include <type_traits>
 
@@ -33,18 +34,18 @@ __global__ void k_clear(uint4 *p, size_t zeros, size_t n)
 // ---- stage 1: signatures, out-degrees, edges by producer -------------------------------------
 // The rows of a workgroup that have too many edges for a thread, as one list of edges that all its threads walk: an entry
 // finds its row by bisection in LDS.
-struct WideRows {
+template <u32 N> struct WideRows {
     u64 n;                              // rows << 32 | edges: one atomic gives a row its place in both
-    u32 row[TPB], lo[TPB], at[TPB];     // row, its first edge, its first entry of the list
+    u32 row[N], lo[N], at[N];     // row, its first edge, its first entry of the list
 };
 constexpr u32 WIDE_STEP = 4;            // entries a thread takes at a time: their reads run side by side
-__device__ inline void wide_add(WideRows &S, u32 row, u32 lo, u32 edges)
+template <u32 N> __device__ inline void wide_add(WideRows<N> &S, u32 row, u32 lo, u32 edges)
 {
     const u64 was = atomicAdd((unsigned long long *)&S.n, (1ull << 32) | edges);
     const u32 i = (u32)(was >> 32);
     S.row[i] = row; S.lo[i] = lo; S.at[i] = (u32)was;
 }
-__device__ inline u32 wide_row(const WideRows &S, u32 rows, u32 x)
+template <u32 N> __device__ inline u32 wide_row(const WideRows<N> &S, u32 rows, u32 x)
 {
     u32 lo = 0, hi = rows;              // at[lo] <= x < at[hi]
     while (hi - lo > 1) {
@@ -69,14 +70,20 @@ __device__ inline u32 wide_row(const WideRows &S, u32 rows, u32 x)
 constexpr u32 INIT_OPS = 8;
 __device__ inline u64 operand_hash(const Tables &T, u32 u, u32 j) { return mix64(comb(0x5bd1e995ULL + j, T.out_dim[u])); }
 
-__global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *keys, u32 *vals)
+template <u32 N> struct InitLds {
+    WideRows<N> wide;
+    u64 sum[N];
+};
+// (a workgroup of N threads, the nodes from `base` on)
+template <u32 N>
+__device__ inline void node_init_part(const Tables &T, int steps, u64 *keys, u32 *vals, InitLds<N> &L, u32 base)
 {
-    __shared__ WideRows S;
-    __shared__ u64 s_sum[TPB];
+    WideRows<N> &S = L.wide;
+    u64 *s_sum = L.sum;
     if (threadIdx.x == 0) S.n = 0;
     s_sum[threadIdx.x] = 0;
     __syncthreads();
-    const u32 v = blockIdx.x * blockDim.x + threadIdx.x;
+    const u32 v = base + threadIdx.x;
     if (v < T.n) {
         const u32 lo = T.in_off[v], hi = T.in_off[v + 1];
         const u32 o = T.op[v];
@@ -100,6 +107,7 @@ __global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *key
             wide_add(S, v, lo, hi - lo);
         }
         T.sig[v] = h;
+        if (T.cells) T.nrec[v] = make_uint4(hi > lo ? T.in_idx[lo] : 0u, hi > lo + 1u ? T.in_idx[lo + 1u] : 0u, o, hi - lo);
         if (steps == 3) {
             T.indeg[v] = hi - lo;
             if (hi == lo) {
@@ -117,18 +125,18 @@ __global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *key
     const u32 rows = (u32)(S.n >> 32), edges = (u32)S.n;
     u32 mine = ~0u;         // row whose sum this thread is adding up
     u64 sum = 0;
-    for (u32 x0 = threadIdx.x; x0 < edges; x0 += WIDE_STEP * TPB) {
+    for (u32 x0 = threadIdx.x; x0 < edges; x0 += WIDE_STEP * N) {
         u32 i[WIDE_STEP], j[WIDE_STEP], u[WIDE_STEP];
 #pragma unroll
         for (u32 q = 0; q < WIDE_STEP; ++q) {
-            const u32 x = x0 + q * TPB < edges ? x0 + q * TPB : x0;
+            const u32 x = x0 + q * N < edges ? x0 + q * N : x0;
             i[q] = wide_row(S, rows, x);
             j[q] = x - S.at[i[q]];
             u[q] = T.in_idx[S.lo[i[q]] + j[q]];
         }
 #pragma unroll
         for (u32 q = 0; q < WIDE_STEP; ++q) {
-            if (x0 + q * TPB >= edges) continue;
+            if (x0 + q * N >= edges) continue;
             const u32 e = S.lo[i[q]] + j[q];
             T.edge_cons[e] = S.row[i[q]];
             keys[e] = u[q];
@@ -145,16 +153,24 @@ __global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *key
     __syncthreads();
     if (threadIdx.x < rows) T.sig[S.row[threadIdx.x]] += s_sum[threadIdx.x];
 }
+__global__ __launch_bounds__(TPB) void k_node_init(Tables T, int steps, u64 *keys, u32 *vals)
+{
+    __shared__ InitLds<TPB> L;
+    node_init_part<TPB>(T, steps, keys, vals, L, blockIdx.x * TPB);
+}
 
 // after the sort: succ_edge[q] = edge id, succ_node[q] = its consumer (which
 // saves the single-workgroup depth pass and the agenda a hop)
-__global__ void k_succ_finish(Tables T, const u32 *sorted_edge, u32 *succ_node)
+__device__ inline void succ_finish_at(const Tables &T, const u32 *sorted_edge, u32 *succ_node, u32 q)
 {
-    const u32 q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= T.E) return;
     const u32 e = sorted_edge[q];
     T.succ_edge[q] = e;
     succ_node[q] = T.edge_cons[e];
+}
+__global__ void k_succ_finish(Tables T, const u32 *sorted_edge, u32 *succ_node)
+{
+    succ_finish_at(T, sorted_edge, succ_node, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---- stage 2: depth by frontier passes (the fallback) --------------------------------------------
@@ -232,6 +248,7 @@ constexpr u32 DEPTH_WIDE_READS = 8;   // operands per lane of one step of such a
 constexpr u32 DEPTH_MAX_ARITY = 60000;   // beyond, the single-workgroup pass counts the operands down instead of walking them
 
 __device__ inline u32 lds_load(const u32 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+__device__ inline void lds_store(u32 *p, u32 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
 __device__ inline void depth_settle(u32 *s_word, u32 *g_word, u32 d)
 {
     __hip_atomic_store(s_word, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -721,19 +738,21 @@ __global__ __launch_bounds__(REP_THREADS) void k_rep_insert(Tables T)
 
 // rep_src: 0 = the node itself (unbatched), 1 = the representative found by k_rep_insert,
 // 2 = none (manual batching: one batch per step, the stable sort keeps ids ascending)
-__global__ void k_sort_keys(Tables T, u64 *keys, u32 *vals, int rep_src)
+__device__ inline void sort_keys_at(const Tables &T, u64 *keys, u32 *vals, int rep_src, u32 v)
 {
-    const u32 v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= T.n) return;
     const u32 rep = rep_src == 1 ? T.ht_vals[T.ht_slot[v]] : (rep_src == 2 ? 0u : v);
     keys[v] = ((u64)T.step[v] << 32) | rep;
     vals[v] = v;
 }
+__global__ void k_sort_keys(Tables T, u64 *keys, u32 *vals, int rep_src)
+{
+    sort_keys_at(T, keys, vals, rep_src, blockIdx.x * blockDim.x + threadIdx.x);
+}
 
 // ---- stage 4: batches from the sorted order -----------------------------------------------------
-__global__ void k_heads(Tables T, const u64 *skey, const u32 *sval, u32 *head_flag, Tri *counts)
+__device__ inline void heads_at(const Tables &T, const u64 *skey, const u32 *sval, u32 *head_flag, Tri *counts, u32 p)
 {
-    const u32 p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= T.n) return;
     const u32 v = sval[p];
     T.order[p] = v;
@@ -748,10 +767,13 @@ __global__ void k_heads(Tables T, const u64 *skey, const u32 *sval, u32 *head_fl
     head_flag[p] = c.a;
     counts[p] = c;
 }
-
-__global__ void k_batch_off(Tables T, const u32 *head_flag, const Tri *before, u32 *item_base, int manual)
+__global__ void k_heads(Tables T, const u64 *skey, const u32 *sval, u32 *head_flag, Tri *counts)
 {
-    const u32 p = blockIdx.x * blockDim.x + threadIdx.x;
+    heads_at(T, skey, sval, head_flag, counts, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+__device__ inline void batch_off_at(const Tables &T, const u32 *head_flag, const Tri *before, u32 *item_base, int manual, u32 p)
+{
     if (p >= T.n) return;
     const Tri ex = before[p];          // batch heads, operand references and parameter uses before position p
     const u32 b = ex.a + head_flag[p] - 1;
@@ -765,6 +787,10 @@ __global__ void k_batch_off(Tables T, const u32 *head_flag, const Tri *before, u
         T.hdr->n_batches = b + 1;
     }
 }
+__global__ void k_batch_off(Tables T, const u32 *head_flag, const Tri *before, u32 *item_base, int manual)
+{
+    batch_off_at(T, head_flag, before, item_base, manual, blockIdx.x * blockDim.x + threadIdx.x);
+}
 
 // Takes bits off a batch's flags.  Flags only fall, so whatever a look returns is safe to act on, and all
 // members of a batch mostly take off the same bits: only the first pay for an atomic on the one word.
@@ -776,9 +802,8 @@ __device__ inline void flags_off(BatchRec &r, u32 bits)
 __host__ __device__ inline u32 cdiv(u64 a, u32 b) { return (u32)((a + b - 1) / b); }
 
 // one thread per batch: record + sizes for the layout scan (entries b >= n_batches are zero)
-__global__ void k_batch_layout(Tables T, Lay *lay_in, int virt)
+__device__ inline void batch_layout_at(const Tables &T, Lay *lay_in, int virt, u32 b)
 {
-    const u32 b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= T.n) return;
     Lay L; L.val = 0; L.dx = 0; L.ind = L.p0 = L.p1 = L.p2 = 0;
     if (b < T.hdr->n_batches) {
@@ -810,10 +835,13 @@ __global__ void k_batch_layout(Tables T, Lay *lay_in, int virt)
     }
     lay_in[b] = L;
 }
-
-__global__ void k_batch_finish(Tables T, const Lay *lay_ex, const Lay *total)
+__global__ void k_batch_layout(Tables T, Lay *lay_in, int virt)
 {
-    const u32 b = blockIdx.x * blockDim.x + threadIdx.x;
+    batch_layout_at(T, lay_in, virt, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+__device__ inline void batch_finish_at(const Tables &T, const Lay *lay_ex, const Lay *total, u32 b)
+{
     const u32 nb = T.hdr->n_batches;
     if (b >= nb) return;
     const Lay L = lay_ex[b];
@@ -829,10 +857,13 @@ __global__ void k_batch_finish(Tables T, const Lay *lay_ex, const Lay *total)
         if (tot.val + tot.dx >= 0xffffffffULL) atomicOr(&T.hdr->err, (u32)ERR_OVERFLOW);
     }
 }
-
-__global__ void k_node_offsets(Tables T)
+__global__ void k_batch_finish(Tables T, const Lay *lay_ex, const Lay *total)
 {
-    const u32 p = blockIdx.x * blockDim.x + threadIdx.x;
+    batch_finish_at(T, lay_ex, total, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+__device__ inline void node_offsets_at(const Tables &T, u32 p)
+{
     if (p >= T.n) return;
     BatchRec &r = T.batches[T.batch_of_pos[p]];
     const u32 row = p - r.pos0;
@@ -852,17 +883,24 @@ __global__ void k_node_offsets(Tables T)
         if (T.op[x] == OP_CONCAT) atomicMin((u32 *)&r.aux0, T.batch_of_pos[T.pos_of[x]]);
     }
 }
+__global__ void k_node_offsets(Tables T)
+{
+    node_offsets_at(T, blockIdx.x * blockDim.x + threadIdx.x);
+}
 
 // SLICE nodes are views: their value is the range [lo, hi) of the operand's row where it lies
 // (through any number of slices of slices), so nothing is copied forward and every reader of the
 // node is pointed there.  Their gradient rows stay in their own batch's block (nat_off).
-__global__ void k_view_offsets(Tables T)
+__device__ inline void view_offsets_at(const Tables &T, u32 v)
 {
-    const u32 v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= T.n || T.op[v] != OP_SLICE) return;
     u32 x = v, acc = 0;
     while (T.op[x] == OP_SLICE) { acc += (u32)T.aux0[x]; x = T.in_idx[T.in_off[x]]; }   // ids fall: ends at a node that owns its row
     T.val_off[v] = T.nat_off[x] + acc;
+}
+__global__ void k_view_offsets(Tables T)
+{
+    view_offsets_at(T, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // CONCAT batches that only matrix products read are not copied (Section 3.3: operands that already lie in
@@ -891,9 +929,8 @@ __device__ inline void xp_check(const Tables &T, u32 p, BatchRec &r)
 // Per node: the check that every member of a batch really has the signature tuple of the batch
 // head (a 64-bit hash collision would otherwise merge incompatible nodes), and whether the
 // float4 component-wise path is allowed.
-__global__ void k_member_check(Tables T)
+__device__ inline void member_check_at(const Tables &T, u32 p)
 {
-    const u32 p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= T.n) return;
     BatchRec &r = T.batches[T.batch_of_pos[p]];
     const u32 v = T.order[p];
@@ -911,14 +948,17 @@ __global__ void k_member_check(Tables T)
     if (r.op == OP_MATVEC && (T.outdeg[v] != 1 || r.d == 1)) flags_off(r, TF_G_ALIAS);
     xp_check(T, p, r);
 }
+__global__ void k_member_check(Tables T)
+{
+    member_check_at(T, blockIdx.x * blockDim.x + threadIdx.x);
+}
 
 __device__ inline bool batch_xp(const BatchRec &r) { return r.op == OP_MATVEC && (r.vec4 & TF_XP) && r.aux1 > 0; }
 
 // Per edge: operand row offsets per batch (slot-major), operand dimensions of the batch, the
 // operand part of the membership check, and the alignment flags.
-__global__ void k_opnd(Tables T)
+__device__ inline void opnd_at(const Tables &T, u32 e)
 {
-    const u32 e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= T.E) return;
     const u32 v = T.edge_cons[e];
     const u32 j = e - T.in_off[v];
@@ -957,6 +997,10 @@ __global__ void k_opnd(Tables T)
     if (row == 0) T.b_indim[r.indim + j] = du;
     if (off & 3u) flags_off(r, (TF_VEC4 | TF_ALIGNED));
     else if (r.op == OP_CONCAT && (du & 3u)) flags_off(r, TF_VEC4);
+}
+__global__ void k_opnd(Tables T)
+{
+    opnd_at(T, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---- launch planning ---------------------------------------------------------------------------------
@@ -1052,7 +1096,7 @@ __device__ inline void bedge_add(const Tables &T, u32 *s_set, u32 *bset, u32 *bl
 __global__ __launch_bounds__(TPB) void k_bedges(Tables T, u32 *bset, u32 *blist)
 {
     __shared__ u32 s_set[BEDGE_SLOTS];
-    __shared__ WideRows S;
+    __shared__ WideRows<TPB> S;
     if (T.hdr->n_batches > SLOT_MAX_NB) return;
     for (u32 i = threadIdx.x; i < BEDGE_SLOTS; i += TPB) s_set[i] = 0;
     if (threadIdx.x == 0) S.n = 0;
@@ -1099,53 +1143,71 @@ __global__ __launch_bounds__(TPB) void k_bedges(Tables T, u32 *bset, u32 *blist)
 // Position p: does a cell end in this product?  Everything that the record relies on is checked here, edge by edge: every node
 // of a cell but its output and c is read inside the cell only.  That the nodes lie in one chain is checked by cell_in_chain, and that they
 // are all of the chain by k_chain_recs, which counts.  What bounds it is the chain of reads from the output back to the
-// operands of S, so each step asks for all nodes at once, whether they turn out to be what they should or not (an id from
-// the wrong place is brought into range), and it runs beside the one workgroup that works out the slots.
+// operands of S, so each step asks for the records of all nodes at once (first two operands, operation, arity), whether they turn
+// out to be what they should or not, and it runs beside the one workgroup that works out the slots (64 trees: 56 us as a launch
+// of its own, read one by one, k_slots 18; both together 24 now).
 __device__ inline void find_cell(const Tables &T, u32 p)
 {
     constexpr u32 NT = CELL_FORGET + 1, NG = NT + 2;      // terms of c; gates: one a term, o, the candidate
     if (p >= T.n) return;
     const u32 h = T.order[p];
-    if (T.op[h] != OP_CMULT) return;
-    auto in = [&](u32 u, u32 j) { const u32 v = T.in_idx[T.in_off[u] + j]; return v < T.n ? v : h; };
-    u32 tc = in(h, 0), o = in(h, 1);
-    const u32 op0 = T.op[tc], op1 = T.op[o];
-    if (op0 == OP_SIGMOID) { const u32 x = tc; tc = o; o = x; }
-    if (!((op0 == OP_TANH && op1 == OP_SIGMOID) || (op0 == OP_SIGMOID && op1 == OP_TANH))) return;
-    const u32 c = in(tc, 0), cop = T.op[c], c0 = T.in_off[c], nt = cop == OP_ADD ? T.in_off[c + 1] - c0 : 1u;
-    if ((cop != OP_ADD && cop != OP_CMULT) || nt > NT || (cop == OP_ADD && nt < 2u)) return;
+    const uint4 rh = T.nrec[h];            // first two operands, operation, arity
+    if (rh.z != OP_CMULT) return;
+    u32 tc = rh.x, o = rh.y;
+    uint4 rtc = T.nrec[tc], ro = T.nrec[o];
+    if (rtc.z == OP_SIGMOID) { const u32 x = tc; tc = o; o = x; const uint4 y = rtc; rtc = ro; ro = y; }
+    if (rtc.z != OP_TANH || ro.z != OP_SIGMOID) return;
+    const u32 c = rtc.x;
+    const uint4 rc = T.nrec[c];
+    const u32 nt = rc.z == OP_ADD ? rc.w : 1u;
+    if ((rc.z != OP_ADD && rc.z != OP_CMULT) || nt > NT || (rc.z == OP_ADD && nt < 2u)) return;
     const u32 b = T.batch_of_pos[p], H = T.out_dim[h];
     const u32 h0 = T.succ_off[h], nh = T.succ_off[h + 1] - h0, r0 = T.succ_off[c], nc = T.succ_off[c + 1] - r0;
     bool ok = H > 1u && T.outdeg[tc] == 1u && nh <= CELL_H_EDGES && nc >= 1u && nc <= 2u;
-    // the terms of c, the gate of each and what it is multiplied by
+    // the terms of c, the gate of each and what it is multiplied by (absent terms: the first once more)
     u32 t[NT], gate[NT], with[NT], ic_at = NT;
+    uint4 rt[NT], rgate[NT], rwith[NT];
+    static_assert(NT == 3, "terms of c");
+    t[0] = rc.z == OP_ADD ? rc.x : c;
+    t[1] = nt > 1u ? rc.y : t[0];
+    t[2] = nt > 2u ? T.in_idx[T.in_off[c] + 2u] : t[0];
 #pragma unroll
-    for (u32 q = 0; q < NT; ++q) t[q] = cop == OP_ADD ? in(c, q < nt ? q : 0u) : c;
+    for (u32 q = 0; q < NT; ++q) rt[q] = T.nrec[t[q]];
 #pragma unroll
     for (u32 q = 0; q < NT; ++q) {
-        const u32 x = in(t[q], 0), y = in(t[q], 1);
-        const bool first = T.op[x] == OP_SIGMOID;
-        gate[q] = first ? x : y; with[q] = first ? y : x;
-        const bool fine = T.op[t[q]] == OP_CMULT && (t[q] == c || T.outdeg[t[q]] == 1u);
-        ok = ok && (q >= nt || fine);
+        gate[q] = rt[q].x; with[q] = rt[q].y;
+        rgate[q] = T.nrec[gate[q]]; rwith[q] = T.nrec[with[q]];
     }
     u32 cand = h;
+    uint4 rcand = rh;
 #pragma unroll
-    for (u32 q = NT; q-- > 0;) if (q < nt && T.op[with[q]] == OP_TANH) { ic_at = q; cand = with[q]; }
+    for (u32 q = NT; q-- > 0;) {
+        if (rgate[q].z != OP_SIGMOID) {
+            const u32 x = gate[q]; gate[q] = with[q]; with[q] = x;
+            const uint4 y = rgate[q]; rgate[q] = rwith[q]; rwith[q] = y;
+        }
+        const bool fine = rt[q].z == OP_CMULT && (t[q] == c || T.outdeg[t[q]] == 1u);
+        ok = ok && (q >= nt || fine);
+        if (q < nt && rwith[q].z == OP_TANH) { ic_at = q; cand = with[q]; rcand = rwith[q]; }
+    }
     ok = ok && ic_at < NT;
     // gates: one a term, o, the candidate; each the activation of a slice of S, and read nowhere else
     u32 node[NG], sl[NG], at[NG], S = 0;
+    uint4 rsl[NG];
 #pragma unroll
-    for (u32 k = 0; k < NG; ++k) node[k] = k < NT ? gate[k < nt ? k : 0u] : (k == NT ? o : cand);
+    for (u32 k = 0; k < NG; ++k) {
+        node[k] = k < NT ? gate[k < nt ? k : 0u] : (k == NT ? o : cand);
+        sl[k] = k < NT ? rgate[k < nt ? k : 0u].x : (k == NT ? ro.x : rcand.x);
+    }
 #pragma unroll
-    for (u32 k = 0; k < NG; ++k) sl[k] = in(node[k], 0);
+    for (u32 k = 0; k < NG; ++k) rsl[k] = T.nrec[sl[k]];
     u32 seen = 0;
 #pragma unroll
     for (u32 k = 0; k < NG; ++k) {
-        const u32 whole = in(sl[k], 0);
-        if (k == 0) S = whole;
-        const bool fine = T.op[node[k]] == (k == NT + 1u ? OP_TANH : OP_SIGMOID) && T.outdeg[node[k]] == 1u &&
-                          T.out_dim[node[k]] == H && T.op[sl[k]] == OP_SLICE && T.outdeg[sl[k]] == 1u && whole == S;
+        const u32 op = k < NT ? rgate[k < nt ? k : 0u].z : (k == NT ? ro.z : rcand.z);
+        if (k == 0) S = rsl[k].x;
+        const bool fine = op == (k == NT + 1u ? OP_TANH : OP_SIGMOID) && T.outdeg[node[k]] == 1u &&
+                          T.out_dim[node[k]] == H && rsl[k].z == OP_SLICE && T.outdeg[sl[k]] == 1u && rsl[k].x == S;
         at[k] = (u32)T.aux0[sl[k]];
         if (k >= nt && k < NT) continue;       // (no such term)
         ok = ok && fine && at[k] % H == 0u;
@@ -1154,9 +1216,9 @@ __device__ inline void find_cell(const Tables &T, u32 p)
     const u32 gates = nt + 2u;
     ok = ok && seen == (1u << gates) - 1u && T.out_dim[S] == gates * H;
     // S: a sum of two rows that nobody else reads belongs to the cell, any other row does not
-    const u32 s0 = T.in_off[S], s1 = T.in_off[S + 1];
-    const bool sums = T.op[S] == OP_ADD && s1 - s0 == 2u && T.outdeg[S] == gates;
-    const u32 a = sums ? T.in_idx[s0] : h, a2 = sums ? T.in_idx[s0 + 1] : h;
+    const uint4 rS = T.nrec[S];
+    const bool sums = rS.z == OP_ADD && rS.w == 2u && T.outdeg[S] == gates;
+    const u32 a = sums ? rS.x : h, a2 = sums ? rS.y : h;
     if (!ok) return;
     // what reads h and c (c is read by its tanh first)
     CellRec R;
@@ -1213,18 +1275,31 @@ __device__ inline void find_cell(const Tables &T, u32 p)
     T.cell_nodes_of[cell] = N;
 }
 
-// A cell counts for its output's batch when all its nodes have been placed in one chain.
+// A cell counts for its output's batch when all its nodes have been placed in one chain.  Called by whole waves: cells of a
+// batch mostly lie side by side, and a wave adds them up before it goes to the batch's counters (an atomic per cell kept
+// the counters of 64 trees' largest batches busy for 20 us).
 __device__ inline void cell_in_chain(const Tables &T, u32 cell)
 {
-    if (cell >= T.hdr->n_cells || cell >= T.cells_cap) return;
-    const CellNodes N = T.cell_nodes_of[cell];
-    const u32 b = N.batch[0] & 0xffffu, slot = T.slot_of[b], label = T.label_of[b];
-    bool one = true;
+    const u32 lane = threadIdx.x & 63u;
+    CellNodes N;
+    N.batch[0] = 0;
+    bool one = cell < T.hdr->n_cells && cell < T.cells_cap;
+    if (one) {
+        N = T.cell_nodes_of[cell];
+        const u32 b = N.batch[0] & 0xffffu, slot = T.slot_of[b], label = T.label_of[b];
 #pragma unroll
-    for (u32 k = 1; k < CELL_NODES; ++k) one = one && T.slot_of[N.batch[k]] == slot && T.label_of[N.batch[k]] == label;
-    if (!one) return;
-    atomicAdd(&T.cell_rows[b], 1u);
-    atomicAdd(&T.cell_nodes[b], N.batch[0] >> 16);
+        for (u32 k = 1; k < CELL_NODES; ++k) one = one && T.slot_of[N.batch[k]] == slot && T.label_of[N.batch[k]] == label;
+    }
+    for (u64 todo = __ballot(one); todo;) {
+        const u32 leader = (u32)__builtin_ctzll(todo), word = (u32)__shfl((int)N.batch[0], (int)leader);
+        const u64 same = __ballot(one && N.batch[0] == word);
+        if (lane == leader) {
+            const u32 rows = (u32)__popcll(same);
+            atomicAdd(&T.cell_rows[word & 0xffffu], rows);
+            atomicAdd(&T.cell_nodes[word & 0xffffu], rows * (word >> 16));
+        }
+        todo &= ~same;
+    }
 }
 
 // One workgroup.  Over the batch dependencies, where a fusable edge costs 0 and any other edge one
@@ -1241,14 +1316,21 @@ __device__ inline void cell_in_chain(const Tables &T, u32 cell)
 // launch at a time.  Batches joined by fusable edges inside one slot then get a common chain
 // label (the smallest batch id of the chain).  (The workgroups behind the first look for gated cells meanwhile.)
 constexpr int SLOT_THREADS = 1024;
-__global__ __launch_bounds__(SLOT_THREADS) void k_slots(Tables T, int fuse, const u32 *blist)
+constexpr u32 CELL_PART = 256;        // nodes a workgroup looks for cells among: it fills a CU's LDS, and 1024 of them with scattered reads each took a CU 49 us
+struct SlotsLds {
+    u32 slot[SLOT_MAX_NB];
+    u32 label[SLOT_MAX_NB];      // tail lengths first, chain labels afterwards
+    u32 edge[BLIST_MAX];
+    u32 changed;
+    u32 flag[3];
+    u32 wsum[SLOT_THREADS / 64];
+};
+// beside(i, k): work of the k threads that have none while two waves walk the dependencies, i = 0 .. k - 1
+template <typename Beside>
+__device__ inline void slots_of(const Tables &T, int fuse, const u32 *blist, SlotsLds &L, Beside beside)
 {
-    __shared__ u32 s_slot[SLOT_MAX_NB];
-    __shared__ u32 s_label[SLOT_MAX_NB];   // tail lengths first, chain labels afterwards
-    __shared__ u32 s_edge[BLIST_MAX];
-    __shared__ u32 s_changed;
-    __shared__ u32 s_flag[3];
-    __shared__ u32 s_wsum[SLOT_THREADS / 64];
+    u32 *s_slot = L.slot, *s_label = L.label, *s_edge = L.edge, *s_flag = L.flag, *s_wsum = L.wsum;
+    u32 &s_changed = L.changed;
     const u32 nb = T.hdr->n_batches;
     const u32 ne = T.hdr->n_bedges;
     const u32 tid = threadIdx.x;
@@ -1257,7 +1339,6 @@ __global__ __launch_bounds__(SLOT_THREADS) void k_slots(Tables T, int fuse, cons
         if (tid == 0) { T.hdr->n_slots = T.hdr->n_steps; T.hdr->slot_sweeps = 0; T.hdr->p0 = 1; }
         return;
     }
-    if (blockIdx.x > 0) { find_cell(T, (blockIdx.x - 1u) * SLOT_THREADS + tid); return; }
     // ---- the dependencies in the order of their consumer: count per consumer (in s_label), exclusive scan,
     // scatter (the order among one consumer's entries does not matter: only maxima and minima are taken)
     for (u32 b = tid; b < SLOT_MAX_NB; b += SLOT_THREADS) { s_slot[b] = 0; s_label[b] = 0; }
@@ -1310,6 +1391,7 @@ __global__ __launch_bounds__(SLOT_THREADS) void k_slots(Tables T, int fuse, cons
             }
         }
     }
+    else beside(tid - 128u, (u32)SLOT_THREADS - 128u);
     if (tid == 64) s_wsum[0] = walked;
     __syncthreads();
     walked += s_wsum[0];
@@ -1358,10 +1440,15 @@ __global__ __launch_bounds__(SLOT_THREADS) void k_slots(Tables T, int fuse, cons
     for (u32 b = tid; b < nb; b += SLOT_THREADS) { T.slot_of[b] = s_slot[b]; T.label_of[b] = s_label[b]; }
     if (tid == 0) T.hdr->slot_sweeps = walked + sweeps;
 }
-
-__global__ void k_launch_keys(Tables T, u64 *keys, u32 *vals, u32 n_pad)
+__global__ __launch_bounds__(SLOT_THREADS) void k_slots(Tables T, int fuse, const u32 *blist)
 {
-    const u32 b = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ SlotsLds L;
+    if (blockIdx.x == 0) slots_of(T, fuse, blist, L, [](u32, u32) {});
+    else if (threadIdx.x < CELL_PART && T.hdr->n_batches <= SLOT_MAX_NB) find_cell(T, (blockIdx.x - 1u) * CELL_PART + threadIdx.x);
+}
+
+__device__ inline void launch_keys_at(const Tables &T, u64 *keys, u32 *vals, u32 n_pad, u32 b)
+{
     const bool in = b < n_pad;
     if (T.cells) cell_in_chain(T, b);
     if (in) vals[b] = b;
@@ -1388,6 +1475,10 @@ __global__ void k_launch_keys(Tables T, u64 *keys, u32 *vals, u32 n_pad)
     // unfused plans are already in launch order (slot = step): equal keys keep that order
     keys[b] = T.hdr->p0 ? 0ull : (((u64)T.slot_of[b] << SLOT_BITS) | T.label_of[b]);
 }
+__global__ void k_launch_keys(Tables T, u64 *keys, u32 *vals, u32 n_pad)
+{
+    launch_keys_at(T, keys, vals, n_pad, blockIdx.x * blockDim.x + threadIdx.x);
+}
 
 __device__ inline u32 rows_per_block(u32 d) { return d >= (u32)EW_TILE ? 1u : (u32)EW_TILE / d; }
 
@@ -1396,9 +1487,8 @@ __device__ inline u64 chain_key(const Tables &T, u32 b) { return ((u64)T.slot_of
 
 // (and the start values of the tables that the next kernels fill in: every slot entry a plan can use,
 // n_slots + 1 <= n + 2, starts out as "no batch here", every chain's layout as empty)
-__global__ void k_chain_flags(Tables T, const u32 *sval, u32 *flag, CLay *clay_in, u32 n_pad)
+__device__ inline void chain_flags_at(const Tables &T, const u32 *sval, u32 *flag, CLay *clay_in, u32 n_pad, u32 i)
 {
-    const u32 i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i <= T.hdr->n_slots) {
         SlotRec r; r.wf = r.wa = r.tb = r.tf = r.ta = r.lmin = r.nlmax = r.dx_free = 0xffffffffu;
         r.lds_need = 0;
@@ -1412,6 +1502,10 @@ __global__ void k_chain_flags(Tables T, const u32 *sval, u32 *flag, CLay *clay_i
     const u32 nb = T.hdr->n_batches;
     if (i < nb) T.lorder[i] = sval[i];
     flag[i] = (i < nb && (i == 0 || chain_key(T, sval[i]) != chain_key(T, sval[i - 1]))) ? 1u : 0u;
+}
+__global__ void k_chain_flags(Tables T, const u32 *sval, u32 *flag, CLay *clay_in, u32 n_pad)
+{
+    chain_flags_at(T, sval, flag, clay_in, n_pad, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // whether batch c reads a result of batch y through a fusable dependency (the set k_bedges filled)
@@ -1430,10 +1524,8 @@ __device__ inline bool bset_has(const u32 *bset, u32 c, u32 y)
 
 constexpr u32 LEVEL_MAX_MEMBERS = 32;   // chains with more members keep their step order and one tile group per member
 
-__global__ void k_chain_recs(Tables T, int agenda, const u32 *bset, const u32 *flag, const u32 *flag_excl, CLay *clay_in,
-                             u32 n_pad)
+__device__ inline void chain_recs_at(const Tables &T, int agenda, const u32 *bset, const u32 *flag, const u32 *flag_excl, CLay *clay_in, u32 n_pad, u32 i)
 {
-    const u32 i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_pad) return;
     const u32 nb = T.hdr->n_batches;
     CLay L; L.tf = L.wf = L.ta = L.wa = L.tb = L.p0 = L.p1 = L.p2 = 0;
@@ -1446,13 +1538,20 @@ __global__ void k_chain_recs(Tables T, int agenda, const u32 *bset, const u32 *f
     if (i < nb && flag[i]) {
         const u32 c = flag_excl[i];
         u32 k = 1;
-        while (i + k < nb && !flag[i + k]) ++k;
+        while (true) {          // (eight flags at a time; beyond the last batch they are 0)
+            u32 f = 8;
+#pragma unroll
+            for (u32 q = 8; q-- > 0;) if (i + k + q >= nb || flag[i + k + q]) f = q;
+            k += f;
+            if (f < 8) break;
+        }
         // Members of a chain run level by level, the tiles of one level without a barrier between
         // them.  In depth mode a member's level is its depth.  Agenda batches are steps of their
         // own, so there the levels come from the dependencies inside the chain (level = 1 + the
         // largest level of the members it reads), and the members are put in (level, batch) order.
-        if (!agenda || T.hdr->p0) {
-            for (u32 m = 0; m < k; ++m) T.blevel[T.lorder[i + m]] = T.batches[T.lorder[i + m]].step;
+        const bool by_step = !agenda || T.hdr->p0;
+        if (by_step) {
+            // (set below)
         } else if (k > LEVEL_MAX_MEMBERS) {
             for (u32 m = 0; m < k; ++m) T.blevel[T.lorder[i + m]] = m;
         } else {
@@ -1476,23 +1575,38 @@ __global__ void k_chain_recs(Tables T, int agenda, const u32 *bset, const u32 *f
         ChainRec cr;
         cr.first = i; cr.k = k; cr.slot = T.slot_of[T.lorder[i]];
         cr.fused = op_chain_source(r0.op, r0.arity) ? 1u : 0u;
-        u32 dmax = r0.d, G = r0.B;
-        for (u32 m = 1; m < k; ++m) {
-            const BatchRec &rm = T.batches[T.lorder[i + m]];
-            dmax = rm.d > dmax ? rm.d : dmax;
-            G = gcd_u32(G, rm.B);
-        }
-        u32 kt = 0, ktf = 0, per_group = 0;   // tiles per block (all members / members with forward work); floats one group of every member takes
+        // one walk over the members, eight side by side (their reads depend on each other in pairs only): a thread that
+        // walked them one read after the other, three times, took 11 us for the longest chain of a graph of a thousand nodes
+        u32 dmax = 0, G = 0, rows = 0, rows_f = 0;
+        u32 floats = 0;         // (a plan of 2^32 and more is refused)
         u32 out = 0xffffffffu, cells = 0, cell_nodes = 0, cell_d = 0;   // the member that gated cells end in
         const bool look = T.cells && T.hdr->n_cells > 0;
-        for (u32 m = 0; m < k; ++m) {
-            const u32 id = T.lorder[i + m];
-            const BatchRec &rm = T.batches[id];
-            if (look && T.cell_rows[id]) { out = id; cells = T.cell_rows[id]; cell_nodes = T.cell_nodes[id]; cell_d = rm.d; }
-            kt += rm.B / G;
-            if (!(rm.vec4 & TF_NOFWD)) ktf += rm.B / G;
-            per_group += (rm.B / G) * rm.d;
+        for (u32 m0 = 0; m0 < k; m0 += 8) {
+            u32 id[8], B[8], d[8], step[8], flags[8], found[8];
+#pragma unroll
+            for (u32 q = 0; q < 8; ++q) id[q] = T.lorder[i + (m0 + q < k ? m0 + q : m0)];
+#pragma unroll
+            for (u32 q = 0; q < 8; ++q) {
+                const BatchRec &rm = T.batches[id[q]];
+                B[q] = rm.B; d[q] = rm.d; step[q] = rm.step; flags[q] = rm.vec4;
+                found[q] = look ? T.cell_rows[id[q]] : 0u;
+            }
+#pragma unroll
+            for (u32 q = 0; q < 8; ++q) {
+                if (m0 + q >= k) break;
+                if (by_step) T.blevel[id[q]] = step[q];
+                dmax = d[q] > dmax ? d[q] : dmax;
+                if (B[q] != G) G = gcd_u32(G, B[q]);
+                rows += B[q];
+                if (!(flags[q] & TF_NOFWD)) rows_f += B[q];
+                floats += B[q] * d[q];
+                if (found[q]) { out = id[q]; cells = found[q]; cell_d = d[q]; }
+            }
         }
+        if (out != 0xffffffffu) cell_nodes = T.cell_nodes[out];
+        // tiles per block (all members / members with forward work); floats one group of every member takes
+        u32 kt = rows / G, ktf = rows_f / G;
+        const u32 per_group = floats / G;
         cr.G = G; cr.Rg = rows_per_block(dmax);
         if (cr.fused && k > 1) {
             // hand results from member to member through LDS when a block of groups fits (each
@@ -1532,14 +1646,17 @@ __global__ void k_chain_recs(Tables T, int agenda, const u32 *bset, const u32 *f
         clay_in[c] = L;
     }
 }
+__global__ void k_chain_recs(Tables T, int agenda, const u32 *bset, const u32 *flag, const u32 *flag_excl, CLay *clay_in, u32 n_pad)
+{
+    chain_recs_at(T, agenda, bset, flag, flag_excl, clay_in, n_pad, blockIdx.x * blockDim.x + threadIdx.x);
+}
 
 // floats of a fused chain's LDS copy taken by one member: its rows of a block of groups, rounded up to 4
 __device__ inline u32 chain_region(const ChainRec &cr, const BatchRec &r) { return (cr.Rg * (r.B / cr.G) * r.d + 3u) & ~3u; }
 
 // per chain: first work item / tile of every launch slot and its run lengths, totals in the header
-__global__ void k_slot_tables(Tables T, const CLay *clay_ex, const CLay *total)
+__device__ inline void slot_tables_at(const Tables &T, const CLay *clay_ex, const CLay *total, u32 c)
 {
-    const u32 c = blockIdx.x * blockDim.x + threadIdx.x;
     const u32 nc = T.hdr->n_chains;
     if (c >= nc) return;
     const ChainRec cr = T.chains[c];
@@ -1573,13 +1690,16 @@ __global__ void k_slot_tables(Tables T, const CLay *clay_ex, const CLay *total)
         T.hdr->works_fwd = t.wf; T.hdr->works_pull = t.wa;
     }
 }
+__global__ void k_slot_tables(Tables T, const CLay *clay_ex, const CLay *total)
+{
+    slot_tables_at(T, clay_ex, total, blockIdx.x * blockDim.x + threadIdx.x);
+}
 
 // launch slots that hold no batch (neither placement produces one today; the launch tables
 // simply do not rely on it) inherit the offsets of the next slot that does, so that their launch
 // range is empty
-__global__ void k_slot_fill(Tables T)
+__device__ inline void slot_fill_at(const Tables &T, u32 s)
 {
-    const u32 s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= T.hdr->n_slots) return;
     u32 t = s;
     while (T.slots[t].wf == 0xffffffffu) ++t;   // entry n_slots is always set
@@ -1588,6 +1708,10 @@ __global__ void k_slot_fill(Tables T)
         SlotRec &S = T.slots[s];
         S.wf = N.wf; S.wa = N.wa; S.tb = N.tb; S.tf = N.tf; S.ta = N.ta;
     }
+}
+__global__ void k_slot_fill(Tables T)
+{
+    slot_fill_at(T, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---- tile descriptors ------------------------------------------------------------------------------
@@ -2009,9 +2133,8 @@ __global__ __launch_bounds__(TPB) void k_tiles(Tables T, const CLay *clay_ex, co
 
 // consumer-edge records in (producer, consumer, slot) order: what the producer adds to its
 // gradient for this use, as one of a few plain formulas over the value / gradient arenas
-__global__ void k_edges(Tables T)
+__device__ inline void edges_at(const Tables &T, u32 q)
 {
-    const u32 q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= T.E) return;
     const u32 e = T.succ_edge[q];
     const u32 v = T.edge_cons[e];
@@ -2044,13 +2167,16 @@ __global__ void k_edges(Tables T)
         if (r.kind != EK_PLAIN || (r.goff & 3u)) flags_off(T.batches[T.batch_of_pos[pu]], TF_G_ALIAS);
     }
 }
+__global__ void k_edges(Tables T)
+{
+    edges_at(T, blockIdx.x * blockDim.x + threadIdx.x);
+}
 
 // ---- parameter-use items: every MATVEC is a use of W (kind 0) and of its bias (kind 1), every
 // LOOKUP a use of (table, row) (kind 2).  Sorted by (parameter, kind, row), stably from
 // schedule order, they give each deferred parameter-gradient reduction a fixed summation order.
-__global__ void k_item_emit(Tables T, const u32 *item_base, u64 *keys, u32 *vals)
+__device__ inline void item_emit_at(const Tables &T, const u32 *item_base, u64 *keys, u32 *vals, u32 p)
 {
-    const u32 p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= T.n) return;
     const u32 v = T.order[p];
     const u32 o = T.op[v];
@@ -2062,10 +2188,13 @@ __global__ void k_item_emit(Tables T, const u32 *item_base, u64 *keys, u32 *vals
         keys[i] = (((u64)((u32)T.param[v] * 4u + 2u)) << 32) | (u32)T.aux0[v]; vals[i] = p;
     }
 }
-
-__global__ void k_item_finish(Tables T, const u64 *keys, const u32 *vals, u32 n_items)
+__global__ void k_item_emit(Tables T, const u32 *item_base, u64 *keys, u32 *vals)
 {
-    const u32 i = blockIdx.x * blockDim.x + threadIdx.x;
+    item_emit_at(T, item_base, keys, vals, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+__device__ inline void item_finish_at(const Tables &T, const u64 *keys, const u32 *vals, u32 n_items, u32 i)
+{
     if (i >= n_items) return;
     const u64 k = keys[i];
     const u32 slot = (u32)(k >> 32);
@@ -2096,6 +2225,298 @@ __global__ void k_item_finish(Tables T, const u64 *keys, const u32 *vals, u32 n_
     T.it_xoff[i] = xoff;
     if (i == 0 || (u32)(keys[i - 1] >> 32) != slot) T.pu_start[slot] = i;
     if (i == n_items - 1 || (u32)(keys[i + 1] >> 32) != slot) T.pu_end[slot] = i + 1;
+}
+__global__ void k_item_finish(Tables T, const u64 *keys, const u32 *vals, u32 n_items)
+{
+    item_finish_at(T, keys, vals, n_items, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// ---- the plan of a small graph, in one launch ---------------------------------------------------------
+// Some forty launches of a few microseconds each plan a graph of a few hundred nodes: what bounds them is the launch (2.4 us
+// when empty) and the first reads of whatever the launch before wrote (2 us each, out of another part of the
+// chip's caches).  So up to SMALL_NODES nodes one workgroup runs the same stages one behind the other, with a
+// barrier where a launch ended, its data in its own cache.  What bounds it now is the chain of dependent reads and barriers
+// of its stages, 0.2 to 6 us each: 71 us for 252 nodes of a recurrent network, 122 for a tree of 944 nodes and 118 for
+// 1 344 of a growing graph (schedules of the first
+// two with everything around them 164 -> 109 and 222 -> 183).
+// Only what takes the whole chip stays a launch of its own: the tile descriptors after it.
+constexpr u32 SMALL_THREADS = 1024;
+constexpr u32 SMALL_NODES = 2 * SMALL_THREADS;
+constexpr u32 SMALL_EDGES = 4096;               // edges and parameter uses: what the sort keeps in LDS
+struct SmallArgs {
+    Tables T;
+    uint4 *clear;           // tables that start at zero
+    u64 *keys; u32 *vals;
+    u32 *succ_node, *head_flag, *s_items, *blist, *cflag, *cflag_excl;
+    Tri *tri_in, *tri_ex;
+    Lay *lay_in, *lay_total;
+    CLay *clay_in, *clay_total;
+    u32 clear_words, spin_limit, n_items, row_bits, use_bits;
+    int fuse, virt;
+};
+// The depth of every node by one workgroup: a thread has the nodes tid, tid + SMALL_THREADS, ..., looks at two operands of each at
+// a time and settles a node when its list is through.  The operand lists and the depths are in LDS, 0 = not known yet.
+// A sweep of a wave is one dependent LDS read and a dozen instructions for each of its nodes, where the pass by ranges, made for four
+// nodes a lane and few waves, takes some hundred: 27 -> 6 us for 252 nodes, 35 -> 20 for 944.
+// Ids are a topological order, so the lowest node that is not settled can be, and every wave comes to look at it: the
+// bound on idle looks only guards against damaged tables.
+struct SmallDepth {
+    u32 dep[SMALL_NODES + 1];                // [SMALL_NODES] holds 1: an absent operand
+    unsigned short op[SMALL_EDGES + 2];
+    u32 quit;
+};
+template <u32 NPT>
+__device__ inline void small_depths(const Tables &T, u32 spin_limit, SmallDepth &S)
+{
+    const u32 tid = threadIdx.x, n = T.n;
+    u32 at[NPT], end[NPT], top[NPT], x[NPT], y[NPT];
+    bool open[NPT];
+#pragma unroll
+    for (u32 j = 0; j < NPT; ++j) {
+        const u32 v = tid + j * SMALL_THREADS;
+        open[j] = v < n;
+        at[j] = open[j] ? T.in_off[v] : 0u;
+        end[j] = open[j] ? T.in_off[v + 1] : 0u;
+        top[j] = 0;
+        S.dep[v] = 0;
+    }
+    for (u32 e = tid; e < T.E; e += SMALL_THREADS) S.op[e] = (unsigned short)T.in_idx[e];
+    if (tid == 0) { S.dep[SMALL_NODES] = 1; S.quit = 0; }
+    __syncthreads();
+    auto pair = [&](u32 j) __attribute__((always_inline)) {
+        x[j] = at[j] < end[j] ? S.op[at[j]] : SMALL_NODES;
+        y[j] = at[j] + 1u < end[j] ? S.op[at[j] + 1u] : SMALL_NODES;
+    };
+#pragma unroll
+    for (u32 j = 0; j < NPT; ++j) {
+        if (at[j] == end[j]) { if (open[j]) lds_store(&S.dep[tid + j * SMALL_THREADS], 1u); open[j] = false; top[j] = 0; }
+        pair(j);
+    }
+    u32 idle = 0;
+    bool gave_up = false;
+    while (true) {
+        u32 dx[NPT], dy[NPT];
+        bool moved = false, left = false;
+#pragma unroll
+        for (u32 j = 0; j < NPT; ++j) { dx[j] = lds_load(&S.dep[x[j]]); dy[j] = lds_load(&S.dep[y[j]]); }
+#pragma unroll
+        for (u32 j = 0; j < NPT; ++j) {
+            if (open[j] && dx[j] != 0u && dy[j] != 0u) {
+                const u32 d = dx[j] > dy[j] ? dx[j] : dy[j];
+                top[j] = d > top[j] ? d : top[j];
+                at[j] += 2u;
+                moved = true;
+                if (at[j] >= end[j]) { open[j] = false; lds_store(&S.dep[tid + j * SMALL_THREADS], top[j] + 1u); }
+                else pair(j);
+            }
+            left = left || open[j];
+        }
+        if (__ballot(left) == 0ull) break;
+        if (__ballot(moved) != 0ull) { idle = 0; continue; }
+        if (++idle > spin_limit || lds_load(&S.quit) != 0u) { gave_up = true; break; }
+        if (idle > 8u) __builtin_amdgcn_s_sleep(1);      // (what this wave waits for is some levels off: the others need the LDS)
+    }
+    u32 done = 0;
+#pragma unroll
+    for (u32 j = 0; j < NPT; ++j) {
+        const u32 v = tid + j * SMALL_THREADS;
+        // (a node that was given up on takes its own id as its step, above the step of every operand)
+        if (v < n) T.step[v] = open[j] ? v : top[j];
+        done += (u32)__popcll(__ballot(v < n && !open[j]));
+    }
+    if ((tid & 63u) == 0u) {
+        atomicAdd(&T.hdr->frontier_done, done);
+        if (gave_up) { lds_store(&S.quit, 1u); atomicOr(&T.hdr->err, (u32)ERR_CYCLE); }
+    }
+}
+
+// Sort keys: the step and the smallest node id with the same step and signature, by way of a table in LDS.
+// Returns the largest step.
+struct SmallReps {
+    u64 key[2 * SMALL_NODES];
+    u32 min[2 * SMALL_NODES], top;
+};
+__device__ inline u32 small_reps(const Tables &T, u64 *keys, u32 *vals, SmallReps &S)
+{
+    constexpr u32 NPT = SMALL_NODES / SMALL_THREADS, SLOTS = 2 * SMALL_NODES;
+    const u32 tid = threadIdx.x;
+    for (u32 i = tid; i < SLOTS; i += SMALL_THREADS) { S.key[i] = 0; S.min[i] = ~0u; }
+    if (tid == 0) S.top = 0;
+    u32 at[NPT], step[NPT];
+    u64 k[NPT];
+#pragma unroll
+    for (u32 j = 0; j < NPT; ++j) {
+        const u32 v = tid + j * SMALL_THREADS;
+        step[j] = v < T.n ? T.step[v] : 0u;
+        k[j] = v < T.n ? batch_key(T.sig[v], step[j]) : 0;
+    }
+    __syncthreads();
+    u32 top = 0;
+#pragma unroll
+    for (u32 j = 0; j < NPT; ++j) {
+        const u32 v = tid + j * SMALL_THREADS;
+        if (v >= T.n) continue;
+        top = step[j] > top ? step[j] : top;
+        for (at[j] = (u32)(k[j] >> 32) & (SLOTS - 1);; at[j] = (at[j] + 1) & (SLOTS - 1)) {   // (twice as many slots as nodes)
+            const u64 cur = atomicCAS((unsigned long long *)&S.key[at[j]], 0ULL, (unsigned long long)k[j]);
+            if (cur == 0 || cur == k[j]) break;
+        }
+        atomicMin(&S.min[at[j]], v);
+    }
+    atomicMax(&S.top, top);
+    __syncthreads();
+#pragma unroll
+    for (u32 j = 0; j < NPT; ++j) {
+        const u32 v = tid + j * SMALL_THREADS;
+        if (v >= T.n) continue;
+        keys[v] = ((u64)step[j] << 32) | S.min[at[j]];
+        vals[v] = v;
+    }
+    top = __builtin_amdgcn_readfirstlane(S.top);
+    __syncthreads();
+    return top;
+}
+
+// The distinct batch dependencies, through a set in LDS that holds all of them; a thread takes an edge.
+struct SmallBedges {
+    u32 set[2 * SMALL_EDGES];
+    u32 count;
+};
+__device__ inline void small_bedges(const Tables &T, u32 *blist, SmallBedges &S)
+{
+    const u32 tid = threadIdx.x;
+    for (u32 i = tid; i < 2 * SMALL_EDGES; i += SMALL_THREADS) S.set[i] = 0;
+    if (tid == 0) S.count = 0;
+    __syncthreads();
+    for (u32 e = tid; e < T.E; e += SMALL_THREADS) {
+        const u32 p = T.pos_of[T.edge_cons[e]], b = T.batch_of_pos[p];
+        const u32 key = bedge_key(T, p, b, T.batches[b], T.in_idx[e]);
+        for (u32 h = (key * 2654435761u) >> 19;; h = (h + 1) & (2 * SMALL_EDGES - 1)) {     // (twice as many slots as edges)
+            static_assert(2 * SMALL_EDGES == 1u << (32 - 19), "the hash gives as many bits as the set has slots");
+            u32 old = lds_load(&S.set[h]);
+            if (old == 0u) old = atomicCAS(&S.set[h], 0u, key);
+            if (old == key) break;
+            if (old == 0u) { blist[atomicAdd(&S.count, 1u)] = key; break; }
+        }
+    }
+    __syncthreads();
+    if (tid == 0) T.hdr->n_bedges = S.count;
+}
+
+union SmallLds {
+    InitLds<SMALL_THREADS> init;
+    RsSmall<SMALL_EDGES> sort;
+    SmallDepth depth;
+    SmallReps reps;
+    SmallBedges small_bedges;
+    SlotsLds slots;
+    u32 scan_u32[SMALL_THREADS / 64];
+    Tri scan_tri[SMALL_THREADS / 64];
+    Lay scan_lay[SMALL_THREADS / 64];
+    CLay scan_clay[SMALL_THREADS / 64];
+};
+static_assert(SMALL_THREADS == RS_THREADS && SMALL_THREADS == (u32)SLOT_THREADS, "one workgroup runs all stages");
+static_assert(SMALL_EDGES <= BLIST_MAX && SMALL_NODES <= SLOT_MAX_NB, "a small graph has a fused plan");
+
+__device__ inline void sort_here(SmallLds &L, u64 *keys, u32 *vals, u32 n, const RsFields &F)
+{
+    if (n <= 2048) rs_small<2>(L.sort, keys, vals, n, F);
+    else rs_small<4>(L.sort, keys, vals, n, F);
+    __syncthreads();
+}
+__device__ inline int bits_of(u32 x) { return x ? 32 - __builtin_clz(x) : 0; }
+
+__global__ __launch_bounds__(SMALL_THREADS) void k_plan_small(SmallArgs)
+{
+    __shared__ SmallLds L;
+    // The arguments are read anew in every stage: kept in scalar registers from the first stage that names one to the last,
+    // most of them would be spilt.
+    using Args = const SmallArgs __attribute__((address_space(4)));
+    auto args = []() __attribute__((always_inline)) -> const SmallArgs & {
+        Args *p = (Args *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return *(const SmallArgs *)p;
+    };
+    const u32 tid = threadIdx.x;
+#define STAGE if (const SmallArgs &A = args(); true)
+#define EACH(count, call)                                                        \
+    STAGE {                                                                      \
+        const Tables &T = A.T;                                                   \
+        for (u32 i = tid; i < (u32)(count); i += SMALL_THREADS) call;            \
+    }                                                                            \
+    __syncthreads()
+#define SCAN(kind, in, out, count, total)                                                            \
+    STAGE scan_one<SMALL_THREADS, SMALL_NODES / SMALL_THREADS + 1>(in, out, (size_t)(count), total, L.kind); \
+    __syncthreads()
+
+    STAGE {
+        for (u32 i = tid; i < A.clear_words; i += SMALL_THREADS) A.clear[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    __syncthreads();
+    // signatures, edges by producer
+    STAGE {
+        for (u32 base = 0; base < A.T.n; base += SMALL_THREADS) {
+            node_init_part<SMALL_THREADS>(A.T, 1, A.keys, A.vals, L.init, base);
+            __syncthreads();
+        }
+    }
+    SCAN(scan_u32, A.T.outdeg, A.T.succ_off, A.T.n + 1, (u32 *)nullptr);
+    STAGE sort_here(L, A.keys, A.vals, A.T.E, RsFields{{0, 0}, {bits_of(A.T.n - 1), 0}});
+    EACH(T.E, succ_finish_at(T, A.vals, A.succ_node, i));
+    // depth, batches
+    STAGE {
+        if (A.T.n <= SMALL_THREADS) small_depths<1>(A.T, A.spin_limit, L.depth);
+        else small_depths<SMALL_NODES / SMALL_THREADS>(A.T, A.spin_limit, L.depth);
+        __syncthreads();
+    }
+    STAGE {
+        // (the bits above those of the largest step need no sorting)
+        const u32 top = small_reps(A.T, A.keys, A.vals, L.reps);
+        sort_here(L, A.keys, A.vals, A.T.n, RsFields{{0, 32}, {bits_of(A.T.n - 1), bits_of(top)}});
+    }
+    EACH(T.n, heads_at(T, A.keys, A.vals, A.head_flag, A.tri_in, i));
+    SCAN(scan_tri, A.tri_in, A.tri_ex, A.T.n, (Tri *)nullptr);
+    EACH(T.n, batch_off_at(T, A.head_flag, A.tri_ex, A.s_items, 0, i));
+    EACH(T.n, batch_layout_at(T, A.lay_in, A.virt, i));
+    SCAN(scan_lay, A.lay_in, A.T.lay, A.T.n, A.lay_total);
+    EACH(T.n, batch_finish_at(T, T.lay, A.lay_total, i));
+    EACH(T.n, node_offsets_at(T, i));
+    EACH(T.n, view_offsets_at(T, i));
+    EACH(T.n, member_check_at(T, i));
+    EACH(T.E, opnd_at(T, i));
+    EACH(T.E, edges_at(T, i));
+    // launch plan
+    STAGE {
+        small_bedges(A.T, A.blist, L.small_bedges);
+        __syncthreads();
+    }
+    STAGE slots_of(A.T, A.fuse, A.blist, L.slots, [&](u32 i, u32 step) __attribute__((always_inline)) {
+        for (; i < A.T.n; i += step) find_cell(A.T, i);
+    });
+    __syncthreads();
+    EACH((T.n + SMALL_THREADS - 1) & ~(SMALL_THREADS - 1), launch_keys_at(T, A.keys, A.vals, T.n, i));   // (whole waves)
+    STAGE {
+        const u32 nb = A.T.hdr->n_batches;
+        sort_here(L, A.keys, A.vals, nb, RsFields{{0, SLOT_BITS}, {bits_of(nb - 1), bits_of(A.T.hdr->n_slots - 1)}});
+    }
+    EACH(T.n + 2, chain_flags_at(T, A.vals, A.cflag, A.clay_in, T.n, i));
+    SCAN(scan_u32, A.cflag, A.cflag_excl, A.T.n, (u32 *)nullptr);
+    EACH(T.n, chain_recs_at(T, 0, (const u32 *)nullptr, A.cflag, A.cflag_excl, A.clay_in, T.n, i));
+    SCAN(scan_clay, A.clay_in, A.T.clay, A.T.n, A.clay_total);
+    EACH(T.n, slot_tables_at(T, T.clay, A.clay_total, i));
+    EACH(T.n + 2, slot_fill_at(T, i));
+    // parameter uses
+    STAGE {
+        if (A.n_items > 0) {
+            for (u32 i = tid; i < A.T.n; i += SMALL_THREADS) item_emit_at(A.T, A.s_items, A.keys, A.vals, i);
+            __syncthreads();
+            sort_here(L, A.keys, A.vals, A.n_items, RsFields{{0, 32}, {(int)A.row_bits, (int)A.use_bits}});
+            for (u32 i = tid; i < A.n_items; i += SMALL_THREADS) item_finish_at(A.T, A.keys, A.vals, A.n_items, i);
+        }
+    }
+#undef SCAN
+#undef EACH
+#undef STAGE
 }
 
 // The header and the slot entries in use, written straight to page-locked host memory: one launch where two
@@ -2144,6 +2565,15 @@ int sched_enqueue(ob_ctx *ctx)
     }
     const size_t n_slots = (size_t)ctx->params.size() * 4 + 4;
 
+    const int fuse = batched && ctx->fuse;
+    const bool part_depth = by_depth && ctx->max_arity < DEPTH_MAX_ARITY && !ctx->force_frontier;
+    ctx->depth_partitioned = part_depth;
+    // One workgroup plans a graph of up to 2 048 nodes.  Schedules of one launch and of many, in us: recurrences of 48, 473
+    // and 1 617 nodes 93 and 140, 112 and 167, 155 and 187; a tagger's 461, 921 and 1 841 nodes 150 and 255, 170 and 218,
+    // 235 and 238; trees of 1 214 and 2 033 nodes 183 and 222, 220 and 230: the two meet where the rule ends.
+    const bool small = fuse && E > 0 && !agenda && part_depth && !ctx->wide_plan && n <= SMALL_NODES &&
+                       E <= SMALL_EDGES && n_items <= SMALL_EDGES;
+
     // ---- allocation (all from the caller's arena) ----
     u32 ht_size = 1;
     while (ht_size < 2 * n) ht_size <<= 1;
@@ -2165,12 +2595,13 @@ int sched_enqueue(ob_ctx *ctx)
     AgendaTables AG{};
     char *zero_lo = (char *)ctx->arena + ctx->top;
     A(T.hdr, SchedHeader, 1);
-    A(T.outdeg, u32, n + 1); A(T.qcount, u32, 64); A(g_dep, u32, n + 1);
+    A(T.outdeg, u32, n + 1); A(T.qcount, u32, 64);
     A(T.pu_start, u32, n_slots); A(T.pu_end, u32, n_slots);
-    A(T.ht_keys, u64, ht_size); A(bset, u32, BSET_SIZE);
-    const bool cells = batched && ctx->fuse && E > 0;      // a fused plan may hold gated cells
+    const bool cells = fuse && E > 0;      // a fused plan may hold gated cells
     T.cells = nullptr;
     if (cells) { A(T.cell_rows, u32, n); A(T.cell_nodes, u32, n); A(T.slot_mixed, u32, n); }
+    char *small_hi = (char *)ctx->arena + ctx->top;     // (the plan of a small graph keeps the others in LDS)
+    A(g_dep, u32, n + 1); A(T.ht_keys, u64, ht_size); A(bset, u32, BSET_SIZE);
     if (agenda) { A(AG.keys, u64, AG_TABLE); A(AG.sum, u64, AG_TABLE); A(AG.cnt, u32, AG_TABLE); }
     char *zero_hi = (char *)ctx->arena + ctx->top;
     A(T.ht_vals, u32, ht_size);
@@ -2178,7 +2609,7 @@ int sched_enqueue(ob_ctx *ctx)
     char *ones_hi = (char *)ctx->arena + ctx->top;
     if (cells) {        // (a cell holds more than eight nodes)
         T.cells_cap = n / 8 + 1;
-        A(T.cells, CellRec, T.cells_cap); A(T.cell_nodes_of, CellNodes, T.cells_cap); A(T.cell_of, u32, n);
+        A(T.nrec, uint4, n); A(T.cells, CellRec, T.cells_cap); A(T.cell_nodes_of, CellNodes, T.cells_cap); A(T.cell_of, u32, n);
     }
     A(T.sig, u64, n); A(T.step, u32, n); A(T.indeg, u32, n);
     A(T.succ_off, u32, n + 1); A(T.succ_edge, u32, E + 1); A(T.edge_cons, u32, E + 1);
@@ -2229,102 +2660,104 @@ int sched_enqueue(ob_ctx *ctx)
 #undef A
 
     // ---- stage 1 ----
-    {   // (sections of the arena start at multiples of 256 bytes)
+    if (!small) {   // (sections of the arena start at multiples of 256 bytes)
         const size_t words = (size_t)(ones_hi - zero_lo) / 16, zeros = (size_t)(zero_hi - zero_lo) / 16;
         const size_t bx = (words + 4 * TPB - 1) / (4 * TPB);
         hipLaunchKernelGGL(k_clear, dim3((unsigned)(bx < 2048 ? bx : 2048)), dim3(TPB), 0, s, (uint4 *)zero_lo, zeros, words);
         ++ctx->n_launch_sched;
     }
-    const bool part_depth = by_depth && ctx->max_arity < DEPTH_MAX_ARITY && !ctx->force_frontier;
-    ctx->depth_partitioned = part_depth;
-    K(k_node_init, n, T, manual ? 2 : (by_depth ? (part_depth ? 1 : 3) : 0), ctx->key_a, ctx->val_a);
-    HIP_TRY(ctx, prim_scan_u32(T.outdeg, T.succ_off, (size_t)n + 1, nullptr, ctx->scratch, s));
-    // a scan of a short array is one launch, up to 256 blocks of 1024 elements two, beyond that three
-    const int scan_launches = (size_t)n + 1 <= 4096 ? 1 : ((size_t)n + 1 <= 256 * 1024 ? 2 : 3);
-    ctx->n_launch_sched += scan_launches;
-    if (E > 0) {
-        HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, E, 0,
-                                     bit_width_u32(n - 1), 0, 0, ctx->scratch, s, &ctx->n_launch_sched));
-        K(k_succ_finish, E, T, ctx->val_a, succ_node);
-    }
-
-    // ---- stage 2 / 3 ----
-    if (by_depth) {
-        if (part_depth)
-            hipLaunchKernelGGL(k_depth_partitioned, dim3(blocks_for(n, DEPTH_PART)), dim3(DEPTH_THREADS), 0, s, T, g_dep,
-                               ctx->depth_spin_limit);
-        else
-            hipLaunchKernelGGL(k_depth_frontier, dim3(1), dim3(FRONTIER_THREADS), 0, s, T, succ_node);
-        ++ctx->n_launch_sched;
-        if (agenda) {   // steps become agenda iterations; T.step holds the depths until k_agenda rewrites it
-            K(k_class_insert, n, T, AG);
-            hipLaunchKernelGGL(k_class_rank, dim3(1), dim3(1024), 0, s, T, AG);
-            K(k_class_of, n, T, AG);
-            hipLaunchKernelGGL(k_agenda, dim3(1), dim3(AGENDA_THREADS), 0, s, T, AG, succ_node);
-            ctx->n_launch_sched += 2;
-        }
-        hipLaunchKernelGGL(k_rep_insert, dim3(blocks_for(n, REP_THREADS)), dim3(REP_THREADS), 0, s, T);
-        ++ctx->n_launch_sched;
-    }
-    K(k_sort_keys, n, T, ctx->key_a, ctx->val_a, manual ? 2 : by_depth);
-    if (manual) {
-        HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n, 32, bit_width_u32(ctx->manual_max | 1u),
-                                     0, 0, ctx->scratch, s, &ctx->n_launch_sched));
-    } else if (by_depth) {
-        const int lb = bit_width_u32(n - 1);
-        HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n, 0, lb, 32, lb,
-                                     ctx->scratch, s, &ctx->n_launch_sched));
-    }
-
-    // ---- stage 4 ----
-    u32 *head_flag = ctx->tmp_u32_a, *s_items = tmp_d;
-    K(k_heads, n, T, ctx->key_a, ctx->val_a, head_flag, tri_in);
-    HIP_TRY(ctx, prim_scan_tri(tri_in, tri_ex, n, nullptr, ctx->scratch, s));
-    ctx->n_launch_sched += scan_launches;
-    K(k_batch_off, n, T, head_flag, tri_ex, s_items, manual);
+    u32 *head_flag = ctx->tmp_u32_a, *s_items = tmp_d, *cflag = ctx->tmp_u32_a, *cflag_excl = ctx->tmp_u32_b;
     const int virt = ctx->concat_views && ctx->n_concat > 0;   // CONCAT batches that only products read stay uncopied
-    K(k_batch_layout, n, T, ctx->lay_in, virt);
-    HIP_TRY(ctx, prim_scan_lay(ctx->lay_in, T.lay, n, ctx->lay_total, ctx->scratch, s));
-    ctx->n_launch_sched += scan_launches;
-    K(k_batch_finish, n, T, T.lay, ctx->lay_total);
-    K(k_node_offsets, n, T);
-    K(k_view_offsets, n, T);
-    K(k_member_check, n, T);
-    if (E > 0) K(k_opnd, E, T);
-    if (E > 0) K(k_edges, E, T);
+    if (small) {
+        SmallArgs a{T, (uint4 *)zero_lo, ctx->key_a, ctx->val_a, succ_node, head_flag, s_items, blist, cflag, cflag_excl, tri_in, tri_ex,
+                    ctx->lay_in, ctx->lay_total, clay_in, clay_total, (u32)((small_hi - zero_lo) / 16), ctx->depth_spin_limit, n_items,
+                    (u32)bit_width_u32((u32)ctx->max_param_rows), (u32)bit_width_u32((u32)n_slots), ctx->fuse, virt};
+        hipLaunchKernelGGL(k_plan_small, dim3(1), dim3(SMALL_THREADS), 0, s, a);
+        ++ctx->n_launch_sched;
+    } else {
+        K(k_node_init, n, T, manual ? 2 : (by_depth ? (part_depth ? 1 : 3) : 0), ctx->key_a, ctx->val_a);
+        HIP_TRY(ctx, prim_scan_u32(T.outdeg, T.succ_off, (size_t)n + 1, nullptr, ctx->scratch, s));
+        // a scan of a short array is one launch, up to 256 blocks of 1024 elements two, beyond that three
+        const int scan_launches = (size_t)n + 1 <= 4096 ? 1 : ((size_t)n + 1 <= 256 * 1024 ? 2 : 3);
+        ctx->n_launch_sched += scan_launches;
+        if (E > 0) {
+            HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, E, 0,
+                                         bit_width_u32(n - 1), 0, 0, ctx->scratch, s, &ctx->n_launch_sched));
+            K(k_succ_finish, E, T, ctx->val_a, succ_node);
+        }
 
-    // ---- launch planning: slots, chains, tile descriptors ----
-    const int fuse = batched && ctx->fuse;
-    if (fuse && E > 0) K(k_bedges, n, T, bset, blist);
-    hipLaunchKernelGGL(k_slots, dim3(cells ? 1 + blocks_for(n, SLOT_THREADS) : 1), dim3(SLOT_THREADS), 0, s, T, (fuse && E > 0) ? ctx->fuse : 0, blist);
-    ++ctx->n_launch_sched;
-    K(k_launch_keys, n, T, ctx->key_a, ctx->val_a, n);
-    if (fuse && E > 0) {
-        const size_t n_sort = n < SLOT_MAX_NB + 1 ? n : SLOT_MAX_NB + 1;
-        // entries from n_batches on carry the largest key and stay where they are
-        HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n_sort, 0, 2 * SLOT_BITS,
-                                     0, 0, ctx->scratch, s, &ctx->n_launch_sched, &T.hdr->n_batches));
+        // ---- stage 2 / 3 ----
+        if (by_depth) {
+            if (part_depth)
+                hipLaunchKernelGGL(k_depth_partitioned, dim3(blocks_for(n, DEPTH_PART)), dim3(DEPTH_THREADS), 0, s, T, g_dep,
+                                   ctx->depth_spin_limit);
+            else
+                hipLaunchKernelGGL(k_depth_frontier, dim3(1), dim3(FRONTIER_THREADS), 0, s, T, succ_node);
+            ++ctx->n_launch_sched;
+            if (agenda) {   // steps become agenda iterations; T.step holds the depths until k_agenda rewrites it
+                K(k_class_insert, n, T, AG);
+                hipLaunchKernelGGL(k_class_rank, dim3(1), dim3(1024), 0, s, T, AG);
+                K(k_class_of, n, T, AG);
+                hipLaunchKernelGGL(k_agenda, dim3(1), dim3(AGENDA_THREADS), 0, s, T, AG, succ_node);
+                ctx->n_launch_sched += 2;
+            }
+            hipLaunchKernelGGL(k_rep_insert, dim3(blocks_for(n, REP_THREADS)), dim3(REP_THREADS), 0, s, T);
+            ++ctx->n_launch_sched;
+        }
+        K(k_sort_keys, n, T, ctx->key_a, ctx->val_a, manual ? 2 : by_depth);
+        if (manual) {
+            HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n, 32, bit_width_u32(ctx->manual_max | 1u),
+                                         0, 0, ctx->scratch, s, &ctx->n_launch_sched));
+        } else if (by_depth) {
+            const int lb = bit_width_u32(n - 1);
+            HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n, 0, lb, 32, lb,
+                                         ctx->scratch, s, &ctx->n_launch_sched));
+        }
+
+        // ---- stage 4 ----
+        K(k_heads, n, T, ctx->key_a, ctx->val_a, head_flag, tri_in);
+        HIP_TRY(ctx, prim_scan_tri(tri_in, tri_ex, n, nullptr, ctx->scratch, s));
+        ctx->n_launch_sched += scan_launches;
+        K(k_batch_off, n, T, head_flag, tri_ex, s_items, manual);
+        K(k_batch_layout, n, T, ctx->lay_in, virt);
+        HIP_TRY(ctx, prim_scan_lay(ctx->lay_in, T.lay, n, ctx->lay_total, ctx->scratch, s));
+        ctx->n_launch_sched += scan_launches;
+        K(k_batch_finish, n, T, T.lay, ctx->lay_total);
+        K(k_node_offsets, n, T);
+        K(k_view_offsets, n, T);
+        K(k_member_check, n, T);
+        if (E > 0) K(k_opnd, E, T);
+        if (E > 0) K(k_edges, E, T);
+
+        // ---- launch planning: slots, chains, tile descriptors ----
+        if (fuse && E > 0) K(k_bedges, n, T, bset, blist);
+        hipLaunchKernelGGL(k_slots, dim3(cells ? 1 + blocks_for(n, CELL_PART) : 1), dim3(SLOT_THREADS), 0, s, T, (fuse && E > 0) ? ctx->fuse : 0, blist);
+        ++ctx->n_launch_sched;
+        K(k_launch_keys, n, T, ctx->key_a, ctx->val_a, n);
+        if (fuse && E > 0) {
+            const size_t n_sort = n < SLOT_MAX_NB + 1 ? n : SLOT_MAX_NB + 1;
+            // entries from n_batches on carry the largest key and stay where they are
+            HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n_sort, 0, 2 * SLOT_BITS,
+                                         0, 0, ctx->scratch, s, &ctx->n_launch_sched, &T.hdr->n_batches));
+        }
+        K(k_chain_flags, (size_t)n + 2, T, ctx->val_a, cflag, clay_in, n);
+        HIP_TRY(ctx, prim_scan_u32(cflag, cflag_excl, n, nullptr, ctx->scratch, s));
+        K(k_chain_recs, n, T, agenda || manual, bset, cflag, cflag_excl, clay_in, n);
+        HIP_TRY(ctx, prim_scan_clay(clay_in, T.clay, n, clay_total, ctx->scratch, s));
+        ctx->n_launch_sched += 2 * scan_launches;
+        K(k_slot_tables, n, T, T.clay, clay_total);
+        if (fuse) K(k_slot_fill, (size_t)n + 2, T);
+        if (n_items > 0) {
+            K(k_item_emit, n, T, s_items, ctx->key_a, ctx->val_a);
+            HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n_items, 0,
+                                         bit_width_u32((u32)ctx->max_param_rows), 32, bit_width_u32((u32)n_slots), ctx->scratch, s,
+                                         &ctx->n_launch_sched));
+            K(k_item_finish, n_items, T, ctx->key_a, ctx->val_a, n_items);
+        }
     }
-    u32 *cflag = ctx->tmp_u32_a, *cflag_excl = ctx->tmp_u32_b;
-    K(k_chain_flags, (size_t)n + 2, T, ctx->val_a, cflag, clay_in, n);
-    HIP_TRY(ctx, prim_scan_u32(cflag, cflag_excl, n, nullptr, ctx->scratch, s));
-    K(k_chain_recs, n, T, agenda || manual, bset, cflag, cflag_excl, clay_in, n);
-    HIP_TRY(ctx, prim_scan_clay(clay_in, T.clay, n, clay_total, ctx->scratch, s));
-    ctx->n_launch_sched += 2 * scan_launches;
-    K(k_slot_tables, n, T, T.clay, clay_total);
-    if (fuse) K(k_slot_fill, (size_t)n + 2, T);
     hipLaunchKernelGGL(k_tiles, dim3(1024), dim3(TPB), 0, s, T, T.clay, clay_total, (u32)cap_f, (u32)cap_a,
                        (u32)cap_b);
     ++ctx->n_launch_sched;
-
-    // ---- parameter-use items ----
-    if (n_items > 0) {
-        K(k_item_emit, n, T, s_items, ctx->key_a, ctx->val_a);
-        HIP_TRY(ctx, prim_sort_pairs_swap(ctx->key_a, ctx->val_a, ctx->key_b, ctx->val_b, n_items, 0,
-                                     bit_width_u32((u32)ctx->max_param_rows), 32, bit_width_u32((u32)n_slots), ctx->scratch, s,
-                                     &ctx->n_launch_sched));
-        K(k_item_finish, n_items, T, ctx->key_a, ctx->val_a, n_items);
-    }
     HIP_TRY(ctx, hipGetLastError());
 
     // ---- the header and a first window of the per-slot tables go to the host ----

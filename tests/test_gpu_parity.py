@@ -1797,6 +1797,78 @@ def test_depths_of_nodes_of_any_arity_across_id_ranges(n, arities, reach):
     c.close()
 
 
+def _dag_of(n, seed, dim):
+    """The first n - 1 nodes of a random graph over all operations, and the squared norm of the last of them as its root."""
+    p, g = wl.random_dag(seed, n_nodes=n + 40, dim=dim)
+    assert len(g.op) >= n
+    g = _graph_part(g, 0, n - 1)
+    last = {"op": wl.OP_SQNORM, "out_dim": 1, "in_off": int(g.in_off[-1]) + 1, "in_idx": n - 2, "param": -1, "bias": -1, "aux0": 0, "aux1": 0}
+    for k, v in last.items():
+        a = getattr(g, k)
+        setattr(g, k, np.append(a, np.asarray(v, a.dtype)))
+    g.root = n - 1
+    return p, g
+
+
+def _plan(p, g, wide, fuse, copy):
+    """Everything that a schedule fixes, and what the forward and backward passes of it give."""
+    from paper_1705_07860_amd import binding as ob
+    c = ob.Context(arena_bytes=512 << 20, mode=ob.OB_BYDEPTH)
+    c.set_fusion(fuse)
+    c.params_create(p)
+    c.param_grad_zero()
+    c.debug_set(ob.OB_DBG_SET_WIDE_PLAN, wide)
+    c.debug_set(ob.OB_DBG_SET_CONCAT_COPY, copy)
+    c.add_bulk(g)
+    root = len(g.op) - 1
+    c.forward(root)
+    out = {k: c.debug_read(getattr(ob, "OB_DBG_" + k)) for k in ("DEPTH", "SIG", "SUCC_OFF", "SUCC_EDGE", "ORDER", "VAL_OFF",
+                                                               "CHAINS", "LORDER")}
+    total = int(g.out_dim.sum())
+    out["values"] = c.all_read(0, total).view(np.uint32)
+    if g.out_dim[root] == 1:
+        c.backward(root)
+        out["gradients"] = c.all_read(1, total).view(np.uint32)
+        for pid, m in enumerate(p.mats):
+            out[f"parameter {pid}"] = c.param_grad_read(pid, m.shape).view(np.uint32)
+    st = c.stats()
+    out["counts"] = np.array([st[k] for k in sorted(st) if k.startswith("n_") and k != "n_launch_sched"])
+    c.close()
+    return out, st["n_launch_sched"]
+
+
+def _same_plan(p, g, fuse=2, copy=0):
+    small, few = _plan(p, g, 0, fuse, copy)
+    wide, many = _plan(p, g, 1, fuse, copy)
+    assert (few < many) == (len(g.op) <= 2048 and 0 < int(g.in_off[-1]) <= 4096)
+    assert small.keys() == wide.keys()
+    for k in small:
+        assert np.array_equal(small[k], wide[k]), k
+
+
+@pytest.mark.parametrize("n", [2, 3, 64, 65, 1023, 1024, 1025, 2047, 2048, 2049])
+@pytest.mark.parametrize("dim,fuse,copy", [(6, 2, 0), (32, 1, 1), (33, 2, 0)])
+def test_a_small_graph_is_scheduled_as_a_large_one_would_be(n, dim, fuse, copy):
+    """Graphs of up to 2 048 nodes and 4 096 edges are scheduled by one workgroup in one launch: every table is that of the
+    launches for larger graphs, around the sizes where a workgroup takes a second round and where the rule ends."""
+    p, g = _dag_of(n, 40 + n + dim, dim)
+    _same_plan(p, g, fuse, copy)
+
+
+@pytest.mark.parametrize("n,arities,reach", [(2048, [0, 0, 0, 1, 2], 40), (1100, [2, 3], 700), (1025, [0] * 400 + [1] * 200 + [9] * 50 + [800] * 2, 1000),
+                                             (700, [4, 5, 6, 9], 8), (2048, [0] * 40 + [33], 2000), (1366, [3], 5), (1368, [3], 5)])
+def test_a_small_graph_of_any_arity_is_scheduled_as_a_large_one_would_be(n, arities, reach):
+    """The same with operand lists of every length and with edges on both sides of the 4 096 that the rule allows."""
+    _same_plan(wl.Params([], []), _random_arity_graph(n, arities, reach, n + len(arities)))
+
+
+@pytest.mark.parametrize("H,nf,sums,rows", [(8, 1, True, 20), (64, 2, False, 12), (100, 0, True, 9)])
+def test_a_small_graph_of_gated_cells_is_scheduled_as_a_large_one_would_be(H, nf, sums, rows):
+    p, g = _cell_graph(H, nf, sums, rows, None)
+    assert len(g.op) <= 2048
+    _same_plan(p, g)
+
+
 def test_depths_of_more_id_ranges_than_the_chip_holds_at_once():
     """1 026 ranges of 1 024 ids, operands drawn from all nodes before: a range waits for any lower one, also where not
     all of them can be on the chip together."""

@@ -1371,6 +1371,120 @@ __device__ inline void cell_bwd_item(const Tables &T, const PullDesc *tiles, u32
     else cell_bwd_rows<NW, false>(T, tiles, rows);
 }
 
+// A tile of a product Y = X W^T + b and of the gated cells behind it (S = Y + another row; four gates, one of them forget).  The tile's
+// 32 columns are eight columns of each gate, so that what comes out of the contraction is all that eight columns of 32
+// cells need: the two slots are one launch, and the cells' records, their other rows and their states are asked for while the
+// operands of the product are on their way.  Every sum is taken in the order of the two launches, so the bits are the same.
+// Bound by latency: descriptor, operands and contraction of a product take some five us of its launch, launch and first reads of
+// the cells three of theirs: 64 sentences, 6.1 and 3.5 us in two launches, 7.4 in one (with the records taken by the whole workgroup, a
+// barrier in front of the contraction, and every lane working out both kinds of gate 8.0).
+constexpr u32 PAIR_COLS = GT / 4;            // columns of a cell in a tile
+constexpr u32 PAIR_WORDS = 28;               // words of a CellRec that the forward pass needs
+constexpr u32 PAIR_LDS_FLOATS = GT * PAIR_WORDS + GT * (GT + 1);
+static_assert(GT == 32 && offsetof(CellRec, at_f) / 4 < PAIR_WORDS && 8 * PAIR_WORDS / 4 <= 64 && sizeof(TileDesc) % 16 == 0 && PAIR_WORDS % 4 == 0,
+              "a lane takes 16 bytes of the records of its wave's eight rows");
+__device__ inline void product_cell_tile(const Tables &T, const TileDesc &d, float *lds)
+{
+    const u32 lane = threadIdx.x & 63u, w = threadIdx.x >> 6, l32 = lane & 31u, h = lane >> 5;
+    const u32 K = d.k, H = d.d / 4u, ntn = (d.d + GT - 1) / GT;
+    const u32 r0 = (d.t / ntn) * GT, c0 = (d.t % ntn) * PAIR_COLS;
+    u32 *recs = (u32 *)(lds + LDS_FLOATS);
+    float *sum = lds + LDS_FLOATS + GT * PAIR_WORDS;
+    // the records of the tile's rows: a wave takes those of the eight rows that it finishes, so nothing here waits for other waves
+    uint4 rec = make_uint4(0u, 0u, 0u, 0u);
+    const u32 mine = 8u * w + lane / (PAIR_WORDS / 4), part = lane % (PAIR_WORDS / 4);
+    const bool has = lane < 8u * (PAIR_WORDS / 4);
+    if (has && r0 + mine < d.B) rec = ((const uint4 *)(T.tiles_f + (d.pad - 1u) + r0 + mine))[part];
+    const u32 row = r0 + l32;
+    const bool row_ok = row < d.B;
+    const u32 xo = row_ok ? opnd_row(T, d, 0, row - d.row0, row) : 0u;
+    const u32 gate = l32 / PAIR_COLS, cc = c0 + l32 % PAIR_COLS, col = gate * H + cc;
+    const bool col_ok = cc < H;
+    gl_float *wrow = as_global(d.w) + (size_t)(col_ok ? col : 0u) * K;
+    const bool fast = (d.flags & 2u) && (K & 3u) == 0;
+    u32 lo, hi;
+    wave_range<4>(K, lo, hi);
+    floatx16 acc;
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    float4 a[KU], b[KU];
+    auto operands = [&](u32 kb) __attribute__((always_inline)) {
+        const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            const u32 k0 = kb + 8 * u + 4 * h;
+            const bool in = kb + 8 * u < hi && k0 < K;
+            a[u] = b[u] = z4;
+            if (fast) {
+                if (in && row_ok) a[u] = ld4(T.V + xo + k0);
+                if (in && col_ok) b[u] = gl_ld4(wrow + k0);
+            } else if (in) {
+                float av[4] = {0.f, 0.f, 0.f, 0.f}, bv[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (u32 q = 0; q < 4; ++q) {
+                    if (row_ok && k0 + q < K) av[q] = T.V[xo + k0 + q];
+                    if (col_ok && k0 + q < K) bv[q] = wrow[k0 + q];
+                }
+                a[u] = make_float4(av[0], av[1], av[2], av[3]);
+                b[u] = make_float4(bv[0], bv[1], bv[2], bv[3]);
+            }
+        }
+    };
+    operands(lo);
+    const float bias = d.b && col_ok ? as_global(d.b)[col] : 0.f;
+    if (has) {
+        u32 *to = recs + mine * PAIR_WORDS + part * 4u;
+        to[0] = rec.x; to[1] = rec.y; to[2] = rec.z; to[3] = rec.w;
+    }
+    __builtin_amdgcn_wave_barrier();      // (a wave reads what it wrote itself; its LDS operations complete in order)
+    // this lane's part of the sums: column l32 of rows 8 w + 4 h + i; of the cells: column l32 % 8 of row 8 w + 4 h + gate
+    float other[4];
+    u32 at_S[4];
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) {
+        const u32 rl = 8u * w + 4u * h + i;
+        const CellRec &R = *(const CellRec *)(recs + rl * PAIR_WORDS);
+        const bool live = r0 + rl < d.B && col_ok;
+        const u32 y = d.val_off + (r0 + rl) * d.d;
+        other[i] = live ? T.V[(R.b == y ? R.a : R.b) + col] : 0.f;
+        at_S[i] = R.S + col;
+    }
+    const u32 rc = 8u * w + 4u * h + gate;
+    const CellRec &C = *(const CellRec *)(recs + rc * PAIR_WORDS);
+    const bool cell = r0 + rc < d.B && col_ok;
+    const float prev = cell ? T.V[C.prev[0] + cc] : 0.f;
+    for (u32 kb = lo; kb < hi; kb += 8 * KU) {
+        if (kb != lo) operands(kb);
+#pragma unroll
+        for (int u = 0; u < KU; ++u) acc = mfma4(a[u], b[u], acc);
+    }
+    float out[4];
+    reduce_waves<4>(acc, lds, out);
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) {
+        const u32 rl = 8u * w + 4u * h + i;
+        const float y = d.b ? add_r(out[i], bias) : out[i] + 0.f, z = add_r(other[i], y);
+        sum[rl * (GT + 1) + l32] = z;
+        if (r0 + rl < d.B && col_ok) {
+            T.V[d.val_off + (r0 + rl) * d.d + col] = y;
+            T.V[at_S[i]] = z;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (cell) {
+        const float *z4 = sum + rc * (GT + 1) + l32 % PAIR_COLS;
+        const u32 H2 = 2u * H;
+        auto of = [&](u32 at) __attribute__((always_inline)) { return z4[(at >= H2 ? (at == H2 ? 2u : 3u) : (at == 0u ? 0u : 1u)) * PAIR_COLS]; };
+        const float i = sigmoidf_(of(C.at_i)), g = tanhf(of(C.at_g)), o = sigmoidf_(of(C.at_o)), f = sigmoidf_(of(C.at_f[0]));
+        const float ic = mul_r(i, g), p = mul_r(f, prev);
+        const float c = C.ic_at == 0u ? add_r(ic, p) : add_r(p, ic);
+        const float tc = tanhf(c);
+        T.V[C.i + cc] = i; T.V[C.g + cc] = g; T.V[C.o + cc] = o; T.V[C.f[0] + cc] = f;
+        T.V[C.ic + cc] = ic; T.V[C.fp[0] + cc] = p; T.V[C.c + cc] = c; T.V[C.tc + cc] = tc;
+        T.V[C.h + cc] = mul_r(o, tc);
+    }
+    __syncthreads();       // the LDS space is free for the workgroup's next tile
+}
+
 // ------------------------------------------------------------------------------------------------
 // kernels
 // ------------------------------------------------------------------------------------------------
@@ -1427,11 +1541,23 @@ __device__ inline void stage_descriptors(const void *src, void *dst, u32 n)
 // tile_lo + (w - work_lo) * run_len and the work records are not read.
 extern __shared__ __align__(16) float dyn_lds[];   // sized per launch: GEMM reduction space or a fused chain's copy
 
+// a launch of products and of the cells behind them
+__global__ __launch_bounds__(WG, 3) void k_fwd_cells(u32 work_lo, u32 work_hi, u32 tile_lo, const TileDesc *tiles_f, Tables T)
+{
+    for (u32 w = work_lo + blockIdx.x; w < work_hi; w += gridDim.x) {
+        const TileDesc d = tiles_f[tile_lo + (w - work_lo)];
+        product_cell_tile(T, d, dyn_lds);
+    }
+}
+
 // KIND: FWD_ANY every kind of tile; FWD_LEAN the launch holds component-wise work only (this instantiation
 // carries no GEMM or reduction code, needs half the registers and keeps twice the waves per CU); FWD_XP every
 // kind, and the products may read their operand rows in pieces.
+// CELLS: the launch may hold gated cells.  Launches of products mostly do not, and with the code for cells, which takes scalar
+// registers away from the tiles', each took 0.3 us more; cells beside products worked as interpreted runs instead cost the
+// character tagger a fourteenth of its time.
 enum : int { FWD_ANY = 0, FWD_LEAN = 1, FWD_XP = 2 };
-template <int KIND>
+template <int KIND, bool CELLS>
 __global__ __launch_bounds__(WG, KIND == FWD_LEAN ? 6 : 3) void k_fwd_step(u32 work_lo, u32 work_hi, u32 tile_lo, u32 run_len,
                                                                 const TileDesc *tiles_f, const WorkRec *works_f, Tables T)
 {
@@ -1444,7 +1570,7 @@ __global__ __launch_bounds__(WG, KIND == FWD_LEAN ? 6 : 3) void k_fwd_step(u32 w
         WorkRec wr;
         if (run_len) { wr.first = tile_lo + (w - work_lo) * (run_len & ~CELL_ITEM); wr.len = run_len; }
         else wr = works_f[w];
-        if (KIND == FWD_LEAN && (wr.len & CELL_ITEM)) { cell_fwd_item<WG / 64>(T, tiles_f + sreg(wr.first), sreg(wr.len) & ~CELL_ITEM); continue; }
+        if (CELLS && (wr.len & CELL_ITEM)) { cell_fwd_item<WG / 64>(T, tiles_f + sreg(wr.first), sreg(wr.len) & ~CELL_ITEM); continue; }
         if (wr.len == 1) {
             const TileDesc d = tiles_f[wr.first];
             if (KIND == FWD_LEAN) ew_fwd_tile(T, d, (lds_float *)lds, threadIdx.x, WG);
@@ -1476,7 +1602,7 @@ __global__ __launch_bounds__(WG, KIND == FWD_LEAN ? 6 : 3) void k_fwd_step(u32 w
 // items.  Both kinds may share a launch only when no dX tile reads a gradient that this slot's
 // pull computes; otherwise the host launches the pull range and the dX range one after the other.
 constexpr int BWD_THREADS = DX_WAVES * 64;
-template <bool LEAN>
+template <bool LEAN, bool CELLS>
 __global__ __launch_bounds__(BWD_THREADS, 4) void k_bwd_step(u32 work_lo, u32 work_hi, u32 tile_lo, u32 run_len,
                                                                         u32 dx_lo, u32 dx_hi, const PullDesc *tiles_a,
                                                                         const WorkRec *works_a, const TileDesc *tiles_b, Tables T)
@@ -1496,7 +1622,7 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_bwd_step(u32 work_lo, u32 wo
         WorkRec wr;
         if (run_len) { wr.first = tile_lo + (w - work_lo) * (run_len & ~CELL_ITEM); wr.len = run_len; }
         else { wr = works_a[w]; wr.first = sreg(wr.first); wr.len = sreg(wr.len); }
-        if (LEAN && (wr.len & CELL_ITEM)) { cell_bwd_item<BWD_THREADS / 64>(T, tiles_a + sreg(wr.first), sreg(wr.len) & ~CELL_ITEM); continue; }
+        if (CELLS && (wr.len & CELL_ITEM)) { cell_bwd_item<BWD_THREADS / 64>(T, tiles_a + sreg(wr.first), sreg(wr.len) & ~CELL_ITEM); continue; }
         if (wr.len == 1) {
             const PullDesc d = tiles_a[wr.first];
             pull_tile(T, d, (lds_float *)lds, threadIdx.x, BWD_THREADS);
@@ -1780,9 +1906,10 @@ static hipError_t allow_large_dynamic_lds()
 {
     static hipError_t result = [] {
         const int bytes = (int)(CHAIN_LDS_FLOATS * 4);
-        const void *kernels[5] = {(const void *)k_fwd_step<FWD_ANY>, (const void *)k_fwd_step<FWD_LEAN>,
-                                  (const void *)k_fwd_step<FWD_XP>,
-                                  (const void *)k_bwd_step<false>, (const void *)k_bwd_step<true>};
+        const void *kernels[8] = {(const void *)k_fwd_step<FWD_ANY, false>, (const void *)k_fwd_step<FWD_ANY, true>,
+                                  (const void *)k_fwd_step<FWD_XP, false>, (const void *)k_fwd_step<FWD_XP, true>,
+                                  (const void *)k_fwd_step<FWD_LEAN, true>, (const void *)k_bwd_step<true, true>,
+                                  (const void *)k_bwd_step<false, false>, (const void *)k_bwd_step<false, true>};
         hipError_t e = hipSuccess;
         for (const void *k : kernels)
             if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -1800,18 +1927,21 @@ static int launch_forward_steps(ob_ctx *ctx)
     for (u32 st = 0; st < ns; ++st) {
         const SlotRec &r = ctx->slots[st];
         const u32 lo = r.wf, hi = ctx->slots[st + 1].wf;
-        if (hi > lo) {
-            if (r.plain & 1u)
-                hipLaunchKernelGGL(k_fwd_step<FWD_LEAN>, dim3(grid_for(hi - lo, GRID_CAP)), dim3(WG), slot_lds_bytes(r, 16), s,
-                                   lo, hi, r.tf, slot_run_len_fwd(r), T.tiles_f, T.works_f, T);
-            else if (r.plain & 2u)
-                hipLaunchKernelGGL(k_fwd_step<FWD_ANY>, dim3(grid_for(hi - lo, GRID_CAP)), dim3(WG),
-                                   slot_lds_bytes(r, FWD_LDS_MIN), s, lo, hi, r.tf, slot_run_len_fwd(r), T.tiles_f, T.works_f, T);
-            else   // a product of the slot reads its operand rows in pieces
-                hipLaunchKernelGGL(k_fwd_step<FWD_XP>, dim3(grid_for(hi - lo, GRID_CAP)), dim3(WG),
-                                   slot_lds_bytes(r, FWD_LDS_MIN), s, lo, hi, r.tf, slot_run_len_fwd(r), T.tiles_f, T.works_f, T);
-            ++ctx->n_launch_fwd;
+        if (hi <= lo) continue;
+        ++ctx->n_launch_fwd;
+        const dim3 grid(grid_for(hi - lo, GRID_CAP));
+        if (st + 1 < ns && !(ctx->slots[st + 1].plain & 4u)) {     // (a work item of such a slot is one tile)
+            hipLaunchKernelGGL(k_fwd_cells, grid, dim3(WG), (LDS_FLOATS + PAIR_LDS_FLOATS) * sizeof(float), s, lo, hi, r.tf,
+                               T.tiles_f, T);
+            ++st;
+            continue;
         }
+        const bool lean = r.plain & 1u, whole = r.plain & 2u, cells = !(r.plain & 8u);
+        auto *kernel = lean ? k_fwd_step<FWD_LEAN, true>      // (without products, or with some that read their operand rows in pieces or not)
+                       : whole ? (cells ? k_fwd_step<FWD_ANY, true> : k_fwd_step<FWD_ANY, false>)
+                               : (cells ? k_fwd_step<FWD_XP, true> : k_fwd_step<FWD_XP, false>);
+        hipLaunchKernelGGL(kernel, grid, dim3(WG), slot_lds_bytes(r, lean ? 16 : FWD_LDS_MIN), s, lo, hi, r.tf, slot_run_len_fwd(r),
+                           T.tiles_f, T.works_f, T);
     }
     return 0;
 }
@@ -1832,18 +1962,19 @@ static int launch_backward_steps(ob_ctx *ctx)
         // (with gradients arriving from later stages a product's gradient is no longer its one consumer's row:
         // the dX tiles then read the rows the slot's own pull has just written)
         if (n_pull && n_dx && r.dx_free && !T.Gx) {
-            hipLaunchKernelGGL(k_bwd_step<false>, dim3(grid_for(n_pull + n_dx, GRID_CAP)), dim3(BWD_THREADS), lds_bytes, s,
+            auto *kernel = r.plain & 8u ? k_bwd_step<false, false> : k_bwd_step<false, true>;
+            hipLaunchKernelGGL(kernel, dim3(grid_for(n_pull + n_dx, GRID_CAP)), dim3(BWD_THREADS), lds_bytes, s,
                                r.wa, e.wa, r.ta, slot_run_len(r), r.tb, e.tb, T.tiles_a, T.works_a, T.tiles_b, T);
             ++ctx->n_launch_bwd;
             continue;
         }
         if (n_pull) {
-            hipLaunchKernelGGL(k_bwd_step<true>, dim3(grid_for(n_pull, GRID_CAP)), dim3(BWD_THREADS), slot_lds_bytes(r, 16), s,
+            hipLaunchKernelGGL((k_bwd_step<true, true>), dim3(grid_for(n_pull, GRID_CAP)), dim3(BWD_THREADS), slot_lds_bytes(r, 16), s,
                                r.wa, e.wa, r.ta, slot_run_len(r), 0u, 0u, T.tiles_a, T.works_a, T.tiles_b, T);
             ++ctx->n_launch_bwd;
         }
         if (n_dx) {
-            hipLaunchKernelGGL(k_bwd_step<false>, dim3(grid_for(n_dx, GRID_CAP)), dim3(BWD_THREADS), BWD_LDS_MIN, s, 0u, 0u,
+            hipLaunchKernelGGL((k_bwd_step<false, false>), dim3(grid_for(n_dx, GRID_CAP)), dim3(BWD_THREADS), BWD_LDS_MIN, s, 0u, 0u,
                                0u, 0u, r.tb, e.tb, T.tiles_a, T.works_a, T.tiles_b, T);
             ++ctx->n_launch_bwd;
         }

@@ -176,7 +176,8 @@ struct CellRec {
 };
 static_assert(sizeof(CellRec) == sizeof(PullDesc), "a CellRec takes a PullDesc's place");
 constexpr u32 CELL_NODES = 4 + CELL_FORGET + 1 + 2 * (CELL_FORGET + 3);
-struct CellNodes { u32 batch[CELL_NODES]; };      // [0]: of h | number of nodes << 16 (a fused plan has at most 4 096 batches)
+// prod: 1 + the batches of the rows whose sum S is, where they are products that nobody else reads (else 0)
+struct CellNodes { u32 batch[CELL_NODES]; u32 prod[2]; };      // [0]: of h | number of nodes << 16 (a fused plan has at most 4 096 batches)
 constexpr u32 CELL_ITEM = 0x80000000u;      // in a work item's length: its tiles are CellRecs, a row each
 constexpr u32 CELL_WAVES = 4;               // waves of the forward kernel: a row takes one to four of them, a work item fills them
 __host__ __device__ inline u32 cell_row_waves(u32 H) { const u32 w = (H + 63u) / 64u; return w < 3u ? w : 4u; }
@@ -212,7 +213,9 @@ struct WorkRec { u32 first, len; };   // a workgroup runs tiles [first, first + 
 // slots without such chains keep more workgroups resident per CU.
 // plain bit 0: every forward work item of the slot is component-wise (no GEMM, reduction or wide-sum
 // tile), so the slot can run the lean instantiation of the forward kernel.  Bit 1: no product of the slot
-// reads its operand rows in pieces (otherwise the slot runs the instantiation that can).
+// reads its operand rows in pieces (otherwise the slot runs the instantiation that can); bit 2 clear: the slot is one chain of
+// cells that takes up every row of the slot before, all products, and the forward work of both slots is that slot's launch.
+// bit 3 clear: the slot holds gated cells.
 // lminf / nlmaxf: the same pair of run lengths over the slot's forward work items (views have none).
 struct SlotRec { u32 wf, wa, tb, tf, ta, lmin, nlmax, dx_free, lds_need, plain, lminf, nlmaxf; };
 
@@ -273,7 +276,9 @@ struct Tables {
     uint4 *nrec;                           // per node: first two operands, operation, arity (with `cells` only)
     CellRec *cells; u32 *cell_of;          // gated cells; per position of an output h: its cell
     CellNodes *cell_nodes_of;              // per cell: the batches of its nodes
-    u32 *slot_mixed;                       // per slot: products, reductions or wide sums run in it
+    u32 *cell_prods;                       // per batch of outputs: cells that take up a product's row from the slot before theirs
+    u32 *prod_cell;                        // per position of such a product: its cell
+    u32 *slot_chains, *slot_rows;          // per slot: chains, and rows of all of them
     u32 *cell_rows, *cell_nodes;           // per batch of outputs: cells whose nodes lie in one chain, and the nodes they hold
     u32 cells_cap;
     ChainRec *chains; CLay *clay; u32 *chain_of_lpos;

@@ -1272,6 +1272,18 @@ __device__ inline void find_cell(const Tables &T, u32 p)
         N.batch[4 + NT + 2 * k] = is ? batch(node[k]) : b;
         N.batch[5 + NT + 2 * k] = is ? batch(sl[k]) : b;
     }
+    // products that only this cell reads
+    N.prod[0] = N.prod[1] = 0;
+    if (sums && nt == 2u) {
+#pragma unroll
+        for (u32 k = 0; k < 2; ++k) {
+            const u32 u = k == 0 ? a : a2;
+            if (T.op[u] != OP_MATVEC || T.outdeg[u] != 1u) continue;
+            const u32 pu = T.pos_of[u];
+            N.prod[k] = T.batch_of_pos[pu] + 1u;
+            T.prod_cell[pu] = cell;
+        }
+    }
     T.cell_nodes_of[cell] = N;
 }
 
@@ -1283,20 +1295,28 @@ __device__ inline void cell_in_chain(const Tables &T, u32 cell)
     const u32 lane = threadIdx.x & 63u;
     CellNodes N;
     N.batch[0] = 0;
+    bool taken = false;
     bool one = cell < T.hdr->n_cells && cell < T.cells_cap;
     if (one) {
         N = T.cell_nodes_of[cell];
         const u32 b = N.batch[0] & 0xffffu, slot = T.slot_of[b], label = T.label_of[b];
 #pragma unroll
         for (u32 k = 1; k < CELL_NODES; ++k) one = one && T.slot_of[N.batch[k]] == slot && T.label_of[N.batch[k]] == label;
+#pragma unroll
+        for (u32 k = 0; k < 2; ++k) {
+            if (!N.prod[k]) continue;
+            const BatchRec &rp = T.batches[N.prod[k] - 1u];
+            taken = taken || (T.slot_of[N.prod[k] - 1u] + 1u == slot && !(rp.vec4 & TF_WIDE) && !batch_xp(rp) && rp.d == 4u * T.batches[b].d);
+        }
     }
     for (u64 todo = __ballot(one); todo;) {
         const u32 leader = (u32)__builtin_ctzll(todo), word = (u32)__shfl((int)N.batch[0], (int)leader);
-        const u64 same = __ballot(one && N.batch[0] == word);
+        const u64 same = __ballot(one && N.batch[0] == word), with = __ballot(one && N.batch[0] == word && taken);
         if (lane == leader) {
             const u32 rows = (u32)__popcll(same);
             atomicAdd(&T.cell_rows[word & 0xffffu], rows);
             atomicAdd(&T.cell_nodes[word & 0xffffu], rows * (word >> 16));
+            if (with) atomicAdd(&T.cell_prods[word & 0xffffu], (u32)__popcll(with));
         }
         todo &= ~same;
     }
@@ -1460,7 +1480,6 @@ __device__ inline void launch_keys_at(const Tables &T, u64 *keys, u32 *vals, u32
         const BatchRec &r = T.batches[b];
         if (r.vec4 & TF_VIEW) { cnt[0] = 1u; cnt[1] = r.B * r.d; }
         if (r.vec4 & TF_VIRT) { cnt[2] = 1u; cnt[3] = r.B * r.d; }
-        if (T.cells && !op_chain_source(r.op, r.arity)) T.slot_mixed[T.slot_of[b]] = 1u;
     }
     if (__ballot(cnt[0] | cnt[2]) != 0ull) {
         for (int q = 0; q < 4; ++q)
@@ -1615,9 +1634,7 @@ __device__ inline void chain_recs_at(const Tables &T, int agenda, const u32 *bse
             if (fit >= 1) { cr.fused = 2u; if (fit < cr.Rg) cr.Rg = fit; }
         }
         cr.pad0 = cr.pad1 = cr.pad2 = 0;
-        if (cr.fused == 2u && cells == G && cell_nodes == kt * G && !T.slot_mixed[cr.slot]) {
-            // gated cells and nothing else (a launch with products in it takes seven microseconds anyway and keeps the kernel that
-            // has no code for cells: with it, and its scalar registers spilt for it, each product launch took 0.3 us more)
+        if (cr.fused == 2u && cells == G && cell_nodes == kt * G) {     // gated cells and nothing else
             cr.fused = 3u; cr.pad0 = out;
             cr.Rg = CELL_WAVES / cell_row_waves(cell_d);
             kt = ktf = cr.Rg;      // a tile a row; the last block's may be left over
@@ -1642,6 +1659,7 @@ __device__ inline void chain_recs_at(const Tables &T, int agenda, const u32 *bse
             L.wf = L.tf;
             L.ta = L.wa = cr.nrb;          // pull tiles are row blocks of the batch
         }
+        if (T.cells) { atomicAdd(&T.slot_chains[cr.slot], 1u); atomicAdd(&T.slot_rows[cr.slot], rows); }
         T.chains[c] = cr;
         clay_in[c] = L;
     }
@@ -1666,6 +1684,9 @@ __device__ inline void slot_tables_at(const Tables &T, const CLay *clay_ex, cons
     if (c == 0 || T.chains[c - 1].slot != s) { S.wf = L.wf; S.wa = L.wa; S.tb = L.tb; S.tf = L.tf; S.ta = L.ta; }
     const BatchRec &hb = T.batches[T.lorder[cr.first]];
     if (hb.op == OP_MATVEC && !(hb.vec4 & TF_G_ALIAS)) S.dx_free = 0;   // this slot's dX tiles need the slot's own pull first
+    if (cr.fused == 3u) atomicAnd(&S.plain, ~8u);
+    // (every row of a product taken up has one reader, so as many rows as cells are all rows of the slot before)
+    if (cr.fused == 3u && s > 0 && T.slot_chains[s] == 1u && T.cell_prods[cr.pad0] == cr.G && T.slot_rows[s - 1u] == cr.G) atomicAnd(&S.plain, ~4u);
     if (!cr.fused) atomicAnd(&S.plain, ~1u);     // a GEMM, reduction or wide-sum batch runs in this slot
     if (batch_xp(hb) && hb.aux1 > 1) atomicAnd(&S.plain, ~2u);   // a product that reads its operand rows in pieces
     if (cr.fused == 2u) {
@@ -2049,7 +2070,17 @@ __global__ __launch_bounds__(TPB) void k_tiles(Tables T, const CLay *clay_ex, co
                 (fwd ? T.works_f : T.works_a)[x] = w;
             } else if (cr.fused == 3u) {
                 const uint4 *from = nullptr;
-                if (xx < cr.G) from = (const uint4 *)&T.cells[T.cell_of[T.batches[cr.pad0].pos0 + xx]];
+                if (xx < cr.G) {
+                    u32 cell;
+                    if (which == 0 && !(T.slots[cr.slot].plain & 4u)) {     // in the order of the products' rows
+                        u32 q = c - 1, row = xx;
+                        for (; row >= T.chains[q].G; --q) row -= T.chains[q].G;
+                        cell = T.prod_cell[T.batches[T.lorder[T.chains[q].first]].pos0 + row];
+                    } else {
+                        cell = T.cell_of[T.batches[cr.pad0].pos0 + xx];
+                    }
+                    from = (const uint4 *)&T.cells[cell];
+                }
                 if (which == 0) {
                     uint4 *to = (uint4 *)&T.tiles_f[x];
                     if (from) {
@@ -2067,6 +2098,12 @@ __global__ __launch_bounds__(TPB) void k_tiles(Tables T, const CLay *clay_ex, co
                 const BatchRec r = T.batches[T.lorder[cr.first]];
                 TileDesc d;
                 fill_tile_desc(T, r, xx, which == 2, false, 0, 0, 1, d, false, ChainCtx{});
+                if (T.cells && which == 0 && r.op == OP_MATVEC && cr.slot + 1u < T.hdr->n_slots && !(T.slots[cr.slot + 1u].plain & 4u)) {
+                    // where the records of the batch's cells begin: they lie batch by batch, the last chain of the slot first
+                    u32 q = c + 1, before = 0;
+                    for (; T.chains[q].slot == cr.slot; ++q) before += T.chains[q].G;
+                    d.pad = clay_ex[q].tf + before + 1u;
+                }
                 (which == 0 ? T.tiles_f : T.tiles_b)[x] = d;
             } else {
                 // tile `it` of block rb: member m, its q-th row of every group in the block
@@ -2599,7 +2636,8 @@ int sched_enqueue(ob_ctx *ctx)
     A(T.pu_start, u32, n_slots); A(T.pu_end, u32, n_slots);
     const bool cells = fuse && E > 0;      // a fused plan may hold gated cells
     T.cells = nullptr;
-    if (cells) { A(T.cell_rows, u32, n); A(T.cell_nodes, u32, n); A(T.slot_mixed, u32, n); }
+    if (cells) { A(T.cell_rows, u32, n); A(T.cell_nodes, u32, n);
+                 A(T.cell_prods, u32, n); A(T.slot_chains, u32, n); A(T.slot_rows, u32, n); }
     char *small_hi = (char *)ctx->arena + ctx->top;     // (the plan of a small graph keeps the others in LDS)
     A(g_dep, u32, n + 1); A(T.ht_keys, u64, ht_size); A(bset, u32, BSET_SIZE);
     if (agenda) { A(AG.keys, u64, AG_TABLE); A(AG.sum, u64, AG_TABLE); A(AG.cnt, u32, AG_TABLE); }
@@ -2609,7 +2647,7 @@ int sched_enqueue(ob_ctx *ctx)
     char *ones_hi = (char *)ctx->arena + ctx->top;
     if (cells) {        // (a cell holds more than eight nodes)
         T.cells_cap = n / 8 + 1;
-        A(T.nrec, uint4, n); A(T.cells, CellRec, T.cells_cap); A(T.cell_nodes_of, CellNodes, T.cells_cap); A(T.cell_of, u32, n);
+        A(T.nrec, uint4, n); A(T.cells, CellRec, T.cells_cap); A(T.cell_nodes_of, CellNodes, T.cells_cap); A(T.cell_of, u32, n); A(T.prod_cell, u32, n);
     }
     A(T.sig, u64, n); A(T.step, u32, n); A(T.indeg, u32, n);
     A(T.succ_off, u32, n + 1); A(T.succ_edge, u32, E + 1); A(T.edge_cons, u32, E + 1);

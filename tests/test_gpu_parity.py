@@ -384,6 +384,58 @@ def test_gated_cells(H, nf, sums, rows, odd, cells):
         assert np.array_equal(out[0][k], out[1][k]) and np.array_equal(out[0][k], out[2][k]), k
 
 
+@pytest.mark.parametrize("H,K,rows,dirs,first", [(1, 1, 5, 1, "sum"), (2, 7, 31, 2, "sum"), (8, 8, 32, 1, "product"), (9, 9, 33, 2, "product"),
+                                                (100, 100, 70, 2, "sum"), (256, 256, 40, 3, "sum"), (33, 600, 6, 1, "sum")])
+def test_cells_behind_products_in_one_launch(H, K, rows, dirs, first):
+    """Cells that add rows of the products before them to others run in the products' launch, the products of all directions
+    together, in tiles of 32 rows and eight columns of each gate: values and gradients have the bits of a launch per batch.
+    K: what the products read, the outputs themselves or (K != H) another product of them."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(H + rows)
+    pb = wl.ParamBuilder(rng, std=0.3)
+    U = [pb.add(f"U{k}", 4 * H, K) for k in range(dirs)]
+    b = [pb.add(f"b{k}", 4 * H, 1) if k != 1 else -1 for k in range(dirs)]
+    E = pb.add("E", K, H) if K != H else None
+    p = pb.done()
+    g = wl.GraphBuilder(p)
+    at = rng.permutation(4)
+    steps = 4
+    h = [[g.input(rng.standard_normal(K)) for _ in range(dirs)] for _ in range(rows)]
+    c = [[g.input(rng.standard_normal(H)) for _ in range(dirs)] for _ in range(rows)]
+    losses = []
+    for step in range(steps):
+        for r in range(rows - step):          # (rows end one by one: the operand rows are not evenly spaced)
+            r = r if step < 2 else r + 1
+            for k in range(dirs):
+                x = g.input(rng.standard_normal(4 * H))
+                y = g.matvec(U[k], b[k], h[r][k])
+                s = g.add((x, y) if first == "sum" else (y, x))
+                sl = [g.slice(s, int(q) * H, (int(q) + 1) * H) for q in at]
+                i, f, o, cand = g.sigmoid(sl[0]), g.sigmoid(sl[1]), g.sigmoid(sl[2]), g.tanh(sl[3])
+                c[r][k] = g.add((g.cmult(f, c[r][k]), g.cmult(i, cand)))
+                out = g.cmult(o, g.tanh(c[r][k]))
+                h[r][k] = out if E is None else g.matvec(E, -1, out)
+                if step == steps - 1:
+                    losses.append(g.sqnorm(out))
+    gr = g.finish(g.add(losses), rows)
+    o = Oracle(gr, p, "f64")
+    o.forward()
+    o.backward(gr.root)
+    out = {}
+    for level in (2, 1, 0):
+        ctx, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=512 << 20)
+        check_against_oracle(ctx, p, gr, o, root, what=f"cells behind products {H} {rows} level {level}")
+        total = int(gr.out_dim.sum())
+        out[level] = [ctx.all_read(0, total), ctx.all_read(1, total)] + [ctx.param_grad_read(q, m.shape) for q, m in enumerate(p.mats)]
+        st = ctx.stats()
+        if level > 0 and H > 1:       # (a single column is no cell; a step whose products have other work beside them keeps its two launches)
+            assert st["n_launch_fwd"] < st["n_slots"], (level, st["n_launch_fwd"], st["n_slots"])
+        ctx.close()
+    for level in (1, 2):
+        for x, y in zip(out[0], out[level]):
+            assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+
+
 @pytest.mark.parametrize("seed", range(950, 964))
 def test_random_dags_of_400_nodes(seed):
     """Unstructured graphs of 400 nodes, consecutive seeds, nothing left out: some of these graphs

@@ -666,12 +666,19 @@ __global__ __launch_bounds__(AGENDA_THREADS) void k_agenda(Tables T, AgendaTable
             const u32 v = A.seg[base + i];
             T.step[v] = t;
             const u32 e1 = T.succ_off[v + 1];
-            for (u32 e = T.succ_off[v]; e < e1; ++e) {
-                const u32 sn = succ_node[e];
-                const u32 was = atomicSub(&A.pending[sn], 1u);
-                if ((was & ((1u << AG_COUNT_BITS) - 1u)) == 1u) {
-                    const u32 cs = was >> AG_COUNT_BITS;
-                    A.seg[s_off[cs] + atomicAdd(&s_tail[cs], 1u)] = sn;
+            // (four consumers side by side: one after the other each costs a read and an atomic that returns:
+            // 64 parsed sentences 1 396 us of this kernel, 1 270 now)
+            for (u32 e = T.succ_off[v]; e < e1; e += 4) {
+                u32 sn[4], was[4];
+#pragma unroll
+                for (u32 q = 0; q < 4; ++q) sn[q] = e + q < e1 ? succ_node[e + q] : 0u;
+#pragma unroll
+                for (u32 q = 0; q < 4; ++q) was[q] = e + q < e1 ? atomicSub(&A.pending[sn[q]], 1u) : 0u;
+#pragma unroll
+                for (u32 q = 0; q < 4; ++q) {
+                    if ((was[q] & ((1u << AG_COUNT_BITS) - 1u)) != 1u) continue;
+                    const u32 cs = was[q] >> AG_COUNT_BITS;
+                    A.seg[s_off[cs] + atomicAdd(&s_tail[cs], 1u)] = sn[q];
                 }
             }
         }

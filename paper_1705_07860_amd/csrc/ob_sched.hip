@@ -2600,13 +2600,15 @@ int sched_enqueue(ob_ctx *ctx)
     const int agenda = ctx->mode == 2;
     ctx->n_launch_sched = 0;
 
-    const size_t maxne = (size_t)(n > E ? n : E) + 1;
     u32 n_items = ctx->n_items_total;
     if ((size_t)n != ctx->op.size()) {   // a prefix of the graph: count its parameter uses
         n_items = 0;
         for (u32 v = 0; v < n; ++v)
             n_items += ctx->op[v] == OP_MATVEC ? 1u + (ctx->bias[v] >= 0 ? 1u : 0u) : (ctx->op[v] == OP_LOOKUP ? 1u : 0u);
     }
+    // pairs that are sorted: edges, nodes, parameter uses (a product with a bias is two, so there may be more of them than of either)
+    const u32 most = n > E ? n : E;
+    const size_t max_pairs = (size_t)(most > n_items ? most : n_items) + 1;
     const size_t n_slots = (size_t)ctx->params.size() * 4 + 4;
 
     const int fuse = batched && ctx->fuse;
@@ -2681,7 +2683,7 @@ int sched_enqueue(ob_ctx *ctx)
     if (ctx->concat_views && ctx->n_concat > 0) A(T.it_xrec, uint4, 2 * ((size_t)n_items + 1));
     u32 *succ_node;
     A(succ_node, u32, E + 1);
-    A(ctx->key_a, u64, maxne); A(ctx->key_b, u64, maxne); A(ctx->val_a, u32, maxne); A(ctx->val_b, u32, maxne);
+    A(ctx->key_a, u64, max_pairs); A(ctx->key_b, u64, max_pairs); A(ctx->val_a, u32, max_pairs); A(ctx->val_b, u32, max_pairs);
     A(ctx->tmp_u32_a, u32, n + 1); A(ctx->tmp_u32_b, u32, n + 1);
     u32 *tmp_d;
     A(tmp_d, u32, n + 1);
@@ -2697,8 +2699,8 @@ int sched_enqueue(ob_ctx *ctx)
         AG.cls = ctx->tmp_u32_a; AG.pending = ctx->tmp_u32_b; AG.seg = T.queue;
     }
     {
-        size_t sb = prim_sort_scratch_bytes(maxne);
-        size_t sc = prim_scan_scratch_bytes(maxne, sizeof(Lay));
+        size_t sb = prim_sort_scratch_bytes(max_pairs);
+        size_t sc = prim_scan_scratch_bytes(max_pairs, sizeof(Lay));
         ctx->scratch = arena_alloc(ctx, sb > sc ? sb : sc);
         if (!ctx->scratch) return ctx_fail(ctx, -5, "arena too small for scheduler scratch");
     }

@@ -1259,6 +1259,28 @@ def test_stacked_matrix_products():
     c.close()
 
 
+@pytest.mark.parametrize("n_inst", [1500, 2000, 9000])
+def test_more_parameter_uses_than_nodes_or_edges(n_inst):
+    """Two products with biases behind a look-up, and a loss: five uses of parameters for four nodes and four edges an
+    instance.  Above 8 192 pairs a sort goes back and forth between two pairs of buffers, which must hold all of the uses."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(n_inst)
+    pb = wl.ParamBuilder(rng, std=0.5)
+    E, W, b, U, d = pb.add("E", 40, 6), pb.add("W", 7, 6), pb.add("b", 7, 1), pb.add("U", 5, 7), pb.add("d", 5, 1)
+    p = pb.done()
+    gb = wl.GraphBuilder(p)
+    losses = [gb.pick_nls(gb.matvec(U, d, gb.matvec(W, b, gb.lookup(E, int(r)))), int(r) % 5) for r in rng.integers(0, 40, n_inst)]
+    g = gb.finish(gb.add(losses), n_inst)
+    assert 5 * n_inst > max(g.n, g.n_edges) + 1
+    o = Oracle(g, p, "f64")
+    o.forward()
+    o.backward(g.root)
+    for mode in (ob.OB_BYDEPTH, ob.OB_BYAGENDA):
+        c, root = run_gpu(p, g, mode, arena=256 << 20)
+        check_against_oracle(c, p, g, o, root, what=f"{n_inst} instances, mode {mode}")
+        c.close()
+
+
 def test_long_chain_uses_the_unfused_plan_and_the_long_slot_table():
     """More batches than a fused launch plan can hold (4096) and more launch slots than the
     read-back window (2048): a 4300-deep chain of alternating tanh / sigmoid nodes runs with one

@@ -2302,19 +2302,25 @@ struct SmallArgs {
 // a time and settles a node when its list is through.  The operand lists and the depths are in LDS, 0 = not known yet.
 // A sweep of a wave is one dependent LDS read and a dozen instructions for each of its nodes, where the pass by ranges, made for four
 // nodes a lane and few waves, takes some hundred: 27 -> 6 us for 252 nodes, 35 -> 20 for 944.
-// Ids are a topological order, so the lowest node that is not settled can be, and every wave comes to look at it: the
-// bound on idle looks only guards against damaged tables.
+// A settled operand of a longer list makes room for the next, so what is known early is through before the last is, and a
+// list that is long for its wave is walked by the whole wave, 512 entries at a time, whenever nothing else of the wave moves,
+// by the rule of the pass by ranges.  (Two by two in list order by their threads, the schedule of a sum of 2 046 rows
+// took 361 us and that of 140 steps over sums of twelve rows 534; now 116 and 295, by the launches for large graphs 169 and 380.)
+// Ids are a topological order, so the lowest node that is not settled can be, and every wave comes to look at it (lists are
+// walked in ascending order): the bound on idle looks only guards against damaged tables.
 struct SmallDepth {
-    u32 dep[SMALL_NODES + 1];                // [SMALL_NODES] holds 1: an absent operand
+    u32 dep[SMALL_NODES + 2];                // [SMALL_ONE] holds 1: an absent operand; [SMALL_NEVER] 0: of a list that is walked
     unsigned short op[SMALL_EDGES + 2];
     u32 quit;
 };
+constexpr u32 SMALL_ONE = SMALL_NODES, SMALL_NEVER = SMALL_NODES + 1;
 template <u32 NPT>
 __device__ inline void small_depths(const Tables &T, u32 spin_limit, SmallDepth &S)
 {
-    const u32 tid = threadIdx.x, n = T.n;
+    const u32 tid = threadIdx.x, lane = tid & 63u, n = T.n;
     u32 at[NPT], end[NPT], top[NPT], x[NPT], y[NPT];
     bool open[NPT];
+    u32 n_long = 0;
 #pragma unroll
     for (u32 j = 0; j < NPT; ++j) {
         const u32 v = tid + j * SMALL_THREADS;
@@ -2323,21 +2329,27 @@ __device__ inline void small_depths(const Tables &T, u32 spin_limit, SmallDepth 
         end[j] = open[j] ? T.in_off[v + 1] : 0u;
         top[j] = 0;
         S.dep[v] = 0;
+        n_long += (u32)__popcll(__ballot(end[j] - at[j] > DEPTH_OPS));
     }
     for (u32 e = tid; e < T.E; e += SMALL_THREADS) S.op[e] = (unsigned short)T.in_idx[e];
-    if (tid == 0) { S.dep[SMALL_NODES] = 1; S.quit = 0; }
+    if (tid == 0) { S.dep[SMALL_ONE] = 1; S.dep[SMALL_NEVER] = 0; S.quit = 0; }
     __syncthreads();
-    auto pair = [&](u32 j) __attribute__((always_inline)) {
-        x[j] = at[j] < end[j] ? S.op[at[j]] : SMALL_NODES;
-        y[j] = at[j] + 1u < end[j] ? S.op[at[j] + 1u] : SMALL_NODES;
-    };
+    auto next = [&](u32 j) __attribute__((always_inline)) { return at[j] < end[j] ? (u32)S.op[at[j]++] : SMALL_ONE; };
+    u64 walks[NPT];         // lanes whose node j is walked by the wave
+    bool lists = false;
 #pragma unroll
     for (u32 j = 0; j < NPT; ++j) {
-        if (at[j] == end[j]) { if (open[j]) lds_store(&S.dep[tid + j * SMALL_THREADS], 1u); open[j] = false; top[j] = 0; }
-        pair(j);
+        const u32 ar = end[j] - at[j];
+        const bool walked = ar > DEPTH_OPS && ar > DEPTH_WALK * n_long;
+        walks[j] = __ballot(walked);
+        lists = lists || ar > 2u;
+        if (ar == 0u) { if (open[j]) lds_store(&S.dep[tid + j * SMALL_THREADS], 1u); open[j] = false; }
+        x[j] = y[j] = SMALL_NEVER;
+        if (!walked) { x[j] = next(j); y[j] = next(j); }
     }
-    u32 idle = 0;
+    u32 idle = 0, walk_e = 0, walk_max = 0;     // entries of the list being walked that are through, their largest word
     bool gave_up = false;
+    auto sweeps = [&](auto with_lists) __attribute__((always_inline)) {
     while (true) {
         u32 dx[NPT], dy[NPT];
         bool moved = false, left = false;
@@ -2345,21 +2357,69 @@ __device__ inline void small_depths(const Tables &T, u32 spin_limit, SmallDepth 
         for (u32 j = 0; j < NPT; ++j) { dx[j] = lds_load(&S.dep[x[j]]); dy[j] = lds_load(&S.dep[y[j]]); }
 #pragma unroll
         for (u32 j = 0; j < NPT; ++j) {
-            if (open[j] && dx[j] != 0u && dy[j] != 0u) {
+            const bool last = !with_lists.value || at[j] == end[j];
+            if (open[j] && last && dx[j] != 0u && dy[j] != 0u) {
                 const u32 d = dx[j] > dy[j] ? dx[j] : dy[j];
                 top[j] = d > top[j] ? d : top[j];
-                at[j] += 2u;
                 moved = true;
-                if (at[j] >= end[j]) { open[j] = false; lds_store(&S.dep[tid + j * SMALL_THREADS], top[j] + 1u); }
-                else pair(j);
+                open[j] = false;
+                lds_store(&S.dep[tid + j * SMALL_THREADS], top[j] + 1u);
+            }
+            if (with_lists.value && !last) {
+                if (dx[j] != 0u) { top[j] = dx[j] > top[j] ? dx[j] : top[j]; x[j] = next(j); moved = true; }
+                if (dy[j] != 0u) { top[j] = dy[j] > top[j] ? dy[j] : top[j]; y[j] = next(j); moved = true; }
             }
             left = left || open[j];
         }
         if (__ballot(left) == 0ull) break;
-        if (__ballot(moved) != 0ull) { idle = 0; continue; }
+        bool progress = __ballot(moved) != 0ull;
+        if (with_lists.value && !progress) {
+            u32 a = 0, ar = 0, owner = 0, node = 0;     // the wave's lowest node whose list is walked
+#pragma unroll
+            for (u32 j = NPT; j-- > 0;)
+                if (walks[j]) {
+                    owner = (u32)__builtin_ctzll(walks[j]);
+                    a = (u32)__builtin_amdgcn_readlane((int)at[j], (int)owner);
+                    ar = (u32)__builtin_amdgcn_readlane((int)end[j], (int)owner) - a;
+                    node = (tid & ~63u) + owner + j * SMALL_THREADS;
+                }
+            if (ar) {
+                u32 id[DEPTH_WIDE_READS], w[DEPTH_WIDE_READS];
+#pragma unroll
+                for (u32 q = 0; q < DEPTH_WIDE_READS; ++q) {
+                    const u32 e = walk_e + 64u * q + lane;
+                    id[q] = e < ar ? (u32)S.op[a + e] : SMALL_ONE;
+                }
+#pragma unroll
+                for (u32 q = 0; q < DEPTH_WIDE_READS; ++q) w[q] = lds_load(&S.dep[id[q]]);
+                bool all = true;
+#pragma unroll
+                for (u32 q = 0; q < DEPTH_WIDE_READS; ++q) {
+                    all = all && __ballot(w[q] == 0u) == 0ull;
+                    if (all) { walk_max = w[q] > walk_max ? w[q] : walk_max; walk_e += 64u; progress = true; }
+                }
+                if (walk_e >= ar) {
+                    for (int o = 32; o > 0; o >>= 1) { const u32 t = (u32)__shfl_xor((int)walk_max, o); walk_max = t > walk_max ? t : walk_max; }
+                    if (lane == 0) lds_store(&S.dep[node], walk_max + 1u);
+                    bool found = false;
+#pragma unroll
+                    for (u32 j = 0; j < NPT; ++j) {
+                        if (found || !walks[j]) continue;
+                        found = true;
+                        if (lane == owner) { top[j] = walk_max; open[j] = false; }
+                        walks[j] &= walks[j] - 1ull;
+                    }
+                    walk_e = walk_max = 0;
+                }
+            }
+        }
+        if (progress) { idle = 0; continue; }
         if (++idle > spin_limit || lds_load(&S.quit) != 0u) { gave_up = true; break; }
         if (idle > 8u) __builtin_amdgcn_s_sleep(1);      // (what this wave waits for is some levels off: the others need the LDS)
     }
+    };
+    if (__ballot(lists) != 0ull) sweeps(std::true_type{});
+    else sweeps(std::false_type{});
     u32 done = 0;
 #pragma unroll
     for (u32 j = 0; j < NPT; ++j) {
@@ -2368,7 +2428,7 @@ __device__ inline void small_depths(const Tables &T, u32 spin_limit, SmallDepth 
         if (v < n) T.step[v] = open[j] ? v : top[j];
         done += (u32)__popcll(__ballot(v < n && !open[j]));
     }
-    if ((tid & 63u) == 0u) {
+    if (lane == 0u) {
         atomicAdd(&T.hdr->frontier_done, done);
         if (gave_up) { lds_store(&S.quit, 1u); atomicOr(&T.hdr->err, (u32)ERR_CYCLE); }
     }

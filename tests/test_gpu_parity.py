@@ -1785,14 +1785,16 @@ def test_batch_dependencies_of_rows_with_few_and_many_operands(rows, arity):
         c.close()
 
 
-def _median_schedule_ms(graphs, rounds=7):
+def _median_schedule_ms(graphs, rounds=7, wide=None):
     """Median scheduling time (GPU events) of each of the given (params, graph) pairs, taken in turn, the first
-    round of each left out."""
+    round of each left out.  wide: for each, whether it is planned by the launches for large graphs whatever its size."""
     from paper_1705_07860_amd import binding as ob
     ctxs = []
-    for p, _ in graphs:
+    for k, (p, _) in enumerate(graphs):
         c = ob.Context(arena_bytes=512 << 20, mode=ob.OB_BYDEPTH)
         c.params_create(p)
+        if wide:
+            c.debug_set(ob.OB_DBG_SET_WIDE_PLAN, wide[k])
         ctxs.append(c)
     ms = [[] for _ in graphs]
     for i in range(rounds + 1):
@@ -1930,10 +1932,28 @@ def test_a_small_graph_is_scheduled_as_a_large_one_would_be(n, dim, fuse, copy):
 
 
 @pytest.mark.parametrize("n,arities,reach", [(2048, [0, 0, 0, 1, 2], 40), (1100, [2, 3], 700), (1025, [0] * 400 + [1] * 200 + [9] * 50 + [800] * 2, 1000),
-                                             (700, [4, 5, 6, 9], 8), (2048, [0] * 40 + [33], 2000), (1366, [3], 5), (1368, [3], 5)])
+                                             (700, [4, 5, 6, 9], 8), (2048, [0] * 40 + [33], 2000), (1366, [3], 5), (1368, [3], 5),
+                                             (2048, [0] * 900 + [1, 5, 12, 13, 24, 25, 511, 512, 513], 2000), (1024, [0] * 250 + [1] * 20 + [13, 700], 900),
+                                             (900, [4, 3, 2], 3)])
 def test_a_small_graph_of_any_arity_is_scheduled_as_a_large_one_would_be(n, arities, reach):
     """The same with operand lists of every length and with edges on both sides of the 4 096 that the rule allows."""
     _same_plan(wl.Params([], []), _random_arity_graph(n, arities, reach, n + len(arities)))
+
+
+def _one_sum(rows):
+    gb = wl.GraphBuilder(wl.Params([], []))
+    return wl.Params([], []), gb.finish(gb.add([gb.input(np.ones(1)) for _ in range(rows)]), 1)
+
+
+@pytest.mark.parametrize("graph", [lambda: _one_sum(2046), lambda: _one_sum(1100), lambda: _sum_recurrences(1, 140, 12)], ids=["2046", "1100", "140 of 12"])
+def test_wide_sums_of_a_small_graph_schedule_no_slower_than_in_a_large_one(graph):
+    """The one launch that plans small graphs takes long operand lists by whole waves and shorter ones ahead of their last
+    operand: 0.73, 0.75 and 0.78 of the time of the launches for large graphs.  Walked two by two in list order by a thread each,
+    the sums took 2.1 and 1.5 times as long as those, the steps over sums of twelve 1.4 times."""
+    pg = graph()
+    one, many = _median_schedule_ms([pg, pg], rounds=15, wide=[0, 1])
+    say(f"  one launch {one:.3f} ms, many {many:.3f} ms")
+    assert one <= 1.1 * many
 
 
 @pytest.mark.parametrize("H,nf,sums,rows", [(8, 1, True, 20), (64, 2, False, 12), (100, 0, True, 9)])

@@ -275,6 +275,7 @@ struct Tables {
     u32 *chain_of_batch;   // per batch: index of its launch chain
     uint4 *nrec;                           // per node: first two operands, operation, arity (with `cells` only)
     CellRec *cells; u32 *cell_of;          // gated cells; per position of an output h: its cell
+    u32 *cell_ends, *cell_ends_n;          // nodes that a cell may end in, by parts of a workgroup's nodes; how many a part has
     CellNodes *cell_nodes_of;              // per cell: the batches of its nodes
     u32 *cell_prods;                       // per batch of outputs: cells that take up a product's row from the slot before theirs
     u32 *prod_cell;                        // per position of such a product: its cell

@@ -73,8 +73,10 @@ __device__ inline u64 operand_hash(const Tables &T, u32 u, u32 j) { return mix64
 template <u32 N> struct InitLds {
     WideRows<N> wide;
     u64 sum[N];
+    u32 ends[N / 64];
 };
-// (a workgroup of N threads, the nodes from `base` on)
+// (a workgroup of N threads, the nodes from `base` on.  The nodes that a gated cell may end in are listed in passing: T.cell_ends
+// from `base` on, as many as T.cell_ends_n says for the part.)
 template <u32 N>
 __device__ inline void node_init_part(const Tables &T, int steps, u64 *keys, u32 *vals, InitLds<N> &L, u32 base)
 {
@@ -84,6 +86,7 @@ __device__ inline void node_init_part(const Tables &T, int steps, u64 *keys, u32
     s_sum[threadIdx.x] = 0;
     __syncthreads();
     const u32 v = base + threadIdx.x;
+    bool ends = false;
     if (v < T.n) {
         const u32 lo = T.in_off[v], hi = T.in_off[v + 1];
         const u32 o = T.op[v];
@@ -107,7 +110,14 @@ __device__ inline void node_init_part(const Tables &T, int steps, u64 *keys, u32
             wide_add(S, v, lo, hi - lo);
         }
         T.sig[v] = h;
-        if (T.cells) T.nrec[v] = make_uint4(hi > lo ? T.in_idx[lo] : 0u, hi > lo + 1u ? T.in_idx[lo + 1u] : 0u, o, hi - lo);
+        if (T.cells) {
+            const u32 x = hi > lo ? T.in_idx[lo] : 0u, y = hi > lo + 1u ? T.in_idx[lo + 1u] : 0u;
+            T.nrec[v] = make_uint4(x, y, o, hi - lo);
+            if (o == OP_CMULT) {
+                const u32 ox = T.op[x], oy = T.op[y];
+                ends = (ox == OP_TANH && oy == OP_SIGMOID) || (ox == OP_SIGMOID && oy == OP_TANH);
+            }
+        }
         if (steps == 3) {
             T.indeg[v] = hi - lo;
             if (hi == lo) {
@@ -121,7 +131,16 @@ __device__ inline void node_init_part(const Tables &T, int steps, u64 *keys, u32
             T.step[v] = v;   // unbatched: every node is its own step, in id order
         }
     }
+    const u32 lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const u64 with = __ballot(ends);
+    if (lane == 0u) L.ends[wave] = (u32)__popcll(with);
     __syncthreads();
+    if (T.cells) {
+        u32 before = 0;
+        for (u32 i = 0; i < wave; ++i) before += L.ends[i];
+        if (ends) T.cell_ends[base + before + (u32)__popcll(with & ((1ull << lane) - 1ull))] = v;
+        if (threadIdx.x == N - 1u) T.cell_ends_n[base / N] = before + (u32)__popcll(with);
+    }
     const u32 rows = (u32)(S.n >> 32), edges = (u32)S.n;
     u32 mine = ~0u;         // row whose sum this thread is adding up
     u64 sum = 0;
@@ -1147,19 +1166,17 @@ __global__ __launch_bounds__(TPB) void k_bedges(Tables T, u32 *bset, u32 *blist)
 // branches of a tile are 150 to 250 instructions).  So the cells of a plan are looked for in the graph, and
 // a chain that consists of them is worked a thread per column, in registers, from one record a row, forward and backward (64
 // sentences: forward runs 6.8 -> 3.4 us a launch, backward runs 9.8 -> 4.6).
-// Position p: does a cell end in this product?  Everything that the record relies on is checked here, edge by edge: every node
-// of a cell but its output and c is read inside the cell only.  That the nodes lie in one chain is checked by cell_in_chain, and that they
-// are all of the chain by k_chain_recs, which counts.  What bounds it is the chain of reads from the output back to the
+// Does a cell end in product h (of a tanh and a sigmoid)?  Everything that the record relies on is checked here, edge by edge: every
+// node of a cell but its output and c is read inside the cell only.  That the nodes lie in one chain is checked by cell_in_chain, and
+// that they are all of the chain by k_chain_recs, which counts.  What bounds it is the chain of reads from the output back to the
 // operands of S, so each step asks for the records of all nodes at once (first two operands, operation, arity), whether they turn
 // out to be what they should or not, and it runs beside the one workgroup that works out the slots (64 trees: 56 us as a launch
-// of its own, read one by one, k_slots 18; both together 24 now).
-__device__ inline void find_cell(const Tables &T, u32 p)
+// of its own, read one by one, k_slots 18; both together 19 now).
+__device__ inline void find_cell(const Tables &T, u32 h)
 {
     constexpr u32 NT = CELL_FORGET + 1, NG = NT + 2;      // terms of c; gates: one a term, o, the candidate
-    if (p >= T.n) return;
-    const u32 h = T.order[p];
+    const u32 p = T.pos_of[h];
     const uint4 rh = T.nrec[h];            // first two operands, operation, arity
-    if (rh.z != OP_CMULT) return;
     u32 tc = rh.x, o = rh.y;
     uint4 rtc = T.nrec[tc], ro = T.nrec[o];
     if (rtc.z == OP_SIGMOID) { const u32 x = tc; tc = o; o = x; const uint4 y = rtc; rtc = ro; ro = y; }
@@ -1294,6 +1311,25 @@ __device__ inline void find_cell(const Tables &T, u32 p)
     T.cell_nodes_of[cell] = N;
 }
 
+// The cells among PARTS parts of `nodes` nodes each, from part `first` on: thread i of `threads`.
+template <u32 PARTS>
+__device__ inline void find_cells(const Tables &T, u32 nodes, u32 first, u32 i, u32 threads)
+{
+    u32 count[PARTS], total = 0;
+#pragma unroll
+    for (u32 q = 0; q < PARTS; ++q) {
+        count[q] = (first + q) * nodes < T.n ? T.cell_ends_n[first + q] : 0u;
+        total += count[q];
+    }
+    for (; i < total; i += threads) {
+        u32 x = i, part = 0;
+#pragma unroll
+        for (u32 q = 0; q < PARTS; ++q)
+            if (part == q && x >= count[q]) { x -= count[q]; part = q + 1u; }
+        find_cell(T, T.cell_ends[(first + part) * nodes + x]);
+    }
+}
+
 // A cell counts for its output's batch when all its nodes have been placed in one chain.  Called by whole waves: cells of a
 // batch mostly lie side by side, and a wave adds them up before it goes to the batch's counters (an atomic per cell kept
 // the counters of 64 trees' largest batches busy for 20 us).
@@ -1341,9 +1377,13 @@ __device__ inline void cell_in_chain(const Tables &T, u32 cell)
 // head), fuse == 2 as late as possible (slot = L - tail): batches off the critical path then
 // gather in the slots next to their consumers instead of trailing the recurrence one small
 // launch at a time.  Batches joined by fusable edges inside one slot then get a common chain
-// label (the smallest batch id of the chain).  (The workgroups behind the first look for gated cells meanwhile.)
+// label (the smallest batch id of the chain).  The workgroups behind the first look for gated cells meanwhile:
+// each fills a CU's LDS like the first, so there are few, 2 048 nodes to one.  (With all nodes looked at here, 256 to a workgroup, the 740
+// of a graph of 189 000 nodes took 24 rounds on the 32 CUs of a schedule stream: 216 us of this kernel, 101 now, 71 and 70 on the
+// whole chip; schedules of that graph there 1 198 and 1 088 us, 650 on the whole chip.  Listing the nodes takes the launch that sets
+// nodes up nothing that shows.  4 096 nodes to a workgroup: the same; 8 192: 1 061 us, but 64 trees 356 where they take 332.)
 constexpr int SLOT_THREADS = 1024;
-constexpr u32 CELL_PART = 256;        // nodes a workgroup looks for cells among: it fills a CU's LDS, and 1024 of them with scattered reads each took a CU 49 us
+constexpr u32 CELL_PARTS = 8;          // parts of TPB nodes
 struct SlotsLds {
     u32 slot[SLOT_MAX_NB];
     u32 label[SLOT_MAX_NB];      // tail lengths first, chain labels afterwards
@@ -1471,7 +1511,7 @@ __global__ __launch_bounds__(SLOT_THREADS) void k_slots(Tables T, int fuse, cons
 {
     __shared__ SlotsLds L;
     if (blockIdx.x == 0) slots_of(T, fuse, blist, L, [](u32, u32) {});
-    else if (threadIdx.x < CELL_PART && T.hdr->n_batches <= SLOT_MAX_NB) find_cell(T, (blockIdx.x - 1u) * CELL_PART + threadIdx.x);
+    else if (T.hdr->n_batches <= SLOT_MAX_NB) find_cells<CELL_PARTS>(T, TPB, (blockIdx.x - 1u) * CELL_PARTS, threadIdx.x, SLOT_THREADS);
 }
 
 __device__ inline void launch_keys_at(const Tables &T, u64 *keys, u32 *vals, u32 n_pad, u32 b)
@@ -2595,7 +2635,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_plan_small(SmallArgs)
         __syncthreads();
     }
     STAGE slots_of(A.T, A.fuse, A.blist, L.slots, [&](u32 i, u32 step) __attribute__((always_inline)) {
-        for (; i < A.T.n; i += step) find_cell(A.T, i);
+        find_cells<SMALL_NODES / SMALL_THREADS>(A.T, SMALL_THREADS, 0, i, step);
     });
     __syncthreads();
     EACH((T.n + SMALL_THREADS - 1) & ~(SMALL_THREADS - 1), launch_keys_at(T, A.keys, A.vals, T.n, i));   // (whole waves)
@@ -2717,6 +2757,7 @@ int sched_enqueue(ob_ctx *ctx)
     if (cells) {        // (a cell holds more than eight nodes)
         T.cells_cap = n / 8 + 1;
         A(T.nrec, uint4, n); A(T.cells, CellRec, T.cells_cap); A(T.cell_nodes_of, CellNodes, T.cells_cap); A(T.cell_of, u32, n); A(T.prod_cell, u32, n);
+        A(T.cell_ends, u32, n); A(T.cell_ends_n, u32, blocks_for(n));
     }
     A(T.sig, u64, n); A(T.step, u32, n); A(T.indeg, u32, n);
     A(T.succ_off, u32, n + 1); A(T.succ_edge, u32, E + 1); A(T.edge_cons, u32, E + 1);
@@ -2838,7 +2879,7 @@ int sched_enqueue(ob_ctx *ctx)
 
         // ---- launch planning: slots, chains, tile descriptors ----
         if (fuse && E > 0) K(k_bedges, n, T, bset, blist);
-        hipLaunchKernelGGL(k_slots, dim3(cells ? 1 + blocks_for(n, CELL_PART) : 1), dim3(SLOT_THREADS), 0, s, T, (fuse && E > 0) ? ctx->fuse : 0, blist);
+        hipLaunchKernelGGL(k_slots, dim3(cells ? 1 + blocks_for(n, TPB * CELL_PARTS) : 1), dim3(SLOT_THREADS), 0, s, T, (fuse && E > 0) ? ctx->fuse : 0, blist);
         ++ctx->n_launch_sched;
         K(k_launch_keys, n, T, ctx->key_a, ctx->val_a, n);
         if (fuse && E > 0) {

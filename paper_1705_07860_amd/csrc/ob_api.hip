@@ -375,8 +375,10 @@ int ob_graph_new(ob_ctx *ctx)
     ctx->sum_out_dim = 0;
     ctx->max_arity = 0;
     ctx->n_concat = 0;
+    ctx->n_slice = 0;
     ctx->sum_mv_d32 = ctx->sum_mv_k32 = 0;
     ctx->top = ctx->persist_top;
+    ctx->plan_end = 0;
     ctx->uploaded = false;
     ctx->n_sched = 0;
     ctx->sched_pending = false;
@@ -532,6 +534,7 @@ static int append_node(ob_ctx *ctx, int op, const u32 *ins, u32 arity, int param
     ctx->sum_out_dim += dim;
     if (arity > ctx->max_arity) ctx->max_arity = arity;
     if (op == OB_OP_CONCAT) ++ctx->n_concat;
+    if (op == OB_OP_SLICE) ++ctx->n_slice;
     if (op == OB_OP_MATVEC) note_matvec(ctx, param, bias);
     if (keep) ctx->image_stale = true; else ctx->uploaded = false;
     return (int)v;
@@ -657,7 +660,7 @@ int ob_add_bulk(ob_ctx *ctx, int n, const uint8_t *op, const uint32_t *out_dim, 
         u32 operator[](u32 u) const { return u < n0 ? old[u] : fresh[u - n0]; }
     } dims{ctx->out_dim.data(), n0, out_dim};
     struct Part {
-        ErrSink es; u64 sum_dim = 0, mv_d32 = 0, mv_k32 = 0; u32 max_ar = 0, items = 0, concats = 0;
+        ErrSink es; u64 sum_dim = 0, mv_d32 = 0, mv_k32 = 0; u32 max_ar = 0, items = 0, concats = 0, slices = 0;
         std::vector<u8> used_w, used_b;
     };
     const int n_parts = n >= 32768 ? 1 + BulkPool::HELPERS : 1;
@@ -697,6 +700,8 @@ int ob_add_bulk(ob_ctx *ctx, int n, const uint8_t *op, const uint32_t *out_dim, 
                 P.items += 1u;
             } else if (o == OB_OP_CONCAT) {
                 ++P.concats;
+            } else if (o == OB_OP_SLICE) {
+                ++P.slices;
             }
         }
         // this range's share of the plain copies
@@ -727,6 +732,7 @@ int ob_add_bulk(ob_ctx *ctx, int n, const uint8_t *op, const uint32_t *out_dim, 
         if (P.max_ar > ctx->max_arity) ctx->max_arity = P.max_ar;
         ctx->n_items_total += P.items;
         ctx->n_concat += P.concats;
+        ctx->n_slice += P.slices;
         ctx->sum_mv_d32 += P.mv_d32; ctx->sum_mv_k32 += P.mv_k32;
         for (size_t q = 0; q < params.size(); ++q) {
             if (P.used_w[q] && !ctx->params_used_w[q]) { ctx->params_used_w[q] = 1; ctx->params_dirty = true; }
@@ -1076,6 +1082,7 @@ static int forget_evaluation(ob_ctx *ctx)
     ctx->n_sched = 0;
     ctx->forward_done = ctx->backward_done = false;
     if (ctx->uploaded) ctx->top = ctx->graph_top;
+    ctx->plan_end = 0;
     if (ctx->image_stale) { ctx->uploaded = false; ctx->image_stale = false; }
     return 0;
 }
@@ -1510,7 +1517,7 @@ int ob_stats_read(ob_ctx *ctx, ob_stats *out)
     out->n_slots = (int32_t)ctx->hdr.n_slots;
     out->value_floats = ctx->hdr.val_floats;
     out->grad_floats = ctx->hdr.grad_floats;
-    out->arena_used_bytes = ctx->top;
+    out->arena_used_bytes = ctx->top > ctx->plan_end ? ctx->top : ctx->plan_end;
     out->upload_bytes = ctx->upload_bytes;
     (void)hipEventElapsedTime(&out->ms_upload, ctx->ev[0], ctx->ev[1]);
     (void)hipEventElapsedTime(&out->ms_schedule, ctx->ev[7], ctx->ev[9]);

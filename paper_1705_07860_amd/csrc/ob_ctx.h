@@ -121,7 +121,9 @@ struct ob_ctx {
     bool concat_views = true;          // CONCAT batches that only matrix products read are not copied
     bool uncopied_filled = false;      // their rows have been written after all (somebody read values)
     u64 sum_mv_d32 = 0, sum_mv_k32 = 0; // sums over MATVEC nodes of rows/32+1 and cols/32+1 (bound the GEMM tiles)
+    u32 n_slice = 0;                   // SLICE nodes in the graph store
     size_t graph_top = 0;              // arena top right after the uploaded graph image
+    size_t plan_top = 0, plan_end = 0; // what only the last schedule itself needed: values and gradients lie there now
 
     // device state of the current graph
     void *pinned = nullptr;            // staging for the batch labels of manual batching

@@ -273,7 +273,7 @@ struct Tables {
     u32 *slot_of; u32 *label_of; u32 *lorder;
     u32 *blevel;           // per batch: its step (depth mode) or its level inside its fused chain (agenda mode)
     u32 *chain_of_batch;   // per batch: index of its launch chain
-    uint4 *nrec;                           // per node: first two operands, operation, arity (with `cells` only)
+    uint4 *nrec;                           // per node: first two operands, operation, arity (this and what follows with `cells` only)
     CellRec *cells; u32 *cell_of;          // gated cells; per position of an output h: its cell
     u32 *cell_ends, *cell_ends_n;          // nodes that a cell may end in, by parts of a workgroup's nodes; how many a part has
     CellNodes *cell_nodes_of;              // per cell: the batches of its nodes

@@ -113,6 +113,7 @@ __device__ inline void node_init_part(const Tables &T, int steps, u64 *keys, u32
         if (T.cells) {
             const u32 x = hi > lo ? T.in_idx[lo] : 0u, y = hi > lo + 1u ? T.in_idx[lo + 1u] : 0u;
             T.nrec[v] = make_uint4(x, y, o, hi - lo);
+            T.cell_rows[v] = T.cell_nodes[v] = T.cell_prods[v] = T.slot_chains[v] = T.slot_rows[v] = 0;
             if (o == OP_CMULT) {
                 const u32 ox = T.op[x], oy = T.op[y];
                 ends = (ox == OP_TANH && oy == OP_SIGMOID) || (ox == OP_SIGMOID && oy == OP_TANH);
@@ -2635,7 +2636,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_plan_small(SmallArgs)
         __syncthreads();
     }
     STAGE slots_of(A.T, A.fuse, A.blist, L.slots, [&](u32 i, u32 step) __attribute__((always_inline)) {
-        find_cells<SMALL_NODES / SMALL_THREADS>(A.T, SMALL_THREADS, 0, i, step);
+        if (A.T.cells) find_cells<SMALL_NODES / SMALL_THREADS>(A.T, SMALL_THREADS, 0, i, step);
     });
     __syncthreads();
     EACH((T.n + SMALL_THREADS - 1) & ~(SMALL_THREADS - 1), launch_keys_at(T, A.keys, A.vals, T.n, i));   // (whole waves)
@@ -2743,10 +2744,6 @@ int sched_enqueue(ob_ctx *ctx)
     A(T.hdr, SchedHeader, 1);
     A(T.outdeg, u32, n + 1); A(T.qcount, u32, 64);
     A(T.pu_start, u32, n_slots); A(T.pu_end, u32, n_slots);
-    const bool cells = fuse && E > 0;      // a fused plan may hold gated cells
-    T.cells = nullptr;
-    if (cells) { A(T.cell_rows, u32, n); A(T.cell_nodes, u32, n);
-                 A(T.cell_prods, u32, n); A(T.slot_chains, u32, n); A(T.slot_rows, u32, n); }
     char *small_hi = (char *)ctx->arena + ctx->top;     // (the plan of a small graph keeps the others in LDS)
     A(g_dep, u32, n + 1); A(T.ht_keys, u64, ht_size); A(bset, u32, BSET_SIZE);
     if (agenda) { A(AG.keys, u64, AG_TABLE); A(AG.sum, u64, AG_TABLE); A(AG.cnt, u32, AG_TABLE); }
@@ -2754,11 +2751,6 @@ int sched_enqueue(ob_ctx *ctx)
     A(T.ht_vals, u32, ht_size);
     if (agenda) A(AG.first, u32, AG_TABLE);
     char *ones_hi = (char *)ctx->arena + ctx->top;
-    if (cells) {        // (a cell holds more than eight nodes)
-        T.cells_cap = n / 8 + 1;
-        A(T.nrec, uint4, n); A(T.cells, CellRec, T.cells_cap); A(T.cell_nodes_of, CellNodes, T.cells_cap); A(T.cell_of, u32, n); A(T.prod_cell, u32, n);
-        A(T.cell_ends, u32, n); A(T.cell_ends_n, u32, blocks_for(n));
-    }
     A(T.sig, u64, n); A(T.step, u32, n); A(T.indeg, u32, n);
     A(T.succ_off, u32, n + 1); A(T.succ_edge, u32, E + 1); A(T.edge_cons, u32, E + 1);
     A(T.queue, u32, n);
@@ -2782,6 +2774,8 @@ int sched_enqueue(ob_ctx *ctx)
     A(T.it_xoff, u32, n_items + 1);
     T.it_xrec = nullptr;
     if (ctx->concat_views && ctx->n_concat > 0) A(T.it_xrec, uint4, 2 * ((size_t)n_items + 1));
+    // What only the plan itself needs lies behind everything else, and sched_finish puts values and gradients in its place.
+    ctx->plan_top = ctx->top;
     u32 *succ_node;
     A(succ_node, u32, E + 1);
     A(ctx->key_a, u64, max_pairs); A(ctx->key_b, u64, max_pairs); A(ctx->val_a, u32, max_pairs); A(ctx->val_b, u32, max_pairs);
@@ -2806,6 +2800,24 @@ int sched_enqueue(ob_ctx *ctx)
         if (!ctx->scratch) return ctx_fail(ctx, -5, "arena too small for scheduler scratch");
     }
 #undef A
+    // A fused plan of a graph with slices may hold gated cells.  Where there is no room for their tables it holds none: its
+    // values and gradients are the same, and an arena that is large enough for the plan stays large enough.
+    T.cells = nullptr;
+    if (fuse && ctx->n_slice > 0) {
+        const size_t before = ctx->top;
+        T.cells_cap = n / 8 + 1;        // (a cell holds more than eight nodes)
+        bool room = true;
+        auto table = [&](auto *&field, size_t count) {
+            field = arena_array<std::remove_reference_t<decltype(*field)>>(ctx, count);
+            room = room && field;
+        };
+        table(T.nrec, n); table(T.cell_nodes_of, T.cells_cap); table(T.cell_of, n); table(T.prod_cell, n);
+        table(T.cell_ends, n); table(T.cell_ends_n, blocks_for(n));
+        table(T.cell_rows, n); table(T.cell_nodes, n); table(T.cell_prods, n); table(T.slot_chains, n); table(T.slot_rows, n);
+        table(T.cells, T.cells_cap);
+        if (!room) { T.cells = nullptr; ctx->top = before; }
+    }
+    ctx->plan_end = ctx->top;
 
     // ---- stage 1 ----
     if (!small) {   // (sections of the arena start at multiples of 256 bytes)
@@ -2879,7 +2891,7 @@ int sched_enqueue(ob_ctx *ctx)
 
         // ---- launch planning: slots, chains, tile descriptors ----
         if (fuse && E > 0) K(k_bedges, n, T, bset, blist);
-        hipLaunchKernelGGL(k_slots, dim3(cells ? 1 + blocks_for(n, TPB * CELL_PARTS) : 1), dim3(SLOT_THREADS), 0, s, T, (fuse && E > 0) ? ctx->fuse : 0, blist);
+        hipLaunchKernelGGL(k_slots, dim3(T.cells ? 1 + blocks_for(n, TPB * CELL_PARTS) : 1), dim3(SLOT_THREADS), 0, s, T, (fuse && E > 0) ? ctx->fuse : 0, blist);
         ++ctx->n_launch_sched;
         K(k_launch_keys, n, T, ctx->key_a, ctx->val_a, n);
         if (fuse && E > 0) {
@@ -2965,6 +2977,7 @@ int sched_finish(ob_ctx *ctx)
     }
 
     // ---- value and gradient arenas ----
+    ctx->top = ctx->plan_top;      // (the plan is made and read)
     T.V = arena_array<float>(ctx, ctx->hdr.val_floats + VAL_ALIGN);
     T.G = arena_array<float>(ctx, ctx->hdr.grad_floats + VAL_ALIGN);
     if (!T.V || !T.G)

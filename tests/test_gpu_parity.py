@@ -1161,6 +1161,63 @@ def test_parameter_gradients_accumulate_until_zeroed(workload_cache):
     c.close()
 
 
+def _smallest_arena(p, g, fuse):
+    """Bytes of the smallest arena, in steps of 256, that holds a forward and a backward pass."""
+    from paper_1705_07860_amd import binding as ob
+
+    def fits(units):
+        c = ob.Context(arena_bytes=256 * units)
+        try:
+            c.set_fusion(fuse)
+            c.params_create(p)
+            c.param_grad_zero()
+            c.add_bulk(g)
+            c.forward(g.root)
+            c.backward(g.root)
+            return True
+        except ob.ObError as e:
+            assert e.code == -5
+            return False
+        finally:
+            c.close()
+
+    no, yes = 0, (64 << 20) // 256
+    assert fits(yes)
+    while yes - no > 1:
+        mid = (no + yes) // 2
+        if fits(mid):
+            yes = mid
+        else:
+            no = mid
+    return 256 * yes
+
+
+@pytest.mark.parametrize("H,rows", [(2, 60), (2, 200), (64, 40)])
+def test_gated_cells_need_no_larger_arena(H, rows):
+    """The tables for gated cells are used where there is room for them: the smallest arena that holds a graph is that of a
+    plan without fusion, which has none, and there the results have the bits that they have in a large one."""
+    from paper_1705_07860_amd import binding as ob
+    p, g = _cell_graph(H, 1, True, rows, "")
+    need = {fuse: _smallest_arena(p, g, fuse) for fuse in (0, 1, 2)}
+    say(f"  {g.n} nodes: smallest arenas {need}")
+    assert need[1] <= need[0] and need[2] <= need[0]
+    total = int(g.out_dim.sum())
+    out = []
+    for arena in (need[2], 128 << 20):
+        c, root = run_gpu(p, g, ob.OB_BYDEPTH, arena=arena)
+        c.backward(root)
+        kinds = c.debug_read(ob.OB_DBG_CHAINS).reshape(-1, 12)[:, 3]
+        assert c.stats()["arena_used_bytes"] <= arena
+        out.append([int(np.sum(kinds == 3))] + [c.grad_read(v, int(g.out_dim[v])).view(np.uint32) for v in range(0, g.n, 7)]
+                   + [c.value_read(v, int(g.out_dim[v])).view(np.uint32) for v in range(0, g.n, 7)]
+                   + [c.param_grad_read(k, m.shape).view(np.uint32) for k, m in enumerate(p.mats)])
+        c.close()
+    say(f"  chains of cells: {out[0][0]} in the smallest arena, {out[1][0]} in a large one")
+    assert out[1][0] >= 2 and (H > 2 or out[0][0] == 0)
+    for a, b in zip(out[0][1:], out[1][1:]):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("streams", ["whole chip", "disjoint compute units"])
 def test_forked_contexts_share_parameters_and_pipeline_scheduling(streams):
     """Two graphs in flight: a forked context schedules its graph on a second stream while the

@@ -305,6 +305,27 @@ def test_small_gated_cells_at_every_fusion_level(rows, H, q):
     c.close()
 
 
+def _state_recurrence(H, rows, steps, late=False):
+    """Cells whose gates do not depend on the output of the step before (only their states are carried on), so that the cells of
+    all steps hang together by component-wise operations.  late: row r begins behind r operations of its own."""
+    rng = np.random.default_rng(H + rows)
+    pb = wl.ParamBuilder(rng, std=0.4)
+    W, b = pb.add("W", 4 * H, H), pb.add("b", 4 * H, 1)
+    p = pb.done()
+    g = wl.GraphBuilder(p)
+    losses = []
+    for r in range(rows):
+        c = g.input(rng.standard_normal(H))
+        for _ in range(r if late else 0):
+            c = g.tanh(c)
+        for _ in range(steps):
+            s = g.add((g.matvec(W, b, g.input(rng.standard_normal(H))), g.input(rng.standard_normal(4 * H))))
+            i, f, o, cand = (g.slice(s, k * H, (k + 1) * H) for k in range(4))
+            c = g.add((g.cmult(g.sigmoid(f), c), g.cmult(g.sigmoid(i), g.tanh(cand))))
+            losses.append(g.sqnorm(g.cmult(g.sigmoid(o), g.tanh(c))))
+    return p, g.finish(g.add(losses), rows)
+
+
 def _cell_graph(H, nf, sums, rows, odd, seed=5):
     """Steps of gated cells with nf forget gates over `rows` rows; sums: the gates are slices of a sum of two rows (of one row
     otherwise).  odd: what keeps a row's cell from being one, or is unusual and must not."""
@@ -339,6 +360,10 @@ def _cell_graph(H, nf, sums, rows, odd, seed=5):
                 losses.append(g.sqnorm(g.add((h, h))))
             cs[r] = [c] + [g.input(rng.standard_normal(H)) for _ in range(nf - 1)] if nf else cs[r]
             hs[r] = h
+            if odd in ("four readers", "five readers"):
+                losses += [g.sqnorm(g.tanh(h)), g.sqnorm(g.sigmoid(h)), g.sqnorm(g.cmult(h, g.input(rng.standard_normal(H))))]
+            if odd == "five readers":
+                losses.append(g.sqnorm(g.add((h, g.input(rng.standard_normal(H))))))
             if odd == "three readers":
                 losses.append(g.sqnorm(g.tanh(h)))
                 losses.append(g.sqnorm(g.sigmoid(h)))
@@ -350,10 +375,12 @@ def _cell_graph(H, nf, sums, rows, odd, seed=5):
     (2, 1, True, 3, "", True), (25, 1, True, 9, "", True), (64, 1, True, 5, "swapped", True), (65, 1, True, 6, "three readers", True),
     (100, 2, True, 7, "", True), (128, 0, False, 4, "", True), (130, 0, True, 5, "swapped", True), (192, 2, False, 3, "", True),
     (256, 1, True, 16, "output read", True), (300, 1, True, 3, "", True), (20, 2, True, 21, "swapped", True),
+    (32, 1, True, 6, "four readers", True), (32, 1, True, 6, "five readers", False),
     (32, 1, True, 6, "gate read", False), (32, 1, True, 6, "state read", False), (1, 1, True, 4, "", False)])
 def test_gated_cells(H, nf, sums, rows, odd, cells):
     """LSTM and tree-LSTM cells are worked row by row from one record: bit for bit what one launch per level gives, in one
-    evaluation and in two, and within tolerance of the oracle; a chain with a cell that is read in other ways is not."""
+    evaluation and in two, and within tolerance of the oracle; a chain with a cell that is read in other ways is not, nor one with
+    more than four readers of an output."""
     from paper_1705_07860_amd import binding as ob
     p, g = _cell_graph(H, nf, sums, rows, odd)
     o = Oracle(g, p, "f64")
@@ -384,13 +411,70 @@ def test_gated_cells(H, nf, sums, rows, odd, cells):
         assert np.array_equal(out[0][k], out[1][k]) and np.array_equal(out[0][k], out[2][k]), k
 
 
-@pytest.mark.parametrize("H,K,rows,dirs,first", [(1, 1, 5, 1, "sum"), (2, 7, 31, 2, "sum"), (8, 8, 32, 1, "product"), (9, 9, 33, 2, "product"),
-                                                (100, 100, 70, 2, "sum"), (256, 256, 40, 3, "sum"), (33, 600, 6, 1, "sum")])
-def test_cells_behind_products_in_one_launch(H, K, rows, dirs, first):
-    """Cells that add rows of the products before them to others run in the products' launch, the products of all directions
-    together, in tiles of 32 rows and eight columns of each gate: values and gradients have the bits of a launch per batch.
-    K: what the products read, the outputs themselves or (K != H) another product of them."""
+@pytest.mark.parametrize("H,cells", [(956, True), (972, False)])
+def test_gated_cells_of_rows_on_both_sides_of_what_a_chain_may_hold(H, cells):
+    """A chain becomes one of cells if a group of all its rows fits the LDS copy of an interpreted one: 17 H floats for a cell
+    with one forget gate whose sum is its own, of 16 384.  Wider cells are interpreted, with the same bits."""
     from paper_1705_07860_amd import binding as ob
+    p, g = _cell_graph(H, 1, True, 2, "")
+    o = Oracle(g, p, "f64")
+    o.forward()
+    o.backward(g.root)
+    total = int(o.v_off[-1])
+    out = []
+    for level in (0, 2):
+        c, root = run_gpu(p, g, ob.OB_BYDEPTH, fuse=level, arena=1 << 30)
+        kinds = c.debug_read(ob.OB_DBG_CHAINS).reshape(-1, 12)[:, 3]
+        assert bool(np.any(kinds == 3)) == (cells and level > 0)
+        check_against_oracle(c, p, g, o, root, what=f"cells of {H} columns, level {level}")
+        out.append([c.all_read(0, total), c.all_read(1, total)] + [c.param_grad_read(k, m.shape) for k, m in enumerate(p.mats)])
+        c.close()
+    for x, y in zip(*out):
+        assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+
+
+@pytest.mark.parametrize("mode", ["agenda", "manual by agenda", "manual by depth"])
+@pytest.mark.parametrize("graph", ["cells", "swapped", "state carried on", "behind products", "uneven"])
+def test_gated_cells_in_agenda_and_manual_plans(graph, mode):
+    """Batches that were put together by other rules than depth: chains of cells occur there too, and their values and gradients
+    have the bits of a launch per batch.  "state carried on" and "uneven" (rows start their steps at different depths):
+    the cells of all steps hang together by their states, so that an output and a cell that reads its state may come into one
+    batch; no chain there is one of cells alone."""
+    from paper_1705_07860_amd import binding as ob
+    if graph == "cells":
+        p, g = _cell_graph(64, 1, True, 7, "")
+    elif graph == "swapped":
+        p, g = _cell_graph(20, 2, True, 11, "swapped")
+    elif graph == "state carried on":
+        p, g = _state_recurrence(24, 6, 5)
+    elif graph == "uneven":
+        p, g = _state_recurrence(40, 9, 4, late=True)
+    else:
+        p, g, _ = _cells_behind_products(32, 32, 21, 2, "sum")
+    o = Oracle(g, p, "f64")
+    o.forward()
+    o.backward(g.root)
+    total = int(o.v_off[-1])
+    labels = None
+    if mode != "agenda":
+        labels = labels_of(*(S.by_agenda if mode == "manual by agenda" else S.by_depth)(g)[:2])
+    out = {}
+    for level in (0, 1, 2):
+        c, root = run_gpu(p, g, ob.OB_BYAGENDA if mode == "agenda" else ob.OB_MANUAL, fuse=level, arena=256 << 20, labels=labels)
+        kinds = c.debug_read(ob.OB_DBG_CHAINS).reshape(-1, 12)[:, 3]
+        check_against_oracle(c, p, g, o, root, what=f"{graph}/{mode}/level {level}")
+        out[level] = [int(np.sum(kinds == 3)), c.all_read(0, total), c.all_read(1, total)] + [c.param_grad_read(k, m.shape) for k, m in enumerate(p.mats)]
+        c.close()
+    say(f"  {graph}/{mode}: chains of cells {[out[k][0] for k in out]}")
+    if graph in ("cells", "behind products"):
+        assert out[1][0] >= 2 and out[2][0] >= 2
+    for level in (1, 2):
+        for x, y in zip(out[0][1:], out[level][1:]):
+            assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+
+
+def _cells_behind_products(H, K, rows, dirs, first, steps=4):
+    """Steps of LSTM cells over `rows` rows, one less from step to step, and `dirs` directions; also the last node of every step."""
     rng = np.random.default_rng(H + rows)
     pb = wl.ParamBuilder(rng, std=0.3)
     U = [pb.add(f"U{k}", 4 * H, K) for k in range(dirs)]
@@ -399,10 +483,9 @@ def test_cells_behind_products_in_one_launch(H, K, rows, dirs, first):
     p = pb.done()
     g = wl.GraphBuilder(p)
     at = rng.permutation(4)
-    steps = 4
     h = [[g.input(rng.standard_normal(K)) for _ in range(dirs)] for _ in range(rows)]
     c = [[g.input(rng.standard_normal(H)) for _ in range(dirs)] for _ in range(rows)]
-    losses = []
+    losses, ends = [], []
     for step in range(steps):
         for r in range(rows - step):          # (rows end one by one: the operand rows are not evenly spaced)
             r = r if step < 2 else r + 1
@@ -417,7 +500,18 @@ def test_cells_behind_products_in_one_launch(H, K, rows, dirs, first):
                 h[r][k] = out if E is None else g.matvec(E, -1, out)
                 if step == steps - 1:
                     losses.append(g.sqnorm(out))
-    gr = g.finish(g.add(losses), rows)
+        ends.append(len(g.op) - 1)
+    return p, g.finish(g.add(losses), rows), ends
+
+
+@pytest.mark.parametrize("H,K,rows,dirs,first", [(1, 1, 5, 1, "sum"), (2, 7, 31, 2, "sum"), (8, 8, 32, 1, "product"), (9, 9, 33, 2, "product"),
+                                                (100, 100, 70, 2, "sum"), (256, 256, 40, 3, "sum"), (33, 600, 6, 1, "sum")])
+def test_cells_behind_products_in_one_launch(H, K, rows, dirs, first):
+    """Cells that add rows of the products before them to others run in the products' launch, the products of all directions
+    together, in tiles of 32 rows and eight columns of each gate: values and gradients have the bits of a launch per batch.
+    K: what the products read, the outputs themselves or (K != H) another product of them."""
+    from paper_1705_07860_amd import binding as ob
+    p, gr, _ = _cells_behind_products(H, K, rows, dirs, first)
     o = Oracle(gr, p, "f64")
     o.forward()
     o.backward(gr.root)
@@ -434,6 +528,50 @@ def test_cells_behind_products_in_one_launch(H, K, rows, dirs, first):
     for level in (1, 2):
         for x, y in zip(out[0], out[level]):
             assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+
+
+@pytest.mark.parametrize("rows", [257, 258, 259, 260])
+def test_cells_behind_products_of_256_rows(rows):
+    """From 256 rows on, products of 64 columns and more are worked in larger tiles and keep a launch of their own; narrower
+    ones do not.  Six steps of `rows` rows and fewer, of which the second to the fifth may be one launch."""
+    from paper_1705_07860_amd import binding as ob
+    for H in (15, 16):
+        p, g, _ = _cells_behind_products(H, H, rows, 1, "sum", steps=6)
+        o = Oracle(g, p, "f64")
+        o.forward()
+        o.backward(g.root)
+        total = int(o.v_off[-1])
+        out = []
+        for level in (0, 2):
+            c, root = run_gpu(p, g, ob.OB_BYDEPTH, fuse=level, arena=512 << 20)
+            check_against_oracle(c, p, g, o, root, what=f"{rows} rows, H {H}, level {level}")
+            st = c.stats()
+            out.append([c.all_read(0, total), c.all_read(1, total)] + [c.param_grad_read(k, m.shape) for k, m in enumerate(p.mats)])
+            c.close()
+        say(f"  rows {rows}, H {H}: {st['n_launch_fwd']} launches of {st['n_slots']} slots")
+        assert st["n_slots"] - st["n_launch_fwd"] == sum(H < 16 or rows - step < 256 for step in (1, 2, 3, 4))
+        for x, y in zip(*out):
+            assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+
+
+@pytest.mark.parametrize("H,rows,first", [(24, 37, "sum"), (64, 33, "product")])
+def test_cells_behind_products_in_a_later_evaluation(H, rows, first):
+    """The same where the graph is evaluated a step or two at a time: the later evaluations, whose first products read copies of
+    earlier outputs, run products and cells together too, and gradients arrive from the evaluations behind them."""
+    from paper_1705_07860_amd import binding as ob
+    p, g, ends = _cells_behind_products(H, H, rows, 1, first, steps=6)
+    o = Oracle(g, p, "f64")
+    o.forward()
+    o.backward(g.root)
+    for cuts in ((ends[0],), (ends[1],), (ends[0], ends[2])):
+        c, _ = run_gpu(p, g, ob.OB_BYDEPTH, arena=512 << 20, n_nodes=cuts[0] + 1)
+        for cut in cuts[1:] + (g.root,):
+            c.forward(cut)
+            st = c.stats()
+            say(f"  up to node {cut}: stage {st['n_stages']}, {st['n_launch_fwd']} launches of {st['n_slots']} slots")
+            assert st["n_stages"] > 1 and st["n_launch_fwd"] < st["n_slots"]
+        check_against_oracle(c, p, g, o, g.root, what=f"cells behind products cut at {cuts}")
+        c.close()
 
 
 @pytest.mark.parametrize("seed", range(950, 964))
@@ -602,6 +740,38 @@ def test_depth_pass_that_gives_up_is_repeated_with_the_single_workgroup_pass(nam
     rbo, rids, rbd = (S.by_depth if mode == "depth" else S.by_agenda)(g)
     assert np.array_equal(bo, rbo) and np.array_equal(ids, rids) and np.array_equal(bd, rbd)
     check_against_oracle(c, p, g, o, g.root, what=f"{name}/{mode} after a depth retry")
+    c.close()
+
+
+@pytest.mark.parametrize("graph", ["rnn", "cells", "dag 1024", "dag 2048", "sums"])
+def test_small_plan_that_gives_up_is_repeated_with_the_single_workgroup_pass(graph, workload_cache):
+    """The same for graphs that are planned in one launch.  A node that was given up on takes its id as its step there, and the
+    stages behind it plan what comes of that before the host sees the error: with a wave that finds nothing to do at its
+    first look giving up, for graphs of both sides of a thread's second node, lists of twelve operands and gated cells."""
+    from paper_1705_07860_amd import binding as ob
+    if graph == "rnn":
+        p, g, _ = workload_cache("rnn")
+    elif graph == "cells":
+        p, g = _cell_graph(20, 1, True, 12, "")
+    elif graph == "sums":
+        p, g = _sum_recurrences(1, 100, 12)
+    else:
+        p, g = _dag_of(int(graph[4:]), 7, 6)
+    assert 64 < g.n <= 2048 and g.n_edges <= 4096
+    o = Oracle(g, p, "f64")
+    o.forward()
+    if g.out_dim[g.root] == 1:
+        o.backward(g.root)
+    c = ob.Context(arena_bytes=256 << 20, mode=ob.OB_BYDEPTH)
+    c.debug_set(ob.OB_DBG_SET_DEPTH_SPIN, 0)
+    c.params_create(p)
+    c.param_grad_zero()
+    c.add_bulk(g)
+    c.forward(g.root)
+    assert c.stats()["n_depth_retries"] == 1
+    for got, want in zip(c.schedule_read(), S.by_depth(g)):
+        assert np.array_equal(got, want)
+    check_against_oracle(c, p, g, o, g.root, what=f"{graph} after a depth retry")
     c.close()
 
 

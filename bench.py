@@ -98,6 +98,10 @@ PAPER_CONTEXT = {
 }
 
 
+# kernels whose launches a step-kernel figure covers: products and the gated cells behind them are forward launches too
+STEP_KERNELS = {"k_fwd_step": ("k_fwd_step", "k_fwd_cells"), "k_bwd_step": ("k_bwd_step",)}
+
+
 def stored_traffic(args, workload, kernel):
     """HBM bytes per launch of `kernel` from the committed counter summary (two rocprofv3 --pmc
     runs, FETCH_SIZE and WRITE_SIZE, scaled by a plain copy of known size).  Counters cannot be
@@ -108,9 +112,11 @@ def stored_traffic(args, workload, kernel):
     path = os.path.join(ROOT, "profiles", f"{workload}_bydepth_hbm_traffic.json")
     try:
         with open(path) as f:
-            k = json.load(f)["kernels"][kernel]
-        return k["fetch_bytes_per_launch"] + k["write_bytes_per_launch"]
-    except (OSError, KeyError, ValueError):
+            stored = json.load(f)["kernels"]
+        ks = [stored[k] for k in STEP_KERNELS[kernel] if k in stored]
+        total = sum((k["fetch_bytes_per_launch"] + k["write_bytes_per_launch"]) * k["launches"] for k in ks)
+        return round(total / sum(k["launches"] for k in ks))
+    except (OSError, KeyError, ValueError, ZeroDivisionError):
         return None
 
 
@@ -298,8 +304,8 @@ def measure(args, ob, torch, name, steps, warmup, sustain_s, cpu_s, headline):
     # whichever took more time.  Each kernel's launches are bracketed by HIP events on the
     # execution stream (forward: ms_forward; backward: ms_backward minus the deferred
     # parameter-gradient kernels, which have an event of their own), so the average launch duration
-    # is measured live.  Each kernel has two instantiations (k_..._step<false>: any work;
-    # k_..._step<true>: launches with component-wise work only); the figures cover both.
+    # is measured live.  The figures cover all instantiations of a kernel, the forward ones also the
+    # launches of k_fwd_cells (products together with the gated cells behind them).
     fwd_ms, n_fwd = phase["ms_forward"], max(launches["n_launch_fwd"], 1)
     bwd_ms, n_bwd = phase["ms_backward"] - phase["ms_param_grads"], max(launches["n_launch_bwd_steps"], 1)
 

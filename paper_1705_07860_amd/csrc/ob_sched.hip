@@ -1165,8 +1165,8 @@ __global__ __launch_bounds__(TPB) void k_bedges(Tables T, u32 *bset, u32 *blist)
 // product.  Worked tile by tile from descriptors a level of it costs 1 400 to 2 600 cycles of one wave whatever it
 // computes (a wave issues an instruction every four or five cycles, a taken branch costs thirty: addresses, flags and
 // branches of a tile are 150 to 250 instructions).  So the cells of a plan are looked for in the graph, and
-// a chain that consists of them is worked a thread per column, in registers, from one record a row, forward and backward (64
-// sentences: forward runs 6.8 -> 3.4 us a launch, backward runs 9.8 -> 4.6).
+// a chain that consists of them is worked a thread per column, in registers, from one record a row, forward and backward
+// (launches in kernel traces: 64 trees, forward 8.2 -> 4.2 us, backward 12.4 -> 5.5; 64 sentences, backward 9.8 -> 4.8).
 // Does a cell end in product h (of a tanh and a sigmoid)?  Everything that the record relies on is checked here, edge by edge: every
 // node of a cell but its output and c is read inside the cell only.  That the nodes lie in one chain is checked by cell_in_chain, and
 // that they are all of the chain by k_chain_recs, which counts.  What bounds it is the chain of reads from the output back to the
@@ -1682,7 +1682,9 @@ __device__ inline void chain_recs_at(const Tables &T, int agenda, const u32 *bse
             if (fit >= 1) { cr.fused = 2u; if (fit < cr.Rg) cr.Rg = fit; }
         }
         cr.pad0 = cr.pad1 = cr.pad2 = 0;
-        if (cr.fused == 2u && cells == G && cell_nodes == kt * G) {     // gated cells and nothing else
+        // gated cells and nothing else (cells so wide that a group of all their rows, 17 H floats for an LSTM's, does not fit the LDS copy
+        // stay an interpreted run, as do those of plans without room for the tables)
+        if (cr.fused == 2u && cells == G && cell_nodes == kt * G) {
             cr.fused = 3u; cr.pad0 = out;
             cr.Rg = CELL_WAVES / cell_row_waves(cell_d);
             kt = ktf = cr.Rg;      // a tile a row; the last block's may be left over
@@ -2081,7 +2083,7 @@ __device__ inline u32 chain_of_index(const CLay *clay_ex, u32 nc, int which, u32
 }
 
 // Bound by the chains of dependent reads behind an entry.  Everything an entry is put together from stays in registers
-// (147 of them, three waves a SIMD; with 400 bytes of scratch a lane it had four): 59 -> 27 us on the tagger, 200 -> 100 us
+// (151 of them, three waves a SIMD; with 400 bytes of scratch a lane it had four): 59 -> 27 us on the tagger, 200 -> 100 us
 // at 512 sentences, together with reading four rows' edges where a tile has at most four rows.
 __global__ __launch_bounds__(TPB) void k_tiles(Tables T, const CLay *clay_ex, const CLay *total, u32 cap_f, u32 cap_a, u32 cap_b)
 {
@@ -2321,9 +2323,8 @@ __global__ void k_item_finish(Tables T, const u64 *keys, const u32 *vals, u32 n_
 // when empty) and the first reads of whatever the launch before wrote (2 us each, out of another part of the
 // chip's caches).  So up to SMALL_NODES nodes one workgroup runs the same stages one behind the other, with a
 // barrier where a launch ended, its data in its own cache.  What bounds it now is the chain of dependent reads and barriers
-// of its stages, 0.2 to 6 us each: 71 us for 252 nodes of a recurrent network, 122 for a tree of 944 nodes and 118 for
-// 1 344 of a growing graph (schedules of the first
-// two with everything around them 164 -> 109 and 222 -> 183).
+// of its stages, 0.2 to 6 us each: in kernel traces 81 us for some 260 nodes of recurrent networks, 94 for a tree of 944 nodes
+// and 133 for 1 344 of a growing graph (whole schedules, by one launch and by many, at the rule in sched_enqueue).
 // Only what takes the whole chip stays a launch of its own: the tile descriptors after it.
 constexpr u32 SMALL_THREADS = 1024;
 constexpr u32 SMALL_NODES = 2 * SMALL_THREADS;
@@ -2342,7 +2343,7 @@ struct SmallArgs {
 // The depth of every node by one workgroup: a thread has the nodes tid, tid + SMALL_THREADS, ..., looks at two operands of each at
 // a time and settles a node when its list is through.  The operand lists and the depths are in LDS, 0 = not known yet.
 // A sweep of a wave is one dependent LDS read and a dozen instructions for each of its nodes, where the pass by ranges, made for four
-// nodes a lane and few waves, takes some hundred: 27 -> 6 us for 252 nodes, 35 -> 20 for 944.
+// nodes a lane and few waves, takes some hundred: 27 -> 6 us for 252 nodes.
 // A settled operand of a longer list makes room for the next, so what is known early is through before the last is, and a
 // list that is long for its wave is walked by the whole wave, 512 entries at a time, whenever nothing else of the wave moves,
 // by the rule of the pass by ranges.  (Two by two in list order by their threads, the schedule of a sum of 2 046 rows
@@ -2716,8 +2717,9 @@ int sched_enqueue(ob_ctx *ctx)
     const bool part_depth = by_depth && ctx->max_arity < DEPTH_MAX_ARITY && !ctx->force_frontier;
     ctx->depth_partitioned = part_depth;
     // One workgroup plans a graph of up to 2 048 nodes.  Schedules of one launch and of many, in us: recurrences of 48, 473
-    // and 1 617 nodes 93 and 140, 112 and 167, 155 and 187; a tagger's 461, 921 and 1 841 nodes 150 and 255, 170 and 218,
-    // 235 and 238; trees of 1 214 and 2 033 nodes 183 and 222, 220 and 230: the two meet where the rule ends.
+    // and 1 617 nodes 92 and 142, 111 and 167, 147 and 187; a tagger's 461, 921 and 1 841 nodes 149 and 257, 165 and 221,
+    // 216 and 240; trees of 1 214 and 2 033 nodes 189 and 223, 217 and 231; a sum of 2 046 rows 116 and 169; a chain of 500
+    // operations 1 255 and 1 300, of 2 000 5 460 and 5 410: the two meet where the rule ends.
     const bool small = fuse && E > 0 && !agenda && part_depth && !ctx->wide_plan && n <= SMALL_NODES &&
                        E <= SMALL_EDGES && n_items <= SMALL_EDGES;
 

@@ -463,6 +463,10 @@ def test_gated_cells_in_agenda_and_manual_plans(graph, mode):
         c, root = run_gpu(p, g, ob.OB_BYAGENDA if mode == "agenda" else ob.OB_MANUAL, fuse=level, arena=256 << 20, labels=labels)
         kinds = c.debug_read(ob.OB_DBG_CHAINS).reshape(-1, 12)[:, 3]
         check_against_oracle(c, p, g, o, root, what=f"{graph}/{mode}/level {level}")
+        if level == 2 and graph == "behind products":
+            st = c.stats()
+            say(f"  {st['n_launch_fwd']} forward launches of {st['n_slots']} slots")
+            assert st["n_launch_fwd"] < st["n_slots"]
         out[level] = [int(np.sum(kinds == 3)), c.all_read(0, total), c.all_read(1, total)] + [c.param_grad_read(k, m.shape) for k, m in enumerate(p.mats)]
         c.close()
     say(f"  {graph}/{mode}: chains of cells {[out[k][0] for k in out]}")
@@ -2066,7 +2070,7 @@ def test_a_fused_plan_on_few_compute_units_costs_little_more_than_an_unfused_one
         ob.stream_destroy(h)
     unfused, fused = float(np.median(ms[0])), float(np.median(ms[2]))
     say(f"  unfused {unfused:.3f} ms, fused {fused:.3f} ms")
-    assert fused <= 1.23 * unfused
+    assert fused <= 1.25 * unfused
 
 
 def _sum_recurrences(n, steps, arity):

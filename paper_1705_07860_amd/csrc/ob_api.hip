@@ -1361,6 +1361,16 @@ static int fill_uncopied(ob_ctx *u, hipStream_t s)
     return OB_OK;
 }
 
+// The same for gradients: rows of products whose gradient is their one reader's row.
+static int fill_product_grads(ob_ctx *u, hipStream_t s)
+{
+    if (!u->backward_done || u->product_grads_filled) return OB_OK;
+    hipError_t e = exec_fill_product_grads(u->T, s);
+    if (e != hipSuccess) return ctx_fail(u, OB_E_HIP, "filling in gradient rows failed: %s", hipGetErrorString(e));
+    u->product_grads_filled = true;
+    return OB_OK;
+}
+
 static int node_read(ob_ctx *ctx, int node, float *out, size_t cap, bool grad)
 {
     if (!out) return ctx_fail(ctx, OB_E_ARG, "null output");
@@ -1379,6 +1389,7 @@ static int node_read(ob_ctx *ctx, int node, float *out, size_t cap, bool grad)
     // (only a CONCAT node's row can be missing: a slice, the one node whose values lie in another's row, keeps a
     // CONCAT it reads from staying uncopied)
     if (!grad && ctx->op[node] == OP_CONCAT) if (int rc = fill_uncopied(ctx, ctx->stream)) return rc;
+    if (grad && ctx->op[node] == OP_MATVEC) if (int rc = fill_product_grads(ctx, ctx->stream)) return rc;
     const float *arena = grad ? ctx->T.G : ctx->T.V;
     u32 *head = (u32 *)((char *)ctx->hdr_pinned + READ_AT);
     float *row = (float *)(head + 4);
@@ -1435,7 +1446,7 @@ int ob_all_read(ob_ctx *ctx, int which, float *host_out, size_t cap)
         for (u32 l = P; l < nl; ++l) loc[l] = off[n0 + (l - P)];
         u32 *off_dev = arena_array<u32>(last, (size_t)nl + 1);
         if (!off_dev) { dst = nullptr; break; }
-        if (!which && fill_uncopied(u, ctx->stream)) { rc = ctx_fail(ctx, OB_E_HIP, "%s", u->err.c_str()); break; }
+        if (which ? fill_product_grads(u, ctx->stream) : fill_uncopied(u, ctx->stream)) { rc = ctx_fail(ctx, OB_E_HIP, "%s", u->err.c_str()); break; }
         hipError_t e = hipMemcpyAsync(off_dev, loc.data(), (size_t)nl * 4, hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess) e = exec_gather_some(u->T, which, dst, off_dev, ctx->stream);
         if (e != hipSuccess) rc = ctx_fail(ctx, OB_E_HIP, "read-back failed: %s", hipGetErrorString(e));

@@ -120,6 +120,7 @@ struct ob_ctx {
     u32 n_concat = 0;                  // CONCAT nodes in the graph store
     bool concat_views = true;          // CONCAT batches that only matrix products read are not copied
     bool uncopied_filled = false;      // their rows have been written after all (somebody read values)
+    bool product_grads_filled = false; // the gradient rows of products that the last backward pass left unwritten are there
     u64 sum_mv_d32 = 0, sum_mv_k32 = 0; // sums over MATVEC nodes of rows/32+1 and cols/32+1 (bound the GEMM tiles)
     u32 n_slice = 0;                   // SLICE nodes in the graph store
     size_t graph_top = 0;              // arena top right after the uploaded graph image

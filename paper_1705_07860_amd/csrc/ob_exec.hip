@@ -788,6 +788,7 @@ __device__ inline void param_w_tile(const Tables &T, const PTile &pt, float *lds
     const u32 per = (all_chunks + nsp_eff - 1) / nsp_eff;
     const u32 c_lo = sp * per, c_hi = (sp + 1) * per < all_chunks ? (sp + 1) * per : all_chunks;
     const u32 n_uses = end - start;
+    const u32 *grows = T.Gx ? T.it_goff : T.it_gsrc;
     // Row offsets run ahead of the rows in two steps, each a round trip to memory of its own: heads() asks for
     // the offsets of the chunk after next, resolve() makes the next chunk's offsets current and, for a use whose
     // operand row is in pieces (its batch reads through an uncopied CONCAT: it_xoff is XP_LIST), asks for the
@@ -801,7 +802,7 @@ __device__ inline void param_w_tile(const Tables &T, const PTile &pt, float *lds
             const u32 it = c * PWC + lu + 16u * p;
             nok[p] = it < n_uses;
             rec[p] = start + it;
-            ngo[p] = nok[p] ? T.it_goff[start + it] : 0u;
+            ngo[p] = nok[p] ? grows[start + it] : 0u;
             nxo[p] = nok[p] ? T.it_xoff[start + it] : 0u;
         }
     };
@@ -930,11 +931,12 @@ __device__ inline void param_b_tile(const Tables &T, const PTile &pt, u32 sp, fl
     const bool i_ok = i < (u32)P.rows;
     const u32 n_uses = end - start, per = (n_uses + nsp - 1) / nsp;
     const u32 lo = start + (sp * per < n_uses ? sp * per : n_uses), hi = start + ((sp + 1) * per < n_uses ? (sp + 1) * per : n_uses);
+    const u32 *grows = T.Gx ? T.it_goff : T.it_gsrc;
     float acc = 0.f;
     for (u32 it0 = lo; it0 < hi; it0 += PB_UNROLL) {
         float g[PB_UNROLL];
 #pragma unroll
-        for (u32 q = 0; q < PB_UNROLL; ++q) g[q] = (it0 + q < hi && i_ok) ? T.G[T.it_goff[it0 + q] + i] : 0.f;
+        for (u32 q = 0; q < PB_UNROLL; ++q) g[q] = (it0 + q < hi && i_ok) ? T.G[grows[it0 + q] + i] : 0.f;
 #pragma unroll
         for (u32 q = 0; q < PB_UNROLL; q += 4) acc += (g[q] + g[q + 1]) + (g[q + 2] + g[q + 3]);
     }
@@ -1821,6 +1823,20 @@ __global__ void k_fill_uncopied(Tables T)
     }
 }
 
+// Gradient rows of products that are one reader's row as it is (TF_G_ALIAS): the backward pass reads that row in their place and
+// leaves theirs unwritten, and they are written when somebody asks for gradients.
+__global__ void k_fill_product_grads(Tables T)
+{
+    const u32 v = blockIdx.x;
+    if (T.op[v] != OP_MATVEC) return;
+    const u32 p = T.pos_of[v];
+    if (!(T.batches[T.batch_of_pos[p]].vec4 & TF_G_ALIAS)) return;
+    float *o = T.G + T.nat_off[v];
+    const float *s = T.G + T.dx_gsrc[p];
+    const u32 d = T.out_dim[v];
+    for (u32 c = threadIdx.x; c < d; c += blockDim.x) o[c] = s[c];
+}
+
 // One node's row for the host: its offset and its first `count` elements go straight to pinned host memory, so a
 // read is one launch and one wait.  What bounds it is the round trip to the host, so what counts is how many there
 // are: looking the offset up by a copy of its own, waiting, and then copying the row took two.  Tagging one sentence
@@ -1959,7 +1975,9 @@ static int launch_backward_steps(ob_ctx *ctx)
     const int before_steps = ctx->n_launch_bwd;
     for (u32 st = ns; st-- > 0;) {
         const SlotRec &r = ctx->slots[st], &e = ctx->slots[st + 1];
-        const u32 n_pull = e.wa - r.wa, n_dx = e.tb - r.tb;
+        // The gradient of a product with one reader that passes its own on is that reader's row: the dX tiles and the weight gradients
+        // read it there and nothing copies it.  (A minibatch of 512 sentences wrote and read again 4 MB a launch for it.)
+        const u32 n_pull = (r.plain & 16u) && !T.Gx ? 0u : e.wa - r.wa, n_dx = e.tb - r.tb;
         const size_t lds_bytes = slot_lds_bytes(r, BWD_LDS_MIN);
         // (with gradients arriving from later stages a product's gradient is no longer its one consumer's row:
         // the dX tiles then read the rows the slot's own pull has just written)
@@ -2039,6 +2057,7 @@ int exec_forward(ob_ctx *ctx)
 int exec_backward(ob_ctx *ctx)
 {
     ctx->n_launch_bwd = 0;
+    ctx->product_grads_filled = ctx->T.Gx != nullptr;
     int rc = run_maybe_graph(ctx, &ctx->graph_bwd, &ctx->gexec_bwd, [ctx]() {
         int r = launch_backward_steps(ctx);
         if (r) return r;
@@ -2110,6 +2129,13 @@ hipError_t exec_upload(const UploadList &L, char *dst, hipStream_t s)
 hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, hipStream_t s)
 {
     hipLaunchKernelGGL(k_node_read, dim3(1), dim3(WG), 0, s, off_tab, arena, node, count, head, row);
+    return hipGetLastError();
+}
+
+hipError_t exec_fill_product_grads(const Tables &T, hipStream_t s)
+{
+    if (T.n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_fill_product_grads, dim3(T.n), dim3(64), 0, s, T);
     return hipGetLastError();
 }
 

@@ -215,7 +215,7 @@ struct WorkRec { u32 first, len; };   // a workgroup runs tiles [first, first + 
 // tile), so the slot can run the lean instantiation of the forward kernel.  Bit 1: no product of the slot
 // reads its operand rows in pieces (otherwise the slot runs the instantiation that can); bit 2 clear: the slot is one chain of
 // cells that takes up every row of the slot before, all products, and the forward work of both slots is that slot's launch.
-// bit 3 clear: the slot holds gated cells.
+// bit 3 clear: the slot holds gated cells.  bit 4 clear: the slot's pull does more than copy the rows of products with TF_G_ALIAS.
 // lminf / nlmaxf: the same pair of run lengths over the slot's forward work items (views have none).
 struct SlotRec { u32 wf, wa, tb, tf, ta, lmin, nlmax, dx_free, lds_need, plain, lminf, nlmaxf; };
 
@@ -289,7 +289,8 @@ struct Tables {
     u32 *root_pos;         // [0] = schedule position of the backward root
     EdgeRec *edges;
     // parameter-use items (deferred dW / db / dE)
-    u64 *it_key; u32 *it_pos; u32 *it_goff; u32 *it_xoff; u32 *pu_start; u32 *pu_end;
+    // (it_gsrc: where a use's gradient row lies while the pull of products with one plain reader is left out; else as it_goff)
+    u64 *it_key; u32 *it_gsrc; u32 *it_goff; u32 *it_xoff; u32 *pu_start; u32 *pu_end;
     uint4 *it_xrec;        // per MATVEC use with it_xoff == XP_LIST, two entries: the operand row's offset per piece (contraction
                            // index k of piece q lies at offset q + k) and the first index behind pieces 0, 1, 2 (0xffffffff: none)
     SchedHeader *hdr;
@@ -327,6 +328,7 @@ hipError_t exec_gather_all(const Tables &T, int which, float *dst, const u32 *ds
 hipError_t exec_stage_scatter(const float *G, const u32 *nat_off, u32 first_proxy, const u32 *src, const u32 *dim, u32 count,
                               const u32 *owner_nat_off, float *owner_gx, hipStream_t s);
 hipError_t exec_fill_uncopied(const Tables &T, hipStream_t s);
+hipError_t exec_fill_product_grads(const Tables &T, hipStream_t s);
 struct UploadList { const void *src[10]; size_t bytes[10], at[10]; };   // host arrays and where they go in one device block
 hipError_t exec_upload(const UploadList &L, char *dst, hipStream_t s);
 hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, hipStream_t s);

@@ -1735,6 +1735,7 @@ __device__ inline void slot_tables_at(const Tables &T, const CLay *clay_ex, cons
     const BatchRec &hb = T.batches[T.lorder[cr.first]];
     if (hb.op == OP_MATVEC && !(hb.vec4 & TF_G_ALIAS)) S.dx_free = 0;   // this slot's dX tiles need the slot's own pull first
     if (cr.fused == 3u) atomicAnd(&S.plain, ~8u);
+    if (hb.op != OP_MATVEC || !(hb.vec4 & TF_G_ALIAS)) atomicAnd(&S.plain, ~16u);
     // (every row of a product taken up has one reader, so as many rows as cells are all rows of the slot before)
     if (cr.fused == 3u && s > 0 && T.slot_chains[s] == 1u && T.cell_prods[cr.pad0] == cr.G && T.slot_rows[s - 1u] == cr.G) atomicAnd(&S.plain, ~4u);
     if (!cr.fused) atomicAnd(&S.plain, ~1u);     // a GEMM, reduction or wide-sum batch runs in this slot
@@ -2288,11 +2289,12 @@ __device__ inline void item_finish_at(const Tables &T, const u64 *keys, const u3
     const u32 p = vals[i];
     const u32 v = T.order[p];
     T.it_key[i] = k;
-    T.it_pos[i] = p;
-    T.it_goff[i] = T.nat_off[v];
+    u32 gsrc = T.nat_off[v];
+    T.it_goff[i] = gsrc;
     u32 xoff = 0;
     if (T.op[v] == OP_MATVEC) {
         const BatchRec &r = T.batches[T.batch_of_pos[p]];
+        if (r.vec4 & TF_G_ALIAS) gsrc = T.dx_gsrc[p];
         xoff = T.val_off[T.in_idx[T.in_off[v]]];
         if (batch_xp(r)) {
             // the operand row in pieces: the row's offsets from the batch's operand list and the cuts between pieces
@@ -2310,6 +2312,7 @@ __device__ inline void item_finish_at(const Tables &T, const u64 *keys, const u3
         }
     }
     T.it_xoff[i] = xoff;
+    T.it_gsrc[i] = gsrc;
     if (i == 0 || (u32)(keys[i - 1] >> 32) != slot) T.pu_start[slot] = i;
     if (i == n_items - 1 || (u32)(keys[i + 1] >> 32) != slot) T.pu_end[slot] = i + 1;
 }
@@ -2772,7 +2775,7 @@ int sched_enqueue(ob_ctx *ctx)
     A(T.tiles_f, TileDesc, cap_f); A(T.tiles_a, PullDesc, cap_a); A(T.tiles_b, TileDesc, cap_b);
     A(T.root_pos, u32, 64);
     A(T.edges, EdgeRec, E + 1);
-    A(T.it_key, u64, n_items + 1); A(T.it_pos, u32, n_items + 1); A(T.it_goff, u32, n_items + 1);
+    A(T.it_key, u64, n_items + 1); A(T.it_gsrc, u32, n_items + 1); A(T.it_goff, u32, n_items + 1);
     A(T.it_xoff, u32, n_items + 1);
     T.it_xrec = nullptr;
     if (ctx->concat_views && ctx->n_concat > 0) A(T.it_xrec, uint4, 2 * ((size_t)n_items + 1));

@@ -411,6 +411,37 @@ def test_gated_cells(H, nf, sums, rows, odd, cells):
         assert np.array_equal(out[0][k], out[1][k]) and np.array_equal(out[0][k], out[2][k]), k
 
 
+def test_gradients_of_products_are_there_when_asked_for():
+    """A product with one reader that passes its gradient on has no row of its own written by the backward pass: one node asked
+    for by itself, all nodes at once, and both again after another backward pass on other values, also of two evaluations."""
+    from paper_1705_07860_amd import binding as ob
+    for cut in (False, True):
+        out = []
+        for seed in (3, 4):
+            p, g = _cell_graph(36, 1, True, 9, "")
+            g.payload[:] = np.random.default_rng(seed).standard_normal(g.payload.size).astype(np.float32)
+            out.append((p, g, Oracle(g, p, "f64")))
+        c = ob.Context(arena_bytes=128 << 20)
+        c.params_create(out[0][0])
+        for p, g, o in out:
+            o.forward()
+            o.backward(g.root)
+            total = int(o.v_off[-1])
+            products = np.nonzero(g.op == wl.OP_MATVEC)[0]
+            c.graph_new()
+            c.param_grad_zero()
+            c.add_bulk(g)
+            if cut:
+                c.forward(g.n * 2 // 3)
+            c.forward(g.root)
+            c.backward(g.root)
+            for v in (int(products[0]), int(products[-1])):
+                lo, hi = int(o.v_off[v]), int(o.v_off[v + 1])
+                assert rel_err(c.grad_read(v, hi - lo), o.grad[lo:hi]) <= TOL
+            assert segment_rel_err(c.all_read(1, total), o.grad[:total], o.v_off) <= TOL
+        c.close()
+
+
 @pytest.mark.parametrize("H,cells", [(956, True), (972, False)])
 def test_gated_cells_of_rows_on_both_sides_of_what_a_chain_may_hold(H, cells):
     """A chain becomes one of cells if a group of all its rows fits the LDS copy of an interpreted one: 17 H floats for a cell

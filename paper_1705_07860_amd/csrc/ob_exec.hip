@@ -1299,78 +1299,229 @@ __device__ inline void cell_fwd_item(const Tables &T, const TileDesc *tiles, u32
     }
 }
 
-// Gradients of all nodes of the cells' rows.  GX: gradients from later evaluation stages are added to every node's.
-template <int NW, bool GX>
+// What the backward pass reads for one column of a cell.  own: a row of gradients of h's readers that is not in memory
+// yet (CELL_MARK: none).
+struct CellIn { float eg[CELL_H_EDGES], ev[CELL_H_EDGES], cg, cv, i, g, o, tc, f[CELL_FORGET], prev[CELL_FORGET]; };
+__device__ inline __attribute__((always_inline)) void cell_bwd_read(const Tables &T, const CellRec &R, u32 col, u32 own, CellIn &x)
+{
+    const float *V = T.V, *G = T.G;
+    const u32 nh = R.n_edges & 0xffu;
+    x.cg = x.cv = 0.f;
+#pragma unroll
+    for (u32 k = 0; k < CELL_H_EDGES; ++k) {
+        x.eg[k] = x.ev[k] = 0.f;
+        if (k >= nh) continue;
+        if (R.he[k].goff != own) x.eg[k] = G[R.he[k].goff + col];
+        if (R.he[k].kind >= (u32)EK_MUL) x.ev[k] = V[R.he[k].voff + col];
+    }
+    if (R.n_edges >> 8) {
+        x.cg = G[R.ce.goff + col];
+        if (R.ce.kind >= (u32)EK_MUL) x.cv = V[R.ce.voff + col];
+    }
+    x.i = V[R.i + col]; x.g = V[R.g + col]; x.o = V[R.o + col]; x.tc = V[R.tc + col];
+#pragma unroll
+    for (u32 k = 0; k < CELL_FORGET; ++k) {
+        x.f[k] = x.prev[k] = 0.f;
+        if (k < R.nf) { x.f[k] = V[R.f[k] + col]; x.prev[k] = V[R.prev[k] + col]; }
+    }
+}
+// Gradients of one column of all nodes of a cell.  GX: gradients from later evaluation stages are added to every node's.
+template <bool GX>
+__device__ inline __attribute__((always_inline)) void cell_bwd_write(const Tables &T, const CellRec &R, u32 col, const CellIn &x)
+{
+    float *G = T.G;
+    const u32 nh = R.n_edges & 0xffu;
+    const float i = x.i, g = x.g, o = x.o, tc = x.tc;
+    auto start = [&](u32 off) __attribute__((always_inline)) { return GX ? T.Gx[off + col] : 0.f; };
+    float gh = start(R.h);
+#pragma unroll
+    for (u32 k = 0; k < CELL_H_EDGES; ++k)
+        if (k < nh) gh = add_r(gh, R.he[k].kind >= (u32)EK_MUL ? mul_r(x.eg[k], edge_factor(R.he[k].kind, x.ev[k])) : x.eg[k]);
+    const float gtc = add_r(start(R.tc), mul_r(gh, o)), go = add_r(start(R.o), mul_r(gh, tc));
+    float gc = add_r(start(R.c), mul_r(gtc, edge_factor(EK_DTANH, tc)));
+    if (R.n_edges >> 8) gc = add_r(gc, R.ce.kind >= (u32)EK_MUL ? mul_r(x.cg, edge_factor(R.ce.kind, x.cv)) : x.cg);
+    G[R.h + col] = gh; G[R.tc + col] = gtc; G[R.o + col] = go; G[R.c + col] = gc;
+    const float gic = R.nf ? add_r(start(R.ic), gc) : gc;
+    const float gi = add_r(start(R.i), mul_r(gic, g)), gg = add_r(start(R.g), mul_r(gic, i));
+    if (R.nf) G[R.ic + col] = gic;
+    G[R.i + col] = gi; G[R.g + col] = gg;
+    float s[3 + CELL_FORGET];
+    s[0] = add_r(start(R.sl_i), mul_r(gi, edge_factor(EK_DSIGM, i)));
+    s[1] = add_r(start(R.sl_g), mul_r(gg, edge_factor(EK_DTANH, g)));
+    s[2] = add_r(start(R.sl_o), mul_r(go, edge_factor(EK_DSIGM, o)));
+    G[R.sl_i + col] = s[0]; G[R.sl_g + col] = s[1]; G[R.sl_o + col] = s[2];
+#pragma unroll
+    for (u32 k = 0; k < CELL_FORGET; ++k) {
+        s[3 + k] = 0.f;
+        if (k >= R.nf) continue;
+        const float gp = add_r(start(R.fp[k]), gc), gf = add_r(start(R.f[k]), mul_r(gp, x.prev[k]));
+        s[3 + k] = add_r(start(R.sl_f[k]), mul_r(gf, edge_factor(EK_DSIGM, x.f[k])));
+        G[R.fp[k] + col] = gp; G[R.f[k] + col] = gf; G[R.sl_f[k] + col] = s[3 + k];
+    }
+    if (R.sums) {
+        const u32 at[3 + CELL_FORGET] = {R.at_i, R.at_g, R.at_o, R.at_f[0], R.at_f[1]};
+#pragma unroll
+        for (u32 k = 0; k < 3 + CELL_FORGET; ++k)
+            if (k < 3u + R.nf) G[R.S + at[k] + col] = add_r(start(R.S + at[k]), s[k]);
+    }
+}
+// REST: without the cells that the launch's dX tiles work
+template <int NW, bool GX, bool REST>
 __device__ inline void cell_bwd_rows(const Tables &T, const PullDesc *tiles, u32 rows)
 {
     const u32 lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const u32 per = NW / rows, t = wave / per, part = wave % per;
     if (t >= rows) return;
     const CellRec R = *reinterpret_cast<const CellRec *>(tiles + t);
-    if (R.mark != CELL_MARK) return;
-    const float *V = T.V;
-    float *G = T.G;
-    const u32 nh = R.n_edges & 0xffu;
+    if (R.mark != CELL_MARK || (REST && R.taken)) return;
     for (u32 col = part * 64u + lane; col < R.H; col += per * 64u) {
-        auto start = [&](u32 off) __attribute__((always_inline)) { return GX ? T.Gx[off + col] : 0.f; };
-        // everything that is read, before anything that waits for it
-        float eg[CELL_H_EDGES], ev[CELL_H_EDGES], cg = 0.f, cv = 0.f;
-#pragma unroll
-        for (u32 k = 0; k < CELL_H_EDGES; ++k) {
-            eg[k] = ev[k] = 0.f;
-            if (k >= nh) continue;
-            eg[k] = G[R.he[k].goff + col];
-            if (R.he[k].kind >= (u32)EK_MUL) ev[k] = V[R.he[k].voff + col];
-        }
-        if (R.n_edges >> 8) {
-            cg = G[R.ce.goff + col];
-            if (R.ce.kind >= (u32)EK_MUL) cv = V[R.ce.voff + col];
-        }
-        const float i = V[R.i + col], g = V[R.g + col], o = V[R.o + col], tc = V[R.tc + col];
-        float f[CELL_FORGET], prev[CELL_FORGET];
-#pragma unroll
-        for (u32 k = 0; k < CELL_FORGET; ++k) {
-            f[k] = prev[k] = 0.f;
-            if (k < R.nf) { f[k] = V[R.f[k] + col]; prev[k] = V[R.prev[k] + col]; }
-        }
-        float gh = start(R.h);
-#pragma unroll
-        for (u32 k = 0; k < CELL_H_EDGES; ++k)
-            if (k < nh) gh = add_r(gh, R.he[k].kind >= (u32)EK_MUL ? mul_r(eg[k], edge_factor(R.he[k].kind, ev[k])) : eg[k]);
-        const float gtc = add_r(start(R.tc), mul_r(gh, o)), go = add_r(start(R.o), mul_r(gh, tc));
-        float gc = add_r(start(R.c), mul_r(gtc, edge_factor(EK_DTANH, tc)));
-        if (R.n_edges >> 8) gc = add_r(gc, R.ce.kind >= (u32)EK_MUL ? mul_r(cg, edge_factor(R.ce.kind, cv)) : cg);
-        G[R.h + col] = gh; G[R.tc + col] = gtc; G[R.o + col] = go; G[R.c + col] = gc;
-        const float gic = R.nf ? add_r(start(R.ic), gc) : gc;
-        const float gi = add_r(start(R.i), mul_r(gic, g)), gg = add_r(start(R.g), mul_r(gic, i));
-        if (R.nf) G[R.ic + col] = gic;
-        G[R.i + col] = gi; G[R.g + col] = gg;
-        float s[3 + CELL_FORGET];
-        s[0] = add_r(start(R.sl_i), mul_r(gi, edge_factor(EK_DSIGM, i)));
-        s[1] = add_r(start(R.sl_g), mul_r(gg, edge_factor(EK_DTANH, g)));
-        s[2] = add_r(start(R.sl_o), mul_r(go, edge_factor(EK_DSIGM, o)));
-        G[R.sl_i + col] = s[0]; G[R.sl_g + col] = s[1]; G[R.sl_o + col] = s[2];
-#pragma unroll
-        for (u32 k = 0; k < CELL_FORGET; ++k) {
-            s[3 + k] = 0.f;
-            if (k >= R.nf) continue;
-            const float gp = add_r(start(R.fp[k]), gc), gf = add_r(start(R.f[k]), mul_r(gp, prev[k]));
-            s[3 + k] = add_r(start(R.sl_f[k]), mul_r(gf, edge_factor(EK_DSIGM, f[k])));
-            G[R.fp[k] + col] = gp; G[R.f[k] + col] = gf; G[R.sl_f[k] + col] = s[3 + k];
-        }
-        if (R.sums) {
-            const u32 at[3 + CELL_FORGET] = {R.at_i, R.at_g, R.at_o, R.at_f[0], R.at_f[1]};
-#pragma unroll
-            for (u32 k = 0; k < 3 + CELL_FORGET; ++k)
-                if (k < 3u + R.nf) G[R.S + at[k] + col] = add_r(start(R.S + at[k]), s[k]);
-        }
+        CellIn x;
+        cell_bwd_read(T, R, col, CELL_MARK, x);
+        cell_bwd_write<GX>(T, R, col, x);
     }
 }
 template <int NW>
 __device__ inline void cell_bwd_item(const Tables &T, const PullDesc *tiles, u32 rows)
 {
-    if (T.Gx) cell_bwd_rows<NW, true>(T, tiles, rows);
-    else cell_bwd_rows<NW, false>(T, tiles, rows);
+    if (T.Gx) cell_bwd_rows<NW, true, false>(T, tiles, rows);
+    else cell_bwd_rows<NW, false, false>(T, tiles, rows);
+}
+
+// A tile of dX = G W and of the gated cells whose outputs are the product's operands: the columns of the tile are columns of the
+// gradients of those outputs, and all that a cell's gradients wait for in them, so the cells are worked where the tile ends and the
+// slot of cells has no launch of its own.  Same sums in the same order, so the same bits; rows that cells take up are not written.
+// Bound by latency: records and values of the cells are asked for while the operands of the product are on their way (in
+// tiles of 32 columns, whose operands take their registers, when the last of them have been multiplied).
+// 64 sentences: 7.8 and 4.8 us in two launches, 8.6 in one; 512: 16.6 and 7.6, 13.1.
+constexpr u32 DXC_WORDS = sizeof(CellRec) / 4, DXC_ROWS = 4;      // rows that a wave finishes
+template <int EDGE>
+constexpr u32 dxc_lds_floats() { return DX_WAVES * (EDGE * EDGE + DXC_ROWS * DXC_WORDS); }
+template <int EDGE>
+__device__ inline void dx_cell_tile(const Tables &T, const TileDesc &d, float *lds)
+{
+    constexpr u32 NV = EDGE * EDGE / 64, LQ = 64 / EDGE, KB = 4 * LQ;     // accumulators; lane groups; contraction indices of a step
+    constexpr u32 NOUT = EDGE == DXT ? 1 : 2;                             // results of a lane
+    static_assert(EDGE == DXT || EDGE == DXTW, "tile edges");
+    static_assert(DXC_ROWS * DXC_WORDS / 4 <= 64, "a lane takes 16 bytes of its wave's records");
+    // (what follows from the thread's place is worked out here: taken out of the launch's loop, for both edges, it would cost registers)
+    u32 tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const u32 lane = tid & 63u, w = sreg(tid >> 6), le = lane % EDGE, q = lane / EDGE;
+    const u32 K = d.k, m = d.d, ntn = (K + EDGE - 1) / EDGE;
+    const u32 r0 = (d.t / ntn) * EDGE, c0 = (d.t % ntn) * EDGE;
+    const u32 col = c0 + le;
+    const bool row_ok = r0 + le < d.B, col_ok = col < K;
+    // the rows a wave finishes: its i-th result of lane group q is row place_row(NOUT * q + i)
+    const bool ends = EDGE != DXT || w < 4u;
+    auto place_row = [&](u32 place) __attribute__((always_inline)) {
+        return EDGE == DXT ? 4u * place + w : 8u * (w >> 1) + 4u * (place >> 1) + 2u * (w & 1u) + (place & 1u);
+    };
+    u32 *recs = (u32 *)(lds + DX_WAVES * EDGE * EDGE) + w * DXC_ROWS * DXC_WORDS;
+    const u32 mine = lane / (DXC_WORDS / 4), part = lane % (DXC_WORDS / 4);
+    const bool has = ends && lane < DXC_ROWS * (DXC_WORDS / 4);
+    const u32 mine_row = r0 + place_row(mine);
+    const u32 at = has && mine_row < d.B ? T.dx_cell[d.pos0 + mine_row] : 0u;
+    const u32 grow_row = row_ok ? r0 + le : r0;
+    const float *grow = T.G + ((d.contig & 1u) ? d.base[0] + (grow_row - r0) * d.sstride[0] : T.dx_gsrc[d.pos0 + grow_row]);
+    uint4 rec = make_uint4(0u, 0u, 0u, 0u);
+    if (at) rec = ((const uint4 *)(T.tiles_a + at - 1u))[part];
+    gl_float *wcol = as_global(d.w) + (col_ok ? col : 0u);
+    const bool fast = (m & 3u) == 0;
+    const u32 steps = (m + KB - 1) / KB, per = (steps + DX_WAVES - 1) / DX_WAVES;
+    u32 lo = w * per * KB, hi = (w + 1) * per * KB;
+    if (lo > steps * KB) lo = steps * KB;
+    if (hi > steps * KB) hi = steps * KB;
+    float4 a[KU], b[KU];
+    auto operands = [&](u32 ib) __attribute__((always_inline)) {
+        const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            const u32 i0 = ib + KB * u + 4 * q;
+            const bool in = ib + KB * u < hi && i0 < m;
+            a[u] = b[u] = z4;
+            if (fast) {
+                if (in && row_ok) a[u] = ld4(grow + i0);
+                if (in && col_ok) {
+                    gl_float *wp = wcol + (size_t)i0 * K;
+                    b[u] = make_float4(wp[0], wp[K], wp[2 * (size_t)K], wp[3 * (size_t)K]);
+                }
+            } else if (in) {
+                float av[4] = {0.f, 0.f, 0.f, 0.f}, bv[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (u32 s = 0; s < 4; ++s)
+                    if (i0 + s < m) {
+                        if (row_ok) av[s] = grow[i0 + s];
+                        if (col_ok) bv[s] = wcol[(size_t)(i0 + s) * K];
+                    }
+                a[u] = make_float4(av[0], av[1], av[2], av[3]);
+                b[u] = make_float4(bv[0], bv[1], bv[2], bv[3]);
+            }
+        }
+    };
+    CellIn x[NOUT];
+    auto values = [&]() __attribute__((always_inline)) {
+        if (has) {
+            u32 *to = recs + mine * DXC_WORDS + part * 4u;
+            to[0] = rec.x; to[1] = rec.y; to[2] = rec.z; to[3] = rec.w;
+        }
+        __builtin_amdgcn_wave_barrier();      // (a wave reads what it wrote itself; its LDS operations complete in order)
+#pragma unroll
+        for (u32 i = 0; i < NOUT; ++i) {
+            const CellRec &R = *(const CellRec *)(recs + (NOUT * q + i) * DXC_WORDS);
+            const u32 row = r0 + place_row(NOUT * q + i);
+            if (ends && col_ok && R.mark == CELL_MARK) cell_bwd_read(T, R, col, d.dx_off + row * K, x[i]);
+        }
+    };
+    float sum[NOUT];
+    if constexpr (EDGE == DXT) {
+        operands(lo);
+        values();
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (u32 ib = lo; ib < hi; ib += KB * KU) {
+            if (ib != lo) operands(ib);
+#pragma unroll
+            for (int u = 0; u < KU; ++u) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].x, b[u].x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].y, b[u].y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].z, b[u].z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].w, b[u].w, acc, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (u32 v = 0; v < NV; ++v) lds[(w * NV + v) * 64 + lane] = acc[v];
+    } else {
+        floatx16 acc;
+        for (u32 v = 0; v < NV; ++v) acc[v] = 0.f;
+        for (u32 ib = lo; ib < hi; ib += KB * KU) {
+            operands(ib);
+#pragma unroll
+            for (int u = 0; u < KU; ++u) acc = mfma4(a[u], b[u], acc);
+        }
+        values();
+#pragma unroll
+        for (u32 v = 0; v < NV; ++v) lds[(w * NV + v) * 64 + lane] = acc[v];
+    }
+    __syncthreads();
+    if (ends && col_ok) {
+#pragma unroll
+        for (u32 i = 0; i < NOUT; ++i) {
+            const u32 v = NOUT * w + i;
+            sum[i] = lds[v * 64 + lane];
+            for (u32 ww = 1; ww < DX_WAVES; ++ww) sum[i] += lds[(ww * NV + v) * 64 + lane];
+        }
+#pragma unroll
+        for (u32 i = 0; i < NOUT; ++i) {
+            const CellRec &R = *(const CellRec *)(recs + (NOUT * q + i) * DXC_WORDS);
+            const u32 row = r0 + place_row(NOUT * q + i), own = d.dx_off + row * K;
+            if (row >= d.B) continue;
+            if (R.mark != CELL_MARK) { T.G[own + col] = sum[i]; continue; }
+#pragma unroll
+            for (u32 k = 0; k < CELL_H_EDGES; ++k)
+                if (k < (R.n_edges & 0xffu) && R.he[k].goff == own) x[i].eg[k] = sum[i];
+            cell_bwd_write<false>(T, R, col, x[i]);
+        }
+    }
+    __syncthreads();       // the LDS space is free for the workgroup's next tile
 }
 
 // A tile of a product Y = X W^T + b and of the gated cells behind it (S = Y + another row; four gates, one of them forget).  The tile's
@@ -1698,6 +1849,27 @@ __global__ __launch_bounds__(BWD_THREADS, 4) void k_bwd_step(u32 work_lo, u32 wo
     if (sink != sink && work_lo == 0xffffffffu) T.G[0] = sink;   // (no launch has this range)
 }
 
+// The dX tiles of a slot and the cells of the slot before it, in one launch: tiles that work the cells whose outputs their rows are,
+// and work items for the cells that no product of the slot reads.
+__global__ __launch_bounds__(BWD_THREADS, 4) void k_bwd_cells(u32 work_lo, u32 work_hi, u32 tile_lo, u32 run_len, u32 dx_lo, u32 dx_hi,
+                                                            const PullDesc *tiles_a, const WorkRec *works_a, const TileDesc *tiles_b, Tables T)
+{
+    const u32 n_dx = dx_hi - dx_lo, n_items = n_dx + (work_hi - work_lo);
+    for (u32 item = blockIdx.x; item < n_items; item += gridDim.x) {
+        if (item < n_dx) {
+            const TileDesc d = tiles_b[dx_lo + item];
+            if (dx_tile_edge(d.flags, d.k) == (u32)DXTW) dx_cell_tile<DXTW>(T, d, dyn_lds);
+            else dx_cell_tile<DXT>(T, d, dyn_lds);
+            continue;
+        }
+        const u32 w = work_lo + (item - n_dx);
+        WorkRec wr;
+        if (run_len) { wr.first = tile_lo + (w - work_lo) * (run_len & ~CELL_ITEM); wr.len = run_len; }
+        else wr = works_a[w];
+        cell_bwd_rows<BWD_THREADS / 64, false, true>(T, tiles_a + sreg(wr.first), sreg(wr.len) & ~CELL_ITEM);
+    }
+}
+
 __global__ void k_set_root(Tables T) { T.root_pos[0] = T.root == 0xffffffffu ? 0xffffffffu : T.pos_of[T.root]; }   // (no root in this graph: nothing is seeded)
 
 // Workgroup g runs on XCD g % 8 and the tile list is ordered so that tile t belongs on XCD t % 8 (an
@@ -1978,6 +2150,14 @@ static int launch_backward_steps(ob_ctx *ctx)
         // The gradient of a product with one reader that passes its own on is that reader's row: the dX tiles and the weight gradients
         // read it there and nothing copies it.  (A minibatch of 512 sentences wrote and read again 4 MB a launch for it.)
         const u32 n_pull = (r.plain & 16u) && !T.Gx ? 0u : e.wa - r.wa, n_dx = e.tb - r.tb;
+        if (n_dx && !n_pull && r.dx_free && !T.Gx && st > 0 && !(ctx->slots[st - 1].plain & 32u)) {
+            const SlotRec &c = ctx->slots[st - 1];
+            hipLaunchKernelGGL(k_bwd_cells, dim3(grid_for(n_dx + (r.wa - c.wa), GRID_CAP)), dim3(BWD_THREADS), dxc_lds_floats<DXTW>() * sizeof(float), s,
+                               c.wa, r.wa, c.ta, slot_run_len(c), r.tb, e.tb, T.tiles_a, T.works_a, T.tiles_b, T);
+            ++ctx->n_launch_bwd;
+            --st;
+            continue;
+        }
         const size_t lds_bytes = slot_lds_bytes(r, BWD_LDS_MIN);
         // (with gradients arriving from later stages a product's gradient is no longer its one consumer's row:
         // the dX tiles then read the rows the slot's own pull has just written)

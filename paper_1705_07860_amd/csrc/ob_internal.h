@@ -172,13 +172,15 @@ struct CellRec {
     u32 sl_i, sl_g, sl_o, sl_f[CELL_FORGET];      // gradient rows of the slices
     u32 n_edges;                     // consumers of h | of c beside tanh (at most one) << 8
     CellEdge he[CELL_H_EDGES], ce;
-    u32 pad;
+    u32 taken;                       // 1 + position of the product that h is the operand of, if the backward pass may work the cell in its dX tiles
 };
 static_assert(sizeof(CellRec) == sizeof(PullDesc), "a CellRec takes a PullDesc's place");
 constexpr u32 CELL_NODES = 4 + CELL_FORGET + 1 + 2 * (CELL_FORGET + 3);
 // prod: 1 + the batches of the rows whose sum S is, where they are products that nobody else reads (else 0)
-struct CellNodes { u32 batch[CELL_NODES]; u32 prod[2]; };      // [0]: of h | number of nodes << 16 (a fused plan has at most 4 096 batches)
+// next, at: of the readers of h and c from elsewhere, 1 + their batches (0: no reader) and, of products, their positions
+struct CellNodes { u32 batch[CELL_NODES]; u32 prod[2]; u32 next[CELL_H_EDGES + 1], at[CELL_H_EDGES + 1]; };      // [0]: of h | number of nodes << 16 (a fused plan has at most 4 096 batches)
 constexpr u32 CELL_ITEM = 0x80000000u;      // in a work item's length: its tiles are CellRecs, a row each
+constexpr u32 CELL_HOLD = 0x80000000u;
 constexpr u32 CELL_WAVES = 4;               // waves of the forward kernel: a row takes one to four of them, a work item fills them
 __host__ __device__ inline u32 cell_row_waves(u32 H) { const u32 w = (H + 63u) / 64u; return w < 3u ? w : 4u; }
 
@@ -215,7 +217,8 @@ struct WorkRec { u32 first, len; };   // a workgroup runs tiles [first, first + 
 // tile), so the slot can run the lean instantiation of the forward kernel.  Bit 1: no product of the slot
 // reads its operand rows in pieces (otherwise the slot runs the instantiation that can); bit 2 clear: the slot is one chain of
 // cells that takes up every row of the slot before, all products, and the forward work of both slots is that slot's launch.
-// bit 3 clear: the slot holds gated cells.  bit 4 clear: the slot's pull does more than copy the rows of products with TF_G_ALIAS.
+// bit 3 clear: the slot holds gated cells.  bit 4 clear: the slot's pull does more than copy the rows of products with TF_G_ALIAS.  bit 5
+// clear: the slot is cells, and all they wait for in the slot after it are its products' dX tiles: one backward launch for both.
 // lminf / nlmaxf: the same pair of run lengths over the slot's forward work items (views have none).
 struct SlotRec { u32 wf, wa, tb, tf, ta, lmin, nlmax, dx_free, lds_need, plain, lminf, nlmaxf; };
 
@@ -279,6 +282,10 @@ struct Tables {
     CellNodes *cell_nodes_of;              // per cell: the batches of its nodes
     u32 *cell_prods;                       // per batch of outputs: cells that take up a product's row from the slot before theirs
     u32 *prod_cell;                        // per position of such a product: its cell
+    u32 *cell_takes;                       // per batch of outputs: cells that a product of the slot after theirs reads and nothing else of it
+                                           // (CELL_HOLD: something else does)
+    u32 *slot_cells;                       // per slot: chains of cells without CELL_HOLD (CELL_HOLD: some of their cells are so read)
+    u32 *dx_cell;                          // per position of a product: 1 + the pull tile of the cell that its operand is the output of, or 0
     u32 *slot_chains, *slot_rows;          // per slot: chains, and rows of all of them
     u32 *cell_rows, *cell_nodes;           // per batch of outputs: cells whose nodes lie in one chain, and the nodes they hold
     u32 cells_cap;

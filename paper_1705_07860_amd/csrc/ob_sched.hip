@@ -113,7 +113,8 @@ __device__ inline void node_init_part(const Tables &T, int steps, u64 *keys, u32
         if (T.cells) {
             const u32 x = hi > lo ? T.in_idx[lo] : 0u, y = hi > lo + 1u ? T.in_idx[lo + 1u] : 0u;
             T.nrec[v] = make_uint4(x, y, o, hi - lo);
-            T.cell_rows[v] = T.cell_nodes[v] = T.cell_prods[v] = T.slot_chains[v] = T.slot_rows[v] = 0;
+            T.cell_rows[v] = T.cell_nodes[v] = T.cell_prods[v] = T.cell_takes[v] = 0;
+            T.slot_chains[v] = T.slot_rows[v] = T.slot_cells[v] = T.dx_cell[v] = 0;
             if (o == OP_CMULT) {
                 const u32 ox = T.op[x], oy = T.op[y];
                 ends = (ox == OP_TANH && oy == OP_SIGMOID) || (ox == OP_SIGMOID && oy == OP_TANH);
@@ -1260,7 +1261,7 @@ __device__ inline void find_cell(const Tables &T, u32 h)
     R.ce = CellEdge{0u, 0u, 0u};
     if (nc == 2u) edge(r0 + 1u, R.ce);
     if (!ok || T.edge_cons[T.succ_edge[r0]] != tc) return;
-    R.mark = CELL_MARK; R.H = H; R.nf = nt - 1u; R.ic_at = ic_at; R.pad = 0;
+    R.mark = CELL_MARK; R.H = H; R.nf = nt - 1u; R.ic_at = ic_at; R.taken = 0;
     R.n_edges = nh | (nc - 1u) << 8;
     R.h = T.val_off[h]; R.tc = T.val_off[tc]; R.o = T.val_off[o]; R.c = T.val_off[c];
     R.S = T.val_off[S]; R.sums = sums ? 1u : 0u;
@@ -1309,6 +1310,15 @@ __device__ inline void find_cell(const Tables &T, u32 h)
             T.prod_cell[pu] = cell;
         }
     }
+    // who reads h and c
+#pragma unroll
+    for (u32 k = 0; k < CELL_H_EDGES + 1; ++k) {
+        N.next[k] = N.at[k] = 0;
+        if (k < CELL_H_EDGES ? k >= nh : nc != 2u) continue;
+        const u32 v = T.edge_cons[T.succ_edge[k < CELL_H_EDGES ? h0 + k : r0 + 1u]], pv = T.pos_of[v];
+        N.next[k] = T.batch_of_pos[pv] + 1u;
+        if (T.op[v] == OP_MATVEC) N.at[k] = pv + 1u;
+    }
     T.cell_nodes_of[cell] = N;
 }
 
@@ -1339,7 +1349,7 @@ __device__ inline void cell_in_chain(const Tables &T, u32 cell)
     const u32 lane = threadIdx.x & 63u;
     CellNodes N;
     N.batch[0] = 0;
-    bool taken = false;
+    bool taken = false, takes = false, hold = false;
     bool one = cell < T.hdr->n_cells && cell < T.cells_cap;
     if (one) {
         N = T.cell_nodes_of[cell];
@@ -1352,15 +1362,27 @@ __device__ inline void cell_in_chain(const Tables &T, u32 cell)
             const BatchRec &rp = T.batches[N.prod[k] - 1u];
             taken = taken || (T.slot_of[N.prod[k] - 1u] + 1u == slot && !(rp.vec4 & TF_WIDE) && !batch_xp(rp) && rp.d == 4u * T.batches[b].d);
         }
+        u32 reader = 0;
+#pragma unroll
+        for (u32 k = 0; k < CELL_H_EDGES + 1; ++k) {
+            if (!N.next[k] || T.slot_of[N.next[k] - 1u] != slot + 1u) continue;
+            hold = hold || takes || !N.at[k];
+            takes = true;
+            reader = N.at[k];
+        }
+        if (one && takes && !hold) T.cells[cell].taken = reader;
     }
     for (u64 todo = __ballot(one); todo;) {
         const u32 leader = (u32)__builtin_ctzll(todo), word = (u32)__shfl((int)N.batch[0], (int)leader);
         const u64 same = __ballot(one && N.batch[0] == word), with = __ballot(one && N.batch[0] == word && taken);
+        const u64 reads = __ballot(one && N.batch[0] == word && takes), held = __ballot(one && N.batch[0] == word && hold);
         if (lane == leader) {
             const u32 rows = (u32)__popcll(same);
             atomicAdd(&T.cell_rows[word & 0xffffu], rows);
             atomicAdd(&T.cell_nodes[word & 0xffffu], rows * (word >> 16));
             if (with) atomicAdd(&T.cell_prods[word & 0xffffu], (u32)__popcll(with));
+            if (reads) atomicAdd(&T.cell_takes[word & 0xffffu], (u32)__popcll(reads));
+            if (held) atomicOr(&T.cell_takes[word & 0xffffu], CELL_HOLD);
         }
         todo &= ~same;
     }
@@ -1688,6 +1710,9 @@ __device__ inline void chain_recs_at(const Tables &T, int agenda, const u32 *bse
             cr.fused = 3u; cr.pad0 = out;
             cr.Rg = CELL_WAVES / cell_row_waves(cell_d);
             kt = ktf = cr.Rg;      // a tile a row; the last block's may be left over
+            const u32 takes = T.cell_takes[out];
+            if (!(takes & CELL_HOLD)) atomicAdd(&T.slot_cells[cr.slot], 1u);
+            if (!(takes & CELL_HOLD) && takes) atomicOr(&T.slot_cells[cr.slot], CELL_HOLD);
         }
         cr.nrb = cdiv(G, cr.Rg); cr.kt = cr.fused ? kt : 1u;
         cr.ktf = cr.fused ? ktf : 1u;
@@ -1738,6 +1763,7 @@ __device__ inline void slot_tables_at(const Tables &T, const CLay *clay_ex, cons
     if (hb.op != OP_MATVEC || !(hb.vec4 & TF_G_ALIAS)) atomicAnd(&S.plain, ~16u);
     // (every row of a product taken up has one reader, so as many rows as cells are all rows of the slot before)
     if (cr.fused == 3u && s > 0 && T.slot_chains[s] == 1u && T.cell_prods[cr.pad0] == cr.G && T.slot_rows[s - 1u] == cr.G) atomicAnd(&S.plain, ~4u);
+    if (cr.fused == 3u && T.slot_cells[s] == (T.slot_chains[s] | CELL_HOLD)) atomicAnd(&S.plain, ~32u);
     if (!cr.fused) atomicAnd(&S.plain, ~1u);     // a GEMM, reduction or wide-sum batch runs in this slot
     if (batch_xp(hb) && hb.aux1 > 1) atomicAnd(&S.plain, ~2u);   // a product that reads its operand rows in pieces
     if (cr.fused == 2u) {
@@ -2143,6 +2169,7 @@ __global__ __launch_bounds__(TPB) void k_tiles(Tables T, const CLay *clay_ex, co
                     if (from) {
 #pragma unroll
                         for (u32 q = 0; q < sizeof(PullDesc) / 16; ++q) to[q] = from[q];
+                        if (const u32 taken = ((const CellRec *)from)->taken) T.dx_cell[taken - 1u] = x + 1u;
                     } else to[0] = make_uint4(0u, 0u, 0u, 0u);
                 }
             } else if (which == 2 || (which == 0 && !cr.fused)) {
@@ -2761,6 +2788,7 @@ int sched_enqueue(ob_ctx *ctx)
     A(T.queue, u32, n);
     A(T.ht_slot, u32, n);
     T.ht_mask = ht_size - 1;
+    T.dx_cell = T.indeg;            // (plans with cells are fused ones, and those of them that count operands down do so before they look for cells)
     A(T.order, u32, n); A(T.pos_of, u32, n); A(T.batch_of_pos, u32, n); A(T.s_aux0, u32, n);
     A(T.s_in_off, u32, n + 1);
     A(T.batch_off, u32, n + 1); A(T.batches, BatchRec, n); A(T.lay, Lay, n); A(T.b_indim, u32, E + (size_t)XP_MAX * n + 1);
@@ -2818,7 +2846,8 @@ int sched_enqueue(ob_ctx *ctx)
         };
         table(T.nrec, n); table(T.cell_nodes_of, T.cells_cap); table(T.cell_of, n); table(T.prod_cell, n);
         table(T.cell_ends, n); table(T.cell_ends_n, blocks_for(n));
-        table(T.cell_rows, n); table(T.cell_nodes, n); table(T.cell_prods, n); table(T.slot_chains, n); table(T.slot_rows, n);
+        table(T.cell_rows, n); table(T.cell_nodes, n); table(T.cell_prods, n); table(T.cell_takes, n); table(T.slot_cells, n);
+        table(T.slot_chains, n); table(T.slot_rows, n);
         table(T.cells, T.cells_cap);
         if (!room) { T.cells = nullptr; ctx->top = before; }
     }

@@ -565,6 +565,58 @@ def test_cells_behind_products_in_one_launch(H, K, rows, dirs, first):
             assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
+@pytest.mark.parametrize("H,rows,dirs,reader", [(2, 3, 1, ""), (16, 16, 1, "late"), (17, 17, 2, "late"), (40, 49, 1, "beside"), (33, 261, 1, "late"),
+                                                (64, 292, 2, ""), (256, 20, 1, "both")])
+def test_cells_worked_in_the_tiles_of_the_products_behind_them(H, rows, dirs, reader):
+    """Backward, cells whose outputs are a product's operands are worked in the tiles of the product's dX (of 16 x 16, from 256 rows
+    on 32 x 32), the others of their slot (rows end one by one) beside them: the bits of a launch per batch.  reader: what else reads the
+    outputs; with a component-wise reader or a second product beside the first the two slots keep their launches."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(H + rows)
+    pb = wl.ParamBuilder(rng, std=0.3)
+    U = [pb.add(f"U{k}", 4 * H, H) for k in range(dirs)]
+    Q = pb.add("Q", 4 * H, H)
+    p = pb.done()
+    g = wl.GraphBuilder(p)
+    h = [[g.input(rng.standard_normal(H)) for _ in range(dirs)] for _ in range(rows)]
+    c = [[g.input(rng.standard_normal(H)) for _ in range(dirs)] for _ in range(rows)]
+    losses, outs = [], []
+    for step in range(4):
+        for r in range(rows - step):
+            for k in range(dirs):
+                x = g.input(rng.standard_normal(4 * H))
+                if reader == "both":
+                    x = g.matvec(Q, -1, h[r][k])
+                s = g.add((x, g.matvec(U[k], -1, h[r][k])))
+                if reader == "beside" and step:
+                    s = g.add((s, g.concat([g.tanh(h[r][k])] * 4)))
+                i, f, o, cand = (g.slice(s, q * H, (q + 1) * H) for q in range(4))
+                c[r][k] = g.add((g.cmult(g.sigmoid(f), c[r][k]), g.cmult(g.sigmoid(i), g.tanh(cand))))
+                h[r][k] = g.cmult(g.sigmoid(o), g.tanh(c[r][k]))
+                outs.append(h[r][k])
+    if reader == "late":
+        losses = [g.sqnorm(g.tanh(v)) for v in outs]
+    else:
+        losses = [g.sqnorm(g.tanh(v)) for row in h for v in row]
+    gr = g.finish(g.add(losses), rows)
+    o = Oracle(gr, p, "f64")
+    o.forward()
+    o.backward(gr.root)
+    total = int(gr.out_dim.sum())
+    out = []
+    for level in (0, 1, 2):
+        ctx, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=512 << 20)
+        check_against_oracle(ctx, p, gr, o, root, what=f"cells before products {H} {rows} level {level}")
+        out.append([ctx.all_read(0, total), ctx.all_read(1, total)] + [ctx.param_grad_read(q, m.shape) for q, m in enumerate(p.mats)])
+        st = ctx.stats()
+        ctx.close()
+    say(f"  {st['n_launch_bwd_steps']} backward launches of {st['n_slots']} slots")
+    assert (st["n_launch_bwd_steps"] < st["n_slots"]) == (reader in ("", "late")), (st["n_launch_bwd_steps"], st["n_slots"])
+    for level in (1, 2):
+        for x, y in zip(out[0], out[level]):
+            assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+
+
 @pytest.mark.parametrize("rows", [257, 258, 259, 260])
 def test_cells_behind_products_of_256_rows(rows):
     """From 256 rows on, products of 64 columns and more are worked in larger tiles and keep a launch of their own; narrower

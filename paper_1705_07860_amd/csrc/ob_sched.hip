@@ -1857,11 +1857,34 @@ __device__ inline u32 chain_own_delta(const Tables &T, const ChainCtx &cc, const
     return lds - (r.val_off + cc.g0 * (r.B / cc.cr.G) * r.d);
 }
 
+// Which tile of a product the t-th workgroup of its launch takes.  Workgroup g runs on XCD g % 8, every XCD has its own L2, and all L2s are
+// cold when a launch starts, so what an XCD reads is the rows and the columns of its tiles.  The eight XCDs are therefore laid out as
+// pr x pc over the tiles, whichever reads least: rows / pr + columns / pc, both as long as the contraction.  (With pr = 1
+// throughout, dX of 512 rows a direction had every XCD read all 4 MB of gradients.)
+__device__ inline u32 xcd_tile(u32 t, u32 ntr, u32 ntn, u32 rows, u32 cols)
+{
+    u32 best = 0xffffffffu, pr = 0;
+#pragma unroll
+    for (u32 p = 1; p <= 8; p *= 2) {
+        const u32 reads = rows / p + cols / (8u / p);
+        if (p <= ntr && ntn % (8u / p) == 0u && reads < best) { best = reads; pr = p; }
+    }
+    if (!pr) return t;
+    const u32 pc = 8u / pr, npc = ntn / pc;
+    if (t >= ntr / pr * pr * ntn) return t;       // rows of tiles that are left over
+    const u32 x = t & 7u, j = t >> 3;
+    return ((j / npc) * pr + x % pr) * ntn + (j % npc) * pc + x / pr;
+}
+
 // descriptor of a forward or dX tile of batch r.  Component-wise tiles (row_block) cover the rows
 // row0 + i * rstride, i < nrows; the other kinds derive their rows from the tile index t.
 __device__ inline void fill_tile_desc(const Tables &T, const BatchRec &r, u32 t, bool dx, bool row_block, u32 row0,
                                       u32 nrows, u32 rstride, TileDesc &d, bool in_chain, const ChainCtx &cc)
 {
+    if (r.op == OP_MATVEC && !row_block) {
+        const u32 edge = dx ? dx_tile_edge(r.vec4, r.k) : (r.vec4 & TF_WIDE) ? (u32)GTW : (u32)GT, cols = dx ? r.k : r.d;
+        t = xcd_tile(t, cdiv(r.B, edge), cdiv(cols, edge), r.B, cols);
+    }
     d.op = r.op; d.B = r.B; d.d = r.d; d.arity = r.arity;
     d.pos0 = r.pos0; d.val_off = r.val_off; d.dx_off = r.dx_off; d.k = r.k;
     d.aux0 = r.aux0; d.rstride = rstride;

@@ -532,6 +532,10 @@ struct AgendaTables {
     u32 *cls;         // [n] rank of each node's signature
     u32 *pending;     // [n] unresolved operands
     u32 *seg;         // [n] ready lists, one segment per rank (each node is appended once)
+    // for graphs whose counters fit into LDS
+    uint2 *edge_to;   // [E] per entry of the successor lists: consumer, rank of its signature (AG_LONG: with more operands than AG_FEW)
+    uint2 *edge_succ; // [E] and that consumer's own successor list, first entry and end
+    uint4 *ready;     // [n] ready lists of nodes with their successor lists
 };
 
 __device__ inline u32 ag_cost_class(u32 op)
@@ -708,6 +712,106 @@ __global__ __launch_bounds__(AGENDA_THREADS) void k_agenda(Tables T, AgendaTable
         __syncthreads();
     }
     if (tid == 0 && s_done != T.n) atomicOr(&T.hdr->err, (u32)ERR_CYCLE);
+}
+
+// The same agenda for up to AG_LDS_NODES nodes.  What bounds it is the chain of dependent reads of an iteration, so the counters of
+// unresolved operands are in LDS, four bits a node (a node with more than AG_FEW operands keeps its word in memory), an entry of a
+// successor list brings the consumer's rank and successor list with it, and so does an entry of a ready list: a batch reads its
+// entries, then their successors, then counts, where it read entry, list bounds, successors and counters in turn.  Every wave finds the
+// lowest rank for itself, which takes two barriers an iteration instead of four.  64 parsed sentences, 662 batches: 1 232 -> 894 us (with 1 024
+// threads and four consumers side by side 966: half of all nodes have one consumer, and what is issued for absent ones counts; with
+// 256 threads 912, with 128 1 045).
+constexpr u32 AG_LDS_THREADS = 512, AG_SIDE = 2;
+constexpr u32 AG_LDS_WORDS = 32768, AG_LDS_NODES = 8 * AG_LDS_WORDS, AG_FEW = 14, AG_LONG = 0x80000000u;
+__global__ void k_agenda_edges(Tables T, AgendaTables A, const u32 *succ_node)
+{
+    const u32 q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= T.E) return;
+    const u32 v = succ_node[q];
+    A.edge_to[q] = make_uint2(v, A.cls[v] | (T.in_off[v + 1] - T.in_off[v] > AG_FEW ? AG_LONG : 0u));
+    A.edge_succ[q] = make_uint2(T.succ_off[v], T.succ_off[v + 1]);
+}
+__global__ __launch_bounds__(AG_LDS_THREADS) void k_agenda_lds(Tables T, AgendaTables A)
+{
+    __shared__ u32 s_head[AG_MAX_CLASSES], s_tail[AG_MAX_CLASSES], s_off[AG_MAX_CLASSES + 1], s_count[AG_LDS_WORDS];
+    constexpr u32 COUNT = (1u << AG_COUNT_BITS) - 1u;
+    if (T.hdr->err & ERR_CLASSES) return;      // (not every node has a rank)
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 C = A.n_classes[0] < AG_MAX_CLASSES ? A.n_classes[0] : AG_MAX_CLASSES;
+    for (u32 c = tid; c < C; c += AG_LDS_THREADS) { s_head[c] = 0; s_tail[c] = 0; }
+    for (u32 c = tid; c <= C; c += AG_LDS_THREADS) s_off[c] = A.seg_off[c];
+    __syncthreads();
+    for (u32 w = tid; 8u * w < T.n; w += AG_LDS_THREADS) {
+        u32 p[8], word = 0;
+#pragma unroll
+        for (u32 k = 0; k < 8; ++k) p[k] = 8u * w + k < T.n ? A.pending[8u * w + k] : 1u;
+#pragma unroll
+        for (u32 k = 0; k < 8; ++k) {
+            const u32 v = 8u * w + k, count = p[k] & COUNT, c = p[k] >> AG_COUNT_BITS;
+            word |= (count <= AG_FEW ? count : AG_FEW + 1u) << (4u * k);
+            if (count == 0u) A.ready[s_off[c] + atomicAdd(&s_tail[c], 1u)] = make_uint4(v, T.succ_off[v], T.succ_off[v + 1], 0u);
+        }
+        s_count[w] = word;
+    }
+    // The lists of successors were written all over the chip: brought into this XCD's L2 first, side by side.
+    u32 sink = 0;
+    for (u32 x0 = tid; x0 < T.E; x0 += 8u * AG_LDS_THREADS) {
+        u32 a[8], b[8];
+#pragma unroll
+        for (u32 k = 0; k < 8; ++k) {
+            const u32 x = x0 + k * AG_LDS_THREADS < T.E ? x0 + k * AG_LDS_THREADS : x0;
+            a[k] = A.edge_to[x].x; b[k] = A.edge_succ[x].x;
+        }
+#pragma unroll
+        for (u32 k = 0; k < 8; ++k) sink |= a[k] | b[k];
+    }
+    asm volatile("" :: "v"(sink));
+    u32 done = 0, prev = AG_NONE, prev_hi = 0;
+    for (u32 t = 0;; ++t) {
+        __syncthreads();
+        u32 c = AG_NONE, lo = 0, hi = 0;
+        for (u32 c0 = 0; c0 < C && c == AG_NONE; c0 += 64u) {
+            const u32 k = c0 + lane;
+            const u32 head = k == prev ? prev_hi : (k < C ? s_head[k] : 0u), tail = k < C ? s_tail[k] : 0u;
+            const u64 some = __ballot(tail > head);
+            if (!some) continue;
+            const int l = __builtin_ctzll(some);
+            c = c0 + (u32)l; lo = (u32)__builtin_amdgcn_readlane((int)head, l); hi = (u32)__builtin_amdgcn_readlane((int)tail, l);
+        }
+        __syncthreads();                  // (every wave has looked: heads and tails may move)
+        if (c == AG_NONE) break;          // nothing available: all done, or a cycle
+        if (tid == 0 && prev != AG_NONE) s_head[prev] = prev_hi;
+        const u32 base = s_off[c];
+        for (u32 i = lo + tid; i < hi; i += AG_LDS_THREADS) {
+            const uint4 e = A.ready[base + i];
+            T.step[e.x] = t;
+            for (u32 q = e.y; q < e.z; q += AG_SIDE) {
+                uint2 to[AG_SIDE], next[AG_SIDE];
+                u32 left[AG_SIDE];
+#pragma unroll
+                for (u32 k = 0; k < AG_SIDE; ++k) {
+                    const u32 x = q + k < e.z ? q + k : q;
+                    to[k] = A.edge_to[x]; next[k] = A.edge_succ[x];
+                }
+#pragma unroll
+                for (u32 k = 0; k < AG_SIDE; ++k) {
+                    left[k] = 0u;
+                    if (q + k >= e.z) continue;
+                    const u32 v = to[k].x, at = 4u * (v & 7u);
+                    left[k] = to[k].y & AG_LONG ? atomicSub(&A.pending[v], 1u) & COUNT : (atomicSub(&s_count[v >> 3], 1u << at) >> at) & 15u;
+                }
+#pragma unroll
+                for (u32 k = 0; k < AG_SIDE; ++k) {
+                    if (left[k] != 1u) continue;
+                    const u32 cs = to[k].y & ~AG_LONG;
+                    A.ready[s_off[cs] + atomicAdd(&s_tail[cs], 1u)] = make_uint4(to[k].x, next[k].x, next[k].y, 0u);
+                }
+            }
+        }
+        prev = c; prev_hi = hi;
+        done += hi - lo;
+    }
+    if (tid == 0 && done != T.n) atomicOr(&T.hdr->err, (u32)ERR_CYCLE);
 }
 
 // ---- stage 3: batch representative = smallest node id with the same (depth, signature) ------
@@ -2915,7 +3019,14 @@ int sched_enqueue(ob_ctx *ctx)
                 K(k_class_insert, n, T, AG);
                 hipLaunchKernelGGL(k_class_rank, dim3(1), dim3(1024), 0, s, T, AG);
                 K(k_class_of, n, T, AG);
-                hipLaunchKernelGGL(k_agenda, dim3(1), dim3(AGENDA_THREADS), 0, s, T, AG, succ_node);
+                if (n <= AG_LDS_NODES && E > 0) {
+                    // (the sort's buffers and the scans' counts are not in use yet)
+                    AG.edge_to = (uint2 *)ctx->key_a; AG.edge_succ = (uint2 *)ctx->key_b; AG.ready = (uint4 *)tri_in;
+                    K(k_agenda_edges, E, T, AG, succ_node);
+                    hipLaunchKernelGGL(k_agenda_lds, dim3(1), dim3(AG_LDS_THREADS), 0, s, T, AG);
+                } else {
+                    hipLaunchKernelGGL(k_agenda, dim3(1), dim3(AGENDA_THREADS), 0, s, T, AG, succ_node);
+                }
                 ctx->n_launch_sched += 2;
             }
             hipLaunchKernelGGL(k_rep_insert, dim3(blocks_for(n, REP_THREADS)), dim3(REP_THREADS), 0, s, T);

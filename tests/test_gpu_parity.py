@@ -1625,6 +1625,35 @@ def test_long_chain_uses_the_unfused_plan_and_the_long_slot_table():
     c.close()
 
 
+@pytest.mark.parametrize("arities,copies", [((13, 14, 15, 16, 17), 40), ((2, 14, 15, 300), 7), ((1,), 131_070), ((1,), 131_080)])
+def test_agenda_counters_of_few_and_many_operands(arities, copies):
+    """Agenda counters of four bits hold up to fourteen operands, longer lists are counted in memory, also where a node is an
+    operand more than once; graphs of up to 262 144 nodes have them in LDS (the last two lie on either side)."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(copies)
+    pb = wl.ParamBuilder(rng, std=0.3)
+    p = pb.done() if len(arities) == 1 else None
+    if p is None:
+        pb.add("E", 3, 4)
+        p = pb.done()
+    g = wl.GraphBuilder(p)
+    nodes = [g.input(rng.standard_normal(4)) for _ in range(copies if len(arities) == 1 else 60)]
+    if len(arities) == 1:
+        out = [g.sqnorm(v) for v in nodes]
+    else:
+        for k in range(copies):
+            for a in arities:
+                nodes.append(g.add([nodes[int(q)] for q in rng.integers(max(0, len(nodes) - 200), len(nodes), a)]))
+                nodes.append(g.tanh(nodes[-1]))
+        out = [g.sqnorm(v) for v in nodes[60:]]
+    gr = g.finish(g.add(out), 1)
+    c, root = run_gpu(p, gr, ob.OB_BYAGENDA, arena=1 << 30)
+    bo, ids, _, _ = c.schedule_read()
+    want = S.by_agenda(gr)
+    assert np.array_equal(bo, want[0]) and np.array_equal(ids, want[1])
+    c.close()
+
+
 def test_agenda_rejects_more_signatures_than_it_can_rank():
     """1100 slices with pairwise different ranges are 1100 signatures; agenda mode ranks at most
     1024 and must fail cleanly (depth-based batching takes the same graph)."""

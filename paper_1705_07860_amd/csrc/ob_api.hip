@@ -833,7 +833,12 @@ int ob_upload(ob_ctx *ctx)
     ctx->top = ctx->persist_top;
     if (ctx->params_dirty)
         if (int rc = upload_param_tables(ctx)) return rc;
-    if (!ctx->hdr_pinned) HIP_TRY(ctx, hipHostMalloc(&ctx->hdr_pinned, PINNED_BYTES, hipHostMallocDefault));
+    if (!ctx->hdr_pinned) {
+        HIP_TRY(ctx, hipHostMalloc(&ctx->hdr_pinned, PINNED_BYTES, hipHostMallocCoherent));
+        // (no launch has left its number here)
+        *(u32 *)((char *)ctx->hdr_pinned + PLAN_DONE_AT) = 0;
+        *(u32 *)((char *)ctx->hdr_pinned + READ_AT + 4) = 0;
+    }
 
     const size_t n = ctx->op.size(), E = ctx->in_idx.size(), P = ctx->payload.size();
     // one block of the arena: op | out_dim | in_off | in_idx | param | bias | aux0 | aux1 | payload | labels,
@@ -1394,8 +1399,8 @@ static int node_read(ob_ctx *ctx, int node, float *out, size_t cap, bool grad)
     u32 *head = (u32 *)((char *)ctx->hdr_pinned + READ_AT);
     float *row = (float *)(head + 4);
     const u32 here = d < (u32)READ_FLOATS ? d : (u32)READ_FLOATS;
-    HIP_TRY(ctx, exec_node_read(grad ? ctx->T.nat_off : ctx->T.val_off, arena, (u32)node, here, head, row, ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    HIP_TRY(ctx, exec_node_read(grad ? ctx->T.nat_off : ctx->T.val_off, arena, (u32)node, here, head, row, ++ctx->read_number, ctx->stream));
+    if (!pinned_done(head + 1, ctx->read_number)) HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     memcpy(out, row, (size_t)here * 4);
     if (here < d) {
         HIP_TRY(ctx, hipMemcpyAsync(out + here, arena + head[0] + here, (size_t)(d - here) * 4, hipMemcpyDeviceToHost, ctx->stream));

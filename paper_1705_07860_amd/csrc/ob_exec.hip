@@ -2013,11 +2013,13 @@ __global__ void k_fill_product_grads(Tables T)
 // read is one launch and one wait.  What bounds it is the round trip to the host, so what counts is how many there
 // are: looking the offset up by a copy of its own, waiting, and then copying the row took two.  Tagging one sentence
 // of 20 tokens and reading its 20 score rows: 1 630 -> 920 us.
-__global__ __launch_bounds__(WG) void k_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row)
+__global__ __launch_bounds__(WG) void k_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row,
+                                                   u32 number)
 {
     const u32 off = off_tab[node];
     if (threadIdx.x == 0) head[0] = off;
     for (u32 c = threadIdx.x; c < count; c += WG) row[c] = arena[off + c];
+    pinned_release(head + 1, number);
 }
 
 // The graph's arrays, read where they lie in page-locked host memory: one launch instead of a copy each.
@@ -2306,9 +2308,9 @@ hipError_t exec_upload(const UploadList &L, char *dst, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, hipStream_t s)
+hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, u32 number, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_node_read, dim3(1), dim3(WG), 0, s, off_tab, arena, node, count, head, row);
+    hipLaunchKernelGGL(k_node_read, dim3(1), dim3(WG), 0, s, off_tab, arena, node, count, head, row, number);
     return hipGetLastError();
 }
 

@@ -338,7 +338,14 @@ hipError_t exec_fill_uncopied(const Tables &T, hipStream_t s);
 hipError_t exec_fill_product_grads(const Tables &T, hipStream_t s);
 struct UploadList { const void *src[10]; size_t bytes[10], at[10]; };   // host arrays and where they go in one device block
 hipError_t exec_upload(const UploadList &L, char *dst, hipStream_t s);
-hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, hipStream_t s);
+hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, u32 number, hipStream_t s);
+// the last of a launch's writes to page-locked memory: everything the workgroup has written there is there before `number` is
+__device__ inline void pinned_release(u32 *word, u32 number)
+{
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(word, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 hipError_t exec_gather_some(const Tables &T, int which, float *dst, const u32 *dst_off, hipStream_t s);
 hipError_t exec_stage_fill(const float *V, const u32 *val_off, const u32 *src, const u32 *dst, const u32 *dim, u32 count,
                            float *payload, hipStream_t s);

@@ -2824,12 +2824,14 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_plan_small(SmallArgs)
 
 // The header and the slot entries in use, written straight to page-locked host memory: one launch where two
 // copies in a row (the second of the whole window, 96 KB) each had a start of their own.
-__global__ void k_read_back(Tables T, u32 *hdr, u32 *slots, u32 window)
+constexpr int READ_BACK_THREADS = 1024;
+__global__ __launch_bounds__(READ_BACK_THREADS) void k_read_back(Tables T, u32 *hdr, u32 *slots, u32 window, u32 number)
 {
-    const u32 i = blockIdx.x * blockDim.x + threadIdx.x, all = gridDim.x * blockDim.x;
+    const u32 i = threadIdx.x, all = READ_BACK_THREADS;
     if (i < sizeof(SchedHeader) / 4) hdr[i] = ((const u32 *)T.hdr)[i];
     const u32 used = T.hdr->n_slots + 1, count = (used < window ? used : window) * (u32)(sizeof(SlotRec) / 4);
     for (u32 k = i; k < count; k += all) slots[k] = ((const u32 *)T.slots)[k];
+    pinned_release(hdr + PLAN_DONE_AT / 4, number);
 }
 
 inline int bit_width_u32(u32 x) { int b = 0; while (x) { ++b; x >>= 1; } return b; }
@@ -3092,7 +3094,7 @@ int sched_enqueue(ob_ctx *ctx)
     // pinned layout: [header 256 B][first hdr_window entries of the slot table]
     ctx->hdr_window = (u32)(slot_cap < SLOT_WINDOW ? slot_cap : SLOT_WINDOW);
     char *hp = (char *)ctx->hdr_pinned;
-    hipLaunchKernelGGL(k_read_back, dim3(8), dim3(TPB), 0, s, T, (u32 *)hp, (u32 *)(hp + 256), ctx->hdr_window);
+    hipLaunchKernelGGL(k_read_back, dim3(1), dim3(READ_BACK_THREADS), 0, s, T, (u32 *)hp, (u32 *)(hp + 256), ctx->hdr_window, ++ctx->plan_number);
     HIP_TRY(ctx, hipGetLastError());
     ++ctx->n_launch_sched;
     ctx->n_items_sched = n_items;
@@ -3107,8 +3109,8 @@ int sched_finish(ob_ctx *ctx)
     hipStream_t s = ctx->sched_stream;
     // wait for this context's own scheduling work only (its event was recorded behind the launch
     // that writes the header): other contexts may already have queued theirs on the same stream
-    HIP_TRY(ctx, hipEventSynchronize(ctx->ev[9]));
     const char *hp = (const char *)ctx->hdr_pinned;
+    if (!pinned_done((const u32 *)(hp + PLAN_DONE_AT), ctx->plan_number)) HIP_TRY(ctx, hipEventSynchronize(ctx->ev[9]));
     ctx->hdr = *(const SchedHeader *)hp;
     if ((ctx->hdr.err & ERR_CYCLE) && ctx->depth_partitioned) {
         // A range of the partitioned depth pass ran into the bound on its wait for another range.

@@ -27,8 +27,12 @@ constexpr int GTW = 64;               // forward GEMM tile edge of batches with 
 constexpr u32 WIDE_MIN_ROWS = 256;
 constexpr int DXT = 16;               // dX GEMM tile edge (16x16 blocks: its output is small, more tiles fill more CUs)
 constexpr int DXTW = 32;              // dX tile edge of batches with at least WIDE_MIN_ROWS rows (when the matrix has 32+ columns)
-// 8u = TF_WIDE of the batch flags
-__host__ __device__ inline u32 dx_tile_edge(u32 batch_flags, u32 k) { return ((batch_flags & 8u) && k >= (u32)DXTW) ? (u32)DXTW : (u32)DXT; }
+// Slots with at least this many elements of dX keep the chip filled with tiles of the larger edge, whatever batches they lie in: two
+// workgroups of the backward kernel on each of 256 units.  Below it the smaller tiles, of which there are four times as many, end sooner.
+// (64 parsed sentences, the products over all feature rows: 149 and 39 -> 75 and 17 us; 512 tagged ones: 154 and 70 -> 85 and 41.)
+constexpr u32 DX_LARGE_SLOT = 2u * 256u * DXTW * DXTW;
+// 8u, 16384u = TF_WIDE, TF_DX_LARGE of the batch flags
+__host__ __device__ inline u32 dx_tile_edge(u32 batch_flags, u32 k) { return ((batch_flags & (8u | 16384u)) && k >= (u32)DXTW) ? (u32)DXTW : (u32)DXT; }
 constexpr int ROWS_PER_RED_TILE = 4;  // rows of one row-reduction tile (one wave per row)
 constexpr int WIDE_ADD_ARITY = 9;     // ADD with at least this many operands reduces per row
 constexpr u32 VAL_ALIGN = 64;         // batch blocks start at multiples of 64 floats (256 B)
@@ -50,6 +54,7 @@ enum : u32 {
     TF_VIRT = 4096u,         // batch flag: a CONCAT batch that only matrix products read; its rows are not written by the forward
                              // pass, the products read the pieces where their producers left them (TF_XP).  The rows are filled
                              // in when a value is read from outside the forward pass.
+    TF_DX_LARGE = 16384u,    // batch flag: a MATVEC batch in a slot of many dX elements (DX_LARGE_SLOT): the larger dX tiles
     TF_XP = 8192u            // batch flag: a MATVEC batch whose operand is read piece by piece (BatchRec::aux1 pieces of
                              // the dimensions b_indim[indim ..]); piece q of row r lies at opnd_off[opnd + q * B + r] + k for the
                              // contraction indices k of the piece (the piece's first index is already subtracted)
@@ -285,6 +290,7 @@ struct Tables {
     u32 *cell_takes;                       // per batch of outputs: cells that a product of the slot after theirs reads and nothing else of it
                                            // (CELL_HOLD: something else does)
     u32 *slot_cells;                       // per slot: chains of cells without CELL_HOLD (CELL_HOLD: some of their cells are so read)
+    u32 *slot_dx;                          // per slot: elements of dX
     u32 *dx_cell;                          // per position of a product: 1 + the pull tile of the cell that its operand is the output of, or 0
     u32 *slot_chains, *slot_rows;          // per slot: chains, and rows of all of them
     u32 *cell_rows, *cell_nodes;           // per batch of outputs: cells whose nodes lie in one chain, and the nodes they hold

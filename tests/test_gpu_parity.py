@@ -617,6 +617,31 @@ def test_cells_worked_in_the_tiles_of_the_products_behind_them(H, rows, dirs, re
             assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
+@pytest.mark.parametrize("K,rows", [(64, 8191), (64, 8193), (33, 15888), (33, 15889), (128, 4200)])
+def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows):
+    """A slot with 524 288 elements of dX and more has the larger dX tiles whatever its batches are: products of `rows` rows in three
+    batches of one slot (by how deep their operands lie), ragged in rows and columns, against the oracle."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(K + rows)
+    pb = wl.ParamBuilder(rng, std=0.3)
+    W, E = pb.add("W", 21, K), pb.add("E", 50, K)
+    p = pb.done()
+    g = wl.GraphBuilder(p)
+    losses = []
+    for r in range(rows):
+        x = g.lookup(E, r % 50)
+        for _ in range(0 if r < 200 else 1 + r % 2):
+            x = g.tanh(x)
+        losses.append(g.sqnorm(g.tanh(g.slice(g.matvec(W, -1, x), 3, 20))))
+    gr = g.finish(g.add(losses), rows)
+    o = Oracle(gr, p, "f64")
+    o.forward()
+    o.backward(gr.root)
+    c, root = run_gpu(p, gr, ob.OB_BYDEPTH, arena=1 << 30)
+    check_against_oracle(c, p, gr, o, root, what=f"dX of {rows} x {K}")
+    c.close()
+
+
 @pytest.mark.parametrize("rows", [257, 258, 259, 260])
 def test_cells_behind_products_of_256_rows(rows):
     """From 256 rows on, products of 64 columns and more are worked in larger tiles and keep a launch of their own; narrower

@@ -182,8 +182,8 @@ struct CellRec {
 static_assert(sizeof(CellRec) == sizeof(PullDesc), "a CellRec takes a PullDesc's place");
 constexpr u32 CELL_NODES = 4 + CELL_FORGET + 1 + 2 * (CELL_FORGET + 3);
 // prod: 1 + the batches of the rows whose sum S is, where they are products that nobody else reads (else 0)
-// next, at: of the readers of h and c from elsewhere, 1 + their batches (0: no reader) and, of products, their positions
-struct CellNodes { u32 batch[CELL_NODES]; u32 prod[2]; u32 next[CELL_H_EDGES + 1], at[CELL_H_EDGES + 1]; };      // [0]: of h | number of nodes << 16 (a fused plan has at most 4 096 batches)
+// next: of the readers of h and (last) of c from elsewhere, 1 + their batches (0: no reader); at: 1 + the positions of the products that read h
+struct CellNodes { u32 batch[CELL_NODES]; u32 prod[2]; u32 next[CELL_H_EDGES + 1], at[CELL_H_EDGES]; };      // [0]: of h | number of nodes << 16 (a fused plan has at most 4 096 batches)
 constexpr u32 CELL_ITEM = 0x80000000u;      // in a work item's length: its tiles are CellRecs, a row each
 constexpr u32 CELL_HOLD = 0x80000000u;
 constexpr u32 CELL_WAVES = 4;               // waves of the forward kernel: a row takes one to four of them, a work item fills them

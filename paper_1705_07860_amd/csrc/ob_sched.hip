@@ -1417,11 +1417,12 @@ __device__ inline void find_cell(const Tables &T, u32 h)
     // who reads h and c
 #pragma unroll
     for (u32 k = 0; k < CELL_H_EDGES + 1; ++k) {
-        N.next[k] = N.at[k] = 0;
+        N.next[k] = 0;
+        if (k < CELL_H_EDGES) N.at[k] = 0;
         if (k < CELL_H_EDGES ? k >= nh : nc != 2u) continue;
         const u32 v = T.edge_cons[T.succ_edge[k < CELL_H_EDGES ? h0 + k : r0 + 1u]], pv = T.pos_of[v];
         N.next[k] = T.batch_of_pos[pv] + 1u;
-        if (T.op[v] == OP_MATVEC) N.at[k] = pv + 1u;
+        if (k < CELL_H_EDGES && T.op[v] == OP_MATVEC) N.at[k] = pv + 1u;
     }
     T.cell_nodes_of[cell] = N;
 }
@@ -1470,9 +1471,11 @@ __device__ inline void cell_in_chain(const Tables &T, u32 cell)
 #pragma unroll
         for (u32 k = 0; k < CELL_H_EDGES + 1; ++k) {
             if (!N.next[k] || T.slot_of[N.next[k] - 1u] != slot + 1u) continue;
-            hold = hold || takes || !N.at[k];
+            // (a product's dX tiles work the cells whose outputs are its operands: one that reads c holds them like any other reader)
+            const u32 product = k < CELL_H_EDGES ? N.at[k] : 0u;
+            hold = hold || takes || !product;
             takes = true;
-            reader = N.at[k];
+            reader = product;
         }
         if (one && takes && !hold) T.cells[cell].taken = reader;
     }

@@ -21,9 +21,12 @@ def say(msg):
     sys.stdout.flush()
 
 
-def run_gpu(p, g, mode, launch=0, arena=2 << 30, n_nodes=None, fuse=2, labels=None):
+def run_gpu(p, g, mode, launch=0, arena=2 << 30, n_nodes=None, fuse=2, labels=None, nan=False):
+    """nan: the arena starts as NaN, so that rows which nobody writes do not hold what an earlier run of the same graph left there."""
     from paper_1705_07860_amd import binding as ob
     c = ob.Context(arena_bytes=arena, mode=mode, launch=launch)
+    if nan:
+        c._arena.fill_(255)
     c.set_fusion(int(fuse))
     pids = c.params_create(p)
     assert pids == list(range(len(p.mats)))
@@ -615,6 +618,61 @@ def test_cells_worked_in_the_tiles_of_the_products_behind_them(H, rows, dirs, re
     for level in (1, 2):
         for x, y in zip(out[0], out[level]):
             assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+
+
+def _states_through_matrices(H, rows, reads):
+    """Two LSTM steps whose cells share their batches; rows then go on through their output h, or (a decoder started from an encoder's
+    state) through their state c and a fresh state, and end a step later.  reads, for the rows that go on through c: what h is read by
+    ("late": a loss at the end, "unread", "also": a product of the same slot); "all": every row goes on through c."""
+    rng = np.random.default_rng(H + rows)
+    pb = wl.ParamBuilder(rng, std=0.3)
+    U, V, Q = pb.add("U", 4 * H, H), pb.add("V", 4 * H, H), pb.add("Q", 4 * H, H)
+    p = pb.done()
+    g = wl.GraphBuilder(p)
+    losses = []
+    for r in range(rows):
+        h, c = g.input(rng.standard_normal(H)), g.input(rng.standard_normal(H))
+        late = []
+        for step in range(4):
+            through_c = step == 2 and (r % 3 == 1 or reads == "all")
+            if through_c:
+                x = g.matvec(Q, -1, h) if reads == "also" else g.input(rng.standard_normal(4 * H))
+                if reads == "late":
+                    late.append(h)
+                s = g.add((x, g.matvec(V, -1, c)))
+                c = g.input(rng.standard_normal(H))
+            else:
+                s = g.add((g.input(rng.standard_normal(4 * H)), g.matvec(U, -1, h)))
+            i, f, o, cand = (g.slice(s, q * H, (q + 1) * H) for q in range(4))
+            c = g.add((g.cmult(g.sigmoid(f), c), g.cmult(g.sigmoid(i), g.tanh(cand))))
+            h = g.cmult(g.sigmoid(o), g.tanh(c))
+        losses += [g.sqnorm(g.tanh(v)) for v in late + [h]]
+    return p, g.finish(g.add(losses), rows)
+
+
+@pytest.mark.parametrize("H,rows,reads", [(20, 7, "late"), (20, 7, "unread"), (16, 9, "also"), (64, 33, "all"), (33, 400, "late"), (40, 270, "all")])
+def test_products_that_read_the_state_of_a_cell(H, rows, reads):
+    """A product of the slot behind a cell may read the cell's state c instead of its output h: its dX is no gradient of h, and the cell
+    must not be worked in its tiles.  Against the oracle, and the bits of a launch per batch, in every batching mode."""
+    from paper_1705_07860_amd import binding as ob
+    p, g = _states_through_matrices(H, rows, reads)
+    o = Oracle(g, p, "f64")
+    o.forward()
+    o.backward(g.root)
+    total = int(g.out_dim.sum())
+    bo, ids, _ = S.by_depth(g)
+    labels = np.zeros(g.n, np.int64)
+    labels[ids] = np.repeat(np.arange(len(bo) - 1), np.diff(bo))
+    for mode in (ob.OB_BYDEPTH, ob.OB_BYAGENDA, ob.OB_MANUAL):
+        out = []
+        for level in (0, 1, 2):
+            c, root = run_gpu(p, g, mode, fuse=level, arena=512 << 20, labels=labels if mode == ob.OB_MANUAL else None, nan=True)
+            check_against_oracle(c, p, g, o, root, what=f"states through matrices {H} {rows} {reads} mode {mode} level {level}")
+            out.append([c.all_read(0, total), c.all_read(1, total)] + [c.param_grad_read(q, m.shape) for q, m in enumerate(p.mats)])
+            c.close()
+        for level in (1, 2):
+            for x, y in zip(out[0], out[level]):
+                assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
 @pytest.mark.parametrize("K,rows", [(64, 8191), (64, 8193), (33, 15888), (33, 15889), (128, 4200)])

@@ -26,7 +26,9 @@ def run_gpu(p, g, mode, launch=0, arena=2 << 30, n_nodes=None, fuse=2, labels=No
     from paper_1705_07860_amd import binding as ob
     c = ob.Context(arena_bytes=arena, mode=mode, launch=launch)
     if nan:
+        import torch
         c._arena.fill_(255)
+        torch.cuda.synchronize()      # (the context has a stream of its own)
     c.set_fusion(int(fuse))
     pids = c.params_create(p)
     assert pids == list(range(len(p.mats)))

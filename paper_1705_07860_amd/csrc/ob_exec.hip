@@ -1091,9 +1091,12 @@ __device__ inline float4 edge_term4_any(const Tables &T, const EdgeRec &er, u32 
     }
 }
 
-// SIDE: consumer edges of a row that are read side by side where rows differ and the edges are plain (the input that stands for a
-// parser's empty places has a hundred consumers, and one after the other each waits for its record and then for its row: 63 -> 34 us
-// for the launch of 64 sentences' inputs, eight side by side no less; taken through the general edge routine four at a time 57)
+// SIDE: consumer edges of a row that are read side by side where rows differ, their records and, if all are plain, their rows (the input
+// that stands for a parser's empty places has a hundred consumers, and one after the other each waits for its record and then for its
+// row: 63 -> 34 us for the launch of 64 sentences' inputs, eight side by side no less; plain ones taken through the general
+// edge routine 57).  Records of other edges are used as they were read, too: a backward pass over 8 rows of 300 products each 303 -> 266 us,
+// of 300 sums 232 -> 88, of both and tanh in turn 264 -> 246 (one edge after the other, and now; with the general routine
+// written out for each of the four 245, 89 and 227, but every launch then has a third more code to read: some 0.5 % of a pass).
 template <u32 SIDE>
 __device__ inline void pull_tile(const Tables &T, const PullDesc &d, lds_float *cl, u32 tid, u32 nthr)
 {
@@ -1148,12 +1151,19 @@ __device__ inline void pull_tile(const Tables &T, const PullDesc &d, lds_float *
                     for (u32 k = 0; k < SIDE; ++k) {
                         acc.x = add_r(acc.x, t[k].x); acc.y = add_r(acc.y, t[k].y); acc.z = add_r(acc.z, t[k].z); acc.w = add_r(acc.w, t[k].w);
                     }
-                    q += SIDE;
                 } else {
-                    const float4 t = edge_term4_any(T, er[0], ownv, col);
-                    acc.x = add_r(acc.x, t.x); acc.y = add_r(acc.y, t.y); acc.z = add_r(acc.z, t.z); acc.w = add_r(acc.w, t.w);
-                    ++q;
+                    // (one copy of the general routine: the launch's code is read anew every time)
+#pragma unroll 1
+                    for (u32 i = 0; i < SIDE && q + i < q1; ++i) {
+                        EdgeRec e = er[0];
+#pragma unroll
+                        for (u32 k = 1; k < SIDE; ++k)
+                            if (k == i) e = er[k];
+                        const float4 t = edge_term4_any(T, e, ownv, col);
+                        acc.x = add_r(acc.x, t.x); acc.y = add_r(acc.y, t.y); acc.z = add_r(acc.z, t.z); acc.w = add_r(acc.w, t.w);
+                    }
                 }
+                q += SIDE;
             }
             st4(T.G + own + col, acc);
             if (keep) {

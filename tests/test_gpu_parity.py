@@ -1019,6 +1019,52 @@ def test_rows_with_differing_consumers_four_columns_at_a_time():
         c.close()
 
 
+@pytest.mark.parametrize("other", ["none", "tanh", "cmult", "slice", "odd offset", "sqnorm"])
+def test_consumer_lists_of_every_length_read_four_at_a_time(other):
+    """Rows whose lists of consumers differ are read four edges at a time: lists of 1 to 24 plain edges with one of another kind at each
+    place, and lists of that kind alone, the bits of a launch per batch."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(24)
+    pb = wl.ParamBuilder(rng, std=0.4)
+    E = pb.add("E", 50, 8)
+    p = pb.done()
+    g = wl.GraphBuilder(p)
+    losses = []
+
+    def reader(x, kind):
+        y = g.input(rng.standard_normal(8))
+        if kind == "tanh":
+            z = g.tanh(x)
+        elif kind == "cmult":
+            z = g.cmult(y, x)
+        elif kind == "slice":
+            z = g.slice(x, 1, 7)
+        elif kind == "odd offset":
+            z = g.concat((g.slice(y, 0, 3), x))
+        elif kind == "sqnorm":
+            losses.append(g.sqnorm(x))
+            return
+        else:
+            z = g.add((x, y))
+        losses.append(g.sqnorm(z))
+
+    for r in range(49):
+        x = g.lookup(E, r)
+        for k in range(1 + r % 24):
+            reader(x, other if r >= 24 and (k == (5 * r) % (1 + r % 24) or r >= 45) else "add")
+    gr = g.finish(g.add(losses), 1)
+    o = Oracle(gr, p, "f64")
+    o.forward()
+    o.backward(gr.root)
+    out = []
+    for level in (0, 2):
+        c, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=128 << 20, nan=True)
+        check_against_oracle(c, p, gr, o, root, what=f"lists with {other} level {level}")
+        out.append(c.param_grad_read(E, (50, 8)))
+        c.close()
+    assert np.array_equal(out[0].view(np.uint32), out[1].view(np.uint32))
+
+
 @pytest.mark.parametrize("mode", ["depth", "agenda", "nobatch"])
 def test_slices_are_views_of_their_operand_rows(mode):
     """SLICE nodes are never copied: readers are pointed at the range of the operand's row.  Covers

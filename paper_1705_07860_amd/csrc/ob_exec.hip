@@ -316,6 +316,22 @@ __device__ inline floatx16 mfma4(float4 a, float4 b, floatx16 acc)
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
     return acc;
 }
+// Two blocks of 8 contraction indices (a0 b0, a1 b1) summed in the order in which v_mfma_f32_16x16x4f32 takes one of 16: index s of
+// the four quarters, then index s + 1.  An instruction of either shape adds its two or four products one after the other, each an
+// fma (measured: 12 800 sums of 512 products in this order have the bits of that chain of fma, with either instruction), so tiles of 16
+// and of 32 rows give the same bits.
+__device__ inline floatx16 mfma4x2(float4 a0, float4 b0, float4 a1, float4 b1, floatx16 acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, b0.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, b1.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, b0.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, b1.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, b0.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, b1.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, b0.w, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, b1.w, acc, 0, 0, 0);
+    return acc;
+}
 
 // Sums the NW waves' accumulators in wave order; on return wave w holds in out[0 .. 16/NW) the
 // accumulator registers v = (16/NW) * w + i, i.e. rows 8*(v/4) + 4*(lane/32) + v%4 of column lane%32.
@@ -334,19 +350,20 @@ __device__ inline void reduce_waves(const floatx16 &acc, float *lds, float *out)
     __syncthreads();
 }
 
-// split [0, total) in units of 8 over the NW waves
-template <int NW>
-__device__ inline void wave_range(u32 total, u32 &lo, u32 &hi)
+// wave w's part of [0, total), split in units of UNIT over NW waves
+template <int NW, u32 UNIT>
+__device__ inline void range_of_wave(u32 w, u32 total, u32 &lo, u32 &hi)
 {
-    const u32 w = threadIdx.x >> 6;
-    const u32 n8 = (total + 7) / 8;
-    const u32 per = (n8 + NW - 1) / NW;
-    lo = w * per * 8;
-    hi = (w + 1) * per * 8;
-    const u32 pad = n8 * 8;
+    const u32 units = (total + UNIT - 1) / UNIT;
+    const u32 per = (units + NW - 1) / NW;
+    lo = w * per * UNIT;
+    hi = (w + 1) * per * UNIT;
+    const u32 pad = units * UNIT;
     if (lo > pad) lo = pad;
     if (hi > pad) hi = pad;
 }
+template <int NW, u32 UNIT = 8>
+__device__ inline void wave_range(u32 total, u32 &lo, u32 &hi) { range_of_wave<NW, UNIT>(threadIdx.x >> 6, total, lo, hi); }
 
 constexpr int KU = 8;   // blocks of 8 contraction indices whose loads are issued together
 
@@ -396,6 +413,7 @@ __device__ inline XRow x_row(const Tables &T, const TileDesc &d, bool row_ok, u3
 }
 
 constexpr int DX_WAVES = 8;   // the dX kernel splits its long contraction (rows of W) over 8 waves
+constexpr u32 DX_UNIT = 16;   // in units of so many rows, which either tile edge sums in the same order
 
 // Y[B x m] = X[B x K] W^T + b.   xrow: this lane's X row (valid when row_ok), W row-major [m x K].
 template <bool XP>
@@ -618,7 +636,7 @@ __device__ inline void matvec_dx_tile_wide(const Tables &T, const TileDesc &d, f
     gl_float *wcol = as_global(d.w) + (col_ok ? col : 0u);
     const bool fast = (m & 3u) == 0;
     u32 lo, hi;
-    wave_range<DX_WAVES>(m, lo, hi);
+    wave_range<DX_WAVES, DX_UNIT>(m, lo, hi);
     floatx16 acc;
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
     const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -648,7 +666,7 @@ __device__ inline void matvec_dx_tile_wide(const Tables &T, const TileDesc &d, f
             }
         }
 #pragma unroll
-        for (int u = 0; u < KU; ++u) acc = mfma4(a[u], b[u], acc);
+        for (int u = 0; u < KU; u += 2) acc = mfma4x2(a[u], b[u], a[u + 1], b[u + 1], acc);
     }
     float out[16 / DX_WAVES];
     reduce_waves<DX_WAVES>(acc, lds, out);
@@ -680,11 +698,8 @@ __device__ inline void matvec_dx_tile(const Tables &T, const TileDesc &d, float 
                                                         : d.val_off + grow_row * m);
     gl_float *wcol = as_global(d.w) + (col_ok ? col : 0u);
     const bool fast = (m & 3u) == 0;
-    // split [0, m) in units of 16 over the waves
-    const u32 n16 = (m + 15) / 16, per = (n16 + DX_WAVES - 1) / DX_WAVES;
-    u32 lo = (u32)w * per * 16, hi = ((u32)w + 1) * per * 16;
-    if (lo > n16 * 16) lo = n16 * 16;
-    if (hi > n16 * 16) hi = n16 * 16;
+    u32 lo, hi;
+    wave_range<DX_WAVES, DX_UNIT>(m, lo, hi);
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
     const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
     for (u32 ib = lo; ib < hi; ib += 16 * KU) {
@@ -1459,10 +1474,8 @@ __device__ inline void dx_cell_tile(const Tables &T, const TileDesc &d, float *l
     if (at) rec = ((const uint4 *)(T.tiles_a + at - 1u))[part];
     gl_float *wcol = as_global(d.w) + (col_ok ? col : 0u);
     const bool fast = (m & 3u) == 0;
-    const u32 steps = (m + KB - 1) / KB, per = (steps + DX_WAVES - 1) / DX_WAVES;
-    u32 lo = w * per * KB, hi = (w + 1) * per * KB;
-    if (lo > steps * KB) lo = steps * KB;
-    if (hi > steps * KB) hi = steps * KB;
+    u32 lo, hi;
+    range_of_wave<DX_WAVES, DX_UNIT>(w, m, lo, hi);
     float4 a[KU], b[KU];
     auto operands = [&](u32 ib) __attribute__((always_inline)) {
         const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1527,7 +1540,7 @@ __device__ inline void dx_cell_tile(const Tables &T, const TileDesc &d, float *l
         for (u32 ib = lo; ib < hi; ib += KB * KU) {
             operands(ib);
 #pragma unroll
-            for (int u = 0; u < KU; ++u) acc = mfma4(a[u], b[u], acc);
+            for (int u = 0; u < KU; u += 2) acc = mfma4x2(a[u], b[u], a[u + 1], b[u + 1], acc);
         }
         values();
 #pragma unroll

@@ -677,29 +677,45 @@ def test_products_that_read_the_state_of_a_cell(H, rows, reads):
                 assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
-@pytest.mark.parametrize("K,rows", [(64, 8191), (64, 8193), (33, 15888), (33, 15889), (128, 4200)])
-def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows):
-    """A slot with 524 288 elements of dX and more has the larger dX tiles whatever its batches are: products of `rows` rows in three
-    batches of one slot (by how deep their operands lie), ragged in rows and columns, against the oracle."""
-    from paper_1705_07860_amd import binding as ob
+def _products_of_one_slot(K, rows, slices, m=21):
+    """`rows` products with 200 to a matrix, half of them behind an operation more: one slot if they are placed late, two if not."""
     rng = np.random.default_rng(K + rows)
     pb = wl.ParamBuilder(rng, std=0.3)
-    W, E = pb.add("W", 21, K), pb.add("E", 50, K)
+    E = pb.add("E", 50, K)
+    Ws = [pb.add(f"W{j}", m, K) for j in range(-(-rows // 200))]
     p = pb.done()
     g = wl.GraphBuilder(p)
     losses = []
     for r in range(rows):
-        x = g.lookup(E, r % 50)
-        for _ in range(0 if r < 200 else 1 + r % 2):
-            x = g.tanh(x)
-        losses.append(g.sqnorm(g.tanh(g.slice(g.matvec(W, -1, x), 3, 20))))
-    gr = g.finish(g.add(losses), rows)
+        j = r // 200
+        x = g.tanh(g.lookup(E, r % 50))
+        y = g.matvec(Ws[j], -1, g.tanh(x) if j % 2 else x)
+        losses.append(g.sqnorm(g.tanh(g.slice(y, 3, m - 1) if slices else y)))
+    return p, g.finish(g.add(losses), rows)
+
+
+@pytest.mark.parametrize("K,rows,m", [(64, 8191, 21), (64, 8192, 21), (33, 15887, 21), (33, 15888, 21), (128, 4095, 260), (128, 4096, 260)])
+def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows, m):
+    """A slot with 524 288 elements of dX and more has the larger dX tiles whatever its batches are (of 200 rows and fewer here, which
+    otherwise have the smaller ones): ragged in rows and columns, against the oracle, and with the bits of the unfused
+    plan, whose slots of half the size have the smaller tiles."""
+    from paper_1705_07860_amd import binding as ob
+    p, gr = _products_of_one_slot(K, rows, True, m)
     o = Oracle(gr, p, "f64")
     o.forward()
     o.backward(gr.root)
-    c, root = run_gpu(p, gr, ob.OB_BYDEPTH, arena=1 << 30)
-    check_against_oracle(c, p, gr, o, root, what=f"dX of {rows} x {K}")
-    c.close()
+    total = int(gr.out_dim.sum())
+    out = []
+    for level in (0, 2):
+        c, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=1 << 30, nan=True)
+        check_against_oracle(c, p, gr, o, root, what=f"dX of {rows} x {K} level {level}")
+        edge = 32 if level and rows * K >= 524288 else 16
+        batches = [200] * (rows // 200) + [rows % 200]
+        assert c.stats()["n_tiles_bwd_dx"] == sum(-(-b // edge) * -(-K // edge) for b in batches)
+        out.append([c.all_read(1, total)] + [c.param_grad_read(q, x.shape) for q, x in enumerate(p.mats)])
+        c.close()
+    for x, y in zip(*out):
+        assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
 @pytest.mark.parametrize("rows", [257, 258, 259, 260])

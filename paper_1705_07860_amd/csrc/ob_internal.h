@@ -27,8 +27,9 @@ constexpr int GTW = 64;               // forward GEMM tile edge of batches with 
 constexpr u32 WIDE_MIN_ROWS = 256;
 constexpr int DXT = 16;               // dX GEMM tile edge (16x16 blocks: its output is small, more tiles fill more CUs)
 constexpr int DXTW = 32;              // dX tile edge of batches with at least WIDE_MIN_ROWS rows (when the matrix has 32+ columns)
-// Slots with at least this many elements of dX keep the chip filled with tiles of the larger edge, whatever batches they lie in: two
-// workgroups of the backward kernel on each of 256 units.  Below it the smaller tiles, of which there are four times as many, end sooner.
+// Slots with at least this many elements of dX, in every kind of plan, keep the chip filled with tiles of the larger edge, whatever batches
+// they lie in: two workgroups of the backward kernel on each of 256 units.  Below it the smaller tiles, of which there are four times as
+// many, end sooner.  Both edges sum in the same order, so the bits do not depend on which it is.
 // (64 parsed sentences, the products over all feature rows: 149 and 39 -> 75 and 17 us; 512 tagged ones: 154 and 70 -> 85 and 41.)
 constexpr u32 DX_LARGE_SLOT = 2u * 256u * DXTW * DXTW;
 // 8u, 16384u = TF_WIDE, TF_DX_LARGE of the batch flags
@@ -281,6 +282,7 @@ struct Tables {
     u32 *slot_of; u32 *label_of; u32 *lorder;
     u32 *blevel;           // per batch: its step (depth mode) or its level inside its fused chain (agenda mode)
     u32 *chain_of_batch;   // per batch: index of its launch chain
+    u32 *slot_dx;          // per slot: elements of dX of its products
     uint4 *nrec;                           // per node: first two operands, operation, arity (this and what follows with `cells` only)
     CellRec *cells; u32 *cell_of;          // gated cells; per position of an output h: its cell
     u32 *cell_ends, *cell_ends_n;          // nodes that a cell may end in, by parts of a workgroup's nodes; how many a part has
@@ -290,7 +292,6 @@ struct Tables {
     u32 *cell_takes;                       // per batch of outputs: cells that a product of the slot after theirs reads and nothing else of it
                                            // (CELL_HOLD: something else does)
     u32 *slot_cells;                       // per slot: chains of cells without CELL_HOLD (CELL_HOLD: some of their cells are so read)
-    u32 *slot_dx;                          // per slot: elements of dX
     u32 *dx_cell;                          // per position of a product: 1 + the pull tile of the cell that its operand is the output of, or 0
     u32 *slot_chains, *slot_rows;          // per slot: chains, and rows of all of them
     u32 *cell_rows, *cell_nodes;           // per batch of outputs: cells whose nodes lie in one chain, and the nodes they hold

@@ -114,7 +114,7 @@ __device__ inline void node_init_part(const Tables &T, int steps, u64 *keys, u32
             const u32 x = hi > lo ? T.in_idx[lo] : 0u, y = hi > lo + 1u ? T.in_idx[lo + 1u] : 0u;
             T.nrec[v] = make_uint4(x, y, o, hi - lo);
             T.cell_rows[v] = T.cell_nodes[v] = T.cell_prods[v] = T.cell_takes[v] = 0;
-            T.slot_chains[v] = T.slot_rows[v] = T.slot_cells[v] = T.slot_dx[v] = T.dx_cell[v] = 0;
+            T.slot_chains[v] = T.slot_rows[v] = T.slot_cells[v] = T.dx_cell[v] = 0;
             if (o == OP_CMULT) {
                 const u32 ox = T.op[x], oy = T.op[y];
                 ends = (ox == OP_TANH && oy == OP_SIGMOID) || (ox == OP_SIGMOID && oy == OP_TANH);
@@ -1002,6 +1002,7 @@ __device__ inline void node_offsets_at(const Tables &T, u32 p)
     const u32 v = T.order[p];
     T.val_off[v] = T.nat_off[v] = r.val_off + row * r.d;
     T.dx_off[v] = (r.op == OP_MATVEC) ? r.dx_off + row * r.k : 0u;
+    T.slot_dx[p] = 0;
     // a CONCAT batch can stay uncopied only with at most XP_MAX pieces whose dimensions are multiples of 4
     if (r.op == OP_CONCAT && (r.vec4 & TF_VIRT)) {
         const u32 ar = T.in_off[v + 1] - T.in_off[v];
@@ -1655,7 +1656,7 @@ __device__ inline void launch_keys_at(const Tables &T, u64 *keys, u32 *vals, u32
     u32 cnt[4] = {0u, 0u, 0u, 0u};
     if (live) {
         const BatchRec &r = T.batches[b];
-        if (T.cells && r.op == OP_MATVEC) atomicAdd(&T.slot_dx[T.slot_of[b]], r.B * r.k);
+        if (r.op == OP_MATVEC) atomicAdd(&T.slot_dx[T.slot_of[b]], r.B * r.k);
         if (r.vec4 & TF_VIEW) { cnt[0] = 1u; cnt[1] = r.B * r.d; }
         if (r.vec4 & TF_VIRT) { cnt[2] = 1u; cnt[3] = r.B * r.d; }
     }
@@ -1831,7 +1832,7 @@ __device__ inline void chain_recs_at(const Tables &T, int agenda, const u32 *bse
             switch (r0.op) {
             case OP_MATVEC: {
                 const u32 gt = (r0.vec4 & TF_WIDE) ? (u32)GTW : (u32)GT;
-                const bool large = T.cells && T.slot_dx[cr.slot] >= DX_LARGE_SLOT;
+                const bool large = T.slot_dx[cr.slot] >= DX_LARGE_SLOT;
                 if (large) T.batches[T.lorder[i]].vec4 |= TF_DX_LARGE;
                 const u32 dt = dx_tile_edge(r0.vec4 | (large ? (u32)TF_DX_LARGE : 0u), r0.k);
                 L.tf = cdiv(r0.B, gt) * cdiv(r0.d, gt); L.tb = cdiv(r0.B, dt) * cdiv(r0.k, dt);
@@ -2923,6 +2924,7 @@ int sched_enqueue(ob_ctx *ctx)
     A(T.queue, u32, n);
     A(T.ht_slot, u32, n);
     T.ht_mask = ht_size - 1;
+    T.slot_dx = T.queue;            // (one depth pass and the agenda list nodes there; both are done when batches have their place)
     T.dx_cell = T.indeg;            // (plans with cells are fused ones, and those of them that count operands down do so before they look for cells)
     A(T.order, u32, n); A(T.pos_of, u32, n); A(T.batch_of_pos, u32, n); A(T.s_aux0, u32, n);
     A(T.s_in_off, u32, n + 1);
@@ -2981,7 +2983,7 @@ int sched_enqueue(ob_ctx *ctx)
         };
         table(T.nrec, n); table(T.cell_nodes_of, T.cells_cap); table(T.cell_of, n); table(T.prod_cell, n);
         table(T.cell_ends, n); table(T.cell_ends_n, blocks_for(n));
-        table(T.cell_rows, n); table(T.cell_nodes, n); table(T.cell_prods, n); table(T.cell_takes, n); table(T.slot_cells, n); table(T.slot_dx, n);
+        table(T.cell_rows, n); table(T.cell_nodes, n); table(T.cell_prods, n); table(T.cell_takes, n); table(T.slot_cells, n);
         table(T.slot_chains, n); table(T.slot_rows, n);
         table(T.cells, T.cells_cap);
         if (!room) { T.cells = nullptr; ctx->top = before; }

@@ -695,12 +695,13 @@ def _products_of_one_slot(K, rows, slices, m=21):
 
 
 @pytest.mark.parametrize("K,rows,m", [(64, 8191, 21), (64, 8192, 21), (33, 15887, 21), (33, 15888, 21), (128, 4095, 260), (128, 4096, 260)])
-def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows, m):
-    """A slot with 524 288 elements of dX and more has the larger dX tiles whatever its batches are (of 200 rows and fewer here, which
+@pytest.mark.parametrize("slices", [True, False])
+def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows, m, slices):
+    """With slices in the graph (which a plan looks for gated cells in) and without: a slot with 524 288 elements of dX and more has the larger dX tiles whatever its batches are (of 200 rows and fewer here, which
     otherwise have the smaller ones): ragged in rows and columns, against the oracle, and with the bits of the unfused
     plan, whose slots of half the size have the smaller tiles."""
     from paper_1705_07860_amd import binding as ob
-    p, gr = _products_of_one_slot(K, rows, True, m)
+    p, gr = _products_of_one_slot(K, rows, slices, m)
     o = Oracle(gr, p, "f64")
     o.forward()
     o.backward(gr.root)
@@ -708,7 +709,7 @@ def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows, m):
     out = []
     for level in (0, 2):
         c, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=1 << 30, nan=True)
-        check_against_oracle(c, p, gr, o, root, what=f"dX of {rows} x {K} level {level}")
+        check_against_oracle(c, p, gr, o, root, what=f"dX of {rows} x {K} slices {slices} level {level}")
         edge = 32 if level and rows * K >= 524288 else 16
         batches = [200] * (rows // 200) + [rows % 200]
         assert c.stats()["n_tiles_bwd_dx"] == sum(-(-b // edge) * -(-K // edge) for b in batches)
@@ -716,6 +717,18 @@ def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows, m):
         c.close()
     for x, y in zip(*out):
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+
+
+def test_dx_tiles_of_a_large_slot_do_not_depend_on_the_arena():
+    """The tables for gated cells are left out where an arena has no room for them; the larger dX tiles are not."""
+    from paper_1705_07860_amd import binding as ob
+    p, g = _products_of_one_slot(32, 16400, True, m=6)
+    tiles = []
+    for arena in (_smallest_arena(p, g, 2, most=512 << 20), 1 << 30):
+        c, root = run_gpu(p, g, ob.OB_BYDEPTH, arena=arena)
+        tiles.append(c.stats()["n_tiles_bwd_dx"])
+        c.close()
+    assert tiles == [82 * 7] * 2, tiles
 
 
 @pytest.mark.parametrize("rows", [257, 258, 259, 260])
@@ -1565,7 +1578,7 @@ def test_parameter_gradients_accumulate_until_zeroed(workload_cache):
     c.close()
 
 
-def _smallest_arena(p, g, fuse):
+def _smallest_arena(p, g, fuse, most=64 << 20):
     """Bytes of the smallest arena, in steps of 256, that holds a forward and a backward pass."""
     from paper_1705_07860_amd import binding as ob
 
@@ -1585,7 +1598,7 @@ def _smallest_arena(p, g, fuse):
         finally:
             c.close()
 
-    no, yes = 0, (64 << 20) // 256
+    no, yes = 0, most // 256
     assert fits(yes)
     while yes - no > 1:
         mid = (no + yes) // 2

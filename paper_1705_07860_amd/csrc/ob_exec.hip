@@ -2119,6 +2119,7 @@ __global__ __launch_bounds__(WG) void k_test_gemm(const float *A, const float *B
 
 inline u32 grid_for(u32 tiles, u32 cap) { return tiles < cap ? tiles : cap; }
 constexpr u32 GRID_CAP = 4096;
+static_assert(GRID_CAP % 8 == 0, "a workgroup's tiles are tiles of one XCD");
 
 }  // namespace
 

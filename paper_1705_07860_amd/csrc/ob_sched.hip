@@ -1968,8 +1968,9 @@ __device__ inline u32 chain_own_delta(const Tables &T, const ChainCtx &cc, const
     return lds - (r.val_off + cc.g0 * (r.B / cc.cr.G) * r.d);
 }
 
-// Which tile of a product the t-th workgroup of its launch takes.  Workgroup g runs on XCD g % 8, every XCD has its own L2, and all L2s are
-// cold when a launch starts, so what an XCD reads is the rows and the columns of its tiles.  The eight XCDs are therefore laid out as
+// Which tile of a product the t-th of its workgroups takes.  Workgroup g of a launch runs on XCD g % 8 (a product that starts at another
+// multiple finds the XCDs renamed, and a workgroup's next tile is a multiple of eight further on), every XCD has its own L2, and all L2s
+// are cold when a launch starts, so what an XCD reads is the rows and the columns of its tiles.  The eight XCDs are therefore laid out as
 // pr x pc over the tiles, whichever reads least: rows / pr + columns / pc, both as long as the contraction.  (With pr = 1
 // throughout, dX of 512 rows a direction had every XCD read all 4 MB of gradients.)
 __device__ inline u32 xcd_tile(u32 t, u32 ntr, u32 ntn, u32 rows, u32 cols)

@@ -719,6 +719,38 @@ def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows, m, slices):
         assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
 
 
+@pytest.mark.parametrize("rows,m,K,grid", [(20, 256, 40, True), (64, 128, 33, True), (128, 64, 130, True), (255, 32, 256, True), (96, 96, 96, False),
+                                           (250, 48, 64, True), (512, 256, 20, True), (300, 200, 48, False), (700, 100, 16, False), (1, 1, 1, False),
+                                           (290, 70, 300, False)])
+def test_order_of_product_tiles(rows, m, K, grid):
+    """Two products of each shape in one slot: every tile is there once, in whichever order, and (grid: the XCDs divide the product evenly)
+    the tiles that workgroups eight apart take, one XCD's, are some rows times some columns of tiles."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(rows)
+    pb = wl.ParamBuilder(rng, std=0.3)
+    E, Ws = pb.add("E", 50, K), [pb.add(f"W{j}", m, K) for j in range(2)]
+    p = pb.done()
+    g = wl.GraphBuilder(p)
+    gr = g.finish(g.add([g.sqnorm(g.tanh(g.matvec(Ws[r % 2], -1, g.lookup(E, r % 50)))) for r in range(2 * rows)]), rows)
+    c, root = run_gpu(p, gr, ob.OB_BYDEPTH, arena=256 << 20, nan=True)
+    tiles = c.debug_read(ob.OB_DBG_TILES_FWD).reshape(-1, 40)
+    o = Oracle(gr, p, "f64")
+    o.forward()
+    o.backward(gr.root)
+    check_against_oracle(c, p, gr, o, root, what=f"tiles of {rows} x {m} x {K}")     # (dX: a tile that is missing leaves NaN)
+    c.close()
+    edge = 64 if rows >= 256 else 32
+    ntr, ntn = -(-rows // edge), -(-m // edge)
+    products = tiles[tiles[:, 0] == wl.OP_MATVEC]
+    assert len(products) == 2 * ntr * ntn
+    for pos0 in np.unique(products[:, 4]):
+        t = products[products[:, 4] == pos0, 17].astype(int)
+        assert sorted(t) == list(range(ntr * ntn))
+        for x in range(8 if grid else 0):
+            mine = t[x::8]
+            assert mine.size == np.unique(mine // ntn).size * np.unique(mine % ntn).size
+
+
 def test_dx_tiles_of_a_large_slot_do_not_depend_on_the_arena():
     """The tables for gated cells are left out where an arena has no room for them; the larger dX tiles are not."""
     from paper_1705_07860_amd import binding as ob

@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "ob_internal.h"
@@ -70,14 +71,18 @@ constexpr size_t READ_AT = 256 + SLOT_WINDOW * sizeof(SlotRec);
 // 15.6 -> 14.8 ms.)
 constexpr size_t PLAN_DONE_AT = 252;   // of a schedule: the last word in front of the slot table
 static_assert(sizeof(SchedHeader) <= PLAN_DONE_AT, "pinned block layout");
-// false: not within a while, ask the runtime
+// The calling thread looks without a pause worth mentioning for some ten us, which is what a value takes to arrive; from then on it
+// offers its core to other threads between one burst of looking and the next.
+// false: not within a while, ask the runtime (which sleeps, and knows of errors)
 inline bool pinned_done(const u32 *word, u32 number)
 {
     const auto t0 = std::chrono::steady_clock::now();
     for (u32 k = 1;; ++k) {
         if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == number) return true;
         __builtin_ia32_pause();
-        if ((k & 1023u) == 0u && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(100)) return false;
+        if ((k & 1023u) != 0u) continue;
+        if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(100)) return false;
+        std::this_thread::yield();
     }
 }
 constexpr size_t READ_FLOATS = 4096;   // floats of a row that k_node_read leaves here itself (behind a 16-byte head)

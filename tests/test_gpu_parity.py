@@ -21,14 +21,13 @@ def say(msg):
     sys.stdout.flush()
 
 
-def run_gpu(p, g, mode, launch=0, arena=2 << 30, n_nodes=None, fuse=2, labels=None, nan=False):
-    """nan: the arena starts as NaN, so that rows which nobody writes do not hold what an earlier run of the same graph left there."""
+def run_gpu(p, g, mode, launch=0, arena=2 << 30, n_nodes=None, fuse=2, labels=None):
+    """The arena starts as NaN, so that rows which nobody writes do not hold what an earlier run of the same graph left there."""
+    import torch
     from paper_1705_07860_amd import binding as ob
     c = ob.Context(arena_bytes=arena, mode=mode, launch=launch)
-    if nan:
-        import torch
-        c._arena.fill_(255)
-        torch.cuda.synchronize()      # (the context has a stream of its own)
+    c._arena.fill_(255)
+    torch.cuda.synchronize()      # (the context has a stream of its own)
     c.set_fusion(int(fuse))
     pids = c.params_create(p)
     assert pids == list(range(len(p.mats)))
@@ -668,7 +667,7 @@ def test_products_that_read_the_state_of_a_cell(H, rows, reads):
     for mode in (ob.OB_BYDEPTH, ob.OB_BYAGENDA, ob.OB_MANUAL):
         out = []
         for level in (0, 1, 2):
-            c, root = run_gpu(p, g, mode, fuse=level, arena=512 << 20, labels=labels if mode == ob.OB_MANUAL else None, nan=True)
+            c, root = run_gpu(p, g, mode, fuse=level, arena=512 << 20, labels=labels if mode == ob.OB_MANUAL else None)
             check_against_oracle(c, p, g, o, root, what=f"states through matrices {H} {rows} {reads} mode {mode} level {level}")
             out.append([c.all_read(0, total), c.all_read(1, total)] + [c.param_grad_read(q, m.shape) for q, m in enumerate(p.mats)])
             c.close()
@@ -708,7 +707,7 @@ def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows, m, slices):
     total = int(gr.out_dim.sum())
     out = []
     for level in (0, 2):
-        c, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=1 << 30, nan=True)
+        c, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=1 << 30)
         check_against_oracle(c, p, gr, o, root, what=f"dX of {rows} x {K} slices {slices} level {level}")
         edge = 32 if level and rows * K >= 524288 else 16
         batches = [200] * (rows // 200) + [rows % 200]
@@ -732,7 +731,7 @@ def test_order_of_product_tiles(rows, m, K, grid):
     p = pb.done()
     g = wl.GraphBuilder(p)
     gr = g.finish(g.add([g.sqnorm(g.tanh(g.matvec(Ws[r % 2], -1, g.lookup(E, r % 50)))) for r in range(2 * rows)]), rows)
-    c, root = run_gpu(p, gr, ob.OB_BYDEPTH, arena=256 << 20, nan=True)
+    c, root = run_gpu(p, gr, ob.OB_BYDEPTH, arena=256 << 20)
     tiles = c.debug_read(ob.OB_DBG_TILES_FWD).reshape(-1, 40)
     o = Oracle(gr, p, "f64")
     o.forward()
@@ -1119,7 +1118,7 @@ def test_consumer_lists_of_every_length_read_four_at_a_time(other):
     o.backward(gr.root)
     out = []
     for level in (0, 2):
-        c, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=128 << 20, nan=True)
+        c, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=128 << 20)
         check_against_oracle(c, p, gr, o, root, what=f"lists with {other} level {level}")
         out.append(c.param_grad_read(E, (50, 8)))
         c.close()

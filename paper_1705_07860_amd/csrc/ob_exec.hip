@@ -2042,7 +2042,7 @@ __global__ void k_fill_uncopied(Tables T)
 }
 
 // Gradient rows of products that are one reader's row as it is (TF_G_ALIAS): the backward pass reads that row in their place and
-// leaves theirs unwritten, and they are written when somebody asks for gradients.
+// leaves theirs unwritten, and they are written when somebody asks for all gradients.
 __global__ void k_fill_product_grads(Tables T)
 {
     const u32 v = blockIdx.x;
@@ -2059,10 +2059,16 @@ __global__ void k_fill_product_grads(Tables T)
 // read is one launch and one wait.  What bounds it is the round trip to the host, so what counts is how many there
 // are: looking the offset up by a copy of its own, waiting, and then copying the row took two.  Tagging one sentence
 // of 20 tokens and reading its 20 score rows: 1 630 -> 920 us.
+// alias: the gradient row of a product may be its one reader's (TF_G_ALIAS) and is read there: writing those of all products first
+// (k_fill_product_grads) took such a read from 23 to 37 us with 48 000 nodes, from 24 to 65 with 189 000.
 __global__ __launch_bounds__(WG) void k_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row,
-                                                   u32 number)
+                                                   u32 number, RowAlias alias)
 {
-    const u32 off = off_tab[node];
+    u32 off = off_tab[node];
+    if (alias.pos_of) {
+        const u32 p = alias.pos_of[node];
+        if (alias.batches[alias.batch_of_pos[p]].vec4 & TF_G_ALIAS) off = alias.dx_gsrc[p];
+    }
     if (threadIdx.x == 0) head[0] = off;
     for (u32 c = threadIdx.x; c < count; c += WG) row[c] = arena[off + c];
     pinned_release(head + 1, number);
@@ -2355,9 +2361,10 @@ hipError_t exec_upload(const UploadList &L, char *dst, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, u32 number, hipStream_t s)
+hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, u32 number,
+                          const RowAlias &alias, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_node_read, dim3(1), dim3(WG), 0, s, off_tab, arena, node, count, head, row, number);
+    hipLaunchKernelGGL(k_node_read, dim3(1), dim3(WG), 0, s, off_tab, arena, node, count, head, row, number, alias);
     return hipGetLastError();
 }
 

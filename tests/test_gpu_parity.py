@@ -415,17 +415,22 @@ def test_gated_cells(H, nf, sums, rows, odd, cells):
         assert np.array_equal(out[0][k], out[1][k]) and np.array_equal(out[0][k], out[2][k]), k
 
 
-def test_gradients_of_products_are_there_when_asked_for():
-    """A product with one reader that passes its gradient on has no row of its own written by the backward pass: one node asked
-    for by itself, all nodes at once, and both again after another backward pass on other values, also of two evaluations."""
+@pytest.mark.parametrize("H,rows", [(36, 9), (1040, 2)])
+def test_gradients_of_products_are_there_when_asked_for(H, rows):
+    """A product with one reader that passes its gradient on has no row of its own written by the backward pass: nodes asked
+    for by themselves (rows of more than 4 096 elements come in two pieces), all at once, and again after another backward pass on
+    other values, also of two evaluations."""
+    import torch
     from paper_1705_07860_amd import binding as ob
     for cut in (False, True):
         out = []
         for seed in (3, 4):
-            p, g = _cell_graph(36, 1, True, 9, "")
+            p, g = _cell_graph(H, 1, True, rows, "")
             g.payload[:] = np.random.default_rng(seed).standard_normal(g.payload.size).astype(np.float32)
             out.append((p, g, Oracle(g, p, "f64")))
-        c = ob.Context(arena_bytes=128 << 20)
+        c = ob.Context(arena_bytes=512 << 20)
+        c._arena.fill_(255)
+        torch.cuda.synchronize()
         c.params_create(out[0][0])
         for p, g, o in out:
             o.forward()
@@ -439,10 +444,13 @@ def test_gradients_of_products_are_there_when_asked_for():
                 c.forward(g.n * 2 // 3)
             c.forward(g.root)
             c.backward(g.root)
-            for v in (int(products[0]), int(products[-1])):
+            alone = [c.grad_read(int(v), int(g.out_dim[v])) for v in products]
+            every = c.all_read(1, total)
+            assert segment_rel_err(every, o.grad[:total], o.v_off) <= TOL
+            for v, row in zip(products, alone):
                 lo, hi = int(o.v_off[v]), int(o.v_off[v + 1])
-                assert rel_err(c.grad_read(v, hi - lo), o.grad[lo:hi]) <= TOL
-            assert segment_rel_err(c.all_read(1, total), o.grad[:total], o.v_off) <= TOL
+                assert np.array_equal(row.view(np.uint32), every[lo:hi].view(np.uint32))
+                assert np.array_equal(c.grad_read(int(v), hi - lo).view(np.uint32), row.view(np.uint32))
         c.close()
 
 

@@ -533,9 +533,8 @@ struct AgendaTables {
     u32 *pending;     // [n] unresolved operands
     u32 *seg;         // [n] ready lists, one segment per rank (each node is appended once)
     // for graphs whose counters fit into LDS
-    uint2 *edge_to;   // [E] per entry of the successor lists: consumer, rank of its signature (AG_LONG: with more operands than AG_FEW)
-    uint2 *edge_succ; // [E] and that consumer's own successor list, first entry and end
-    uint4 *ready;     // [n] ready lists of nodes with their successor lists
+    uint2 *edge_to;   // [E] per entry of the successor lists: consumer (ag_entry) | rank of its signature << AG_RANK
+    uint2 *ready;     // [n] ready lists of such entries
 };
 
 __device__ inline u32 ag_cost_class(u32 op)
@@ -714,22 +713,38 @@ __global__ __launch_bounds__(AGENDA_THREADS) void k_agenda(Tables T, AgendaTable
     if (tid == 0 && s_done != T.n) atomicOr(&T.hdr->err, (u32)ERR_CYCLE);
 }
 
-// The same agenda for up to AG_LDS_NODES nodes.  What bounds it is the chain of dependent reads of an iteration, so the counters of
-// unresolved operands are in LDS, four bits a node (a node with more than AG_FEW operands keeps its word in memory), an entry of a
-// successor list brings the consumer's rank and successor list with it, and so does an entry of a ready list: a batch reads its
-// entries, then their successors, then counts, where it read entry, list bounds, successors and counters in turn.  Every wave finds the
-// lowest rank for itself, which takes two barriers an iteration instead of four.  64 parsed sentences, 662 batches: 1 232 -> 894 us (with 1 024
-// threads and four consumers side by side 966: half of all nodes have one consumer, and what is issued for absent ones counts; with
-// 256 threads 912, with 128 1 045).
+// The same agenda for up to AG_LDS_NODES nodes.  Batches of few nodes are bound by the chain of dependent reads of an iteration, so the
+// counters of unresolved operands are in LDS, four bits a node (a node with more than AG_FEW operands keeps its word in memory), an
+// entry of a successor list brings the consumer's rank and successor list with it, and so does an entry of a ready list: a batch reads
+// its entries, then their successors, then counts, where it read entry, list bounds, successors and counters in turn.  Every wave finds
+// the lowest rank for itself, which takes two barriers an iteration instead of four.  Batches of many nodes are bound by the bytes this
+// one workgroup moves, so an entry is eight bytes (entries of 16 in two arrays and ready lists of 16: 4.2 ns a node in batches of
+// 40 000, where the agenda over memory takes 1.6), and by sums over everything, whose counter all lanes want at once.  Kernel
+// over memory / with entries of 16 bytes / now: 64 parsed sentences, 662 batches, 1 323, 989, 965 us; 512 chains of a tanh network
+// 97, 103, 83; 5 000 chains 747, 1 002, 632; 40 000 rows of five operations and their sum 1 025, 1 695, 723.  (A schedule with 1 024
+// threads 0 to 3 % slower up to 64 sentences and 1 to 3 % faster from 500 rows on; four consumers side by side 1 to 4 % slower, as half of
+// all nodes have one.)
 constexpr u32 AG_LDS_THREADS = 512, AG_SIDE = 2;
-constexpr u32 AG_LDS_WORDS = 32768, AG_LDS_NODES = 8 * AG_LDS_WORDS, AG_FEW = 14, AG_LONG = 0x80000000u;
+constexpr u32 AG_LDS_WORDS = 32768, AG_LDS_NODES = 8 * AG_LDS_WORDS, AG_FEW = 14;
+// An entry names a node and its successor list in eight bytes: id, number of successors (AG_MANY: look it up), whether the
+// node has more operands than AG_FEW, rank of its signature | first successor.
+constexpr u32 AG_ID = 18, AG_MANY = 7, AG_LONG = 1u << 21, AG_RANK = 22;
+static_assert(AG_LDS_NODES <= 1u << AG_ID && AG_MAX_CLASSES <= 1u << (32 - AG_RANK), "entry layout");
+__device__ inline uint2 ag_entry(u32 v, u32 lo, u32 hi) { return make_uint2(v | (hi - lo < AG_MANY ? hi - lo : AG_MANY) << AG_ID, lo); }
+__device__ inline u32 ag_id(uint2 e) { return e.x & ((1u << AG_ID) - 1u); }
+__device__ inline u32 ag_end(const Tables &T, uint2 e)
+{
+    const u32 deg = (e.x >> AG_ID) & AG_MANY;
+    return deg < AG_MANY ? e.y + deg : T.succ_off[ag_id(e) + 1u];
+}
 __global__ void k_agenda_edges(Tables T, AgendaTables A, const u32 *succ_node)
 {
     const u32 q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= T.E) return;
     const u32 v = succ_node[q];
-    A.edge_to[q] = make_uint2(v, A.cls[v] | (T.in_off[v + 1] - T.in_off[v] > AG_FEW ? AG_LONG : 0u));
-    A.edge_succ[q] = make_uint2(T.succ_off[v], T.succ_off[v + 1]);
+    uint2 e = ag_entry(v, T.succ_off[v], T.succ_off[v + 1]);
+    e.x |= A.cls[v] << AG_RANK | (T.in_off[v + 1] - T.in_off[v] > AG_FEW ? AG_LONG : 0u);
+    A.edge_to[q] = e;
 }
 __global__ __launch_bounds__(AG_LDS_THREADS) void k_agenda_lds(Tables T, AgendaTables A)
 {
@@ -742,30 +757,44 @@ __global__ __launch_bounds__(AG_LDS_THREADS) void k_agenda_lds(Tables T, AgendaT
     for (u32 c = tid; c <= C; c += AG_LDS_THREADS) s_off[c] = A.seg_off[c];
     __syncthreads();
     for (u32 w = tid; 8u * w < T.n; w += AG_LDS_THREADS) {
-        u32 p[8], word = 0;
+        u32 p[8], bound[9], word = 0;
 #pragma unroll
         for (u32 k = 0; k < 8; ++k) p[k] = 8u * w + k < T.n ? A.pending[8u * w + k] : 1u;
 #pragma unroll
+        for (u32 k = 0; k < 9; ++k) bound[k] = T.succ_off[8u * w + k < T.n ? 8u * w + k : T.n];
+#pragma unroll
         for (u32 k = 0; k < 8; ++k) {
-            const u32 v = 8u * w + k, count = p[k] & COUNT, c = p[k] >> AG_COUNT_BITS;
+            const u32 count = p[k] & COUNT, c = p[k] >> AG_COUNT_BITS;
             word |= (count <= AG_FEW ? count : AG_FEW + 1u) << (4u * k);
-            if (count == 0u) A.ready[s_off[c] + atomicAdd(&s_tail[c], 1u)] = make_uint4(v, T.succ_off[v], T.succ_off[v + 1], 0u);
+            if (count == 0u) A.ready[s_off[c] + atomicAdd(&s_tail[c], 1u)] = ag_entry(8u * w + k, bound[k], bound[k + 1]);
         }
         s_count[w] = word;
     }
     // The lists of successors were written all over the chip: brought into this XCD's L2 first, side by side.
     u32 sink = 0;
     for (u32 x0 = tid; x0 < T.E; x0 += 8u * AG_LDS_THREADS) {
-        u32 a[8], b[8];
+        u32 a[8];
 #pragma unroll
-        for (u32 k = 0; k < 8; ++k) {
-            const u32 x = x0 + k * AG_LDS_THREADS < T.E ? x0 + k * AG_LDS_THREADS : x0;
-            a[k] = A.edge_to[x].x; b[k] = A.edge_succ[x].x;
-        }
+        for (u32 k = 0; k < 8; ++k) a[k] = A.edge_to[x0 + k * AG_LDS_THREADS < T.E ? x0 + k * AG_LDS_THREADS : x0].x;
 #pragma unroll
-        for (u32 k = 0; k < 8; ++k) sink |= a[k] | b[k];
+        for (u32 k = 0; k < 8; ++k) sink |= a[k];
     }
     asm volatile("" :: "v"(sink));
+    // One operand less of a node whose counter is in memory, for each lane that gets here; how many there were.  Lanes of one node, a sum of
+    // all losses in the first place, are counted by one of them.
+    auto count_long = [&](u32 v) __attribute__((always_inline)) {
+        u32 was = 0;
+        for (u64 todo = __ballot(true); todo;) {
+            const u32 leader = (u32)__builtin_ctzll(todo), vl = (u32)__builtin_amdgcn_readlane((int)v, (int)leader);
+            const u64 same = __ballot(v == vl) & todo;
+            u32 had = 0;
+            if (lane == leader) had = atomicSub(&A.pending[vl], (u32)__popcll(same)) & COUNT;
+            had = (u32)__builtin_amdgcn_readlane((int)had, (int)leader);
+            if (v == vl) was = had - (u32)__popcll(same & ((1ull << lane) - 1ull));
+            todo &= ~same;
+        }
+        return was;
+    };
     u32 done = 0, prev = AG_NONE, prev_hi = 0;
     for (u32 t = 0;; ++t) {
         __syncthreads();
@@ -783,30 +812,28 @@ __global__ __launch_bounds__(AG_LDS_THREADS) void k_agenda_lds(Tables T, AgendaT
         if (tid == 0 && prev != AG_NONE) s_head[prev] = prev_hi;
         const u32 base = s_off[c];
         for (u32 i = lo + tid; i < hi; i += AG_LDS_THREADS) {
-            const uint4 e = A.ready[base + i];
-            T.step[e.x] = t;
-            for (u32 q = e.y; q < e.z; q += AG_SIDE) {
-                uint2 to[AG_SIDE], next[AG_SIDE];
+            const uint2 e = A.ready[base + i];
+            const u32 end = ag_end(T, e);
+            for (u32 q = e.y; q < end; q += AG_SIDE) {
+                uint2 to[AG_SIDE];
                 u32 left[AG_SIDE];
 #pragma unroll
-                for (u32 k = 0; k < AG_SIDE; ++k) {
-                    const u32 x = q + k < e.z ? q + k : q;
-                    to[k] = A.edge_to[x]; next[k] = A.edge_succ[x];
-                }
+                for (u32 k = 0; k < AG_SIDE; ++k) to[k] = A.edge_to[q + k < end ? q + k : q];
 #pragma unroll
                 for (u32 k = 0; k < AG_SIDE; ++k) {
                     left[k] = 0u;
-                    if (q + k >= e.z) continue;
-                    const u32 v = to[k].x, at = 4u * (v & 7u);
-                    left[k] = to[k].y & AG_LONG ? atomicSub(&A.pending[v], 1u) & COUNT : (atomicSub(&s_count[v >> 3], 1u << at) >> at) & 15u;
+                    if (q + k >= end) continue;
+                    const u32 v = ag_id(to[k]), at = 4u * (v & 7u);
+                    left[k] = to[k].x & AG_LONG ? count_long(v) : (atomicSub(&s_count[v >> 3], 1u << at) >> at) & 15u;
                 }
 #pragma unroll
                 for (u32 k = 0; k < AG_SIDE; ++k) {
                     if (left[k] != 1u) continue;
-                    const u32 cs = to[k].y & ~AG_LONG;
-                    A.ready[s_off[cs] + atomicAdd(&s_tail[cs], 1u)] = make_uint4(to[k].x, next[k].x, next[k].y, 0u);
+                    const u32 cs = to[k].x >> AG_RANK;
+                    A.ready[s_off[cs] + atomicAdd(&s_tail[cs], 1u)] = to[k];
                 }
             }
+            T.step[ag_id(e)] = t;
         }
         prev = c; prev_hi = hi;
         done += hi - lo;
@@ -3032,7 +3059,7 @@ int sched_enqueue(ob_ctx *ctx)
                 K(k_class_of, n, T, AG);
                 if (n <= AG_LDS_NODES && E > 0) {
                     // (the sort's buffers and the scans' counts are not in use yet)
-                    AG.edge_to = (uint2 *)ctx->key_a; AG.edge_succ = (uint2 *)ctx->key_b; AG.ready = (uint4 *)tri_in;
+                    AG.edge_to = (uint2 *)ctx->key_a; AG.ready = (uint2 *)tri_in;
                     K(k_agenda_edges, E, T, AG, succ_node);
                     hipLaunchKernelGGL(k_agenda_lds, dim3(1), dim3(AG_LDS_THREADS), 0, s, T, AG);
                 } else {

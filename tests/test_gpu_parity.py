@@ -1853,6 +1853,32 @@ def test_agenda_counters_of_few_and_many_operands(arities, copies):
     c.close()
 
 
+@pytest.mark.parametrize("rows,wide", [(3, 15), (70, 14), (70, 16), (600, 900)])
+def test_agenda_entries_of_nodes_with_few_and_many_consumers(rows, wide):
+    """An entry of an agenda list holds up to six consumers, more are looked up: 1 to 12 of them a node.  Sums of `wide` operands, the
+    same node twice and more among them, are counted down by several lanes of a wave at once, some lanes of it for different sums."""
+    from paper_1705_07860_amd import binding as ob
+    rng = np.random.default_rng(rows + wide)
+    pb = wl.ParamBuilder(rng, std=0.3)
+    pb.add("E", 3, 4)
+    p = pb.done()
+    g = wl.GraphBuilder(p)
+    ends = []
+    for r in range(rows):
+        x = g.tanh(g.input(rng.standard_normal(4)))
+        ends += [g.sigmoid(x) if (r + k) % 3 else g.tanh(g.tanh(x)) for k in range(1 + r % 12)]
+    sums = []
+    for k in range(7):
+        sums.append(g.add([ends[int(q)] for q in rng.integers(0, len(ends), wide)]))
+        sums.append(g.add([ends[k % len(ends)]] * wide + [ends[-1]]))
+    gr = g.finish(g.add([g.sqnorm(v) for v in sums + ends]), 1)
+    c, root = run_gpu(p, gr, ob.OB_BYAGENDA, arena=256 << 20)
+    bo, ids, _, _ = c.schedule_read()
+    want = S.by_agenda(gr)
+    assert np.array_equal(bo, want[0]) and np.array_equal(ids, want[1])
+    c.close()
+
+
 def test_agenda_rejects_more_signatures_than_it_can_rank():
     """1100 slices with pairwise different ranges are 1100 signatures; agenda mode ranks at most
     1024 and must fail cleanly (depth-based batching takes the same graph)."""

@@ -208,10 +208,11 @@ int ob_sync(ob_ctx *ctx);
 int ob_reset(ob_ctx *ctx);
 
 /* ---- reads ------------------------------------------------------------------------------------
- * All wait for everything that was queued on the context's stream before.  ob_value_read and ob_grad_read of rows of up to
- * 4 096 elements wait by looking for the result in page-locked memory, as ob_schedule and ob_forward do for the schedule
- * header: the calling thread keeps its core busy for as long as that takes, offering it to other threads every few tens of
- * microseconds, and sleeps in the runtime only after 0.1 s. */
+ * All wait for everything that was queued on the context's stream before.  ob_value_read and ob_grad_read of
+ * rows of up to 4 096 elements wait by looking for the result in page-locked memory, as ob_schedule and
+ * ob_forward do for the schedule header if there is no schedule stream: the calling thread keeps its core busy
+ * for as long as that takes, offering it to other threads every few tens of microseconds, and sleeps in the
+ * runtime only after 0.1 s. */
 
 int ob_value_read(ob_ctx *ctx, int node, float *host_out, size_t cap);
 int ob_grad_read(ob_ctx *ctx, int node, float *host_out, size_t cap);

@@ -98,8 +98,8 @@ PAPER_CONTEXT = {
 }
 
 
-# kernels whose launches a step-kernel figure covers: products and the gated cells behind them are forward launches too
-STEP_KERNELS = {"k_fwd_step": ("k_fwd_step", "k_fwd_cells"), "k_bwd_step": ("k_bwd_step",)}
+# kernels whose launches a step-kernel figure covers: products and the gated cells behind (forward) or before them are step launches too
+STEP_KERNELS = {"k_fwd_step": ("k_fwd_step", "k_fwd_cells"), "k_bwd_step": ("k_bwd_step", "k_bwd_cells")}
 
 
 def stored_traffic(args, workload, kernel):

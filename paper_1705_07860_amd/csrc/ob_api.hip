@@ -1395,13 +1395,14 @@ static int node_read(ob_ctx *ctx, int node, float *out, size_t cap, bool grad)
     // CONCAT it reads from staying uncopied)
     if (!grad && ctx->op[node] == OP_CONCAT) if (int rc = fill_uncopied(ctx, ctx->stream)) return rc;
     const Tables &T = ctx->T;
-    RowAlias alias = {nullptr, nullptr, nullptr, nullptr};
-    if (grad && ctx->op[node] == OP_MATVEC && !ctx->product_grads_filled) alias = {T.pos_of, T.batch_of_pos, T.dx_gsrc, T.batches};
+    const RowAlias alias = {T.pos_of, T.batch_of_pos, T.dx_gsrc, T.batches};
+    const bool reader = grad && ctx->op[node] == OP_MATVEC && !ctx->product_grads_filled;
     const float *arena = grad ? ctx->T.G : ctx->T.V;
     u32 *head = (u32 *)((char *)ctx->hdr_pinned + READ_AT);
     float *row = (float *)(head + 4);
     const u32 here = d < (u32)READ_FLOATS ? d : (u32)READ_FLOATS;
-    HIP_TRY(ctx, exec_node_read(grad ? ctx->T.nat_off : ctx->T.val_off, arena, (u32)node, here, head, row, ++ctx->read_number, alias, ctx->stream));
+    HIP_TRY(ctx, exec_node_read(grad ? ctx->T.nat_off : ctx->T.val_off, arena, (u32)node, here, head, row, ++ctx->read_number,
+                                reader ? &alias : nullptr, ctx->stream));
     if (!pinned_done(head + 1, ctx->read_number)) HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     memcpy(out, row, (size_t)here * 4);
     if (here < d) {

@@ -2059,19 +2059,26 @@ __global__ void k_fill_product_grads(Tables T)
 // read is one launch and one wait.  What bounds it is the round trip to the host, so what counts is how many there
 // are: looking the offset up by a copy of its own, waiting, and then copying the row took two.  Tagging one sentence
 // of 20 tokens and reading its 20 score rows: 1 630 -> 920 us.
-// alias: the gradient row of a product may be its one reader's (TF_G_ALIAS) and is read there: writing those of all products first
-// (k_fill_product_grads) took such a read from 23 to 37 us with 48 000 nodes, from 24 to 65 with 189 000.
-__global__ __launch_bounds__(WG) void k_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row,
-                                                   u32 number, RowAlias alias)
+__device__ inline void node_read(u32 off, const float *arena, u32 count, u32 *head, float *row, u32 number)
 {
-    u32 off = off_tab[node];
-    if (alias.pos_of) {
-        const u32 p = alias.pos_of[node];
-        if (alias.batches[alias.batch_of_pos[p]].vec4 & TF_G_ALIAS) off = alias.dx_gsrc[p];
-    }
     if (threadIdx.x == 0) head[0] = off;
     for (u32 c = threadIdx.x; c < count; c += WG) row[c] = arena[off + c];
     pinned_release(head + 1, number);
+}
+__global__ __launch_bounds__(WG) void k_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row,
+                                                   u32 number)
+{
+    node_read(off_tab[node], arena, count, head, row, number);
+}
+// The gradient row of a product may be its one reader's (TF_G_ALIAS) and is read there: writing those of all products first
+// (k_fill_product_grads) took such a read from 23 to 37 us with 48 000 nodes, from 24 to 65 with 189 000.  (A launch of its own: the
+// four pointers more cost every read of a value 0.45 us.)
+__global__ __launch_bounds__(WG) void k_product_grad_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row,
+                                                          u32 number, RowAlias alias)
+{
+    const u32 p = alias.pos_of[node];
+    const bool one = (alias.batches[alias.batch_of_pos[p]].vec4 & TF_G_ALIAS) != 0u;
+    node_read(one ? alias.dx_gsrc[p] : off_tab[node], arena, count, head, row, number);
 }
 
 // The graph's arrays, read where they lie in page-locked host memory: one launch instead of a copy each.
@@ -2362,9 +2369,10 @@ hipError_t exec_upload(const UploadList &L, char *dst, hipStream_t s)
 }
 
 hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, u32 number,
-                          const RowAlias &alias, hipStream_t s)
+                          const RowAlias *alias, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_node_read, dim3(1), dim3(WG), 0, s, off_tab, arena, node, count, head, row, number, alias);
+    if (alias) hipLaunchKernelGGL(k_product_grad_read, dim3(1), dim3(WG), 0, s, off_tab, arena, node, count, head, row, number, *alias);
+    else hipLaunchKernelGGL(k_node_read, dim3(1), dim3(WG), 0, s, off_tab, arena, node, count, head, row, number);
     return hipGetLastError();
 }
 

@@ -345,9 +345,10 @@ hipError_t exec_fill_uncopied(const Tables &T, hipStream_t s);
 hipError_t exec_fill_product_grads(const Tables &T, hipStream_t s);
 struct UploadList { const void *src[10]; size_t bytes[10], at[10]; };   // host arrays and where they go in one device block
 hipError_t exec_upload(const UploadList &L, char *dst, hipStream_t s);
-struct RowAlias { const u32 *pos_of, *batch_of_pos, *dx_gsrc; const BatchRec *batches; };      // of Tables; null: rows lie where the offsets say
+struct RowAlias { const u32 *pos_of, *batch_of_pos, *dx_gsrc; const BatchRec *batches; };      // of Tables
+// alias: for the gradient of a product whose row may be its reader's; else null
 hipError_t exec_node_read(const u32 *off_tab, const float *arena, u32 node, u32 count, u32 *head, float *row, u32 number,
-                          const RowAlias &alias, hipStream_t s);
+                          const RowAlias *alias, hipStream_t s);
 // the last of a launch's writes to page-locked memory: everything the workgroup has written there is there before `number` is
 __device__ inline void pinned_release(u32 *word, u32 number)
 {

@@ -701,12 +701,14 @@ def _products_of_one_slot(K, rows, slices, m=21):
     return p, g.finish(g.add(losses), rows)
 
 
-@pytest.mark.parametrize("K,rows,m", [(64, 8191, 21), (64, 8192, 21), (33, 15887, 21), (33, 15888, 21), (128, 4095, 260), (128, 4096, 260)])
+@pytest.mark.parametrize("K,rows,m", [(64, 8191, 21), (64, 8192, 21), (33, 15887, 21), (33, 15888, 21), (128, 4095, 260), (128, 4096, 260),
+                                      (64, 16400, 21)])
 @pytest.mark.parametrize("slices", [True, False])
 def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows, m, slices):
-    """With slices in the graph (which a plan looks for gated cells in) and without: a slot with 524 288 elements of dX and more has the larger dX tiles whatever its batches are (of 200 rows and fewer here, which
-    otherwise have the smaller ones): ragged in rows and columns, against the oracle, and with the bits of the unfused
-    plan, whose slots of half the size have the smaller tiles."""
+    """A slot with 524 288 elements of dX and more has the larger dX tiles whatever its batches are (of 200 rows and fewer here, which
+    otherwise have the smaller ones), in graphs with slices (in which a plan looks for gated cells) and without: ragged in rows and
+    columns, against the oracle, and with the bits of the unfused plan, whose slots of half the size have the smaller tiles (but
+    for the last shape, where they are large enough, too)."""
     from paper_1705_07860_amd import binding as ob
     p, gr = _products_of_one_slot(K, rows, slices, m)
     o = Oracle(gr, p, "f64")
@@ -717,7 +719,7 @@ def test_dx_tiles_on_both_sides_of_a_large_slot(K, rows, m, slices):
     for level in (0, 2):
         c, root = run_gpu(p, gr, ob.OB_BYDEPTH, fuse=level, arena=1 << 30)
         check_against_oracle(c, p, gr, o, root, what=f"dX of {rows} x {K} slices {slices} level {level}")
-        edge = 32 if level and rows * K >= 524288 else 16
+        edge = 32 if rows * K // (1 if level else 2) >= 524288 else 16
         batches = [200] * (rows // 200) + [rows % 200]
         assert c.stats()["n_tiles_bwd_dx"] == sum(-(-b // edge) * -(-K // edge) for b in batches)
         out.append([c.all_read(1, total)] + [c.param_grad_read(q, x.shape) for q, x in enumerate(p.mats)])
